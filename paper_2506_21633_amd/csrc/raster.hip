@@ -91,53 +91,111 @@ __device__ __forceinline__ uint64_t xor_lane64(uint64_t v)
     return ((uint64_t)xor_lane<S>((uint32_t)(v >> 32)) << 32) | xor_lane<S>((uint32_t)v);
 }
 
-// Lanes with bit S clear keep their own LO blocks and take the partner's LO
-// blocks moved up; the others keep their high blocks and take the partner's
-// high blocks moved down. Both results are formed and one is picked by a
-// lane mask, so the step has no branch (a select between the two shifted
-// forms compiles to divergent half-wave paths).
-template <int S, uint64_t LO>
-__device__ __forceinline__ uint64_t transpose_step(uint64_t v)
-{
-    const uint64_t p = xor_lane64<S>(v);
-    const uint64_t lo = (v & LO) | ((p & LO) << S);
-    const uint64_t hi = (v & ~LO) | ((p & ~LO) >> S);
-    const uint64_t up = (lane_id() & S) ? ~0ull : 0ull;
-    return (lo & ~up) | (hi & up);
-}
-
 // 64x64 bit-matrix transpose across the wave: on return, bit j of lane i is
-// bit i of lane j's input. Recursive block swap: at step s, lanes i and
-// i ^ s exchange the s-wide bit blocks that sit off the diagonal.
-__device__ __forceinline__ uint64_t transpose64(uint64_t v)
+// bit i of lane j's input. Recursive block swap: at step s, lanes i and i ^ s
+// exchange the s-wide bit blocks that sit off the diagonal. It is bound by
+// instruction issue (few waves share a SIMD in the rasterizers), so each step
+// uses what moves most per instruction: the two 32-bit halves are exchanged
+// whole by one permlane32 swap, the 16-bit blocks of both words by byte
+// permutes around one permlane16 swap, whose unpacking is the packing of the
+// 8-bit step (byte selectors that depend on the lane, one DPP rotation), and
+// the blocks within bytes by a DPP move, a rotate and a bit-field insert per
+// word: 30 instructions where shifting, masking and selecting both forms of
+// every block took about 120. N transposes go step by step together, so that
+// no instruction waits on the one before it.
+struct TransposeLane {
+    uint32_t send8, keep8, lo8, hi8;   // byte selectors of the 8-bit step
+    uint32_t rot4, rot2, rot1;         // rotations of the partner's word
+    uint32_t m4, m2, m1;               // bits of the own word that stay
+};
+
+__device__ __forceinline__ TransposeLane transpose_lane()
 {
-    v = transpose_step<32, 0x00000000FFFFFFFFull>(v);
-    v = transpose_step<16, 0x0000FFFF0000FFFFull>(v);
-    v = transpose_step<8, 0x00FF00FF00FF00FFull>(v);
-    v = transpose_step<4, 0x0F0F0F0F0F0F0F0Full>(v);
-    v = transpose_step<2, 0x3333333333333333ull>(v);
-    v = transpose_step<1, 0x5555555555555555ull>(v);
-    return v;
+    const int l = lane_id();
+    const bool u8 = (l & 8) != 0, u4 = (l & 4) != 0, u2 = (l & 2) != 0, u1 = (l & 1) != 0;
+    TransposeLane t;
+    t.send8 = u8 ? 0x06020400u : 0x07030501u;
+    t.keep8 = u8 ? 0x07030501u : 0x06020400u;
+    t.lo8 = u8 ? 0x01050004u : 0x05010400u;
+    t.hi8 = u8 ? 0x03070206u : 0x07030602u;
+    t.rot4 = u4 ? 4u : 28u;
+    t.rot2 = u2 ? 2u : 30u;
+    t.rot1 = u1 ? 1u : 31u;
+    t.m4 = u4 ? 0xF0F0F0F0u : 0x0F0F0F0Fu;
+    t.m2 = u2 ? 0xCCCCCCCCu : 0x33333333u;
+    t.m1 = u1 ? 0xAAAAAAAAu : 0x55555555u;
+    return t;
 }
 
-// N independent transposes, step by step over all of them, so that their
-// cross-lane moves and bit operations interleave (one transpose after the
-// other is a chain of dependent instructions).
-template <int N>
-__device__ __forceinline__ void transpose64_n(uint64_t (&v)[N])
+// Own blocks of word x where `keep` is set, the partner's (lane ^ S) moved
+// next to them elsewhere.
+template <int S>
+__device__ __forceinline__ uint32_t transpose_bits(uint32_t x, uint32_t keep, uint32_t rot)
 {
+    uint32_t r;
+    if constexpr (S == 4) {
+        // lane + 4 in banks 0 and 2 of each row, lane - 4 in banks 1 and 3
+        r = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x104, 0xF, 0x5, false);
+        r = (uint32_t)__builtin_amdgcn_update_dpp((int)r, (int)x, 0x114, 0xF, 0xA, false);
+    } else {
+        r = xor_lane<S>(x);
+    }
+    r = __builtin_amdgcn_alignbit(r, r, rot);
+    return r ^ (keep & (x ^ r));   // one bit-field insert
+}
+
+template <int N>
+__device__ __forceinline__ void transpose64_n(uint64_t (&v)[N], const TransposeLane& t)
+{
+    uint32_t lo[N], hi[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = transpose_step<32, 0x00000000FFFFFFFFull>(v[i]);
+    for (int i = 0; i < N; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)v[i], (uint32_t)(v[i] >> 32),
+                                                        false, false);
+        lo[i] = r[0];
+        hi[i] = r[1];
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = transpose_step<16, 0x0000FFFF0000FFFFull>(v[i]);
+    for (int i = 0; i < N; ++i) {
+        // low halves of both words, high halves of both words
+        const uint32_t a = __builtin_amdgcn_perm(hi[i], lo[i], 0x05040100u);
+        const uint32_t b = __builtin_amdgcn_perm(hi[i], lo[i], 0x07060302u);
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        lo[i] = r[0];
+        hi[i] = r[1];
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = transpose_step<8, 0x00FF00FF00FF00FFull>(v[i]);
+    for (int i = 0; i < N; ++i) {
+        const uint32_t s = __builtin_amdgcn_perm(hi[i], lo[i], t.send8);
+        const uint32_t k = __builtin_amdgcn_perm(hi[i], lo[i], t.keep8);
+        const uint32_t r = xor_lane<8>(s);
+        lo[i] = __builtin_amdgcn_perm(r, k, t.lo8);
+        hi[i] = __builtin_amdgcn_perm(r, k, t.hi8);
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = transpose_step<4, 0x0F0F0F0F0F0F0F0Full>(v[i]);
+    for (int i = 0; i < N; ++i) {
+        lo[i] = transpose_bits<4>(lo[i], t.m4, t.rot4);
+        hi[i] = transpose_bits<4>(hi[i], t.m4, t.rot4);
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = transpose_step<2, 0x3333333333333333ull>(v[i]);
+    for (int i = 0; i < N; ++i) {
+        lo[i] = transpose_bits<2>(lo[i], t.m2, t.rot2);
+        hi[i] = transpose_bits<2>(hi[i], t.m2, t.rot2);
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = transpose_step<1, 0x5555555555555555ull>(v[i]);
+    for (int i = 0; i < N; ++i) {
+        lo[i] = transpose_bits<1>(lo[i], t.m1, t.rot1);
+        hi[i] = transpose_bits<1>(hi[i], t.m1, t.rot1);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = ((uint64_t)hi[i] << 32) | lo[i];
+}
+
+__device__ __forceinline__ uint64_t transpose64(uint64_t v, const TransposeLane& t)
+{
+    uint64_t one[1] = {v};
+    transpose64_n(one, t);
+    return one[0];
 }
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
@@ -151,15 +209,22 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
-__device__ __forceinline__ uint64_t wave_or_u64(uint64_t v)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void or_step(uint32_t& x)
 {
-    v |= xor_lane64<1>(v);
-    v |= xor_lane64<2>(v);
-    v |= xor_lane64<4>(v);
-    v |= xor_lane64<8>(v);
-    v |= xor_lane64<16>(v);
-    v |= xor_lane64<32>(v);
-    return v;
+    x |= (uint32_t)dpp_from<CTRL, ROWS>((int)x);
+}
+
+// OR of a word over the lanes up to each one; the last lane holds the wave's.
+__device__ __forceinline__ uint32_t or_scan_u32(uint32_t x)
+{
+    or_step<0x111, 0xF>(x);
+    or_step<0x112, 0xF>(x);
+    or_step<0x114, 0xF>(x);
+    or_step<0x118, 0xF>(x);
+    or_step<0x142, 0xA>(x);
+    or_step<0x143, 0xC>(x);
+    return x;
 }
 
 template <int CTRL, int ROWS>
@@ -347,8 +412,8 @@ k_pair_masks(const DevView* __restrict__ views, int nv, int64_t cap, RasterParam
                                local / V.txc);
             pmask[p] = m;
         }
-        m = wave_or_u64(m);
-        if (lane_id() == 0) psum[p / WAVE] = m;
+        const uint32_t olo = or_scan_u32((uint32_t)m), ohi = or_scan_u32((uint32_t)(m >> 32));
+        if (lane_id() == WAVE - 1) psum[p / WAVE] = ((uint64_t)ohi << 32) | olo;
     }
 }
 
@@ -397,6 +462,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     struct alignas(16) RayF { uint32_t o; float t, T; uint32_t last; };
     __shared__ RayF s_ray[WAVE];
     const int lane = threadIdx.x;
+    const TransposeLane tl = transpose_lane();
     if (blockIdx.x >= status[ST_WORK_TILES]) return;
     const int64_t bucket = worklist[blockIdx.x];
     const TileCell tc = tile_cell(views, nv, bucket, true);
@@ -528,7 +594,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
             // 4096 each) are summed two to a word
 #pragma unroll
             for (int k = 0; k < NB; ++k) col[k] = s_m[k][lane];
-            transpose64_n(col);
+            transpose64_n(col, tl);
 #pragma unroll
             for (int k = 0; k < NB; ++k) col[k] = (k < nb && alive) ? col[k] : 0ull;
             {
@@ -748,6 +814,7 @@ k_raster_b_fwd(const DevView* __restrict__ views, int nv, RasterParams rp, int64
     __shared__ float4 s_q[RASTER_WAVES][WAVE];
     __shared__ float2 s_w[RASTER_WAVES][WAVE];
     const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+    const TransposeLane tl = transpose_lane();
     const uint32_t ki = status[ST_PAIRS_I];
     const uint32_t nblk = (uint32_t)(((uint64_t)ki + (uint64_t)B_SEGMENT * RASTER_WAVES - 1) /
                                      ((uint64_t)B_SEGMENT * RASTER_WAVES));
@@ -806,7 +873,7 @@ k_raster_b_fwd(const DevView* __restrict__ views, int nv, RasterParams rp, int64
                 acc = 0.0f;
                 cur = k;
             }
-            uint64_t col = transpose64(((sel >> lane) & 1ull) ? m : 0ull);
+            uint64_t col = transpose64(((sel >> lane) & 1ull) ? m : 0ull, tl);
             if (pix < 0) col = 0ull;
             for (;;) {
                 if (__ballot(col != 0ull) == 0ull) break;
@@ -851,6 +918,7 @@ k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int6
     __shared__ float4 s_q[RASTER_WAVES][WAVE];
     __shared__ float2 s_w[RASTER_WAVES][WAVE];
     const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+    const TransposeLane tl = transpose_lane();
     const int64_t t = (int64_t)blockIdx.x * RASTER_WAVES + w;
     if (t >= tiles_i) return;
     const uint2 rg = ranges_i[t];
@@ -874,7 +942,7 @@ k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int6
         wave_lds_sync();
         // the transpose exchanges bits between lanes: every lane takes part,
         // pixels outside the image drop their column afterwards
-        uint64_t col = transpose64(m);
+        uint64_t col = transpose64(m, tl);
         if (!tc.inside) col = 0ull;
         while (col != 0ull) {
             const int j = __builtin_ctzll(col);
@@ -1074,6 +1142,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
         }
     }
     const int lane = threadIdx.x;
+    const TransposeLane tl = transpose_lane();
     const int64_t bucket = worklist[wi];
     const TileCell tc = tile_cell(views, nv, bucket, true);
     const DevView& V = views[tc.v];
@@ -1290,7 +1359,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             uint32_t hk[NB];   // hits of each chunk over the wave
 #pragma unroll
             for (int k = 0; k < NB; ++k) col[k] = m[k];
-            transpose64_n(col);
+            transpose64_n(col, tl);
 #pragma unroll
             for (int k = 0; k < NB; ++k) {
                 uint64_t used = 0ull;
