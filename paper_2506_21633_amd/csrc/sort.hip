@@ -43,6 +43,12 @@ __global__ void __launch_bounds__(256) k_fill(uint32_t* p, uint32_t v, int64_t n
 }
 
 
+__global__ void __launch_bounds__(256) k_iota(uint32_t* p, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = (uint32_t)i;
+}
+
 // Digit width of a sort: the fewest passes of at most 10 bits, then the
 // narrowest digit (8 to 10 bits) that covers the key in that many passes.
 inline int digit_bits(int bits)
@@ -514,7 +520,14 @@ hipError_t radix_sort(uint32_t* keys[2], uint32_t* vals[2], int64_t cap, const u
 {
     int cur = 0;
     *which = 0;
-    if (cap <= 0 || bits <= 0) return hipSuccess;
+    if (cap <= 0) return hipSuccess;
+    if (bits <= 0) {
+        // one bucket: the input is the result, and every item's position its own
+        if (vals2)
+            hipLaunchKernelGGL(k_iota, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s,
+                               vals2[0], cap);
+        return hipGetLastError();
+    }
     if (segt && (S < 1 || S > SEG_MAX)) return hipErrorInvalidValue;
     const hipError_t e =
         segt ? radix_sort_t<true>(keys, vals, cap, n_dev, bits, iota_vals, hist, &cur, s, shift0,

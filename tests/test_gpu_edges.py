@@ -85,3 +85,39 @@ def test_tile_worklist_blocks(cuda, grids):
     wide = max(a for a, _ in grids), max(b for _, b in grids)
     scene = spread_scene(7, 1500, (0.5, 0.8 * wide[0], 0.5 * wide[1]), 0.15, 0.6)
     check(scene, views, cuda)
+
+
+@pytest.mark.parametrize("kappa", [0.02, 3.0], ids=["thin", "opaque"])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 256, 257, 1500])
+def test_list_lengths(cuda, n, kappa):
+    """One tile's list around the chunk (64) and the batch (4 chunks) of pass
+    A, with few and with many hits per ray, stored for the backward, re-derived
+    by it, and in the deterministic mode."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(n, n, (0.5, 0.7, 0.5), 0.15, 0.4)
+    scene.ext[:] = np.float32(kappa) * scene.ext
+    view = scenes.View.from_degrees(20.0, 40.0, 8, 0.2)
+    for options in (api.RenderOptions(), api.RenderOptions(recompute=True),
+                    api.RenderOptions(deterministic=True)):
+        check(scene, [view], cuda, options)
+
+
+@pytest.mark.parametrize("units", [0, 200, 16384, 5 * 16384])
+def test_hit_stream_parts(cuda, units):
+    """Streams of no, one, one full and five parts: tiles that find no room
+    re-derive their hits, with the same gradients."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(11, 6000, (2.0, 9.0, 9.0), 0.15, 0.5)
+    views = [grid_view(12, 12, 0.2, 45.0, a) for a in (0.0, 50.0)]
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    r = api.Renderer([g], views)
+    cot = torch.as_tensor(np.random.default_rng(1).standard_normal(2 * 96 * 96)
+                          .astype(np.float32), device=cuda)
+    want = r.backward(r.forward(), cot)[0]
+    plan = r.plan()
+    plan.hit_bytes = min(plan.hit_bytes, 16 * units)
+    res = r.forward(plan)
+    got = r.backward(res, cot)[0]
+    r.status(res)
+    for k, t in want.items():   # FP32 rounding of re-derived against stored sums
+        assert elem_err(got[k].cpu().numpy(), t.cpu().numpy()) <= 1e-5, k
