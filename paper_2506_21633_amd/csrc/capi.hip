@@ -338,6 +338,7 @@ struct Bufs {
     // stored hits of pass A's forward for its backward (RasterParams::hits)
     uint4* hits = nullptr;
     uint32_t* hit_tail = nullptr;   // per computation-plane tile
+    unsigned long long* hit_tops = nullptr;   // units taken of each part of the stream
     float* hit_part = nullptr;      // backward: per-pair partials, see RasterParams::hit_part
     unsigned char* hit_touched = nullptr;
 };
@@ -395,6 +396,7 @@ void layout(const Problem& P, int64_t cap_c, int64_t cap_i, Phase ph, char* stat
         if (P.hit_units > 0) {
             b.hits = a.take<uint4>(P.hit_units + 16);   // slack for the backward's part copies
             b.hit_tail = a.take<uint32_t>(P.tiles_c);
+            b.hit_tops = a.take<unsigned long long>(HIT_SUBS * HIT_TOP_STRIDE);
         }
     };
     auto transient = [&](Arena& a) {
@@ -577,8 +579,8 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
     StageTimer t(SG_RANGES, s);
     SDGR_HIP(launch_tile_ranges(pk[pw], plan->pairs_c, b.status + ST_PAIRS_C, P.tiles_c,
                                 b.ranges, s));
-    SDGR_HIP(launch_pair_masks(b.views, P.nv, plan->pairs_c, P.rp, b.status, pk[pw], pv[pw],
-                               b.crec, b.pmask, b.psum, s));
+    SDGR_HIP(launch_pair_masks(b.views, P.nv, plan->pairs_c, P.rp, P.hit_units == 0, b.status,
+                               pk[pw], pv[pw], b.crec, b.pmask, b.psum, s));
     SDGR_HIP(launch_tile_worklist(b.ranges, P.tiles_c, b.worklist, b.status + WL_BINS, b.status, s));
     return SDGR_OK;
 }
@@ -831,8 +833,13 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
         if (b.hits) {
             rp.hits = b.hits;
             rp.hit_tail = b.hit_tail;
-            rp.hit_top = reinterpret_cast<unsigned long long*>(b.status + ST_HIT_TOP);
+            rp.hit_tops = b.hit_tops;
             rp.hit_cap = (uint32_t)P.hit_units;
+            rp.hit_subs = (uint32_t)std::min<int64_t>(
+                std::max<int64_t>(P.hit_units / HIT_SUB_MIN, 1), HIT_SUBS);
+            rp.hit_sub_cap = rp.hit_cap / rp.hit_subs;
+            SDGR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(b.hit_tops), 0u,
+                                     2 * HIT_SUBS * HIT_TOP_STRIDE, s));
         }
         if (P.det) {
             // one partial per (tile, record) pair, summed per record in list order
@@ -940,7 +947,7 @@ int sdgr_backward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
         // stored hits first (their sums are stored, not added), then the
         // tiles whose hits are re-derived (atomics)
         SDGR_HIP(launch_raster_a_bwd_hits(b.views, P.nv, P.tiles_c, rp, b.status, b.worklist,
-                                          b.crec, b.tau, b.grad_c, P.records, s));
+                                          b.pval[pw], b.crec, b.tau, b.grad_c, P.records, s));
         if (b.hits)
             SDGR_HIP(launch_reduce_touched(plan->pairs_c, P.records, b.status,
                                            b.hit_touched, b.hit_part, b.grad_c, s));

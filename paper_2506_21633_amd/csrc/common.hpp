@@ -92,19 +92,24 @@ struct RasterParams {
     int64_t part_stride = 0;
     // stored hits (null = off): pass A's forward keeps the hits each tile's
     // rays processed, hit group by hit group, in `hits` (hit_cap 16-byte
-    // units, taken in blocks through the counter at status[ST_HIT_TOP]) as a
+    // units in hit_subs equal parts of hit_sub_cap, taken in blocks through
+    // a counter per part, hit_tops[part * HIT_TOP_STRIDE]) as a
     // chain of records whose last one is hit_tail[tile]; the backward walks
     // each chain back to front instead of re-deriving the hits from the
-    // footprint masks. A record is three header units (the previous record
-    // or HIT_NONE and the hit count; the list positions / 64 of the batch's
-    // eight chunks) and then one 8-byte word per hit in processing order
-    // (ray-major, each ray front to back): the record id in bits 0..31, the
-    // ray (cell of the tile) in bits 32..37, the entry's slot in the batch
-    // (chunk * 64 + entry) in bits 40..48.
+    // footprint masks. A record is two header units (the previous record or
+    // HIT_NONE, the hit count, whether it is the first of its batch of chunks
+    // and the record before the previous one; the list positions / 64 of the
+    // batch's four chunks) and then one 2-byte word per hit in processing
+    // order (ray-major, each ray front to back): the entry in bits 0..5, its
+    // chunk in the batch in bits 6..7, the ray (cell of the tile) in bits
+    // 8..13. (8-byte words with the record id spared the backward a load, but
+    // filled the stream four times as fast: 71 MB for 36 views of a
+    // 50k-Gaussian building whose plan has 39, so two thirds of its tiles
+    // re-derived their hits.)
     uint4* hits = nullptr;
     uint32_t* hit_tail = nullptr;
-    unsigned long long* hit_top = nullptr;
-    uint32_t hit_cap = 0;
+    unsigned long long* hit_tops = nullptr;
+    uint32_t hit_cap = 0, hit_subs = 0, hit_sub_cap = 0;
     // the stored-hit backward's output: per list entry it touched, its six
     // sums and its record (plain stores of a row of HIT_PART_STRIDE floats
     // at the pair's position before the pair sort, hit_ppos) and a mark in
@@ -117,7 +122,16 @@ struct RasterParams {
 
 constexpr uint32_t HIT_NONE = 0xFFFFFFFFu;       // chain end / a tile with no hits
 constexpr uint32_t HIT_OVERFLOW = 0xFFFFFFFEu;   // the stream was full: backward re-derives
-constexpr uint32_t HIT_HEADER_UNITS = 3;
+constexpr uint32_t HIT_HEADER_UNITS = 2;
+// Parts of the stream: one counter for all tiles had them queue for its
+// returning atomics, about 5 ns each (pass A's forward 286 us of which 160 on
+// 9k tiles of 500k Gaussians, 260 us of which 110 on 6k tiles of a 36-view
+// building). 64 parts of at least HIT_SUB_MIN units, each counter in a line
+// of its own; a tile that finds its part full tries the HIT_TRIES - 1 after it.
+constexpr int HIT_SUBS = 64;
+constexpr int HIT_TOP_STRIDE = 16;
+constexpr int64_t HIT_SUB_MIN = 16384;   // 256 KB
+constexpr int HIT_TRIES = 3;
 constexpr int GC_STRIDE = 8;   // floats per record in grad_c and grad_i
 constexpr int HIT_PART_STRIDE = 8;   // floats per pair partial: six sums, the record, spare
 
@@ -140,7 +154,6 @@ enum StatusSlot : int {
     ST_PAIRS_I = 2,    // imaging-plane pairs of records with nonzero intensity
     ST_WORK_TILES = 4, // non-empty computation-plane tiles in the worklist
     ST_ACTIVE = 5,     // records pass A used (backward list length)
-    ST_HIT_TOP = 6,    // u64 (words 6, 7): 16-byte units of the hit stream taken so far
     ST_COUNT = 8       // u64 pair totals of the projection at status + 8
 };
 
@@ -299,40 +312,65 @@ __device__ inline uint32_t block_excl_scan_256(uint32_t v, uint32_t* s_w, uint32
     return off + inc - v;
 }
 
+// Float to unsigned with the hardware's saturation (negative values and NaN
+// give 0; the language leaves both undefined).
+__device__ __forceinline__ uint32_t sat_u32(float x)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
 // Cells of tile (tx, ty) inside the ellipse q < q_max of a Gaussian with
 // centre (cx, cy) and conic (a, b, c): per row the column span from the
 // quadratic, widened by a slack that covers the rounding of the hardware
 // reciprocal and square root, so the mask holds every cell whose FP32 q is
-// below q_max (callers test q itself). Bit 8 * row + col.
+// below q_max (callers test q itself). Bit 8 * row + col. The eight rows are
+// all instruction issue (the masks of 25M pairs ran at two thirds of the
+// VALU's rate), so a row's cells lo..e-1 are two saturating conversions and
+// two bit-field masks, and a row out of reach is a negative square root's
+// NaN, which converts to none. TIGHT: the cells in which a row out of reach
+// by rounding counts as touching in its middle, and the slack is cut at whole
+// columns; without it (fewer instructions) a few more cells just outside.
+template <bool TIGHT>
 __device__ inline uint64_t footprint_mask(float cx, float cy, float a, float b, float c, float qm,
-                                   int tx, int ty)
+                                          int tx, int ty)
 {
     const float det = a * c - b * b;
     if (!(det > 0.0f) || !(a > 0.0f)) return 0ull;
     const float slack = 1e-3f;
     const float ia = __builtin_amdgcn_rcpf(a);
     const float aq = a * qm, dmin = -1e-4f * aq;
-    // rows 0-3 and 4-7 in two 32-bit words, each row's cells j0..j1 as 8
-    // bits without a branch (none when the row is out of reach)
-    uint32_t m[2] = {0u, 0u};
-    const float x0 = (float)(tx * TILE) + 0.5f;
+    uint32_t m[2] = {0u, 0u};   // rows 0-3 and 4-7
+    const float x0 = (float)(tx * TILE) + 0.5f, y0 = (float)(ty * TILE) + 0.5f;
+    const float sx = -b * ia, rx = cx - x0 + 1.0f, ry = y0 - cy, aqw = aq - dmin;
 #pragma unroll
     for (int k = 0; k < TILE; ++k) {
-        const float dy = (float)(ty * TILE + k) + 0.5f - cy;
-        const float D = aq - det * dy * dy;
-        const float half = __builtin_amdgcn_sqrtf(fmaxf(D, 0.0f)) * ia + slack;
-        const float xc = cx - b * ia * dy;
-        // local columns j with |x0 + j - xc| <= half
-        const float lo = fmaxf(ceilf(xc - half - x0), 0.0f);
-        const float hi = fminf(floorf(xc + half - x0), (float)(TILE - 1));
-        const bool reach = !(D < dmin) && lo <= hi;
-        const uint32_t j0 = reach ? (uint32_t)lo : 8u, j1 = reach ? (uint32_t)hi : 0u;
-        const uint32_t row = (0xFFu << j0) & (0xFFu >> (7u - j1)) & 0xFFu;
-        m[k >> 2] |= row << (TILE * (k & 3));
+        uint32_t lo, e;   // local columns lo <= j < e
+        if constexpr (TIGHT) {
+            const float dy = y0 + (float)k - cy;
+            const float D = aq - det * dy * dy;
+            const float half =
+                __builtin_amdgcn_sqrtf(D < dmin ? -1.0f : fmaxf(D, 0.0f)) * ia + slack;
+            const float xc = cx - b * ia * dy;
+            lo = sat_u32(ceilf(xc - half - x0));
+            e = sat_u32(floorf(xc + half - x0) + 1.0f);
+        } else {
+            const float dy = ry + (float)k;
+            const float half = __builtin_amdgcn_sqrtf(aqw - det * dy * dy) * ia + slack;
+            const float x1 = sx * dy + rx;   // the centre's column, plus 1
+            lo = sat_u32(x1 - half);
+            e = sat_u32(x1 + half);
+        }
+        lo = min(lo, (uint32_t)TILE);
+        e = min(e, (uint32_t)TILE);
+        constexpr int B = TILE;
+        const uint32_t below = ((1u << lo) - 1u) << (B * (k & 3));
+        const uint32_t upto = ((1u << e) - 1u) << (B * (k & 3));
+        m[k >> 2] |= upto & ~below;
     }
     return ((uint64_t)m[1] << 32) | m[0];
 }
-
 
 }  // namespace sdgr
 
@@ -448,7 +486,10 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_or_word(const uint32_t* src, uint32_t* dst, hipStream_t s);
 hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t s);
 
+// tight: the masks whose hits the re-deriving backward and the deterministic
+// sums go by (see footprint_mask)
 hipError_t launch_pair_masks(const DevView* views, int nv, int64_t cap_c, const RasterParams& rp,
+                             bool tight,
                              const uint32_t* status, const uint32_t* pkey,
                              const uint32_t* pvals, const CRec* crec,
                              uint64_t* pmask, uint64_t* psum, hipStream_t s);
@@ -484,9 +525,9 @@ hipError_t launch_image_bwd(const DevView* views, const DevScene* scenes, int nv
 // records with one tile
 hipError_t launch_raster_a_bwd_hits(const DevView* views, int nv, int64_t tiles_c,
                                     const RasterParams& rp, const uint32_t* status,
-                                    const uint32_t* worklist, const CRec* crec,
-                                    const float* tau, float* grad_c, int64_t stride,
-                                    hipStream_t s);
+                                    const uint32_t* worklist, const uint32_t* pvals,
+                                    const CRec* crec, const float* tau, float* grad_c,
+                                    int64_t stride, hipStream_t s);
 // the other tiles (all without stored hits), adding into grad_c with atomics
 hipError_t launch_raster_a_bwd(const DevView* views, int nv, int64_t tiles_c,
                                const RasterParams& rp, const uint32_t* status,

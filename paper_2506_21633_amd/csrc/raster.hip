@@ -73,15 +73,15 @@ __device__ __forceinline__ uint32_t xor_lane(uint32_t v)
         const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
         return (lane & 16) ? r[0] : r[1];
     } else if constexpr (S == 8) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);
     } else if constexpr (S == 4) {
         const uint32_t from_below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
         const uint32_t from_above = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0xF, false);
         return (lane & 4) ? from_below : from_above;
     } else if constexpr (S == 2) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
     } else {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
     }
 }
 
@@ -141,7 +141,7 @@ __device__ __forceinline__ uint32_t transpose_bits(uint32_t x, uint32_t keep, ui
         r = xor_lane<S>(x);
     }
     r = __builtin_amdgcn_alignbit(r, r, rot);
-    return r ^ (keep & (x ^ r));   // one bit-field insert
+    return (x & keep) | (r & ~keep);   // one three-operand bit operation
 }
 
 template <int N>
@@ -317,6 +317,40 @@ __device__ __forceinline__ void wait_all_memory()
     __builtin_amdgcn_s_waitcnt(0);
 }
 
+// Gather of one 32-byte record per lane (every lane takes part, each with a
+// valid id). A lane's two 16-byte loads would touch one line twice, and the L1
+// stalls on a line that is still in flight, so the lanes of a pair load the
+// two halves of the even lane's record, then those of the odd lane's: both
+// halves of a line in one instruction, and swap what belongs to the other.
+__device__ __forceinline__ float4 dpp_pair_swap(float4 v)
+{
+    return make_float4(__uint_as_float(xor_lane<1>(__float_as_uint(v.x))),
+                       __uint_as_float(xor_lane<1>(__float_as_uint(v.y))),
+                       __uint_as_float(xor_lane<1>(__float_as_uint(v.z))),
+                       __uint_as_float(xor_lane<1>(__float_as_uint(v.w))));
+}
+
+struct RecPair { float4 a, b; };   // halves of the even and of the odd lane's record
+
+__device__ __forceinline__ RecPair load_rec_pair(const CRec* __restrict__ crec, uint32_t id)
+{
+    const uint32_t ie = (uint32_t)__builtin_amdgcn_mov_dpp((int)id, 0xA0, 0xF, 0xF, true);
+    const uint32_t io = (uint32_t)__builtin_amdgcn_mov_dpp((int)id, 0xF5, 0xF, 0xF, true);
+    const float4* base = reinterpret_cast<const float4*>(crec);
+    const uint32_t half = (uint32_t)lane_id() & 1u;
+    return RecPair{base[2u * (uint64_t)ie + half], base[2u * (uint64_t)io + half]};
+}
+
+__device__ __forceinline__ CRec own_rec(const RecPair& p)
+{
+    const bool odd = (lane_id() & 1) != 0;
+    auto pick = [&](const float4& x, const float4& y) {
+        return make_float4(odd ? x.x : y.x, odd ? x.y : y.y, odd ? x.z : y.z, odd ? x.w : y.w);
+    };
+    const float4 other = dpp_pair_swap(pick(p.a, p.b));
+    return CRec{pick(other, p.a), pick(p.b, other)};
+}
+
 struct TileCell {
     int v;
     int tx, ty;
@@ -372,6 +406,7 @@ __device__ __forceinline__ TileCell tile_cell_i(const DevView* views, int nv, ui
 // reads in flight.
 constexpr int PM_ITEMS = 4;
 
+template <bool TIGHT>
 __global__ void __launch_bounds__(256)
 k_pair_masks(const DevView* __restrict__ views, int nv, int64_t cap, RasterParams rp,
              const uint32_t* __restrict__ status, const uint32_t* __restrict__ pkey,
@@ -390,26 +425,22 @@ k_pair_masks(const DevView* __restrict__ views, int nv, int64_t cap, RasterParam
         bucket[k] = p < kc ? pkey[p] : 0u;
         r[k] = p < kc ? pvals[p] : 0u;
     }
-    float4 g[PM_ITEMS], g2[PM_ITEMS];
+    RecPair g[PM_ITEMS];
 #pragma unroll
-    for (int k = 0; k < PM_ITEMS; ++k) {
-        if (base + k * 256 < kc) {
-            g[k] = crec[r[k]].q;
-            g2[k] = crec[r[k]].w;
-        }
-    }
+    for (int k = 0; k < PM_ITEMS; ++k) g[k] = load_rec_pair(crec, r[k]);   // (record 0 past the end)
 #pragma unroll
     for (int k = 0; k < PM_ITEMS; ++k) {
         const int64_t p = base + k * 256;
         if (p - lane_id() >= kc) break;   // this and later chunks of the wave are past the end
         uint64_t m = 0ull;
+        const CRec rec = own_rec(g[k]);
         if (p < kc) {
             const int v = find_view(nv, (int64_t)bucket[k],
                                     [&](int j) { return (int64_t)views[j].tile_c; });
             const DevView& V = views[v];
             const int local = (int)(bucket[k] - (uint32_t)V.tile_c);
-            m = footprint_mask(g[k].x, g[k].y, g[k].z, g[k].w, g2[k].x, rp.q_max, local % V.txc,
-                               local / V.txc);
+            m = footprint_mask<TIGHT>(rec.q.x, rec.q.y, rec.q.z, rec.q.w, rec.w.x, rp.q_max,
+                                      local % V.txc, local / V.txc);
             pmask[p] = m;
         }
         const uint32_t olo = or_scan_u32((uint32_t)m), ohi = or_scan_u32((uint32_t)(m >> 32));
@@ -431,10 +462,23 @@ k_pair_masks(const DevView* __restrict__ views, int nv, int64_t cap, RasterParam
 // however the hits are spread over the rays. Per-entry sums collect in LDS
 // and leave with one global atomic per (tile, entry).
 constexpr int A_BATCH = 4;
+// Hits of a compaction group: all of a batch's when at most half of these
+// are left, else each ray's next GROUP_RAY.
+constexpr uint32_t GROUP_RAY = 16;
+constexpr uint32_t GROUP_HITS = WAVE * GROUP_RAY;
+// Chunks of a batch where hits are stored (and entry slots of the backward).
+constexpr int HB_CHUNKS = 4;
+constexpr int HB_SLOTS = HB_CHUNKS * WAVE;
+constexpr int HB_CHUNK_BITS = 2, HB_RAY_SHIFT = 6 + HB_CHUNK_BITS;
+static_assert(HB_CHUNKS == 1 << HB_CHUNK_BITS, "chunk index bits of a stored hit");
 
-// DET: deterministic mode (per-pair partials at their pre-sort positions)
-template <bool DET>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(1, 2)))
+// DET: deterministic mode (per-pair partials at their pre-sort positions).
+// HITS: the hits are stored for the backward. Only then may a group be cut by
+// ray: without stored hits the backward takes a ray's hits to be those in
+// front of its last used entry, with the optical depth this kernel's sums
+// give, so there the groups stay whole chunks of up to 4096 hits.
+template <bool DET, bool HITS>
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(1, HITS ? 8 : 2)))
 k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                const uint32_t* __restrict__ status, const uint32_t* __restrict__ worklist,
                const uint2* __restrict__ ranges, const uint32_t* __restrict__ pvals,
@@ -442,22 +486,21 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                const CRec* __restrict__ crec,
                float* __restrict__ A, float* __restrict__ tau, uint32_t* __restrict__ nlast)
 {
-    constexpr int NB = 2 * A_BATCH;   // the forward keeps less per chunk in LDS
-    constexpr int HKB = NB <= 8 ? 3 : 4;   // bits of a hit's chunk index
+    constexpr int NB = HITS ? HB_CHUNKS : 2 * A_BATCH;
+    constexpr int HKB = NB == 4 ? 2 : 3;   // bits of a hit's chunk index
     constexpr int HRS = 6 + HKB;           // shift of a hit's ray index
-    static_assert(NB <= 16, "hits are packed in 16 bits");
-    static_assert(NB == 8, "stored-hit records carry eight chunk ids");
+    static_assert(NB == 4 || NB == 8, "chunk index bits");
+    static_assert(!HITS || NB <= 4 * ((int)HIT_HEADER_UNITS - 1), "chunk ids of a stored-hit record");
     __shared__ float4 s_q[NB][WAVE];
     __shared__ float s_wc[NB][WAVE], s_wk[NB][WAVE];   // conic c and extinction
     // per-entry sums in GC copies picked by ray (as in the backward; one
     // atomic per hit conflicts little enough that one copy is fastest here)
     constexpr int GC = 1;
-    __shared__ float s_A[GC][NB][WAVE + 1];
-    __shared__ uint64_t s_m[NB][WAVE];
-    __shared__ uint32_t s_r[NB][WAVE];        // record of each entry (stored hits)
+    __shared__ double s_A[GC][NB][WAVE + 1];
     __shared__ uint32_t s_chk[NB];
-    __shared__ uint16_t s_hit[WAVE * WAVE];   // (ray, chunk, entry) packed, ray-major
-    // per ray during a chunk: first hit in s_hit, optical depth, transmittance,
+    constexpr uint32_t GROUP_MAX = HITS ? GROUP_HITS : WAVE * WAVE;
+    __shared__ uint16_t s_hit[GROUP_MAX];     // (ray, chunk, entry) packed, ray-major
+    // per ray during a group: first hit in s_hit, optical depth, transmittance,
     // last list position used (one 16-byte read per hit)
     struct alignas(16) RayF { uint32_t o; float t, T; uint32_t last; };
     __shared__ RayF s_ray[WAVE];
@@ -472,12 +515,11 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
 #pragma unroll
     for (int g = 0; g < GC; ++g)
 #pragma unroll
-        for (int k = 0; k < NB; ++k) s_A[g][k][lane] = 0.0f;
+        for (int k = 0; k < NB; ++k) s_A[g][k][lane] = 0.0;
     float T = 1.0f, t = 0.0f;
     bool alive = tc.inside;
     uint32_t last = 0;
-    unsigned long long n_iter = 0, n_hits = 0;   // work counters
-    unsigned long long n_batch = 0, n_group = 0;
+    uint32_t n_iter = 0, n_hits = 0, n_batch = 0, n_extra = 0;   // work counters
     uint64_t live = __ballot(alive);
     // per-entry sums of the last processed batch leave with one atomic each;
     // they are sent once the next batch's loads have landed, so the wait for
@@ -488,8 +530,10 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     // has room; h_prev becomes HIT_OVERFLOW when it runs out), the block of
     // the stream the tile writes into [h_top, h_end) and the block size it
     // takes next, the current record and its hit count
-    bool h_on = !DET && rp.hits != nullptr;
-    uint32_t h_top = 0u, h_end = 0u, h_blk = 256u, h_prev = HIT_NONE, h_rec = 0u, h_kept = 0u;
+    bool h_on = HITS;
+    uint32_t h_top = 0u, h_end = 0u, h_blk = 128u, h_prev = HIT_NONE, h_rec = 0u, h_kept = 0u;
+    uint32_t h_prev2 = HIT_NONE;   // the record before h_prev
+    uint32_t h_sub = HITS ? blockIdx.x % rp.hit_subs : 0u;   // part of the stream
     // (a nonzero sum means a live ray hit the entry, so its record was
     // gathered and r_prev holds it: all eight sums are read at once, without
     // a branch per chunk)
@@ -497,14 +541,15 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
         float a[NB];
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-            a[k] = 0.0f;
+            double sum = 0.0;
 #pragma unroll
-            for (int g = 0; g < GC; ++g) a[k] += s_A[g][k][lane];
+            for (int g = 0; g < GC; ++g) sum += s_A[g][k][lane];
+            a[k] = (float)sum;
         }
 #pragma unroll
         for (int k = 0; k < NB; ++k)
 #pragma unroll
-            for (int g = 0; g < GC; ++g) s_A[g][k][lane] = 0.0f;
+            for (int g = 0; g < GC; ++g) s_A[g][k][lane] = 0.0;
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             if (a[k] != 0.0f) {
@@ -547,35 +592,32 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
         while (nb_n > 0 && live != 0ull) {
             ++n_batch;
             const int nb = nb_n;
-            {
-                uint32_t chk[NB];
-                uint64_t m[NB];
-                uint32_t* r = r_cur;
+            // the batch's chunks; col[k] is first lane = entry (the cells it
+            // covers), then transposed to lane = ray (the entries covering it)
+            uint64_t col[NB];
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    chk[k] = chk_n[k];
-                    m[k] = m_n[k];
-                    r[k] = r_n[k];
-                    if constexpr (DET) d_cur[k] = d_n[k];
-                }
-                // records straight into LDS, all in flight together (entries
-                // no live ray needs read record 0, one shared line)
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const bool need = (m[k] & live) != 0ull;
-                    const uint32_t rk = need ? r[k] : 0u;
-                    const float* w = reinterpret_cast<const float*>(&crec[rk].w);
-                    load16_to_lds(&crec[rk].q, &s_q[k][0]);
-                    load4_to_lds(w, &s_wc[k][0]);
-                    load4_to_lds(w + 1, &s_wk[k][0]);
-                }
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    s_m[k][lane] = m[k];
-                    if (h_on) s_r[k][lane] = r[k];
-                    if (lane == k) s_chk[k] = chk[k];
-                }
+            for (int k = 0; k < NB; ++k) {
+                col[k] = m_n[k];
+                r_cur[k] = r_n[k];
+                if constexpr (DET) d_cur[k] = d_n[k];
             }
+            // records straight into LDS, all in flight together (entries no
+            // live ray needs read record 0, one shared line)
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const bool need = (col[k] & live) != 0ull;
+                const uint32_t rk = need ? r_cur[k] : 0u;
+                const float* w = reinterpret_cast<const float*>(&crec[rk].w);
+                load16_to_lds(&crec[rk].q, &s_q[k][0]);
+                load4_to_lds(w, &s_wc[k][0]);
+                load4_to_lds(w + 1, &s_wk[k][0]);
+                if (lane == k) s_chk[k] = chk_n[k];
+            }
+            // the transposes run while the records come in; rays already out
+            // of play and unused chunk slots keep no hits
+            transpose64_n(col, tl);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) col[k] = (k < nb && alive) ? col[k] : 0ull;
             wait_all_memory();
             wave_lds_sync();
             fetch();   // the next batch's masks and values
@@ -585,19 +627,9 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                 r_prev[k] = r_cur[k];
                 if constexpr (DET) d_prev[k] = d_cur[k];
             }
-            // the batch's chunks, transposed: bit j of col[k] is entry j of
-            // chunk k covering my cell (rays already out of play keep none)
-            uint64_t col[NB];
-            uint32_t hk[NB];   // hits of each chunk over the wave
-            // every chunk slot is transposed (the unused ones' stale masks are
-            // dropped), all eight together; the chunks' hit totals (at most
-            // 4096 each) are summed two to a word
-#pragma unroll
-            for (int k = 0; k < NB; ++k) col[k] = s_m[k][lane];
-            transpose64_n(col, tl);
-#pragma unroll
-            for (int k = 0; k < NB; ++k) col[k] = (k < nb && alive) ? col[k] : 0ull;
-            {
+            uint32_t hk[HITS ? 1 : NB];   // hits of each chunk over the wave
+            if constexpr (!HITS) {
+                // (at most 4096 each: summed two to a word)
                 uint32_t tot[NB / 2];
 #pragma unroll
                 for (int i = 0; i < NB / 2; ++i)
@@ -610,174 +642,214 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                     hk[2 * i + 1] = tot[i] >> 16;
                 }
             }
-            if (h_on) {
-                // room for the batch's records, one per hit group (so that no
-                // ray's hits interleave with another group's in a record):
-                // their headers and at most every hit; a new block when the
-                // tile's is short (sizes doubling up to 64 KB, so short tiles
-                // waste little and long ones seldom ask)
-                uint32_t H = 0u;
+            // The batch's hits in groups, compacted ray-major (front to back
+            // along each ray) and taken 64 per round. Stored hits: all that
+            // are left when they are few, else each ray's next GROUP_RAY;
+            // after each group the rays that reached tau_max drop their
+            // remaining hits, so dense lists do not compact and evaluate what
+            // lies behind. Otherwise consecutive chunks whose hits fit s_hit.
+            bool fresh = true;   // no record of this batch is stored yet
+            int g0 = 0, g1 = NB;
+            for (uint32_t group = 0;; ++group) {
+                uint32_t nr = 0, H, o, o_end;
+                if constexpr (HITS) {
 #pragma unroll
-                for (int k = 0; k < NB; ++k) H += hk[k];
-                const uint32_t units = NB * (HIT_HEADER_UNITS + 1u) + (H + 1u) / 2u;
-                if (h_end - h_top < units) {
-                    const uint32_t take = max(units, h_blk);
-                    h_blk = min(2u * h_blk, 4096u);
-                    unsigned long long base = 0ull;
-                    if (lane == 0) base = atomicAdd(rp.hit_top, (unsigned long long)take);
-                    base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
-                                (int)(uint32_t)(base >> 32)) << 32) |
-                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
-                    if (base + take > (unsigned long long)rp.hit_cap) {
-                        h_on = false;
-                        h_prev = HIT_OVERFLOW;
-                    } else {
-                        h_top = (uint32_t)base;
-                        h_end = h_top + take;
-                    }
-                }
-            }
-            // groups of consecutive chunks whose hits fit s_hit; each group's
-            // hits are compacted ray-major (chunk by chunk, front to back) and
-            // taken 64 per round
-            for (int g0 = 0; g0 < nb && live != 0ull;) {
-                ++n_group;
-                h_rec = h_top;
-                h_kept = 0u;
-                int g1 = g0;
-                uint32_t H = 0;
-                bool open = true;
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    if (k < g0 || k >= nb || !open) continue;
-                    if (H + hk[k] <= (uint32_t)(WAVE * WAVE)) {
-                        H += hk[k];
-                        g1 = k + 1;
-                    } else {
-                        open = false;
-                    }
-                }
-                uint32_t nr = 0;
-#pragma unroll
-                for (int k = 0; k < NB; ++k)
-                    if (k >= g0 && k < g1) nr += (uint32_t)__popcll(col[k]);
-                const uint32_t o = wave_excl_scan_u32(nr);
-                if (H > 0u) {
-                    uint32_t w = o;
+                    for (int k = 0; k < NB; ++k) nr += (uint32_t)__popcll(col[k]);
+                    if (__ballot(nr != 0u) == 0ull) break;
+                    // hits left and hits of a limited group, scanned together
+                    // (at most 64 x 512 and 64 x GROUP_RAY: two to a word)
+                    const uint32_t lim = min(nr, GROUP_RAY);
+                    const uint32_t both = nr | (lim << 16);
+                    const uint32_t ex = wave_excl_scan_u32(both);
+                    const uint32_t tot =
+                        (uint32_t)__builtin_amdgcn_readlane((int)(ex + both), WAVE - 1);
+                    const bool few = (tot & 0xFFFFu) <= GROUP_HITS / 2;
+                    H = few ? (tot & 0xFFFFu) : (tot >> 16);
+                    o = few ? (ex & 0xFFFFu) : (ex >> 16);
+                    o_end = o + (few ? nr : lim);
+                } else {
+                    if (g0 >= nb || live == 0ull) break;
+                    H = 0u;
+                    bool open = true;
 #pragma unroll
                     for (int k = 0; k < NB; ++k) {
-                        if (k < g0 || k >= g1) continue;
-                        uint64_t c = col[k];
-                        while (c != 0ull) {
-                            const int j = __builtin_ctzll(c);
-                            c &= c - 1ull;
-                            s_hit[w++] = (uint16_t)((lane << HRS) | (k << 6) | j);
+                        if (k < g0 || k >= nb || !open) continue;
+                        if (H + hk[k] <= GROUP_MAX) {
+                            H += hk[k];
+                            g1 = k + 1;
+                        } else {
+                            open = false;
                         }
                     }
-                    s_ray[lane] = RayF{o, t, T, last};
-                    wave_lds_sync();
-                    for (uint32_t base = 0; base < H; base += WAVE) {
-                        ++n_iter;
-                        const uint32_t L = base + lane;
-                        const bool valid = L < H;
-                        const uint32_t hv = valid ? (uint32_t)s_hit[L] : 0u;
-                        const int rr = (int)(hv >> HRS), k = (int)((hv >> 6) & ((1u << HKB) - 1u)),
-                                  j = (int)(hv & 63u);
-                        // ray state and entry record, read together (lanes past
-                        // the last hit read entry 0 of ray 0 and ignore it)
-                        const RayF rs = s_ray[rr];
-                        const float4 g = s_q[k][j];
-                        const float gc = s_wc[k][j], gk = s_wk[k][j];
-                        const uint32_t pos = s_chk[k] * WAVE + (uint32_t)j - rg.x;   // list position
-                        const int seg0 = valid ? max((int)rs.o - (int)base, 0) : lane;
-                        bool real = false;
-                        float x = 0.0f, E = 1.0f;
-                        if (valid) {
-                            const float dx = x0 + (float)(rr & (TILE - 1)) - g.x;
-                            const float dy = y0 + (float)(rr / TILE) - g.y;
-                            const float q = quadform(g, gc, dx, dy);
-                            if (q < rp.q_max) {
-                                real = true;
-                                x = gk * ((__expf(-0.5f * q) - rp.eps) * rp.inv1meps);
-                                E = __expf(-x);
+#pragma unroll
+                    for (int k = 0; k < NB; ++k)
+                        if (k >= g0 && k < g1) nr += (uint32_t)__popcll(col[k]);
+                    o = wave_excl_scan_u32(nr);
+                    o_end = o + nr;
+                }
+                if (group > 0) ++n_extra;
+                if (h_on) {
+                    // room for the group's record (header and at most every
+                    // hit); a new block when the tile's is short (sizes
+                    // doubling up to 16 KB, so short tiles waste little and
+                    // long ones seldom ask), from the tile's part of the
+                    // stream or one of the next ones (never an earlier one:
+                    // a tile's records lie in increasing order)
+                    const uint32_t units = HIT_HEADER_UNITS + (H + 7u) / 8u;
+                    if (h_end - h_top < units) {
+                        const uint32_t take = max(units, h_blk);
+                        h_blk = min(2u * h_blk, 1024u);
+                        h_on = false;
+                        for (int k = 0; k < HIT_TRIES && h_sub < rp.hit_subs; ++k, ++h_sub) {
+                            unsigned long long base = 0ull;
+                            if (lane == 0)
+                                base = atomicAdd(&rp.hit_tops[h_sub * HIT_TOP_STRIDE],
+                                                 (unsigned long long)take);
+                            base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
+                                        (int)(uint32_t)(base >> 32)) << 32) |
+                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
+                            if (base + take <= rp.hit_sub_cap) {
+                                h_on = true;
+                                h_top = h_sub * rp.hit_sub_cap + (uint32_t)base;
+                                h_end = h_top + take;
+                                break;
                             }
                         }
-                        const float incl = seg_incl_scan(x, lane == seg0);
-                        const float excl = incl - x;
-                        const float tr = valid ? rs.t : 0.0f;
-                        const float Tr = valid ? rs.T : 1.0f;
-                        // a ray's hits are processed up to the first one reached
-                        // with an optical depth of tau_max (a prefix of its segment)
-                        const uint64_t stop =
-                            __ballot(valid && rp.shadowing && !(tr + excl < rp.tau_max));
-                        const uint64_t after = stop & (~0ull << seg0);
-                        const bool proc = valid && (after == 0ull || lane < __builtin_ctzll(after));
-                        if (h_on) {
-                            // the processed hits, in processing order: record,
-                            // ray and the entry's slot in the batch
-                            const uint64_t kb = __ballot(proc);
-                            if (proc)
-                                reinterpret_cast<unsigned long long*>(
-                                    rp.hits + h_rec + HIT_HEADER_UNITS)[h_kept + lanes_below(kb)] =
-                                    (unsigned long long)s_r[k][j] | ((unsigned long long)rr << 32) |
-                                    ((unsigned long long)(k * WAVE + j) << 40);
-                            h_kept += (uint32_t)__popcll(kb);
-                        }
-                        if (proc && real) {
-                            // at least FLT_MIN, so that A > 0 marks exactly the
-                            // records some ray used (the exact alpha T is > 0
-                            // for every footprint hit)
-                            const float a = fmaxf(
-                                (1.0f - E) * (rp.shadowing ? Tr * __expf(-excl) : 1.0f), FLT_MIN);
-                            atomicAdd(&s_A[(rr + (rr >> 3)) & (GC - 1)][k][j], a);
-                        }
-                        const uint64_t hb = __ballot(proc && real);
-                        if (lane == 0) n_hits += (unsigned long long)__popcll(hb);
-                        // the last processed hit of each ray in this round updates the ray
-                        const int nxt = from_lane_above(proc ? (int)hv : -1);
-                        const bool endseg = proc && (lane == WAVE - 1 || (nxt >> HRS) != rr);
-                        wave_lds_sync();
-                        if (endseg)
-                            s_ray[rr] = RayF{rs.o, tr + incl, rp.shadowing ? Tr * __expf(-incl) : Tr,
-                                             pos + 1u};
-                        wave_lds_sync();
+                        if (!h_on) h_prev = HIT_OVERFLOW;
                     }
-                    {
-                        const RayF rs = s_ray[lane];
-                        t = rs.t;
-                        T = rs.T;
-                        last = rs.last;
+                }
+                h_rec = h_top;
+                h_kept = 0u;
+                uint32_t w = o;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    if (!HITS && (k < g0 || k >= g1)) continue;
+                    uint32_t half[2] = {(uint32_t)col[k], (uint32_t)(col[k] >> 32)};
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const uint32_t tag = (uint32_t)((lane << HRS) | (k << 6) | (q << 5));
+                        while (half[q] != 0u && w < o_end) {
+                            const uint32_t j = (uint32_t)__builtin_ctz(half[q]);
+                            half[q] &= half[q] - 1u;
+                            s_hit[w++] = (uint16_t)(tag | j);
+                        }
                     }
-                    if (rp.shadowing && t >= rp.tau_max) alive = false;
-                    live = __ballot(alive);
+                    col[k] = ((uint64_t)half[1] << 32) | half[0];
+                }
+                s_ray[lane] = RayF{o, t, T, last};
+                wave_lds_sync();
+                for (uint32_t base = 0; base < H; base += WAVE) {
+                    ++n_iter;
+                    const uint32_t L = base + lane;
+                    const bool valid = L < H;
+                    const uint32_t hv = valid ? (uint32_t)s_hit[L] : 0u;
+                    const int rr = (int)(hv >> HRS), k = (int)((hv >> 6) & ((1u << HKB) - 1u)),
+                              j = (int)(hv & 63u);
+                    // ray state and entry record, read together (lanes past
+                    // the last hit read entry 0 of ray 0 and ignore it)
+                    const RayF rs = s_ray[rr];
+                    const float4 g = s_q[k][j];
+                    const float gc = s_wc[k][j], gk = s_wk[k][j];
+                    const uint32_t pos = s_chk[k] * WAVE + (uint32_t)j - rg.x;   // list position
+                    const int seg0 = valid ? max((int)rs.o - (int)base, 0) : lane;
+                    bool real = false;
+                    float x = 0.0f, E = 1.0f;
+                    if (valid) {
+                        const float dx = x0 + (float)(rr & (TILE - 1)) - g.x;
+                        const float dy = y0 + (float)(rr / TILE) - g.y;
+                        const float q = quadform(g, gc, dx, dy);
+                        if (q < rp.q_max) {
+                            real = true;
+                            x = gk * ((__expf(-0.5f * q) - rp.eps) * rp.inv1meps);
+                            E = __expf(-x);
+                        }
+                    }
+                    const float incl = seg_incl_scan(x, lane == seg0);
+                    const float excl = incl - x;
+                    const float tr = valid ? rs.t : 0.0f;
+                    const float Tr = valid ? rs.T : 1.0f;
+                    // a ray's hits are processed up to the first one reached
+                    // with an optical depth of tau_max (a prefix of its segment)
+                    const uint64_t stop =
+                        __ballot(valid && rp.shadowing && !(tr + excl < rp.tau_max));
+                    const uint64_t after = stop & (~0ull << seg0);
+                    const bool proc = valid && (after == 0ull || lane < __builtin_ctzll(after));
+                    if (h_on) {
+                        // the processed hits, in processing order
+                        const uint64_t kb = __ballot(proc);
+                        if (proc)
+                            reinterpret_cast<uint16_t*>(
+                                rp.hits + h_rec + HIT_HEADER_UNITS)[h_kept + lanes_below(kb)] =
+                                (uint16_t)hv;
+                        h_kept += (uint32_t)__popcll(kb);
+                    }
+                    if (proc && real) {
+                        // at least FLT_MIN, so that A > 0 marks exactly the
+                        // records some ray used (the exact alpha T is > 0
+                        // for every footprint hit)
+                        const float a = fmaxf(
+                            (1.0f - E) * (rp.shadowing ? Tr * __expf(-excl) : 1.0f), FLT_MIN);
+                        atomicAdd(&s_A[(rr + (rr >> 3)) & (GC - 1)][k][j], (double)a);
+                    }
+                    n_hits += (uint32_t)__popcll(__ballot(proc && real));
+                    // the last processed hit of each ray in this round updates the ray
+                    const int nxt = from_lane_above(proc ? (int)hv : -1);
+                    const bool endseg = proc && (lane == WAVE - 1 || (nxt >> HRS) != rr);
+                    float tn = tr + incl;
+                    if constexpr (HITS) {
+                        // stopped in front of a further hit of its own: done,
+                        // also where this sum rounds to just below tau_max
+                        const int fol = from_lane_above(valid ? (int)hv : -1);
+                        if (lane < WAVE - 1 && (fol >> HRS) == rr && rp.shadowing)
+                            tn = fmaxf(tn, rp.tau_max);
+                    }
+                    wave_lds_sync();
+                    if (endseg)
+                        s_ray[rr] = RayF{rs.o, tn, rp.shadowing ? Tr * __expf(-incl) : Tr,
+                                         pos + 1u};
                     wave_lds_sync();
                 }
+                {
+                    const RayF rs = s_ray[lane];
+                    t = rs.t;
+                    T = rs.T;
+                    last = rs.last;
+                }
+                if (rp.shadowing && t >= rp.tau_max) {
+                    alive = false;
+                    if constexpr (HITS) {
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) col[k] = 0ull;
+                    }
+                }
+                live = __ballot(alive);
+                g0 = g1;
+                wave_lds_sync();
                 if (h_on && h_kept > 0u) {   // the group's record
-                    if (lane == 0) rp.hits[h_rec] = make_uint4(h_prev, h_kept, 0u, 0u);
+                    if (lane == 0)
+                        rp.hits[h_rec] = make_uint4(h_prev, h_kept, fresh ? 1u : 0u, h_prev2);
                     if (lane == 1)
                         rp.hits[h_rec + 1] = make_uint4(s_chk[0], s_chk[1], s_chk[2], s_chk[3]);
-                    if (lane == 2)
-                        rp.hits[h_rec + 2] = make_uint4(s_chk[4], s_chk[5], s_chk[6], s_chk[7]);
+                    h_prev2 = h_prev;
                     h_prev = h_rec;
-                    h_top = h_rec + HIT_HEADER_UNITS + (h_kept + 1u) / 2u;
+                    h_top = h_rec + HIT_HEADER_UNITS + (h_kept + 7u) / 8u;
+                    fresh = false;
                 }
-                g0 = g1;
             }
             wave_lds_sync();
         }
     }
     flush();
-    if (!DET && rp.hits != nullptr && lane == 0) rp.hit_tail[bucket] = h_prev;
+    if (HITS && lane == 0) rp.hit_tail[bucket] = h_prev;
     if (rp.work) {
-        n_hits = wave_sum_u64(n_hits);
         const uint32_t used = wave_max_u32(last);   // list prefix any ray used
         const uint64_t stopped = __ballot(tc.inside && rp.shadowing && t >= rp.tau_max);
         if (lane == 0) {
-            atomicAdd(&rp.work[4], n_iter);
-            atomicAdd(&rp.work[0], n_hits);
+            atomicAdd(&rp.work[4], (unsigned long long)n_iter);
+            atomicAdd(&rp.work[0], (unsigned long long)n_hits);
             atomicAdd(&rp.work[7], (unsigned long long)used);
-            atomicMax(&rp.work[8], n_batch);
-            atomicAdd(&rp.work[10], n_group - n_batch);
+            atomicMax(&rp.work[8], (unsigned long long)n_batch);
+            atomicAdd(&rp.work[10], (unsigned long long)n_extra);
             atomicAdd(&rp.work[12], (unsigned long long)__popcll(stopped));
             atomicMax(&rp.work[13], (unsigned long long)used);
         }
@@ -853,7 +925,7 @@ k_raster_b_fwd(const DevView* __restrict__ views, int nv, RasterParams rp, int64
             s_w[w][lane] = g2;
             const TileCell tk = tile_cell_i(views, nv, key, vm != 0);
             if (g2.y != 0.0f)   // zero intensity adds nothing
-                m = footprint_mask(g.x, g.y, g.z, g.w, g2.x, rp.q_max, tk.tx, tk.ty);
+                m = footprint_mask<false>(g.x, g.y, g.z, g.w, g2.x, rp.q_max, tk.tx, tk.ty);
         }
         wave_lds_sync();
         uint64_t rest = __ballot(in);
@@ -937,7 +1009,7 @@ k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int6
             s_q[w][lane] = g;
             s_w[w][lane] = g2;
             if (g2.y != 0.0f)   // zero intensity adds nothing
-                m = footprint_mask(g.x, g.y, g.z, g.w, g2.x, rp.q_max, tc.tx, tc.ty);
+                m = footprint_mask<false>(g.x, g.y, g.z, g.w, g2.x, rp.q_max, tc.tx, tc.ty);
         }
         wave_lds_sync();
         // the transpose exchanges bits between lanes: every lane takes part,
@@ -1090,12 +1162,12 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
     // per-entry gradient sums in GC copies, picked by ray so that the hits
     // of one entry from neighbouring rays in a round add to different
     // addresses (rows padded by one word: copies and rows differ in bank)
-    constexpr int GC = FLUSHER ? 2 : 1;
+    constexpr int GC = 1;
     // two buffers with the flusher: the second wave of the workgroup sends
     // one batch's sums with atomics while the first accumulates the next
     // batch in the other
     constexpr int GB = FLUSHER ? 2 : 1;
-    __shared__ float s_G[GB][GC][NB][6][WAVE + 1];
+    __shared__ double s_G[GB][GC][NB][6][WAVE + 1];
     __shared__ uint32_t s_rf[GB][FLUSHER ? NB : 1][WAVE];   // records of the handed-off entries
     __shared__ uint32_t s_cmd[GB][WAVE];      // per entry lane: chunks gathered (bits), last flag
     __shared__ uint32_t s_chk[NB];
@@ -1127,12 +1199,13 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                 const uint32_t rk = s_rf[hb][k][fl];
 #pragma unroll
                 for (int c = 0; c < 6; ++c) {
-                    float v = 0.0f;
+                    double sum = 0.0;
 #pragma unroll
                     for (int g = 0; g < GC; ++g) {
-                        v += s_G[hb][g][k][c][fl];
-                        s_G[hb][g][k][c][fl] = 0.0f;
+                        sum += s_G[hb][g][k][c][fl];
+                        s_G[hb][g][k][c][fl] = 0.0;
                     }
+                    const float v = (float)sum;
                     if (v == 0.0f) continue;
                     if constexpr (DET) rp.part[c * rp.part_stride + rk] = v;
                     else unsafeAtomicAdd(&grad_c[(int64_t)rk * GC_STRIDE + c], v);
@@ -1159,7 +1232,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
 #pragma unroll
             for (int k = 0; k < NB; ++k)
 #pragma unroll
-                for (int c = 0; c < 6; ++c) s_G[b][g][k][c][lane] = 0.0f;
+                for (int c = 0; c < 6; ++c) s_G[b][g][k][c][lane] = 0.0;
     unsigned long long n_iter = 0, n_hits = 0;   // work counters
     unsigned long long n_batch = 0, n_group = 0;
     const uint32_t n_max = wave_max_u32(n_mine);
@@ -1186,8 +1259,8 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                 if (!(got_prev & (1u << k))) continue;
 #pragma unroll
                 for (int c = 0; c < 6; ++c) {
-                    const float v = s_G[0][0][k][c][lane];
-                    s_G[0][0][k][c][lane] = 0.0f;
+                    const float v = (float)s_G[0][0][k][c][lane];
+                    s_G[0][0][k][c][lane] = 0.0;
                     if (v == 0.0f) continue;
                     if constexpr (DET) rp.part[c * rp.part_stride + r_prev[k]] = v;
                     else unsafeAtomicAdd(&grad_c[(int64_t)r_prev[k] * GC_STRIDE + c], v);
@@ -1246,12 +1319,12 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             const float dxx = dalpha * E;   // d alpha / d x = exp(-x)
             const float dq = dxx * g2.y * (-0.5f * ex * rp.inv1meps);
             const int gc = (rr + (rr >> 3)) & (GC - 1);
-            atomicAdd(&s_G[hb][gc][k][0][j], -2.0f * dq * (g.z * dx + g.w * dy));
-            atomicAdd(&s_G[hb][gc][k][1][j], -2.0f * dq * (g.w * dx + g2.x * dy));
-            atomicAdd(&s_G[hb][gc][k][2][j], dq * dx * dx);
-            atomicAdd(&s_G[hb][gc][k][3][j], 2.0f * dq * dx * dy);
-            atomicAdd(&s_G[hb][gc][k][4][j], dq * dy * dy);
-            atomicAdd(&s_G[hb][gc][k][5][j], dxx * f);
+            atomicAdd(&s_G[hb][gc][k][0][j], (double)(-2.0f * dq * (g.z * dx + g.w * dy)));
+            atomicAdd(&s_G[hb][gc][k][1][j], (double)(-2.0f * dq * (g.w * dx + g2.x * dy)));
+            atomicAdd(&s_G[hb][gc][k][2][j], (double)(dq * dx * dx));
+            atomicAdd(&s_G[hb][gc][k][3][j], (double)(2.0f * dq * dx * dy));
+            atomicAdd(&s_G[hb][gc][k][4][j], (double)(dq * dy * dy));
+            atomicAdd(&s_G[hb][gc][k][5][j], (double)(dxx * f));
         }
         const uint64_t hbits = __ballot(real);
         if (lane == 0) n_hits += (unsigned long long)__popcll(hbits);
@@ -1457,295 +1530,382 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
 }
 
 // Pass A backward over the hits the forward stored (RasterParams::hits).
-// The tile's records are walked back to front, 64 hits a round, each round
-// from the back of one record (one hit group of the forward, so each ray's
-// hits are contiguous and back to front, as the segmented scans need). A
-// hit gathers its list entry's record into registers; loads run ahead of
-// the arithmetic (hit words HB_HIT_AHEAD rounds, records HB_REC_AHEAD
-// rounds). The six gradient terms collect per entry slot of the record in
-// LDS; once per record a second wave, while the first goes on, stores each
-// touched entry's six sums with plain stores at its pair's position before
-// the pair sort and marks it, and launch_reduce_touched adds them per
-// record (float atomics, one per sum, would cost several times the whole
-// pass); an entry whose record has no other tile stores its sums as the
-// record's directly. Only these sums and the rays' state live in LDS, so many tiles
-// run per CU. Records that do not fit the stream, links that do not go
-// back in it, record ids past the record count and list positions past the
-// pair count end the walk or are skipped, so a stream that holds anything
-// else cannot send the kernel out of bounds.
-constexpr int HB_HIT_AHEAD = 4, HB_REC_AHEAD = 2;
-constexpr int HB_SLOTS = 8 * WAVE;   // entry slots of a record (chunks x entries)
+// A workgroup takes a tile and walks its records back to front. The chain
+// along the rays (optical depth and U, carried from hit to hit) is serial,
+// everything else is not, so the work is split over its waves, a step being
+// up to HB_HELPERS rounds of 64 hits from the back of one record:
+//   helper waves, one round of the step each: the chain of loads (hit words
+//     of the step three ahead, list entries' record ids, records), then the
+//     footprint, x = kappa f and c = P dL/dI of each hit, handed to the main
+//     wave one step ahead; one step later the six gradient terms
+//     from the main wave's dL/dx, added per entry slot of the batch in LDS;
+//   the main wave: the rounds of the step one after the other, lane = hit
+//     (each ray's hits contiguous and back to front): optical depths and U by
+//     segmented scans, dL/dx per hit, each ray's state after its last hit.
+// Once a batch's records are done, one more wave stores each touched entry's
+// six sums with plain stores at its pair's position before the pair sort and
+// marks it (a buffer per batch, two in turn), and launch_reduce_touched adds
+// them per record (float atomics, one per sum, would cost several times the
+// whole pass); an entry whose record has no other tile stores its sums as the
+// record's directly. One barrier per step. One wave that loaded, evaluated
+// and scanned its rounds alone, with a second one storing, took 2.8 us per
+// round on the longest tiles (a full memory latency in each, however far
+// ahead the loads were issued).
+// Records that do not fit the stream, links that do not go back in it, record
+// ids past the record count and list positions past the pair count end the
+// walk or are skipped, so a stream that holds anything else cannot send the
+// kernel out of bounds.
+constexpr int HB_HELPERS = 4;
+constexpr int HB_THREADS = (2 + HB_HELPERS) * WAVE;
 
-__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return ((unsigned long long)hi << 32) | lo;
-}
+// A step's rounds: the stream index of the first of its n hit words (n = 0
+// once the chain is done; round r's lane i takes word base + n - 1 - 64 r -
+// i), whether it ends its batch, the batch's buffer and its chunks' list
+// positions / 64 (lane k: chunk k).
+struct HitStep {
+    uint64_t base;
+    uint32_t n, chunks;
+    int buf;
+    bool last;
+};
 
-__global__ void __launch_bounds__(2 * WAVE)
+// What a helper keeps of a hit from its evaluation to its gradient terms.
+struct HitTerm {
+    float dx, dy, a, b, c, dqx, f;   // offsets, conic, d(q)/d(x) factor, footprint
+    uint32_t id, pos;                // record and pair position (HIT_NONE: it has one tile)
+    uint32_t slot;                   // entry slot, bit 16: inside the footprint
+};
+
+__global__ void __launch_bounds__(HB_THREADS)
 k_raster_a_bwd_hits(const DevView* __restrict__ views, int nv, RasterParams rp,
                     const uint32_t* __restrict__ status, const uint32_t* __restrict__ worklist,
-                    const CRec* __restrict__ crec, const float* __restrict__ tau,
-                    float* __restrict__ grad_c, int64_t stride)
+                    const uint32_t* __restrict__ pvals, const CRec* __restrict__ crec,
+                    const float* __restrict__ tau, float* __restrict__ grad_c, int64_t stride)
 {
-    // two buffers of per-slot sums and the record of each touched slot
-    // (HIT_NONE: untouched); the flusher empties one while the main wave
-    // fills the other
-    __shared__ float s_G[2][6][HB_SLOTS];
+    // per batch buffer: the slots' sums, each touched slot's record
+    // (HIT_NONE: untouched) and pair position (HIT_NONE: the record has only
+    // this tile)
+    __shared__ double s_G[2][6][HB_SLOTS];
     __shared__ uint32_t s_rec[2][HB_SLOTS];
-    __shared__ unsigned char s_one[2][HB_SLOTS];   // the record has only this tile
-    __shared__ uint32_t s_last[2], s_hrec[2];   // per hand-off: last one?, the stream record
+    __shared__ uint32_t s_pos[2][HB_SLOTS];
+    // per batch, two in turn: record id and pair position of its list entries
+    __shared__ uint2 s_ent[2][HB_SLOTS];
+    // per step, two in turn: x (then dL/dx), c and the ray (-1: no hit) of
+    // each hit, the step's hits, and the batch buffer it completes (2: none)
+    __shared__ float2 s_in[2][HB_HELPERS][WAVE];
+    __shared__ signed char s_key[2][HB_HELPERS][WAVE];
+    __shared__ uint32_t s_n[2], s_done[2];
     __shared__ float2 s_ray[WAVE];   // per ray: optical depth, U
     if (blockIdx.x >= status[ST_WORK_TILES]) return;
     const int64_t bucket = worklist[blockIdx.x];
     const uint32_t tail = rp.hit_tail[bucket];
     if (tail == HIT_OVERFLOW) return;   // k_raster_a_bwd re-derives this tile's hits
-    for (int i = threadIdx.x; i < 2 * HB_SLOTS; i += 2 * WAVE) {
+    for (int i = threadIdx.x; i < 2 * HB_SLOTS; i += HB_THREADS) {
         (&s_rec[0][0])[i] = HIT_NONE;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) s_G[i / HB_SLOTS][c][i % HB_SLOTS] = 0.0f;
+        for (int c = 0; c < 6; ++c) s_G[i / HB_SLOTS][c][i % HB_SLOTS] = 0.0;
     }
-    __syncthreads();
-    if (threadIdx.x >= WAVE) {
-        // the flusher: per hand-off, each touched slot's sums to its pair's
-        // partial (slot = chunk * 64 + entry; the record's header holds the
-        // chunks' list positions), and the buffer cleared for reuse
-        const int fl = threadIdx.x - WAVE;
-        const uint32_t kc = status[ST_PAIRS_C];
-        const uint32_t* hw32 = reinterpret_cast<const uint32_t*>(rp.hits);
-        constexpr int NBLK = HB_SLOTS / WAVE;
-        for (int fb = 0;; fb ^= 1) {
-            __syncthreads();
-            const uint32_t hr = s_hrec[fb];
-            const uint32_t chw = hr != HIT_NONE && fl < 8 ? hw32[((uint64_t)hr + 1) * 4 + fl] : 0u;
-            // every slot's pair position in flight together (one latency),
-            // the sums read and cleared, then all the stores (no store waits
-            // on another)
-            uint32_t rk[NBLK], pp[NBLK];
-            bool one[NBLK];
-#pragma unroll
-            for (int i = 0; i < NBLK; ++i) {
-                const int sl = i * WAVE + fl;
-                rk[i] = s_rec[fb][sl];
-                one[i] = s_one[fb][sl] != 0;
-                const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)chw, i) * WAVE + fl;
-                pp[i] = rk[i] != HIT_NONE && !one[i] && pos < kc ? rp.hit_ppos[pos] : kc;
-            }
-            float v[NBLK][6];
-#pragma unroll
-            for (int i = 0; i < NBLK; ++i) {
-                const int sl = i * WAVE + fl;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) v[i][c] = 0.0f;
-                if (rk[i] == HIT_NONE) continue;
-                s_rec[fb][sl] = HIT_NONE;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    v[i][c] = s_G[fb][c][sl];
-                    s_G[fb][c][sl] = 0.0f;
-                }
-            }
-            // one store path: a record with no other tile takes its sums
-            // directly (its eight floats: six sums and two spare), any other
-            // entry its pair's partial row (six sums, the record, a spare);
-            // the mark of a direct store lands in the spare byte at the pair
-            // count, which the reduction never reads
-#pragma unroll
-            for (int i = 0; i < NBLK; ++i) {
-                if (rk[i] == HIT_NONE || (!one[i] && pp[i] >= kc)) continue;
-                float4* dst = reinterpret_cast<float4*>(
-                    one[i] ? grad_c + (int64_t)rk[i] * GC_STRIDE
-                           : rp.hit_part + (uint64_t)pp[i] * HIT_PART_STRIDE);
-                dst[0] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
-                dst[1] = make_float4(v[i][4], v[i][5], __uint_as_float(rk[i]), 0.0f);
-                rp.hit_touched[one[i] ? kc : pp[i]] = 1;
-            }
-            if (s_last[fb]) return;
-        }
-    }
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
     const TileCell tc = tile_cell(views, nv, bucket, true);
     const DevView& V = views[tc.v];
+
+    if (wave == 0) {   // the main wave
+        const int64_t ray = V.ray_off + (int64_t)tc.row * V.Wc + tc.col;
+        s_ray[lane] = make_float2(tc.inside ? tau[ray] : 0.0f, 0.0f);
+        uint32_t n_iter = 0;   // work counter
+        __syncthreads();
+        for (int t = 0;; ++t) {
+            const uint32_t n = s_n[t & 1];
+            if (n == 0u) break;
+            for (uint32_t r = 0; r * WAVE < n; ++r) {
+                ++n_iter;
+                float2& hit = s_in[t & 1][r][lane];
+                const float2 in = hit;
+                const int key = s_key[t & 1][r][lane];
+                const float E = __expf(-in.x);
+                const bool valid = key >= 0;
+                const int rr = valid ? key : 0;
+                const float2 rs = s_ray[rr];
+                // the neighbours' rays, read by every lane (a cross-lane read
+                // inside a condition would see the lanes it skips as zero)
+                const int below = from_lane_below(key), above = from_lane_above(key);
+                const bool head = !valid || lane == 0 || below != key;
+                const float c = in.y;
+                const float sx = seg_incl_scan(in.x, head);   // this and the later hits
+                float sa = E, sb = c * (1.0f - E);
+                seg_incl_affine(sa, sb, head);
+                float ea = __int_as_float(from_lane_below(__float_as_int(sa)));
+                float eb = __int_as_float(from_lane_below(__float_as_int(sb)));
+                if (head) {
+                    ea = 1.0f;
+                    eb = 0.0f;
+                }
+                const float tr = valid ? rs.x : 0.0f;
+                const float Ur = valid ? rs.y : 0.0f;
+                float dalpha = c;
+                if (rp.shadowing) {
+                    const float Tn = __expf(-fmaxf(tr - sx, 0.0f));
+                    dalpha = Tn * (c - (ea * Ur + eb));
+                }
+                hit.x = dalpha * E;   // d alpha / d x = exp(-x)
+                const bool endseg = valid && (lane == WAVE - 1 || above != key);
+                wave_lds_sync();
+                if (endseg && rp.shadowing) s_ray[rr] = make_float2(tr - sx, sa * Ur + sb);
+                wave_lds_sync();
+            }
+            __syncthreads();
+        }
+        // the helpers' last terms, then their last sums
+        if (n_iter != 0u) __syncthreads();
+        if (rp.work && lane == 0) {
+            atomicAdd(&rp.work[5], (unsigned long long)n_iter);
+            atomicAdd(&rp.work[16], 1ull);
+        }
+        return;
+    }
+
+    if (wave == 1 + HB_HELPERS) {
+        // the storing wave, which loads nothing: a wait for a load would wait
+        // for every store before it
+        const uint32_t kc = status[ST_PAIRS_C];
+        __syncthreads();
+        // step t: the batch whose last terms were added in the step before
+        bool drained = false;   // step t - 1 was the first empty one
+        for (int t = 0;; ++t) {
+            const uint32_t n = drained ? 0u : s_n[t & 1];
+            const uint32_t fb = t > 0 ? s_done[(t - 1) & 1] : 2u;
+            if (fb < 2u) {
+#pragma unroll
+                for (int i = 0; i < HB_CHUNKS; ++i) {
+                    const int sl = i * WAVE + lane;
+                    const uint32_t rk = s_rec[fb][sl];
+                    if (rk == HIT_NONE) continue;
+                    // one store path: a record with no other tile takes its
+                    // sums directly (its eight floats: six sums and two
+                    // spare), any other entry its pair's partial row (six
+                    // sums, the record, a spare); the mark of a direct store
+                    // lands in the spare byte at the pair count, which the
+                    // reduction never reads
+                    const uint32_t pos = s_pos[fb][sl];
+                    const bool one = pos == HIT_NONE;
+                    float v[6];
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) {
+                        v[c] = (float)s_G[fb][c][sl];
+                        s_G[fb][c][sl] = 0.0;
+                    }
+                    s_rec[fb][sl] = HIT_NONE;
+                    if (!one && pos >= kc) continue;
+                    float4* dst = reinterpret_cast<float4*>(
+                        one ? grad_c + (int64_t)rk * GC_STRIDE
+                            : rp.hit_part + (uint64_t)pos * HIT_PART_STRIDE);
+                    dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+                    dst[1] = make_float4(v[4], v[5], __uint_as_float(rk), 0.0f);
+                    rp.hit_touched[one ? kc : pos] = 1;
+                }
+            }
+            if (drained || (t == 0 && n == 0u)) return;
+            __syncthreads();
+            drained = n == 0u;
+        }
+    }
+
+    // a helper wave
+    const int hw = wave - 1;
+    const uint32_t kc = status[ST_PAIRS_C];
     const uint32_t rec0 = (uint32_t)V.rec_off;   // read by lanes without a hit
     const float x0 = (float)(tc.tx * TILE) + 0.5f, y0 = (float)(tc.ty * TILE) + 0.5f;
-    const int64_t ray = V.ray_off + (int64_t)tc.row * V.Wc + tc.col;
-    s_ray[lane] = make_float2(tc.inside ? tau[ray] : 0.0f, 0.0f);
-    const unsigned long long* hw = reinterpret_cast<const unsigned long long*>(rp.hits);
+    const uint32_t* hw32 = reinterpret_cast<const uint32_t*>(rp.hits);
+    const uint16_t* hit16 = reinterpret_cast<const uint16_t*>(rp.hits);
     const uint64_t cap = rp.hit_cap;
-    unsigned long long n_iter = 0, n_hits = 0, n_batch = 0;   // work counters
+    uint32_t n_hits = 0, n_batch = 0;   // work counters
 
-    // the cursor (wave-uniform): the record rounds are taken from, its hits
-    // not yet taken, the record before it and that one's header, loaded
-    // when the cursor enters a record
-    uint32_t cur = HIT_NONE, left = 0u, prev = HIT_NONE;
-    unsigned long long pend = 0ull;
-    auto enter = [&](uint32_t r, unsigned long long h) {
-        const uint32_t kept = (uint32_t)(h >> 32), pv = (uint32_t)h;
-        if (kept == 0u || (uint64_t)r + HIT_HEADER_UNITS + (kept + 1u) / 2u > cap) {
+    // the cursor: the record steps are taken from, its hits not yet taken,
+    // whether it is the first of its batch, its header (lanes 0..7; chunk k's
+    // list position in lane 4 + k), the record before it and the headers of
+    // the two before it (a header names both, so two loads are in flight and
+    // a step does not wait for one)
+    uint32_t cur = HIT_NONE, left = 0u, prev = HIT_NONE, first = 0u, chunks = 0u;
+    uint32_t pend = 0u, pend2 = 0u;
+    int buf = 0;
+    auto load_header = [&](uint32_t r) {
+        return lane < 4 * (int)HIT_HEADER_UNITS && (uint64_t)r + HIT_HEADER_UNITS <= cap
+                   ? hw32[(uint64_t)r * 4 + lane] : 0u;
+    };
+    auto enter = [&](uint32_t r, uint32_t header) {
+        const uint32_t pv = (uint32_t)__builtin_amdgcn_readlane((int)header, 0);
+        const uint32_t kept = (uint32_t)__builtin_amdgcn_readlane((int)header, 1);
+        first = (uint32_t)__builtin_amdgcn_readlane((int)header, 2);
+        const uint32_t pv2 = (uint32_t)__builtin_amdgcn_readlane((int)header, 3);
+        if (kept == 0u || (uint64_t)r + HIT_HEADER_UNITS + (kept + 7u) / 8u > cap) {
             cur = HIT_NONE;
             return;
         }
-        ++n_batch;
+        chunks = header;
         cur = r;
         left = kept;
         prev = pv < r ? pv : HIT_NONE;
-        if (prev != HIT_NONE) pend = hw[(uint64_t)prev * 2];
+        pend = pend2;
+        pend2 = load_header(pv2);   // (zeros for none: no hits, the walk ends)
     };
-    // the next round: index of its first hit word in the stream, its hit
-    // count (0 once the chain is done; lane i takes word base + n - 1 - i),
-    // whether it ends its record and the record
-    auto next = [&](uint64_t& base, uint32_t& n, bool& last, uint32_t& rec) {
+    auto next = [&]() {
+        HitStep q{0, 0u, 0u, buf, false};
         if (cur != HIT_NONE && left == 0u) {
             if (prev == HIT_NONE) cur = HIT_NONE;
-            else enter(prev, uniform_u64(pend));
+            else enter(prev, pend);
         }
-        rec = cur;
-        if (cur == HIT_NONE) {
-            base = 0;
-            n = 0u;
-            last = true;
-            return;
-        }
-        n = min(left, (uint32_t)WAVE);
-        left -= n;
-        base = ((uint64_t)cur + HIT_HEADER_UNITS) * 2 + left;
-        last = left == 0u;
+        if (cur == HIT_NONE) return q;
+        q.n = min(left, (uint32_t)(HB_HELPERS * WAVE));
+        left -= q.n;
+        q.base = ((uint64_t)cur + HIT_HEADER_UNITS) * 8 + left;
+        // a batch's records share their chunks, so its sums stay in one
+        // buffer until the first of them is done
+        q.last = left == 0u && (first != 0u || prev == HIT_NONE);
+        q.chunks = chunks;
+        if (q.last) buf ^= 1;
+        return q;
     };
-    if ((uint64_t)tail + HIT_HEADER_UNITS <= cap) enter(tail, uniform_u64(hw[(uint64_t)tail * 2]));
-
-    struct Rec { float4 q; float2 w; float c; bool one; };
-    auto load_hit = [&](uint64_t base, uint32_t n) {
-        return (uint32_t)lane < n ? hw[base + n - 1u - (uint32_t)lane] : 0ull;
+    const uint32_t my = (uint32_t)(hw * WAVE + lane);   // my hit of a step, from its end
+    auto load_hit = [&](const HitStep& q) {
+        return my < q.n ? (uint32_t)hit16[q.base + q.n - 1u - my] : 0u;
     };
-    auto gather = [&](unsigned long long h, uint32_t n) {
-        const uint32_t id = (uint32_t)h;
-        const uint32_t rk = ((uint32_t)lane < n && (int64_t)id < stride) ? id : rec0;
-        Rec g;
-        g.q = crec[rk].q;
-        const float4 w = crec[rk].w;
-        g.w = make_float2(w.x, w.y);
-        g.one = __float_as_uint(w.z) == 1u;
-        g.c = w.w;
-        return g;
+    // record id (HIT_NONE: no hit) and pair position of the hit's list entry
+    struct Entry { uint32_t id, pos; };
+    auto load_entry = [&](uint32_t hv, const HitStep& q) {
+        const uint32_t chunk =
+            (uint32_t)__shfl((int)q.chunks, 4 + (int)((hv >> 6) & (HB_CHUNKS - 1)), WAVE);   // all lanes take part
+        const uint32_t pos = chunk * WAVE + (hv & 63u);
+        Entry e{HIT_NONE, 0u};
+        if (my < q.n && pos < kc) e = Entry{pvals[pos], rp.hit_ppos[pos]};
+        return e;
     };
-    uint64_t b[HB_HIT_AHEAD + 1];
-    uint32_t nn[HB_HIT_AHEAD + 1];
-    bool ends[HB_HIT_AHEAD + 1];
-    uint32_t rc[HB_HIT_AHEAD + 1];
-    unsigned long long h[HB_HIT_AHEAD + 1];
-    Rec g[HB_REC_AHEAD + 1];
-#pragma unroll
-    for (int i = 0; i <= HB_HIT_AHEAD; ++i) {
-        next(b[i], nn[i], ends[i], rc[i]);
-        h[i] = load_hit(b[i], nn[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < HB_REC_AHEAD; ++i) g[i] = gather(h[i], nn[i]);
-    wave_lds_sync();
-    int hb = 0;   // buffer the current record's sums go to
-    while (nn[0] > 0u) {
-        ++n_iter;
-        g[HB_REC_AHEAD] = gather(h[HB_REC_AHEAD], nn[HB_REC_AHEAD]);
-        // the round: lane = hit, each ray's hits back to front
-        const bool valid = (uint32_t)lane < nn[0];
-        const uint32_t id = (uint32_t)h[0];
-        const int rr = valid ? (int)((h[0] >> 32) & (uint64_t)(WAVE - 1)) : 0;
-        const int sl = (int)((h[0] >> 40) & (uint64_t)(HB_SLOTS - 1));
-        const float2 rs = s_ray[rr];
-        // the neighbours' rays, read by every lane (a cross-lane read inside
-        // a condition would see the lanes it skips as zero)
-        const int key = valid ? rr : -1;
-        const int below = from_lane_below(key), above = from_lane_above(key);
-        const bool head = !valid || lane == 0 || below != rr;
-        const float4 q = g[0].q;
-        const float2 w = g[0].w;   // conic c, extinction
-        bool real = false;
-        float x = 0.0f, E = 1.0f, ex = 0.0f, f = 0.0f, dx = 0.0f, dy = 0.0f, c = 0.0f;
-        if (valid && (int64_t)id < stride) {
-            dx = x0 + (float)(rr & (TILE - 1)) - q.x;
-            dy = y0 + (float)(rr / TILE) - q.y;
-            const float qf = quadform(q, w.x, dx, dy);
+    auto gather = [&](uint32_t id) {
+        return load_rec_pair(crec, (int64_t)id < stride ? id : rec0);
+    };
+    // the same for my chunk of a batch's list entries (lane = entry)
+    auto load_chunk = [&](const HitStep& q) {
+        const uint32_t chunk = (uint32_t)__builtin_amdgcn_readlane((int)q.chunks, 4 + hw);
+        const uint32_t pos = chunk * WAVE + (uint32_t)lane;
+        Entry e{HIT_NONE, 0u};
+        if (q.n != 0u && pos < kc) e = Entry{pvals[pos], rp.hit_ppos[pos]};
+        return e;
+    };
+    // footprint and attenuation of the hit; its part of the main wave's input
+    auto evaluate = [&](uint32_t hv, const Entry& e, const CRec& R, const HitStep& q, int t) {
+        HitTerm o;
+        const bool valid = my < q.n;
+        const int rr = (int)((hv >> HB_RAY_SHIFT) & (uint32_t)(WAVE - 1));
+        float2 in = make_float2(0.0f, 0.0f);
+        o.dx = x0 + (float)(rr & (TILE - 1)) - R.q.x;
+        o.dy = y0 + (float)(rr / TILE) - R.q.y;
+        o.a = R.q.z;
+        o.b = R.q.w;
+        o.c = R.w.x;
+        o.id = e.id;
+        o.pos = __float_as_uint(R.w.z) == 1u ? HIT_NONE : e.pos;
+        o.slot = hv & (uint32_t)(HB_SLOTS - 1);
+        o.dqx = o.f = 0.0f;
+        if (valid && (int64_t)e.id < stride) {
+            const float qf = quadform(R.q, R.w.x, o.dx, o.dy);
             if (qf < rp.q_max) {
-                real = true;
-                c = g[0].c;
-                ex = __expf(-0.5f * qf);
-                f = (ex - rp.eps) * rp.inv1meps;
-                x = w.y * f;
-                E = __expf(-x);
+                const float ex = __expf(-0.5f * qf);
+                o.f = (ex - rp.eps) * rp.inv1meps;
+                o.dqx = R.w.y * (-0.5f * ex * rp.inv1meps);
+                o.slot |= 1u << 16;
+                in.x = R.w.y * o.f;
+                in.y = R.w.w;
             }
         }
-        const float sx = seg_incl_scan(x, head);   // this and the later hits
-        float sa = E, sb = real ? c * (1.0f - E) : 0.0f;
-        seg_incl_affine(sa, sb, head);
-        float ea = __int_as_float(from_lane_below(__float_as_int(sa)));
-        float eb = __int_as_float(from_lane_below(__float_as_int(sb)));
-        if (head) {
-            ea = 1.0f;
-            eb = 0.0f;
-        }
-        const float tr = valid ? rs.x : 0.0f;
-        const float Ur = valid ? rs.y : 0.0f;
-        if (real) {
-            float dalpha;
-            if (rp.shadowing) {
-                const float Tn = __expf(-fmaxf(tr - sx, 0.0f));
-                dalpha = Tn * (c - (ea * Ur + eb));
-            } else {
-                dalpha = c;
-            }
-            const float dxx = dalpha * E;   // d alpha / d x = exp(-x)
-            const float dq = dxx * w.y * (-0.5f * ex * rp.inv1meps);
-            s_rec[hb][sl] = id;
-            s_one[hb][sl] = g[0].one ? 1 : 0;
-            atomicAdd(&s_G[hb][0][sl], -2.0f * dq * (q.z * dx + q.w * dy));
-            atomicAdd(&s_G[hb][1][sl], -2.0f * dq * (q.w * dx + w.x * dy));
-            atomicAdd(&s_G[hb][2][sl], dq * dx * dx);
-            atomicAdd(&s_G[hb][3][sl], 2.0f * dq * dx * dy);
-            atomicAdd(&s_G[hb][4][sl], dq * dy * dy);
-            atomicAdd(&s_G[hb][5][sl], dxx * f);
-        }
-        const uint64_t hbits = __ballot(real);
-        if (lane == 0) n_hits += (unsigned long long)__popcll(hbits);
-        const bool endseg = valid && (lane == WAVE - 1 || above != rr);
-        wave_lds_sync();
-        if (endseg && rp.shadowing) s_ray[rr] = make_float2(tr - sx, sa * Ur + sb);
-        wave_lds_sync();
-        if (ends[0]) {
-            // the record's sums to the flusher (the barrier also returns the
-            // buffer it emptied last)
-            if (lane == 0) {
-                s_last[hb] = nn[1] == 0u ? 1u : 0u;
-                s_hrec[hb] = rc[0];
-            }
-            __syncthreads();
-            hb ^= 1;
-        }
-#pragma unroll
-        for (int i = 0; i < HB_HIT_AHEAD; ++i) {
-            b[i] = b[i + 1];
-            nn[i] = nn[i + 1];
-            ends[i] = ends[i + 1];
-            rc[i] = rc[i + 1];
-            h[i] = h[i + 1];
-        }
-#pragma unroll
-        for (int i = 0; i < HB_REC_AHEAD; ++i) g[i] = g[i + 1];
-        next(b[HB_HIT_AHEAD], nn[HB_HIT_AHEAD], ends[HB_HIT_AHEAD], rc[HB_HIT_AHEAD]);
-        h[HB_HIT_AHEAD] = load_hit(b[HB_HIT_AHEAD], nn[HB_HIT_AHEAD]);
+        s_in[t & 1][hw][lane] = in;
+        s_key[t & 1][hw][lane] = (signed char)(valid ? rr : -1);
+        if (hw == 0 && lane == 0) s_n[t & 1] = q.n;
+        n_hits += (uint32_t)__popcll(__ballot((o.slot >> 16) & 1u));
+        return o;
+    };
+    // steps t - 1 .. t + 3 and what is loaded for them, relative to step t
+    HitStep st[5];   // [0]: t - 1
+    HitTerm term[3];
+    uint32_t h[5];
+    Entry en[4], chunk4;
+    RecPair rec;
+    st[0] = HitStep{0, 0u, 0u, 0, false};
+    if ((uint64_t)tail + HIT_HEADER_UNITS <= cap) {
+        const uint32_t header = load_header(tail);
+        pend2 = load_header((uint32_t)__builtin_amdgcn_readlane((int)header, 0));
+        enter(tail, header);
     }
-    if (n_iter == 0) {   // no round: release the flusher
-        if (lane == 0) {
-            s_last[hb] = 1u;
-            s_hrec[hb] = HIT_NONE;
+#pragma unroll
+    for (int i = 1; i < 5; ++i) {
+        st[i] = next();
+        h[i] = load_hit(st[i]);
+    }
+#pragma unroll
+    for (int i = 1; i < 4; ++i) en[i] = load_entry(h[i], st[i]);
+    {
+        const RecPair r1 = gather(en[1].id);
+        rec = gather(en[2].id);
+        chunk4 = load_chunk(st[4]);
+        term[1] = evaluate(h[1], en[1], own_rec(r1), st[1], 0);
+    }
+    bool fresh4 = true;   // step t + 3's entries are not in s_ent yet
+    __syncthreads();
+    for (int t = 0;; ++t) {
+        // loads of later steps, waited for at the start of the next step
+        const bool fresh_far = st[4].last;
+        const HitStep far = next();
+        const uint32_t h_far = load_hit(far);
+        Entry chunk_far{HIT_NONE, 0u};
+        if (fresh_far) chunk_far = load_chunk(far);
+        const RecPair rec_far = gather(en[3].id);
+        // the entries of step t + 3's batch, for the hits of its steps
+        if (fresh4) s_ent[st[4].buf][hw * WAVE + lane] = make_uint2(chunk4.id, chunk4.pos);
+        // the gradient terms of step t - 1
+        if (t > 0 && ((term[0].slot >> 16) & 1u)) {
+            const HitTerm& m = term[0];
+            const int gb = st[0].buf, sl = (int)(m.slot & (uint32_t)(HB_SLOTS - 1));
+            const float dxx = s_in[(t - 1) & 1][hw][lane].x;
+            const float dq = dxx * m.dqx;
+            s_rec[gb][sl] = m.id;
+            s_pos[gb][sl] = m.pos;
+            atomicAdd(&s_G[gb][0][sl], (double)(-2.0f * dq * (m.a * m.dx + m.b * m.dy)));
+            atomicAdd(&s_G[gb][1][sl], (double)(-2.0f * dq * (m.b * m.dx + m.c * m.dy)));
+            atomicAdd(&s_G[gb][2][sl], (double)(dq * m.dx * m.dx));
+            atomicAdd(&s_G[gb][3][sl], (double)(2.0f * dq * m.dx * m.dy));
+            atomicAdd(&s_G[gb][4][sl], (double)(dq * m.dy * m.dy));
+            atomicAdd(&s_G[gb][5][sl], (double)(dxx * m.f));
         }
-        __syncthreads();
+        if (hw == 0) {
+            n_batch += st[0].last ? 1u : 0u;
+            if (lane == 0) s_done[t & 1] = st[0].last ? (uint32_t)st[0].buf : 2u;
+        }
+        // step t + 1 for the main wave
+        const bool more = st[1].n != 0u;
+        if (more) term[2] = evaluate(h[2], en[2], own_rec(rec), st[2], t + 1);
+        else if (t == 0) break;   // nothing at all
+        __syncthreads();          // one per step, and one for the first empty step
+        if (!more) break;
+        __builtin_amdgcn_sched_barrier(0);   // the loads are waited for after the barrier
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st[i] = st[i + 1];
+        st[4] = far;
+        term[0] = term[1];
+        term[1] = term[2];
+        h[2] = h[3];
+        h[3] = h[4];
+        h[4] = h_far;
+        en[2] = en[3];
+        {
+            const uint2 e = s_ent[st[3].buf][h[3] & (uint32_t)(HB_SLOTS - 1)];
+            en[3] = my < st[3].n ? Entry{e.x, e.y} : Entry{HIT_NONE, 0u};
+        }
+        chunk4 = chunk_far;
+        fresh4 = fresh_far;
+        rec = rec_far;
     }
     if (rp.work && lane == 0) {
-        atomicAdd(&rp.work[5], n_iter);
-        atomicAdd(&rp.work[1], n_hits);
-        atomicMax(&rp.work[9], n_batch);
-        atomicAdd(&rp.work[16], 1ull);
+        atomicAdd(&rp.work[1], (unsigned long long)n_hits);
+        if (hw == 0) atomicMax(&rp.work[9], (unsigned long long)n_batch);
     }
 }
 
@@ -1851,14 +2011,19 @@ inline unsigned grid256(int64_t n) { return (unsigned)((n + 255) / 256); }
 }  // namespace
 
 hipError_t launch_pair_masks(const DevView* views, int nv, int64_t cap_c, const RasterParams& rp,
+                             bool tight,
                              const uint32_t* status, const uint32_t* pkey,
                              const uint32_t* pvals, const CRec* crec,
                              uint64_t* pmask, uint64_t* psum, hipStream_t s)
 {
     if (cap_c <= 0) return hipSuccess;
     const unsigned grid = (unsigned)((cap_c + 256 * PM_ITEMS - 1) / (256 * PM_ITEMS));
-    hipLaunchKernelGGL(k_pair_masks, dim3(grid), dim3(256), 0, s, views, nv, cap_c, rp, status,
-                       pkey, pvals, crec, pmask, psum);
+    if (tight)
+        hipLaunchKernelGGL(k_pair_masks<true>, dim3(grid), dim3(256), 0, s, views, nv, cap_c, rp,
+                           status, pkey, pvals, crec, pmask, psum);
+    else
+        hipLaunchKernelGGL(k_pair_masks<false>, dim3(grid), dim3(256), 0, s, views, nv, cap_c, rp,
+                           status, pkey, pvals, crec, pmask, psum);
     return hipGetLastError();
 }
 
@@ -1886,14 +2051,14 @@ hipError_t launch_raster_a_fwd(const DevView* views, int nv, int64_t tiles_c,
                                float* A, float* tau, uint32_t* nlast, hipStream_t s)
 {
     if (tiles_c <= 0) return hipSuccess;
-    if (rp.ppos)
-        hipLaunchKernelGGL(k_raster_a_fwd<true>, dim3((unsigned)tiles_c), dim3(WAVE), 0, s, views,
-                           nv, rp, status, worklist, ranges, pvals, pmask, psum, crec, A, tau,
-                           nlast);
-    else
-        hipLaunchKernelGGL(k_raster_a_fwd<false>, dim3((unsigned)tiles_c), dim3(WAVE), 0, s, views,
-                           nv, rp, status, worklist, ranges, pvals, pmask, psum, crec, A, tau,
-                           nlast);
+    auto run = [&](auto det, auto hits) {
+        hipLaunchKernelGGL((k_raster_a_fwd<decltype(det)::value, decltype(hits)::value>),
+                           dim3((unsigned)tiles_c), dim3(WAVE), 0, s, views, nv, rp, status,
+                           worklist, ranges, pvals, pmask, psum, crec, A, tau, nlast);
+    };
+    if (rp.ppos) run(std::true_type{}, std::false_type{});
+    else if (rp.hits) run(std::false_type{}, std::true_type{});
+    else run(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 
@@ -1945,13 +2110,13 @@ hipError_t launch_image_bwd(const DevView* views, const DevScene* scenes, int nv
 
 hipError_t launch_raster_a_bwd_hits(const DevView* views, int nv, int64_t tiles_c,
                                     const RasterParams& rp, const uint32_t* status,
-                                    const uint32_t* worklist, const CRec* crec,
-                                    const float* tau, float* grad_c, int64_t stride,
-                                    hipStream_t s)
+                                    const uint32_t* worklist, const uint32_t* pvals,
+                                    const CRec* crec, const float* tau, float* grad_c,
+                                    int64_t stride, hipStream_t s)
 {
     if (tiles_c <= 0 || !rp.hits || rp.ppos) return hipSuccess;
-    hipLaunchKernelGGL(k_raster_a_bwd_hits, dim3((unsigned)tiles_c), dim3(2 * WAVE), 0, s, views,
-                       nv, rp, status, worklist, crec, tau, grad_c, stride);
+    hipLaunchKernelGGL(k_raster_a_bwd_hits, dim3((unsigned)tiles_c), dim3(HB_THREADS), 0, s, views,
+                       nv, rp, status, worklist, pvals, crec, tau, grad_c, stride);
     return hipGetLastError();
 }
 
