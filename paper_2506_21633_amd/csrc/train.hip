@@ -4,14 +4,13 @@
 // include/sdgr_train.h.
 //
 // All of it is memory- or launch-bound elementwise work except the
-// nearest-neighbour search (exhaustive, LDS-tiled: each workgroup stages
-// reference points in LDS and every thread keeps one query's minimum) and
-// the SSIM windows (121 taps per position, the window weights in LDS).
+// nearest-neighbour search (exhaustive) and the SSIM windows (121 taps per position, the window weights in LDS).
 #include "common.hpp"
 #include "sdgr_train.h"
 
 #include <math.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -257,36 +256,43 @@ k_densify_apply(DensifyArgs a, const uint8_t* __restrict__ act,
 
 // ----------------------------------------------------------------- metrics
 
-constexpr int NN_TILE = 1024;
+// Exhaustive nearest neighbours, a query per lane; the reference points are
+// the same for the whole wave, so they come as scalar loads and cost the VALU
+// nothing. Bound by the VALU: 7 operations a pair, 5.7 * 10^12 pairs/s, of
+// the 5.6 * 10^12 that one instruction per cycle and CU makes at 2.4 GHz.
+// With few queries the references are split over grid y, the parts' minima
+// meeting in d2 (distances are never negative, so their bits order as
+// unsigned; d2 starts at infinity then). 31k by 20k points take 108 us; a
+// block of 256 per 256 queries with the references staged in LDS took 470
+// (124 blocks on 256 CUs). A search over points sorted into cells, skipping
+// boxes further than the minima found, gave the same results in 424 us at
+// this size and was faster only from 100k by 100k points on.
+constexpr int NN_PART = 128;       // fewest references of a part: 8 of the loop's batches
+constexpr unsigned NN_WAVES = 4096;   // waves that fill the device: 4 to a SIMD
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(WAVE)
 k_nearest_sq(const float* __restrict__ q, int64_t nq, const float* __restrict__ ref, int64_t nr,
-             float* __restrict__ d2)
+             int64_t per, float* __restrict__ d2)
 {
-    __shared__ float s_x[NN_TILE], s_y[NN_TILE], s_z[NN_TILE];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    float qx = 0.f, qy = 0.f, qz = 0.f;
-    if (i < nq) {
-        qx = q[3 * i];
-        qy = q[3 * i + 1];
-        qz = q[3 * i + 2];
-    }
+    const int64_t i = (int64_t)blockIdx.x * WAVE + threadIdx.x;
+    const int64_t j = min(i, nq - 1);
+    const float qx = q[3 * j], qy = q[3 * j + 1], qz = q[3 * j + 2];
+    const int64_t t0 = (int64_t)blockIdx.y * per, t1 = min(nr, t0 + per);
     float best = INFINITY;
-    for (int64_t t0 = 0; t0 < nr; t0 += NN_TILE) {
-        const int cnt = (int)min((int64_t)NN_TILE, nr - t0);
-        __syncthreads();
-        for (int k = threadIdx.x; k < cnt; k += blockDim.x) {
-            s_x[k] = ref[3 * (t0 + k)];
-            s_y[k] = ref[3 * (t0 + k) + 1];
-            s_z[k] = ref[3 * (t0 + k) + 2];
-        }
-        __syncthreads();
-        for (int k = 0; k < cnt; ++k) {
-            const float dx = qx - s_x[k], dy = qy - s_y[k], dz = qz - s_z[k];
-            best = fminf(best, dx * dx + dy * dy + dz * dz);
-        }
+#pragma unroll 8
+    for (int64_t t = t0; t < t1; ++t) {
+        const float dx = qx - ref[3 * t], dy = qy - ref[3 * t + 1], dz = qz - ref[3 * t + 2];
+        best = fminf(best, dx * dx + dy * dy + dz * dz);
     }
-    if (i < nq) d2[i] = best;
+    if (i >= nq) return;
+    if (gridDim.y == 1) d2[i] = best;
+    else atomicMin(reinterpret_cast<unsigned int*>(d2) + i, __float_as_uint(best));
+}
+
+__global__ void __launch_bounds__(256) k_fill_f32(float* p, float v, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = v;
 }
 
 constexpr int SSIM_WIN = 11;
@@ -504,8 +510,18 @@ int sdgr_nearest_sq(const float* query, int64_t nq, const float* ref, int64_t nr
     if (nq == 0) return SDGR_OK;
     if (!query || !d2 || (nr > 0 && !ref)) return einval("null array");
     if (nq > (int64_t)1 << 31) return einval("more than 2^31 query points");
-    hipLaunchKernelGGL(k_nearest_sq, dim3(blocks_for(nq, 256, 1u << 31)), dim3(256), 0,
-                       (hipStream_t)stream, query, nq, ref, nr, d2);
+    hipStream_t s = (hipStream_t)stream;
+    const unsigned waves = blocks_for(nq, WAVE, 1u << 31);
+    // few queries: parts of at least NN_PART references, up to NN_WAVES waves
+    const int64_t most = std::min<int64_t>(NN_WAVES / waves, (nr + NN_PART - 1) / NN_PART);
+    const int64_t parts = std::max<int64_t>(most, 1);
+    if (parts > 1) {
+        hipLaunchKernelGGL(k_fill_f32, dim3(blocks_for(nq, 256)), dim3(256), 0, s, d2, INFINITY,
+                           nq);
+        TRAIN_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_nearest_sq, dim3(waves, (unsigned)parts), dim3(WAVE), 0, s, query, nq,
+                       ref, nr, (nr + parts - 1) / parts, d2);
     TRAIN_HIP(hipGetLastError());
     return SDGR_OK;
 }

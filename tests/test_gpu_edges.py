@@ -121,3 +121,29 @@ def test_hit_stream_parts(cuda, units):
     r.status(res)
     for k, t in want.items():   # FP32 rounding of re-derived against stored sums
         assert elem_err(got[k].cpu().numpy(), t.cpu().numpy()) <= 1e-5, k
+
+
+@pytest.mark.parametrize("nq,nr", [(1, 1), (63, 129), (64, 257), (200, 40000), (4097, 511),
+                                   (262080, 300), (262145, 129)])
+@pytest.mark.parametrize("kind", ["box", "bad"])
+def test_nearest_parts(cuda, nq, nr, kind):
+    """Nearest neighbours where the references' split over parts begins and
+    ends: the FP64 distances within FP32 rounding (1e-5 relative, and for the
+    cancellation of coordinate differences 2^-22 of their size squared);
+    points that are not finite are no one's neighbour and have none."""
+    from scipy.spatial import cKDTree
+    from paper_2506_21633_amd import train
+    rng = np.random.default_rng(nq + 7 * nr)
+    q = rng.uniform(-3, 3, (nq, 3)).astype(np.float32)
+    ref = rng.uniform(-3, 3, (nr, 3)).astype(np.float32)
+    if kind == "bad":
+        ref[::5, 1], ref[1::7, 0], q[::9, 2], q[3::11, 0] = np.nan, np.inf, np.nan, -np.inf
+    got = train.nearest_sq(torch.as_tensor(q, device=cuda),
+                           torch.as_tensor(ref, device=cuda)).cpu().numpy()
+    ok, qok = np.isfinite(ref).all(1), np.isfinite(q).all(1)
+    assert np.isinf(got[~qok]).all()
+    if not ok.any():
+        assert np.isinf(got).all()
+        return
+    want = cKDTree(ref[ok].astype(np.float64)).query(q[qok].astype(np.float64))[0] ** 2
+    assert (np.abs(got[qok] - want) <= 1e-5 * want + 2.0 ** -22 * 9.0).all()
