@@ -129,6 +129,18 @@ int sdgr_image_metrics(const float* x, const float* ref, int32_t nimg, int32_t h
                        float data_range, float* ssim, float* mse, float* ref_max,
                        void* stream);
 
+/* The same metrics with the window positions of each image spread over the
+ * device. `workspace` holds sdgr_image_metrics_workspace_bytes(nimg, h, w)
+ * bytes, 256-byte aligned. With `range` not NULL, L is the largest value of
+ * ref (NaN if ref holds one) instead of data_range, and is written to *range
+ * (device); the caller checks that it is positive and finite.
+ * SDGR_EUNSUPPORTED above 65535 tiles of 32 x 8 positions per image. */
+size_t sdgr_image_metrics_workspace_bytes(int32_t nimg, int32_t h, int32_t w);
+int sdgr_image_metrics_tiled(const float* x, const float* ref, int32_t nimg, int32_t h,
+                             int32_t w, float data_range, float* ssim, float* mse,
+                             float* ref_max, float* range, void* workspace,
+                             size_t workspace_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

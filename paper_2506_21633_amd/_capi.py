@@ -25,7 +25,9 @@ EXPORTED = ("sdgr_version", "sdgr_last_error", "sdgr_default_options",
             "sdgr_plan_resize", "sdgr_forward_static", "sdgr_plan_host", "sdgr_status_accumulate",
             # reconstruction loop and metrics
             "sdgr_adam_step", "sdgr_densify_stats", "sdgr_densify_workspace_bytes",
-            "sdgr_densify", "sdgr_nearest_sq", "sdgr_image_metrics")
+            "sdgr_densify", "sdgr_nearest_sq",
+            "sdgr_image_metrics", "sdgr_image_metrics_workspace_bytes",
+            "sdgr_image_metrics_tiled")
 
 STATIC_SCRATCH_BYTES = 64 << 20   # SDGR_STATIC_SCRATCH_BYTES
 
@@ -170,8 +172,12 @@ def lib():
     L.sdgr_nearest_sq.argtypes = [vp, ctypes.c_int64, vp, ctypes.c_int64, vp, vp]
     L.sdgr_image_metrics.argtypes = [vp, vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                      ctypes.c_float, vp, vp, vp, vp]
+    L.sdgr_image_metrics_workspace_bytes.argtypes = [ctypes.c_int32] * 3
+    L.sdgr_image_metrics_workspace_bytes.restype = ctypes.c_size_t
+    L.sdgr_image_metrics_tiled.argtypes = [vp, vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
+                                           ctypes.c_float, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
     for name in ("sdgr_adam_step", "sdgr_densify_stats", "sdgr_densify", "sdgr_nearest_sq",
-                 "sdgr_image_metrics"):
+                 "sdgr_image_metrics", "sdgr_image_metrics_tiled"):
         getattr(L, name).restype = ctypes.c_int
     for name in ("sdgr_plan_resize", "sdgr_profile_count", "sdgr_read_work",
                  "sdgr_profile_enable", "sdgr_profile_read", "sdgr_plan_query", "sdgr_forward", "sdgr_backward", "sdgr_status",

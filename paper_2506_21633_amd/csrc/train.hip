@@ -4,7 +4,8 @@
 // include/sdgr_train.h.
 //
 // All of it is memory- or launch-bound elementwise work except the
-// nearest-neighbour search (exhaustive) and the SSIM windows (121 taps per position, the window weights in LDS).
+// nearest-neighbour search (exhaustive) and the SSIM windows (separable, in
+// FP64).
 #include "common.hpp"
 #include "sdgr_train.h"
 
@@ -295,77 +296,216 @@ __global__ void __launch_bounds__(256) k_fill_f32(float* p, float v, int64_t n)
     if (i < n) p[i] = v;
 }
 
-constexpr int SSIM_WIN = 11;
+// --------------------------------------------------------- image metrics
 
-// One workgroup per image: every thread takes window positions in turn and
-// keeps partial sums; the workgroup adds them in a fixed order, so the
-// result does not depend on timing.
-__global__ void __launch_bounds__(256)
-k_image_metrics(const float* __restrict__ x, const float* __restrict__ ref, int h, int w,
-                float c1, float c2, float* __restrict__ ssim, float* __restrict__ mse,
-                float* __restrict__ rmax)
+constexpr int SSIM_WIN = 11;
+// A workgroup takes SSIM_TX x SSIM_TY window positions: the pixels under them
+// in LDS, the window's sums of x, y, x^2, y^2 and x y along the rows, then
+// along the columns, all in FP64 (where the moments' differences need no
+// second pass over the 121 taps). A workgroup per image, a thread per position
+// over all taps twice in FP32: the call took 140 us for 24 images of 64 x 64
+// (24 workgroups, four host synchronisations), now 47 (168 workgroups and one,
+// the read of the results).
+constexpr int SSIM_TX = 32, SSIM_TY = 8;
+constexpr int SSIM_PX = SSIM_TX + SSIM_WIN - 1, SSIM_PY = SSIM_TY + SSIM_WIN - 1;
+
+// A workgroup's part of an image's metrics.
+struct MetricsPart {
+    double ssim, err;
+    float max;
+    float pad;
+};
+
+// Largest value, NaN if there is one (as torch's max).
+__device__ __forceinline__ float max_or_nan(float a, float b)
 {
-    __shared__ float s_w[SSIM_WIN * SSIM_WIN];
-    __shared__ double s_a[256], s_b[256];
-    __shared__ float s_m[256];
-    if (threadIdx.x < SSIM_WIN * SSIM_WIN) {
-        const int r = threadIdx.x / SSIM_WIN - SSIM_WIN / 2, c = threadIdx.x % SSIM_WIN - SSIM_WIN / 2;
-        s_w[threadIdx.x] = expf(-(float)(r * r + c * c) / (2.0f * 1.5f * 1.5f));
+    return a != a ? a : (b != b ? b : fmaxf(a, b));
+}
+
+constexpr int RANGE_PARTS = 256;
+
+__global__ void __launch_bounds__(256)
+k_max_parts(const float* __restrict__ a, int64_t n, float* __restrict__ parts)
+{
+    __shared__ float s_m[4];
+    float m = -INFINITY;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        m = max_or_nan(m, a[i]);
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) m = max_or_nan(m, __shfl_xor(m, d, WAVE));
+    if (lane_id() == 0) s_m[threadIdx.x / WAVE] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        parts[blockIdx.x] = max_or_nan(max_or_nan(s_m[0], s_m[1]), max_or_nan(s_m[2], s_m[3]));
+}
+
+struct MetricsShared {
+    float x[SSIM_PY][SSIM_PX], y[SSIM_PY][SSIM_PX];
+    double row[5][SSIM_PY][SSIM_TX];
+    double win[SSIM_WIN];
+    double a[4], b[4];
+    float m[4];
+};
+
+// The part of window positions (tx, ty) in units of the tile, and the error
+// and maximum of the pixels it owns (the last tiles own the rest of a row or
+// column); the whole workgroup calls, thread 0 gets the result.
+__device__ MetricsPart metrics_tile(MetricsShared& S, const float* __restrict__ X,
+                                    const float* __restrict__ Y, int h, int w, int tx, int ty,
+                                    double c1, double c2)
+{
+    const int vw = w - SSIM_WIN + 1, vh = h - SSIM_WIN + 1;
+    const int c0 = tx * SSIM_TX, r0 = ty * SSIM_TY;
+    const int own_c = (tx + 1) * SSIM_TX >= vw ? w - c0 : SSIM_TX;
+    const int own_r = (ty + 1) * SSIM_TY >= vh ? h - r0 : SSIM_TY;
+    double err = 0.0, acc = 0.0;
+    float mx = -INFINITY;
+    __syncthreads();   // the tile before is done with S
+    for (int k = threadIdx.x; k < SSIM_PX * SSIM_PY; k += blockDim.x) {
+        const int r = k / SSIM_PX, c = k % SSIM_PX;
+        const bool in = r0 + r < h && c0 + c < w;
+        const float x = in ? X[(int64_t)(r0 + r) * w + c0 + c] : 0.0f;
+        const float y = in ? Y[(int64_t)(r0 + r) * w + c0 + c] : 0.0f;
+        S.x[r][c] = x;
+        S.y[r][c] = y;
+        if (r < own_r && c < own_c) {
+            const float d = x - y;
+            err += (double)d * d;
+            mx = fmaxf(mx, y);
+        }
     }
     __syncthreads();
-    float wsum = 0.f;
-    for (int k = 0; k < SSIM_WIN * SSIM_WIN; ++k) wsum += s_w[k];
-    const float iw = 1.0f / wsum;
+    for (int k = threadIdx.x; k < SSIM_PY * SSIM_TX; k += blockDim.x) {
+        const int r = k / SSIM_TX, c = k % SSIM_TX;
+        double sx = 0.0, sy = 0.0, xx = 0.0, yy = 0.0, xy = 0.0;
+#pragma unroll
+        for (int t = 0; t < SSIM_WIN; ++t) {
+            const double x = S.x[r][c + t], y = S.y[r][c + t];
+            const double wx = S.win[t] * x, wy = S.win[t] * y;
+            sx += wx;
+            sy += wy;
+            xx += wx * x;
+            yy += wy * y;
+            xy += wx * y;
+        }
+        S.row[0][r][c] = sx;
+        S.row[1][r][c] = sy;
+        S.row[2][r][c] = xx;
+        S.row[3][r][c] = yy;
+        S.row[4][r][c] = xy;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < SSIM_TX * SSIM_TY; k += blockDim.x) {
+        const int r = k / SSIM_TX, c = k % SSIM_TX;
+        if (r0 + r >= vh || c0 + c >= vw) continue;
+        double s[5] = {};
+#pragma unroll
+        for (int t = 0; t < SSIM_WIN; ++t)
+#pragma unroll
+            for (int q = 0; q < 5; ++q) s[q] += S.win[t] * S.row[q][r + t][c];
+        const double ma = s[0], mb = s[1];
+        const double va = s[2] - ma * ma, vb = s[3] - mb * mb, cv = s[4] - ma * mb;
+        acc += ((2.0 * ma * mb + c1) * (2.0 * cv + c2)) /
+               ((ma * ma + mb * mb + c1) * (va + vb + c2));
+    }
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        acc += __shfl_xor(acc, d, WAVE);
+        err += __shfl_xor(err, d, WAVE);
+        mx = fmaxf(mx, __shfl_xor(mx, d, WAVE));
+    }
+    const int wv = threadIdx.x / WAVE;
+    if (lane_id() == 0) {
+        S.a[wv] = acc;
+        S.b[wv] = err;
+        S.m[wv] = mx;
+    }
+    __syncthreads();
+    return MetricsPart{(S.a[0] + S.a[1]) + (S.a[2] + S.a[3]),
+                       (S.b[0] + S.b[1]) + (S.b[2] + S.b[3]),
+                       fmaxf(fmaxf(S.m[0], S.m[1]), fmaxf(S.m[2], S.m[3])), 0.0f};
+}
+
+// One workgroup per tile of positions, its part into parts[image][tile]; or
+// (parts null) one per image over all its tiles, the metrics themselves out.
+// range_parts: the data range is the largest of them instead of `range`.
+// Sums run in a fixed order, so the result does not depend on timing.
+__global__ void __launch_bounds__(256)
+k_image_metrics(const float* __restrict__ x, const float* __restrict__ ref, int h, int w,
+                float range, const float* __restrict__ range_parts, int nrange, int ntx, int nty,
+                MetricsPart* __restrict__ parts, float* __restrict__ ssim,
+                float* __restrict__ mse, float* __restrict__ rmax)
+{
+    __shared__ MetricsShared S;
+    if (threadIdx.x < SSIM_WIN) {
+        double sum = 0.0, mine = 0.0;
+        for (int t = 0; t < SSIM_WIN; ++t) {
+            const double d = t - SSIM_WIN / 2, e = exp(-d * d / (2.0 * 1.5 * 1.5));
+            sum += e;
+            if (t == (int)threadIdx.x) mine = e;
+        }
+        S.win[threadIdx.x] = mine / sum;
+    }
+    float L = range;
+    if (range_parts) {
+        L = -INFINITY;
+        for (int k = 0; k < nrange; ++k) L = max_or_nan(L, range_parts[k]);
+    }
+    const double c1 = (0.01 * L) * (0.01 * L), c2 = (0.03 * L) * (0.03 * L);
     const int64_t img = blockIdx.x;
     const float* X = x + img * (int64_t)h * w;
     const float* Y = ref + img * (int64_t)h * w;
-    const int vh = h - SSIM_WIN + 1, vw = w - SSIM_WIN + 1;
-    const int64_t npos = (int64_t)vh * vw, npix = (int64_t)h * w;
-    double acc = 0.0, err = 0.0;
-    float mx = -INFINITY;
-    for (int64_t p = threadIdx.x; p < npos; p += blockDim.x) {
-        const int r0 = (int)(p / vw), c0 = (int)(p % vw);
-        float ma = 0.f, mb = 0.f;
-        for (int r = 0; r < SSIM_WIN; ++r)
-            for (int c = 0; c < SSIM_WIN; ++c) {
-                const float wt = s_w[r * SSIM_WIN + c] * iw;
-                ma += wt * X[(int64_t)(r0 + r) * w + c0 + c];
-                mb += wt * Y[(int64_t)(r0 + r) * w + c0 + c];
-            }
-        float va = 0.f, vb = 0.f, cv = 0.f;
-        for (int r = 0; r < SSIM_WIN; ++r)
-            for (int c = 0; c < SSIM_WIN; ++c) {
-                const float wt = s_w[r * SSIM_WIN + c] * iw;
-                const float da = X[(int64_t)(r0 + r) * w + c0 + c] - ma;
-                const float db = Y[(int64_t)(r0 + r) * w + c0 + c] - mb;
-                va += wt * da * da;
-                vb += wt * db * db;
-                cv += wt * da * db;
-            }
-        acc += (double)(((2.f * ma * mb + c1) * (2.f * cv + c2)) /
-                        ((ma * ma + mb * mb + c1) * (va + vb + c2)));
+    if (parts) {
+        const int tile = blockIdx.y;
+        const MetricsPart p = metrics_tile(S, X, Y, h, w, tile % ntx, tile / ntx, c1, c2);
+        if (threadIdx.x == 0) parts[img * gridDim.y + tile] = p;
+        return;
     }
-    for (int64_t p = threadIdx.x; p < npix; p += blockDim.x) {
-        const float d = X[p] - Y[p];
-        err += (double)d * d;
-        mx = fmaxf(mx, Y[p]);
-    }
-    s_a[threadIdx.x] = acc;
-    s_b[threadIdx.x] = err;
-    s_m[threadIdx.x] = mx;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if ((int)threadIdx.x < d) {
-            s_a[threadIdx.x] += s_a[threadIdx.x + d];
-            s_b[threadIdx.x] += s_b[threadIdx.x + d];
-            s_m[threadIdx.x] = fmaxf(s_m[threadIdx.x], s_m[threadIdx.x + d]);
-        }
-        __syncthreads();
+    MetricsPart all{0.0, 0.0, -INFINITY, 0.0f};
+    for (int tile = 0; tile < ntx * nty; ++tile) {
+        const MetricsPart p = metrics_tile(S, X, Y, h, w, tile % ntx, tile / ntx, c1, c2);
+        all.ssim += p.ssim;
+        all.err += p.err;
+        all.max = fmaxf(all.max, p.max);
     }
     if (threadIdx.x == 0) {
-        ssim[img] = (float)(s_a[0] / (double)npos);
-        mse[img] = (float)(s_b[0] / (double)npix);
-        rmax[img] = s_m[0];
+        ssim[img] = (float)(all.ssim / ((double)(h - SSIM_WIN + 1) * (w - SSIM_WIN + 1)));
+        mse[img] = (float)(all.err / ((double)h * w));
+        rmax[img] = all.max;
+    }
+}
+
+// The images' metrics from their tiles' parts, a wave per image.
+__global__ void __launch_bounds__(WAVE)
+k_metrics_sum(const MetricsPart* __restrict__ parts, int tiles, int h, int w,
+              const float* __restrict__ range_parts, int nrange, float* __restrict__ ssim,
+              float* __restrict__ mse, float* __restrict__ rmax, float* __restrict__ range_out)
+{
+    const int64_t img = blockIdx.x;
+    double a = 0.0, b = 0.0;
+    float m = -INFINITY;
+    for (int t = threadIdx.x; t < tiles; t += WAVE) {
+        const MetricsPart p = parts[img * tiles + t];
+        a += p.ssim;
+        b += p.err;
+        m = fmaxf(m, p.max);
+    }
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        a += __shfl_xor(a, d, WAVE);
+        b += __shfl_xor(b, d, WAVE);
+        m = fmaxf(m, __shfl_xor(m, d, WAVE));
+    }
+    if (threadIdx.x == 0) {
+        ssim[img] = (float)(a / ((double)(h - SSIM_WIN + 1) * (w - SSIM_WIN + 1)));
+        mse[img] = (float)(b / ((double)h * w));
+        rmax[img] = m;
+        if (img == 0 && range_out) {
+            float L = -INFINITY;
+            for (int k = 0; k < nrange; ++k) L = max_or_nan(L, range_parts[k]);
+            *range_out = L;
+        }
     }
 }
 
@@ -526,6 +666,22 @@ int sdgr_nearest_sq(const float* query, int64_t nq, const float* ref, int64_t nr
     return SDGR_OK;
 }
 
+static int check_metrics(const float* x, const float* ref, int32_t nimg, int32_t h, int32_t w,
+                         const float* ssim, const float* mse, const float* ref_max)
+{
+    if (nimg < 0) return einval("negative image count");
+    if (h < SSIM_WIN || w < SSIM_WIN) return einval("images smaller than the 11 x 11 window");
+    if (nimg > 0 && (!x || !ref || !ssim || !mse || !ref_max)) return einval("null array");
+    return SDGR_OK;
+}
+
+static int metrics_tiles(int h, int w, int* ntx, int* nty)
+{
+    *ntx = (w - SSIM_WIN + SSIM_TX) / SSIM_TX;
+    *nty = (h - SSIM_WIN + SSIM_TY) / SSIM_TY;
+    return *ntx * *nty;
+}
+
 int sdgr_image_metrics(const float* x, const float* ref, int32_t nimg, int32_t h, int32_t w,
                        float data_range, float* ssim, float* mse, float* ref_max, void* stream)
 {
@@ -534,11 +690,54 @@ int sdgr_image_metrics(const float* x, const float* ref, int32_t nimg, int32_t h
     if (h < SSIM_WIN || w < SSIM_WIN) return einval("images smaller than the 11 x 11 window");
     if (!(data_range > 0.0f) || !std::isfinite(data_range)) return einval("data_range must be > 0");
     if (nimg == 0) return SDGR_OK;
-    if (!x || !ref || !ssim || !mse || !ref_max) return einval("null array");
-    const float c1 = (0.01f * data_range) * (0.01f * data_range);
-    const float c2 = (0.03f * data_range) * (0.03f * data_range);
+    if (const int rc = check_metrics(x, ref, nimg, h, w, ssim, mse, ref_max)) return rc;
+    int ntx, nty;
+    metrics_tiles(h, w, &ntx, &nty);
     hipLaunchKernelGGL(k_image_metrics, dim3((unsigned)nimg), dim3(256), 0, (hipStream_t)stream,
-                       x, ref, h, w, c1, c2, ssim, mse, ref_max);
+                       x, ref, h, w, data_range, (const float*)nullptr, 0, ntx, nty,
+                       (MetricsPart*)nullptr, ssim, mse, ref_max);
+    TRAIN_HIP(hipGetLastError());
+    return SDGR_OK;
+}
+
+size_t sdgr_image_metrics_workspace_bytes(int32_t nimg, int32_t h, int32_t w)
+{
+    if (nimg <= 0 || h < SSIM_WIN || w < SSIM_WIN) return 0;
+    int ntx, nty;
+    const int64_t tiles = (int64_t)metrics_tiles(h, w, &ntx, &nty);
+    return align256(RANGE_PARTS * sizeof(float)) +
+           align256((size_t)nimg * (size_t)tiles * sizeof(MetricsPart));
+}
+
+int sdgr_image_metrics_tiled(const float* x, const float* ref, int32_t nimg, int32_t h,
+                             int32_t w, float data_range, float* ssim, float* mse,
+                             float* ref_max, float* range, void* workspace,
+                             size_t workspace_bytes, void* stream)
+{
+    clear_error();
+    if (const int rc = check_metrics(x, ref, nimg, h, w, ssim, mse, ref_max)) return rc;
+    if (!range && (!(data_range > 0.0f) || !std::isfinite(data_range)))
+        return einval("data_range must be > 0");
+    if (nimg == 0) return SDGR_OK;
+    if (!workspace || workspace_bytes < sdgr_image_metrics_workspace_bytes(nimg, h, w))
+        return report_error(SDGR_EWORKSPACE, "workspace too small for the image metrics");
+    if ((uintptr_t)workspace & 255) return einval("workspace not 256-byte aligned");
+    int ntx, nty;
+    const int tiles = metrics_tiles(h, w, &ntx, &nty);
+    if (tiles > 65535)   // grid y: one workgroup per image covers any size
+        return report_error(SDGR_EUNSUPPORTED, "images too large for the tiled metrics");
+    hipStream_t s = (hipStream_t)stream;
+    float* rp = (float*)workspace;
+    MetricsPart* parts = (MetricsPart*)((char*)workspace + align256(RANGE_PARTS * sizeof(float)));
+    const int64_t px = (int64_t)nimg * h * w;
+    const int nrange = range ? (int)blocks_for(px, 4096, RANGE_PARTS) : 0;
+    if (range)
+        hipLaunchKernelGGL(k_max_parts, dim3((unsigned)nrange), dim3(256), 0, s, ref, px, rp);
+    hipLaunchKernelGGL(k_image_metrics, dim3((unsigned)nimg, (unsigned)tiles), dim3(256), 0, s, x,
+                       ref, h, w, data_range, range ? rp : (const float*)nullptr, nrange, ntx,
+                       nty, parts, ssim, mse, ref_max);
+    hipLaunchKernelGGL(k_metrics_sum, dim3((unsigned)nimg), dim3(WAVE), 0, s, parts, tiles, h, w,
+                       rp, nrange, ssim, mse, ref_max, range);
     TRAIN_HIP(hipGetLastError());
     return SDGR_OK;
 }

@@ -267,14 +267,28 @@ def image_metrics(images: torch.Tensor, refs: torch.Tensor, data_range: Optional
     images = images.contiguous().float()
     refs = refs.contiguous().float()
     N, H, W = refs.shape
-    L = float(refs.max()) if data_range is None else float(data_range)
-    ss = torch.empty(N, dtype=torch.float32, device=refs.device)
-    mse = torch.empty_like(ss)
-    mx = torch.empty_like(ss)
-    C.check(C.lib().sdgr_image_metrics(images.data_ptr(), refs.data_ptr(), N, H, W, L,
-                                       ss.data_ptr(), mse.data_ptr(), mx.data_ptr(),
-                                       _stream(refs.device)))
-    ss, mse, mx = ss.cpu().numpy(), mse.cpu().numpy(), mx.cpu().numpy()
+    L = C.lib()
+    if refs.numel() == 0 and data_range is None:
+        data_range = float(refs.max())   # raises: there is no largest value
+    # one device buffer of results, read back once: SSIM, MSE, maxima, range
+    out = torch.empty(3 * N + 1, dtype=torch.float32, device=refs.device)
+    ptr = [out.data_ptr() + 4 * N * k for k in range(4)]
+    ws_bytes = int(L.sdgr_image_metrics_workspace_bytes(N, H, W))
+    ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=refs.device)
+    rc = L.sdgr_image_metrics_tiled(images.data_ptr(), refs.data_ptr(), N, H, W,
+                                    0.0 if data_range is None else float(data_range), *ptr[:3],
+                                    ptr[3] if data_range is None else None, ws.data_ptr(),
+                                    ws.numel(), _stream(refs.device))
+    if rc == C.SDGR_EUNSUPPORTED:
+        if data_range is None:
+            data_range = float(refs.max())
+        rc = L.sdgr_image_metrics(images.data_ptr(), refs.data_ptr(), N, H, W, float(data_range),
+                                  *ptr[:3], _stream(refs.device))
+    C.check(rc)
+    host = out.cpu().numpy()
+    if data_range is None and not 0.0 < host[3 * N] < np.inf:
+        raise C.SDGRError(C.SDGR_EINVAL, "data_range must be > 0")
+    ss, mse, mx = host[:N], host[N:2 * N], host[2 * N:3 * N]
     psnr = np.where(mse > 0, 10.0 * np.log10(np.maximum(mx, 1e-30) ** 2 / np.maximum(mse, 1e-300)),
                     np.inf)
     return dict(ssim=float(ss.mean()), psnr=float(psnr.mean()), ssim_per=ss, psnr_per=psnr)

@@ -147,3 +147,33 @@ def test_nearest_parts(cuda, nq, nr, kind):
         return
     want = cKDTree(ref[ok].astype(np.float64)).query(q[qok].astype(np.float64))[0] ** 2
     assert (np.abs(got[qok] - want) <= 1e-5 * want + 2.0 ** -22 * 9.0).all()
+
+
+@pytest.mark.parametrize("h,w", [(11, 11), (18, 42), (19, 43), (12, 75), (41, 200)])
+@pytest.mark.parametrize("given", [True, False])
+def test_image_metrics_tiles(cuda, h, w, given):
+    """SSIM and PSNR where the tiles of 32 x 8 window positions end, the data
+    range given or the references' maximum: within 1e-5 and 1e-4 of the
+    reference (FP32 results of FP64 sums), the one-workgroup form of the
+    call the same within FP32 rounding."""
+    import ctypes
+    from oracle import training as T
+    from paper_2506_21633_amd import _capi as C
+    from paper_2506_21633_amd import train
+    rng = np.random.default_rng(h * w)
+    ref = rng.gamma(2.0, 1.0, (3, h, w)).astype(np.float32)
+    img = (ref + rng.normal(0, 0.4, ref.shape)).astype(np.float32)
+    L = 5.0 if given else float(ref.max())
+    x, y = torch.as_tensor(img, device=cuda), torch.as_tensor(ref, device=cuda)
+    got = train.image_metrics(x, y, L if given else None)
+    one = torch.full((3, 3), -1.0, device=cuda)
+    C.check(C.lib().sdgr_image_metrics(
+        x.data_ptr(), y.data_ptr(), 3, h, w, L, one[0].data_ptr(), one[1].data_ptr(),
+        one[2].data_ptr(), ctypes.c_void_p(torch.cuda.current_stream(cuda).cuda_stream)))
+    for k in range(3):
+        assert abs(got["ssim_per"][k] - T.ssim(img[k], ref[k], L)) <= 1e-5, k
+        assert abs(got["psnr_per"][k] - T.psnr(img[k], ref[k])) <= 1e-4, k
+        assert abs(got["ssim_per"][k] - float(one[0, k])) <= 1e-6, k
+    if not given:
+        with pytest.raises(C.SDGRError):
+            train.image_metrics(x, torch.zeros_like(y))
