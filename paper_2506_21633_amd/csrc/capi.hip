@@ -106,6 +106,19 @@ int bits_for(int64_t max_value)
     return b;
 }
 
+// The lists of small views (launch_view_lists) by comparing all pairs of
+// records and having every tile read its view's rectangles, where that costs
+// less than the sorts' launches. A whole forward without and with them: 1000
+// Gaussians in one view 182 and 113 us, 16k in one view 224 and 190 (23k 230
+// and 239), 4000 in 36 views (576M pairs) 303 and 266, 11k in 8 views (968M)
+// 276 and 274, 20k in 8 views 288 and 430; 4000 Gaussians on 4096 tiles (16M
+// reads) 275 and 204, 16k on 4096 tiles (66M) 274 and 263, 8000 in 4 such
+// views (131M) 308 and 334; 100 Gaussians on 16k tiles 289 and 233, 1000 on
+// 147k tiles 484 and 745.
+constexpr int64_t VL_PAIRS = int64_t(5) << 27;
+constexpr int64_t VL_READS = int64_t(1) << 26;
+constexpr int64_t VL_ALL_TILES = int64_t(1) << 15;
+
 // Everything the host knows about a call before touching the device.
 struct Problem {
     std::vector<DevView> views;
@@ -121,6 +134,8 @@ struct Problem {
     bool seg = false;       // depth and pair sorts segmented by view
     int cbits = 0;          // bits of the computation-plane tile within a view
     int ikey_bits = 0;      // bits of the tile within a view
+    bool view_lists = false;   // lists of small views, see launch_view_lists
+    int64_t max_n = 0;         // most records of a view
     int64_t hit_units = 0;  // 16-byte units of the stored-hit stream (0: none)
 };
 
@@ -282,6 +297,17 @@ int build_problem(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
         max_tc = std::max<int64_t>(max_tc, (int64_t)P.views[v].txc * P.views[v].tyc);
     P.cbits = bits_for(max_tc - 1);
     P.seg = nv <= SEG_MAX;
+    // the lists of small views without the sorts
+    bool fits = nv <= TOTAL_SLOTS && tc <= VL_ALL_TILES;
+    int64_t reads = 0, pairs = 0;
+    for (const DevView& V : P.views) {
+        P.max_n = std::max<int64_t>(P.max_n, V.n);
+        fits = fits && V.txc <= VL_SIDE && V.tyc <= VL_SIDE &&
+               (V.txc + 1) * (V.tyc + 1) <= VL_TILES;
+        reads += (int64_t)V.txc * V.tyc * V.n;
+        pairs += (int64_t)V.n * V.n;
+    }
+    P.view_lists = fits && P.max_n <= VL_MAX && reads <= VL_READS && pairs <= VL_PAIRS;
     P.image_floats = img;
     P.pixels = pix;
     return SDGR_OK;
@@ -515,6 +541,16 @@ int bits_pairs_i(const Problem& P)
 int final_buffer_c(const Problem& P) { return radix_passes_for(bits_pairs_c(P)) & 1; }
 int final_buffer_i(const Problem& P) { return radix_passes_for(bits_pairs_i(P)) & 1; }
 
+// Footprint masks of the sorted pairs and the tile worklist.
+int finish_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, const uint32_t* pkey,
+                   const uint32_t* pval, hipStream_t s)
+{
+    SDGR_HIP(launch_pair_masks(b.views, P.nv, plan->pairs_c, P.rp, P.hit_units == 0, b.status,
+                               pkey, pval, b.crec, b.pmask, b.psum, s));
+    SDGR_HIP(launch_tile_worklist(b.ranges, P.tiles_c, b.worklist, b.status + WL_BINS, b.status, s));
+    return SDGR_OK;
+}
+
 // Projection, depth sort and the computation-plane lists: binning, the
 // stable bucket sort, tile ranges, footprint masks and the tile worklist
 // (shared by the forward and the recomputing backward).
@@ -534,6 +570,18 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
                                    zero_A ? b.A : nullptr, b.prec, b.slots,
                                    reinterpret_cast<unsigned long long*>(b.status + ST_COUNT),
                                    s));
+    }
+    if (P.view_lists) {
+        const int pb = final_buffer_c(P);
+        {
+            StageTimer t(SG_DEPTH_SORT, s);
+            SDGR_HIP(launch_view_lists(b.views, P.nv, P.max_n, P.tiles_c, plan->pairs_c,
+                                       b.dkey[0], b.rect_c, b.dval[0], b.rect_c_sorted, b.dkey[1],
+                                       b.slots, b.status, b.ranges, b.pkey[pb], b.pval[pb],
+                                       b.ppos[pb], b.dord, b.poff, s));
+        }
+        StageTimer t(SG_RANGES, s);
+        return finish_lists_c(P, plan, b, b.pkey[pb], b.pval[pb], s);
     }
     // depth order of the records of every view
     uint32_t* dk[2] = {b.dkey[0], b.dkey[1]};
@@ -579,10 +627,7 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
     StageTimer t(SG_RANGES, s);
     SDGR_HIP(launch_tile_ranges(pk[pw], plan->pairs_c, b.status + ST_PAIRS_C, P.tiles_c,
                                 b.ranges, s));
-    SDGR_HIP(launch_pair_masks(b.views, P.nv, plan->pairs_c, P.rp, P.hit_units == 0, b.status,
-                               pk[pw], pv[pw], b.crec, b.pmask, b.psum, s));
-    SDGR_HIP(launch_tile_worklist(b.ranges, P.tiles_c, b.worklist, b.status + WL_BINS, b.status, s));
-    return SDGR_OK;
+    return finish_lists_c(P, plan, b, pk[pw], pv[pw], s);
 }
 
 // Imaging-plane lists, after pass A: only records with nonzero intensity

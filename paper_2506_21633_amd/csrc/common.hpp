@@ -480,6 +480,21 @@ hipError_t launch_emit_pairs_i(const DevView* views, int nv, int64_t records,
                                const uint32_t* bscan_i, int64_t cap_c, int64_t cap_i, bool vm,
                                const uint32_t* status, uint32_t* pkey, uint32_t* pval,
                                hipStream_t s);
+// Computation-plane lists of views of at most VL_MAX records, VL_SIDE tiles
+// to a side and VL_TILES tiles (with a border of one): depth order, tile
+// ranges, pair keys and records, and the pair count in status. vtot: nv
+// words of scratch; rank_off: one per record. Optional: ppos, the pairs'
+// positions in record order, and for every depth rank its record and first
+// pair (dord, poff).
+constexpr int VL_MAX = 16384;
+constexpr int VL_TILES = 8192;
+constexpr int VL_SIDE = 256;
+hipError_t launch_view_lists(const DevView* views, int nv, int64_t max_records, int64_t tiles_c,
+                             int64_t cap_c, const uint32_t* dkey, const uint2* rect,
+                             uint32_t* order, uint2* rect_sorted, uint32_t* rank_off,
+                             unsigned long long* vtot, uint32_t* status, uint2* ranges,
+                             uint32_t* pkey, uint32_t* pval, uint32_t* ppos, uint32_t* dord,
+                             uint32_t* poff, hipStream_t s);
 hipError_t launch_tile_ranges(const uint32_t* keys, int64_t cap, const uint32_t* n_dev,
                               int64_t buckets, uint2* ranges, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);

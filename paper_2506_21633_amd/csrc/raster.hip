@@ -2001,6 +2001,52 @@ k_worklist_place(const uint2* __restrict__ ranges, int64_t tiles_c, uint32_t* __
         if (bin[k]) worklist[s_base[bin[k]] + rank[k]] = (uint32_t)(t0 + k * 256);
 }
 
+// The three steps in one workgroup, for at most WL_SMALL tiles (three
+// launches of 4 us each otherwise).
+constexpr int WL_SMALL_THREADS = 1024;
+constexpr int WL_SMALL_PER = 8;
+constexpr int64_t WL_SMALL = WL_SMALL_THREADS * WL_SMALL_PER;
+
+__global__ void __launch_bounds__(WL_SMALL_THREADS)
+k_worklist_small(const uint2* __restrict__ ranges, int64_t tiles_c, uint32_t* __restrict__ bins,
+                 uint32_t* __restrict__ status, uint32_t* __restrict__ worklist)
+{
+    __shared__ uint32_t s_cnt[WL_BINS_N], s_base[WL_BINS_N];
+    if (threadIdx.x < WL_BINS_N) s_cnt[threadIdx.x] = 0u;
+    __syncthreads();
+    int bin[WL_SMALL_PER];
+    uint32_t rank[WL_SMALL_PER];
+#pragma unroll
+    for (int k = 0; k < WL_SMALL_PER; ++k)
+        bin[k] = list_bin(ranges, (int64_t)(k * WL_SMALL_THREADS) + threadIdx.x, tiles_c);
+#pragma unroll
+    for (int k = 0; k < WL_SMALL_PER; ++k) rank[k] = bin_rank(s_cnt, bin[k]);
+    __syncthreads();
+    if (threadIdx.x < WAVE) {
+        // bins in descending order of length: lane l holds bin 32 - l
+        const int lane = threadIdx.x, b = 32 - lane;
+        const uint32_t c = lane < 32 ? s_cnt[b] : 0u;
+        uint32_t inc = c;
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) {
+            const uint32_t t = __shfl_up(inc, d, WAVE);
+            if (lane >= d) inc += t;
+        }
+        if (lane < 32) {
+            s_base[b] = inc - c;
+            bins[b] = c;
+            bins[33 + b] = inc;
+        }
+        if (lane == 31) status[ST_WORK_TILES] = inc;
+        if (lane == 32) bins[0] = bins[33] = 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < WL_SMALL_PER; ++k)
+        if (bin[k])
+            worklist[s_base[bin[k]] + rank[k]] = (uint32_t)(k * WL_SMALL_THREADS + threadIdx.x);
+}
+
 inline unsigned raster_grid(int64_t waves)
 {
     return (unsigned)((waves + RASTER_WAVES - 1) / RASTER_WAVES);
@@ -2030,6 +2076,11 @@ hipError_t launch_pair_masks(const DevView* views, int nv, int64_t cap_c, const 
 hipError_t launch_tile_worklist(const uint2* ranges, int64_t tiles_c, uint32_t* worklist,
                                 uint32_t* bins, uint32_t* status, hipStream_t s)
 {
+    if (tiles_c <= WL_SMALL) {
+        hipLaunchKernelGGL(k_worklist_small, dim3(1), dim3(WL_SMALL_THREADS), 0, s, ranges,
+                           tiles_c, bins, status, worklist);
+        return hipGetLastError();
+    }
     hipError_t e = launch_fill_u32(bins, 0u, 66, s);
     if (e != hipSuccess) return e;
     const unsigned wl_grid = (unsigned)((tiles_c + WL_TILES - 1) / WL_TILES);

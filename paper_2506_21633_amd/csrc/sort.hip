@@ -1068,6 +1068,304 @@ k_emit_i(const DevView* __restrict__ views, int nv, int64_t records,
                     pkey + cap_c, pval + cap_c);
 }
 
+// ---- computation-plane lists of small views
+// Where every view has at most VL_MAX records, three kernels take the place
+// of the depth sort, the binning, the pair sort and the tile ranges: every
+// record counts the records before it in its view, a workgroup per view
+// counts the pairs of its tiles, and a workgroup per tile walks the view's
+// records in depth order and writes its own list. The lists, their places
+// and the pairs' positions in record order are those of the sorts, which are
+// 23 to 29 launches of about 4 us moving a few hundred KB.
+constexpr int VL_THREADS = 1024;
+constexpr int VL_WAVES = VL_THREADS / WAVE;
+
+// Depth rank of each record in its view: a workgroup takes 64 records (lane
+// = record), its waves share out the keys they are compared with, which are
+// scalar loads. Bound by the VALU, two operations a pair: 7300 records in
+// each of three views take 22 us, 1000 in one view 8, where the radix sort's
+// 12 launches took 66 and 48 (and a radix sort in one workgroup's LDS 35 and
+// 10).
+__global__ void __launch_bounds__(VL_THREADS)
+k_view_rank(const DevView* __restrict__ views, const uint32_t* __restrict__ dkey,
+            const uint2* __restrict__ rect, uint32_t* __restrict__ order,
+            uint2* __restrict__ rect_sorted)
+{
+    __shared__ uint32_t s_n[VL_WAVES][WAVE];
+    const DevView& V = views[blockIdx.y];
+    const int n = V.n, i0 = (int)blockIdx.x * WAVE;
+    if (i0 >= n) return;
+    const int64_t rec0 = V.rec_off;
+    const uint32_t* keys = dkey + rec0;
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+    const int i = i0 + lane;
+    const uint32_t mine = keys[min(i, n - 1)];
+    const int per = (n + VL_WAVES - 1) / VL_WAVES;
+    const int j0 = min(n, w * per), j1 = min(n, j0 + per);
+    const int a1 = max(j0, min(j1, i0)), b1 = max(a1, min(j1, i0 + WAVE));
+    uint32_t cnt = 0u;
+    // equal keys keep their order: those of earlier records count as smaller
+#pragma unroll 16
+    for (int j = j0; j < a1; ++j) cnt += keys[j] <= mine ? 1u : 0u;
+    for (int j = a1; j < b1; ++j) {
+        const uint32_t k = keys[j];
+        cnt += k < mine || (k == mine && j < i) ? 1u : 0u;
+    }
+#pragma unroll 16
+    for (int j = b1; j < j1; ++j) cnt += keys[j] < mine ? 1u : 0u;
+    s_n[w][lane] = cnt;
+    __syncthreads();
+    if (w != 0 || i >= n) return;
+    const uint2 rc = rect[rec0 + i];
+    uint32_t rank = 0u;
+#pragma unroll
+    for (int k = 0; k < VL_WAVES; ++k) rank += s_n[k][lane];
+    order[rec0 + rank] = (uint32_t)(rec0 + i);
+    rect_sorted[rec0 + rank] = rc;
+}
+
+// Block-wide exclusive prefix of v over VL_THREADS threads.
+__device__ __forceinline__ uint32_t view_scan(uint32_t v, uint32_t* s_w, uint32_t& total)
+{
+    const int lane = lane_id(), w = (int)threadIdx.x / WAVE;
+    uint32_t inc = v;
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        const uint32_t t = __shfl_up(inc, d, WAVE);
+        if (lane >= d) inc += t;
+    }
+    __syncthreads();   // s_w may still be read from the scan before
+    if (lane == WAVE - 1) s_w[w] = inc;
+    __syncthreads();
+    uint32_t off = 0u;
+    total = 0u;
+#pragma unroll
+    for (int k = 0; k < VL_WAVES; ++k) {
+        if (k < w) off += s_w[k];
+        total += s_w[k];
+    }
+    return off + inc - v;
+}
+
+// A view's pair offsets per depth rank, its tiles' ranges relative to its
+// first pair, and its pair count. A tile's count is the number of rectangles
+// that cover it: four marks per record in a difference array over the tiles
+// (with a border), then prefix sums along the rows and the columns.
+__global__ void __launch_bounds__(VL_THREADS)
+k_view_counts(const DevView* __restrict__ views, const uint2* __restrict__ rect_sorted,
+              uint32_t* __restrict__ rank_off, uint2* __restrict__ ranges,
+              unsigned long long* __restrict__ vtot)
+{
+    __shared__ uint32_t s_t[VL_TILES];
+    __shared__ uint32_t s_w[VL_WAVES];
+    const DevView& V = views[blockIdx.x];
+    const int64_t rec0 = V.rec_off;
+    const int n = V.n, txc = V.txc, tyc = V.tyc;
+    const int tid = threadIdx.x;
+    const int gw = txc + 1, cells = gw * (tyc + 1);
+    for (int k = tid; k < cells; k += VL_THREADS) s_t[k] = 0u;
+    __syncthreads();
+    constexpr int GRP = 8;   // records of a thread in flight, consecutive ranks
+    uint32_t carry = 0u, total;
+    for (int p0 = 0; p0 < n; p0 += VL_THREADS * GRP) {
+        uint2 rc[GRP];
+        uint32_t cnt[GRP], sum = 0u;
+#pragma unroll
+        for (int k = 0; k < GRP; ++k) {
+            const int p = p0 + tid * GRP + k;
+            rc[k] = p < n ? rect_sorted[rec0 + p] : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < GRP; ++k) {
+            const uint32_t tx0 = rc[k].x & 0xFFFFu, tx1 = rc[k].x >> 16;
+            const uint32_t y0 = rc[k].y & 0xFFFFu, y1 = rc[k].y >> 16;
+            cnt[k] = (tx1 - tx0) * (y1 - y0);
+            if (cnt[k]) {
+                atomicAdd(&s_t[y0 * gw + tx0], 1u);
+                atomicAdd(&s_t[y0 * gw + tx1], 0xFFFFFFFFu);
+                atomicAdd(&s_t[y1 * gw + tx0], 0xFFFFFFFFu);
+                atomicAdd(&s_t[y1 * gw + tx1], 1u);
+            }
+            sum += cnt[k];
+        }
+        uint32_t off = carry + view_scan(sum, s_w, total);
+        carry += total;
+#pragma unroll
+        for (int k = 0; k < GRP; ++k) {
+            const int p = p0 + tid * GRP + k;
+            if (p < n) rank_off[rec0 + p] = off;
+            off += cnt[k];
+        }
+    }
+    if (tid == 0) vtot[blockIdx.x] = carry;
+    __syncthreads();
+    constexpr int STEP = 8;
+    auto prefix = [&](int at, int count, int stride) {
+        uint32_t acc = 0u;
+        for (int i = 0; i < count; i += STEP) {
+            uint32_t v[STEP];
+#pragma unroll
+            for (int j = 0; j < STEP; ++j) v[j] = i + j < count ? s_t[at + (i + j) * stride] : 0u;
+#pragma unroll
+            for (int j = 0; j < STEP; ++j) {
+                acc += v[j];
+                if (i + j < count) s_t[at + (i + j) * stride] = acc;
+            }
+        }
+    };
+    for (int y = tid; y < tyc; y += VL_THREADS) prefix(y * gw, txc, 1);
+    __syncthreads();
+    for (int x = tid; x < txc; x += VL_THREADS) prefix(x, tyc, gw);
+    __syncthreads();
+    // tiles in row-major order, VL_TILES / VL_THREADS to a thread
+    constexpr int PER = VL_TILES / VL_THREADS;
+    uint32_t c[PER];
+    uint32_t sum = 0u;
+    const int t0 = tid * PER, tiles = txc * tyc;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int t = t0 + k, y = t / txc;
+        c[k] = t < tiles ? s_t[y * gw + t - y * txc] : 0u;
+        sum += c[k];
+    }
+    uint32_t off = view_scan(sum, s_w, total);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (t0 + k < tiles) ranges[V.tile_c + t0 + k] = make_uint2(off, off + c[k]);
+        off += c[k];
+    }
+}
+
+// The list of one tile (a workgroup): which of the view's records, in depth
+// order, cover it (a wave takes a quarter of them, 64 at a time), then the
+// list's entries at the places k_view_lists counted. Sets the pair count (0
+// and the overflow flag above the capacity, with empty ranges).
+constexpr int TL_WAVES = 4;
+constexpr int TL_CHUNKS = VL_MAX / WAVE / TL_WAVES;   // of 64 records, per wave
+
+__global__ void __launch_bounds__(TL_WAVES * WAVE)
+k_tile_lists(const DevView* __restrict__ views, int nv, int64_t cap_c,
+             const uint32_t* __restrict__ order, const uint2* __restrict__ rect_sorted,
+             const uint32_t* __restrict__ rank_off, const unsigned long long* __restrict__ vtot,
+             uint32_t* __restrict__ status, uint2* __restrict__ ranges,
+             uint32_t* __restrict__ pkey, uint32_t* __restrict__ pval,
+             uint32_t* __restrict__ ppos, uint32_t* __restrict__ dord,
+             uint32_t* __restrict__ poff)
+{
+    __shared__ uint64_t s_m[TL_WAVES][TL_CHUNKS];
+    __shared__ unsigned long long s_before[TL_WAVES], s_all[TL_WAVES];
+    __shared__ uint32_t s_n[TL_WAVES];
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / WAVE;
+    const uint32_t tile = blockIdx.x;
+    const int vi = find_view(nv, (int64_t)tile, [&](int k) { return (int64_t)views[k].tile_c; });
+    const DevView& V = views[vi];
+    const int64_t rec0 = V.rec_off;
+    const int n = V.n, chunks = (n + WAVE - 1) / WAVE, per = (chunks + TL_WAVES - 1) / TL_WAVES;
+    const uint32_t local = tile - (uint32_t)V.tile_c;
+    const uint32_t ty = local / (uint32_t)V.txc, tx = local - ty * (uint32_t)V.txc;
+    // pairs of the views before, and of all
+    unsigned long long before = 0ull, all = 0ull;
+    for (int k = tid; k < nv; k += TL_WAVES * WAVE) {
+        const unsigned long long c = vtot[k];
+        all += c;
+        if (k < vi) before += c;
+    }
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        before += (unsigned long long)__shfl_xor((long long)before, d, WAVE);
+        all += (unsigned long long)__shfl_xor((long long)all, d, WAVE);
+    }
+    auto covers = [&](uint2 rc) {
+        return tx >= (rc.x & 0xFFFFu) && tx < rc.x >> 16 && ty >= (rc.y & 0xFFFFu) &&
+               ty < rc.y >> 16;
+    };
+    const int c0 = w * per, c1 = min(chunks, c0 + per);
+    uint32_t count = 0u;
+    constexpr int AHEAD = 8;   // loads in flight
+    for (int cb = c0; cb < c1; cb += AHEAD) {
+        uint2 rc[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const int p = (cb + k) * WAVE + lane;
+            rc[k] = cb + k < c1 && p < n ? rect_sorted[rec0 + p] : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const uint64_t m = __ballot(covers(rc[k]));
+            if (lane == 0 && cb + k < c1) s_m[w][cb + k - c0] = m;
+            count += (uint32_t)__popcll(m);
+        }
+    }
+    if (lane == 0) {
+        s_before[w] = before;
+        s_all[w] = all;
+        s_n[w] = count;
+    }
+    const uint2 rg = ranges[tile];
+    __syncthreads();
+    before = all = 0ull;
+#pragma unroll
+    for (int k = 0; k < TL_WAVES; ++k) {
+        before += s_before[k];
+        all += s_all[k];
+    }
+    const bool over = all > (unsigned long long)cap_c;
+    if (tile == 0 && tid == 0) {
+        status[ST_OVERFLOW] |= over ? 1u : 0u;
+        status[ST_PAIRS_C] = over ? 0u : (uint32_t)all;
+    }
+    if (tid == 0)
+        ranges[tile] = over || rg.y <= rg.x ? make_uint2(0u, 0u)
+                                            : make_uint2((uint32_t)before + rg.x,
+                                                         (uint32_t)before + rg.y);
+    // (deterministic mode) the first pair and the record of every depth rank:
+    // the view's tiles take equal parts
+    if (poff) {
+        const int64_t tiles = (int64_t)V.txc * V.tyc;
+        const int p1 = (int)((int64_t)n * (local + 1) / tiles);
+        for (int p = (int)((int64_t)n * local / tiles) + tid; p < p1; p += TL_WAVES * WAVE) {
+            poff[rec0 + p] = (uint32_t)before + rank_off[rec0 + p];
+            dord[rec0 + p] = order[rec0 + p];
+        }
+    }
+    if (over) return;
+    uint32_t o = (uint32_t)before + rg.x;
+    for (int k = 0; k < w; ++k) o += s_n[k];
+    const uint64_t lower = (1ull << lane) - 1ull;
+    for (int cb = c0; cb < c1; cb += AHEAD) {
+        uint64_t m[AHEAD];
+        uint32_t rec[AHEAD], off[AHEAD];
+        uint2 rc[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            m[k] = cb + k < c1 ? s_m[w][cb + k - c0] : 0ull;
+            const int64_t p = rec0 + (cb + k) * WAVE + lane;
+            rec[k] = off[k] = 0u;
+            rc[k] = make_uint2(0u, 0u);
+            if (m[k] >> lane & 1ull) {
+                rec[k] = order[p];
+                if (ppos) {
+                    rc[k] = rect_sorted[p];
+                    off[k] = rank_off[p];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            if (m[k] >> lane & 1ull) {
+                const uint32_t at = o + (uint32_t)__popcll(m[k] & lower);
+                pkey[at] = tile;
+                pval[at] = rec[k];
+                if (ppos) {
+                    const uint32_t rx = rc[k].x & 0xFFFFu, rw = (rc[k].x >> 16) - rx;
+                    ppos[at] = (uint32_t)before + off[k] + (ty - (rc[k].y & 0xFFFFu)) * rw + tx - rx;
+                }
+            }
+            o += (uint32_t)__popcll(m[k]);
+        }
+    }
+}
+
 // Tile ranges from the sorted bucket ids, four keys per thread (one 16-byte
 // load when the four are in range) and the neighbours of the first and last.
 __global__ void __launch_bounds__(256)
@@ -1281,6 +1579,26 @@ hipError_t launch_tile_ranges(const uint32_t* keys, int64_t cap, const uint32_t*
     if (e != hipSuccess || cap <= 0) return e;
     hipLaunchKernelGGL(k_ranges, dim3(grid256((cap + 3) / 4)), dim3(256), 0, s, keys, n_dev,
                        buckets, ranges);
+    return hipGetLastError();
+}
+
+hipError_t launch_view_lists(const DevView* views, int nv, int64_t max_records, int64_t tiles_c,
+                             int64_t cap_c, const uint32_t* dkey, const uint2* rect,
+                             uint32_t* order, uint2* rect_sorted, uint32_t* rank_off,
+                             unsigned long long* vtot, uint32_t* status, uint2* ranges,
+                             uint32_t* pkey, uint32_t* pval, uint32_t* ppos, uint32_t* dord,
+                             uint32_t* poff, hipStream_t s)
+{
+    if (nv < 1 || max_records > VL_MAX) return hipErrorInvalidValue;
+    if (max_records > 0)
+        hipLaunchKernelGGL(k_view_rank, dim3((unsigned)((max_records + WAVE - 1) / WAVE),
+                                             (unsigned)nv),
+                           dim3(VL_THREADS), 0, s, views, dkey, rect, order, rect_sorted);
+    hipLaunchKernelGGL(k_view_counts, dim3((unsigned)nv), dim3(VL_THREADS), 0, s, views,
+                       rect_sorted, rank_off, ranges, vtot);
+    hipLaunchKernelGGL(k_tile_lists, dim3((unsigned)tiles_c), dim3(TL_WAVES * WAVE), 0, s, views,
+                       nv, cap_c, order, rect_sorted, rank_off, vtot, status, ranges, pkey, pval,
+                       ppos, dord, poff);
     return hipGetLastError();
 }
 

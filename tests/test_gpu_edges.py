@@ -177,3 +177,54 @@ def test_image_metrics_tiles(cuda, h, w, given):
     if not given:
         with pytest.raises(C.SDGRError):
             train.image_metrics(x, torch.zeros_like(y))
+
+
+def run_views(scenes_, views, cuda, options, cots):
+    """A, images and gradients per view set (one call)."""
+    from paper_2506_21633_amd import api
+    gs = [api.GaussianTensors.from_numpy(s, cuda) for s in scenes_]
+    r = api.Renderer(gs, views, options)
+    res = r.forward()
+    A = r.intensity_shares(res).cpu().numpy()
+    images = [res.image(v).cpu().numpy() for v in range(len(views))]
+    flat = torch.as_tensor(np.concatenate([c.ravel() for c in cots]).astype(np.float32),
+                           device=cuda)
+    d = r.backward(res, flat)
+    r.status(res)
+    return A, images, [{k: t.cpu().numpy() for k, t in g.items()} for g in d]
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 8192, 8193, 16384, 16385])
+def test_small_view_lists(cuda, n):
+    """Views around the list-building kernels' record counts, beside a second
+    scene of another count: the deterministic mode gives the same A, bit for
+    bit, as in a call that also has a view too wide for these kernels (the
+    sorts build every list then), and gradients and images within the
+    rounding of FP32 sums; the other modes agree with it."""
+    from paper_2506_21633_amd import api
+    rng = np.random.default_rng(n)
+    sc = [spread_scene(n, m, (2.0, 8.0, 8.0), 0.1, 0.3) for m in (n, max(n // 3, 1))]
+    sc[0].means[:: 7] = sc[0].means[0]   # equal depths keep their order
+    views = [grid_view(12, 12), grid_view(5, 30, azimuth=40.0), grid_view(9, 4, azimuth=80.0)]
+    views[1].scene = 1
+    wide = grid_view(257, 1, azimuth=10.0)
+    cots = [rng.standard_normal((v.img_h, v.img_w)) for v in views]
+    det = api.RenderOptions(deterministic=True)
+    A, images, grads = run_views(sc, views, cuda, det, cots)
+    A2, images2, grads2 = run_views(sc, views + [wide], cuda, det,
+                                    cots + [np.zeros((wide.img_h, wide.img_w))])
+    assert np.array_equal(A, A2[:A.size])
+    for a, b in zip(images, images2):
+        assert elem_err(a, b) <= 1e-6
+    for g, g2 in zip(grads, grads2):
+        for k in g:
+            assert elem_err(g[k], g2[k]) <= 1e-5, k
+    for options in (api.RenderOptions(), api.RenderOptions(recompute=True)):
+        B, imagesB, gradsB = run_views(sc, views, cuda, options, cots)
+        assert elem_err(B, A) <= ELEM
+        for a, b in zip(imagesB, images):
+            assert elem_err(a, b) <= ELEM
+        for g, g2 in zip(gradsB, grads):
+            for k in g:
+                a, b = g[k].ravel().astype(np.float64), g2[k].ravel().astype(np.float64)
+                assert np.linalg.norm(a - b) <= GRAD_L2 * np.linalg.norm(b), k
