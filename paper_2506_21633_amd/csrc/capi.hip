@@ -136,6 +136,8 @@ struct Problem {
     int ikey_bits = 0;      // bits of the tile within a view
     bool view_lists = false;   // lists of small views, see launch_view_lists
     int64_t max_n = 0;         // most records of a view
+    bool images_apart = false; // the views' images follow one another
+    int64_t reads_i = 0;       // records of the view, summed over the imaging tiles
     int64_t hit_units = 0;  // 16-byte units of the stored-hit stream (0: none)
 };
 
@@ -308,6 +310,13 @@ int build_problem(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
         pairs += (int64_t)V.n * V.n;
     }
     P.view_lists = fits && P.max_n <= VL_MAX && reads <= VL_READS && pairs <= VL_PAIRS;
+    P.images_apart = true;
+    int64_t end = 0;
+    for (const DevView& V : P.views) {
+        P.images_apart = P.images_apart && V.img_off >= end;
+        end = V.img_off + (int64_t)V.W * V.H;
+        P.reads_i += (int64_t)V.txi * V.tyi * V.n;
+    }
     P.image_floats = img;
     P.pixels = pix;
     return SDGR_OK;
@@ -540,6 +549,24 @@ int bits_pairs_i(const Problem& P)
 }
 int final_buffer_c(const Problem& P) { return radix_passes_for(bits_pairs_c(P)) & 1; }
 int final_buffer_i(const Problem& P) { return radix_passes_for(bits_pairs_i(P)) & 1; }
+
+// Whether pass B goes without imaging-plane lists: where its longer time is
+// less than the launches it saves (about 6.5 us each with what they do).
+// That time, fitted in us over 1 to 36 views of 64 to 700 pixels and 100 to
+// 64k Gaussians: 0.65 per million rectangles read, 73 per million pairs, 0.55
+// per thousand records of a view (a wave's chain), 1.9 per thousand tiles. A
+// whole forward with and without lists: 1000 Gaussians in one view 112 and 79
+// us, 32k 242 and 231, 64k 256 and 271; 4000 in 36 views 268 and 254, 7000
+// 323 and 328; 4000 on 4096 tiles (two sort passes) 204 and 122, 1000 on 65k
+// tiles 381 and 463. The images must not overlap: each pixel is stored, not
+// added to.
+bool without_lists_i(const Problem& P, const sdgr_plan* plan)
+{
+    const int launches = 3 + 3 * radix_passes_for(bits_pairs_i(P));
+    const double us = 0.65e-6 * (double)P.reads_i + 73e-6 * (double)plan->pairs_i +
+                      0.55e-3 * (double)P.max_n + 1.9e-3 * (double)P.tiles_i;
+    return P.images_apart && us < 5.5 * launches;
+}
 
 // Footprint masks of the sorted pairs and the tile worklist.
 int finish_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, const uint32_t* pkey,
@@ -903,6 +930,13 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
         StageTimer t(SG_INTENSITY, s);
         SDGR_HIP(launch_set_intensity(b.views, b.scenes, P.nv, P.records, b.A, b.prec, b.iw,
                                       b.rect_i, b.cnt_i, b.bsum_i, b.status, b.active, s));
+    }
+    if (without_lists_i(P, plan)) {
+        StageTimer t(SG_RASTER_B_FWD, s);
+        SDGR_HIP(launch_raster_b_direct(b.views, P.nv, P.tiles_c, P.tiles_i, P.records,
+                                        plan->pairs_i, P.rp, b.bsum_i, b.status, b.rect_i, b.iq,
+                                        b.iw, images, s));
+        return SDGR_OK;
     }
     if ((rc = build_lists_i(P, plan, b, s))) return rc;
     const int pwi = final_buffer_i(P);

@@ -520,6 +520,14 @@ hipError_t launch_raster_b_fwd(const DevView* views, int nv, int64_t pixels, int
                                int64_t cap_i, const RasterParams& rp, const uint32_t* status,
                                const uint32_t* pkey, const uint32_t* pvals, const float4* iq,
                                const float2* iw, float* images, bool vm, hipStream_t s);
+// Pass B over the views' records themselves, without imaging-plane lists:
+// stores every pixel, sets the pair count in status (bsum: counts per 256
+// records).
+hipError_t launch_raster_b_direct(const DevView* views, int nv, int64_t tiles_c, int64_t tiles_i,
+                                  int64_t records, int64_t cap_i, const RasterParams& rp,
+                                  const uint32_t* bsum, uint32_t* status, const uint2* rect,
+                                  const float4* iq, const float2* iw, float* images,
+                                  hipStream_t s);
 hipError_t launch_ranges_i(const DevView* views, const uint32_t* keys, const uint32_t* status,
                            int64_t cap_i, int64_t tiles_c, int64_t tiles_i, bool vm,
                            uint2* ranges, hipStream_t s);

@@ -1029,6 +1029,134 @@ k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int6
     if (tc.inside) images[V.img_off + (int64_t)tc.row * V.W + tc.col] = acc;
 }
 
+// Pass B without lists, for few records per tile: a workgroup takes a tile
+// of the image and goes over the view's records itself. Each wave takes an
+// equal run of them, keeps those whose rectangle has the tile and whose
+// intensity is not zero, and adds them to its pixels 64 at a time as pass B
+// does; the waves' sums meet in LDS and every pixel is stored once. It takes
+// the place of the scan, the emission, the sort (3 to 6 launches), the
+// zeroing and the tile sums, which were bound by their launches. Also counts
+// the pairs the lists would have (for the overflow flag).
+constexpr int BD_WAVES = 8;
+
+__global__ void __launch_bounds__(BD_WAVES * WAVE)
+k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, int64_t tiles_c,
+                  int64_t cap_i, const uint32_t* __restrict__ bsum, int64_t nbsum,
+                  uint32_t* __restrict__ status, const uint2* __restrict__ rect,
+                  const float4* __restrict__ iq, const float2* __restrict__ iw,
+                  float* __restrict__ images)
+{
+    __shared__ float4 s_q[BD_WAVES][2 * WAVE];
+    __shared__ float2 s_w[BD_WAVES][2 * WAVE];
+    __shared__ float s_acc[BD_WAVES][WAVE];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), lane = lane_id();
+    const TransposeLane tl = transpose_lane();
+    const TileCell tc = tile_cell(views, nv, tiles_c + blockIdx.x, false);
+    const DevView& V = views[tc.v];
+    const int64_t rec0 = V.rec_off;
+    const int n = V.n, chunks = (n + WAVE - 1) / WAVE, per = (chunks + BD_WAVES - 1) / BD_WAVES;
+    const int c0 = w * per, c1 = min(chunks, c0 + per);
+    const uint32_t tx = (uint32_t)tc.tx, ty = (uint32_t)tc.ty;
+    const float px = tc.col + 0.5f, py = tc.row + 0.5f;
+    float acc = 0.0f;
+    unsigned long long n_iter = 0, n_hits = 0;   // work counters
+    // the first cnt (up to 64) records kept
+    auto add = [&](uint32_t cnt) {
+        uint64_t m = 0ull;
+        if ((uint32_t)lane < cnt) {
+            const float4 g = s_q[w][lane];
+            m = footprint_mask<false>(g.x, g.y, g.z, g.w, s_w[w][lane].x, rp.q_max, tc.tx, tc.ty);
+        }
+        uint64_t col = transpose64(m, tl);
+        if (!tc.inside) col = 0ull;
+        while (__ballot(col != 0ull) != 0ull) {
+            ++n_iter;
+            if (col != 0ull) {
+                const int j = __builtin_ctzll(col);
+                col &= col - 1ull;
+                const float4 g = s_q[w][j];
+                const float2 g2 = s_w[w][j];
+                const float q = quadform(g, g2.x, px - g.x, py - g.y);
+                if (q < rp.q_max) {
+                    ++n_hits;
+                    acc += (__expf(-0.5f * q) - rp.eps) * rp.inv1meps * g2.y;
+                }
+            }
+        }
+    };
+    uint32_t kept = 0u;
+    constexpr int AHEAD = 4;   // chunks whose loads are in flight together
+    for (int cb = c0; cb < c1; cb += AHEAD) {
+        uint2 rc[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const int p = (cb + k) * WAVE + lane;
+            rc[k] = cb + k < c1 && p < n ? rect[rec0 + p] : make_uint2(0u, 0u);
+        }
+        float4 g[AHEAD];
+        float2 g2[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const int64_t r = rec0 + (cb + k) * WAVE + lane;
+            g2[k] = make_float2(0.0f, 0.0f);
+            if (tx >= (rc[k].x & 0xFFFFu) && tx < rc[k].x >> 16 && ty >= (rc[k].y & 0xFFFFu) &&
+                ty < rc[k].y >> 16) {
+                g[k] = iq[r];
+                g2[k] = iw[r];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const bool hit = g2[k].y != 0.0f;   // zero intensity adds nothing
+            const uint64_t m = __ballot(hit);
+            if (m == 0ull) continue;
+            if (hit) {
+                const uint32_t at = kept + lanes_below(m);
+                s_q[w][at] = g[k];
+                s_w[w][at] = g2[k];
+            }
+            kept += (uint32_t)__popcll(m);
+            wave_lds_sync();
+            if (kept >= WAVE) {
+                add(WAVE);
+                kept -= WAVE;
+                wave_lds_sync();
+                if ((uint32_t)lane < kept) {
+                    s_q[w][lane] = s_q[w][WAVE + lane];
+                    s_w[w][lane] = s_w[w][WAVE + lane];
+                }
+                wave_lds_sync();
+            }
+        }
+    }
+    if (kept) add(kept);
+    s_acc[w][lane] = acc;
+    __syncthreads();
+    if (w == 0 && tc.inside) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < BD_WAVES; ++k) sum += s_acc[k][lane];
+        images[V.img_off + (int64_t)tc.row * V.W + tc.col] = sum;
+    }
+    if (blockIdx.x == 0 && w == 1) {
+        unsigned long long pairs = 0ull;
+        for (int64_t k = lane; k < nbsum; k += WAVE) pairs += bsum[k];
+        pairs = wave_sum_u64(pairs);
+        if (lane == 0) {
+            const bool over = pairs > (unsigned long long)cap_i;
+            status[ST_OVERFLOW] |= over ? 1u : 0u;
+            status[ST_PAIRS_I] = over ? 0u : (uint32_t)pairs;
+        }
+    }
+    if (rp.work) {
+        n_hits = wave_sum_u64(n_hits);
+        if (lane == 0) {
+            atomicAdd(&rp.work[6], n_iter);
+            atomicAdd(&rp.work[2], n_hits);
+        }
+    }
+}
+
 // Imaging-plane backward, one thread per used record (view, Gaussian): the
 // additive image formation has no order, so each thread walks its own
 // footprint ellipse q < q_max row by row (exact column span from the conic,
@@ -2125,6 +2253,19 @@ hipError_t launch_raster_b_fwd(const DevView* views, int nv, int64_t pixels, int
     const int64_t segs = (cap_i + B_SEGMENT - 1) / B_SEGMENT;
     hipLaunchKernelGGL(k_raster_b_fwd, dim3(raster_grid(segs)), dim3(RASTER_THREADS), 0, s, views,
                        nv, rp, cap_c, status, pkey, pvals, iq, iw, images, vm ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_raster_b_direct(const DevView* views, int nv, int64_t tiles_c, int64_t tiles_i,
+                                  int64_t records, int64_t cap_i, const RasterParams& rp,
+                                  const uint32_t* bsum, uint32_t* status, const uint2* rect,
+                                  const float4* iq, const float2* iw, float* images,
+                                  hipStream_t s)
+{
+    if (tiles_i <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_raster_b_direct, dim3((unsigned)tiles_i), dim3(BD_WAVES * WAVE), 0, s,
+                       views, nv, rp, tiles_c, cap_i, bsum, (records + 255) / 256, status, rect,
+                       iq, iw, images);
     return hipGetLastError();
 }
 

@@ -228,3 +228,37 @@ def test_small_view_lists(cuda, n):
             for k in g:
                 a, b = g[k].ravel().astype(np.float64), g2[k].ravel().astype(np.float64)
                 assert np.linalg.norm(a - b) <= GRAD_L2 * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 513, 4000])
+@pytest.mark.parametrize("deterministic", [False, True], ids=["any", "ordered"])
+def test_images_without_lists(cuda, n, deterministic):
+    """Small calls form their images without imaging-plane lists: against the
+    oracle, ragged tiles and one view alone included; images that overlap in
+    the buffer still add up (with atomics), and a plan with too few pairs is
+    still refused."""
+    from paper_2506_21633_amd import _capi as C
+    from paper_2506_21633_amd import api
+    scene = spread_scene(n + 3, n, (2.0, 6.0, 6.0), 0.1, 0.4)
+    views = [grid_view(9, 7), grid_view(1, 13, azimuth=70.0), grid_view(6, 6, azimuth=33.0)]
+    views[0].img_w, views[0].img_h = 69, 53   # ragged tiles
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    options = api.RenderOptions(deterministic=deterministic)
+    r = api.Renderer([g], views, options)
+    res = r.forward()
+    r.status(res)
+    _, _, want = oracle.forward(scene, views)
+    for v in range(len(views)):
+        alone = api.Renderer([g], views[v:v + 1], options).forward()
+        assert elem_err(res.image(v).cpu().numpy(), want[v]) <= ELEM, v
+        assert elem_err(alone.image(0).cpu().numpy(), want[v]) <= ELEM, v
+    if not deterministic:
+        both = api.Renderer([g], [views[2], grid_view(6, 6, azimuth=-20.0)], options)
+        both.views_c[1].img_offset = 0
+        _, _, add = oracle.forward(scene, [views[2], grid_view(6, 6, azimuth=-20.0)])
+        assert elem_err(both.forward().images.reshape(-1)[:48 * 48].cpu().numpy(),
+                        (add[0] + add[1]).ravel()) <= ELEM
+    if n >= 513:
+        plan = r.plan_for(r.plan().pairs_c, 100)
+        with pytest.raises(C.SDGRError):
+            r.status(r.forward(plan))
