@@ -251,7 +251,9 @@ class Renderer:
         plan = plan or self.plan()
         state = _buf(plan.state_bytes, self.device)
         scratch = _buf(plan.fwd_scratch_bytes, self.device)
-        images = torch.zeros(max(int(plan.image_floats), 1), dtype=torch.float32,
+        # the forward writes every pixel of every view, and the views' images
+        # fill the buffer
+        images = torch.empty(max(int(plan.image_floats), 1), dtype=torch.float32,
                              device=self.device)
         C.check(self.lib.sdgr_forward(self.scenes_c, len(self.scenes), self.views_c, self.nv,
                                       ctypes.byref(self.opts_c), ctypes.byref(plan),

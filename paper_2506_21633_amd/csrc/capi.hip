@@ -491,7 +491,7 @@ struct ViewsCache {
 ViewsCache g_views;
 constexpr size_t VIEWS_CACHE_STATES = 64;
 
-int upload_tables(const Problem& P, const Bufs& b, hipStream_t s, const void* state, bool forward)
+void upload_tables(const Problem& P, const Bufs& b, Setup& setup, const void* state, bool forward)
 {
     const size_t nb = sizeof(DevView) * (size_t)P.nv;
     const char* bytes = reinterpret_cast<const char*>(P.views.data());
@@ -502,15 +502,27 @@ int upload_tables(const Problem& P, const Bufs& b, hipStream_t s, const void* st
         skip = it != g_views.last.end() && it->second.size() == nb &&
                std::memcmp(it->second.data(), bytes, nb) == 0;
     }
-    if (!skip) SDGR_HIP(launch_upload(b.views, P.views.data(), nb, s));
-    SDGR_HIP(launch_upload(b.scenes, P.scenes.data(), sizeof(DevScene) * P.ns, s));
+    if (!skip) setup.table(b.views, P.views.data(), nb);
+    setup.table(b.scenes, P.scenes.data(), sizeof(DevScene) * P.ns);
     if (forward) {
         std::lock_guard<std::mutex> g(g_views.mu);
         if (g_views.last.size() >= VIEWS_CACHE_STATES && !g_views.last.count(state))
             g_views.last.clear();
         g_views.last[state].assign(bytes, bytes + nb);
     }
-    return SDGR_OK;
+}
+
+// What the list building starts from: its status words (the work counters
+// and the imaging-plane pair count of the forward survive a recomputing
+// backward) and empty tile ranges.
+void setup_lists_c(const Problem& P, const Bufs& b, Setup& setup)
+{
+    setup.fill(b.status, 0u, ST_PAIRS_I);
+    setup.fill(b.status + ST_PAIRS_I + 1, 0u, ST_RECORDS - ST_PAIRS_I - 1);
+    setup.fill(b.status + ST_RECORDS, (uint32_t)P.records, 1);
+    setup.fill(b.status + ST_RECORDS + 1, 0u, WORK_WORD - ST_RECORDS - 1);
+    setup.fill(b.status + WL_BINS, 0u, STATUS_WORDS - WL_BINS);
+    if (!P.view_lists) setup.fill((uint32_t*)b.ranges, 0u, 2 * P.tiles_c);
 }
 
 int check_plan(Problem& P, const sdgr_plan* plan)
@@ -585,18 +597,11 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
                   hipStream_t s)
 {
     const int64_t R = P.records;
-    // list-building words only: the work counters and the imaging-plane pair
-    // count of the forward survive a recomputing backward
-    SDGR_HIP(launch_fill_u32(b.status, 0u, ST_PAIRS_I, s));
-    SDGR_HIP(launch_fill_u32(b.status + ST_PAIRS_I + 1, 0u, WORK_WORD - ST_PAIRS_I - 1, s));
-    SDGR_HIP(launch_fill_u32(b.status + ST_RECORDS, (uint32_t)R, 1, s));
     {
         StageTimer t(SG_PREPROCESS, s);
         SDGR_HIP(launch_preprocess(b.views, b.scenes, P.nv, P.ns, P.items, P.rp, true, b.crec, b.iq,
                                    b.iw, b.rect_c, b.rect_i, b.dkey[0],
-                                   zero_A ? b.A : nullptr, b.prec, b.slots,
-                                   reinterpret_cast<unsigned long long*>(b.status + ST_COUNT),
-                                   s));
+                                   zero_A ? b.A : nullptr, b.prec, nullptr, nullptr, s));
     }
     if (P.view_lists) {
         const int pb = final_buffer_c(P);
@@ -631,8 +636,8 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
     {
         StageTimer t(SG_BIN, s);
         SDGR_HIP(launch_gather_rects(dv[which], b.rect_c, R, b.rect_c_sorted, b.bsum_c, s));
-        SDGR_HIP(launch_scan_blocks(b.bsum_c, (R + 255) / 256, plan->pairs_c, b.status, -1, s));
-        SDGR_HIP(launch_pair_total_c(plan->pairs_c, b.status, s));
+        SDGR_HIP(launch_scan_blocks(b.bsum_c, (R + 255) / 256, plan->pairs_c, b.status, ST_PAIRS_C,
+                                    s));
         SDGR_HIP(launch_emit_pairs_c(b.views, P.nv, R, dv[which], b.rect_c_sorted, b.bsum_c,
                                      plan->pairs_c, b.status, pk[0], pv[0],
                                      P.seg ? b.segt[1].seg : nullptr, b.dord, b.poff, s));
@@ -696,9 +701,12 @@ int count_and_plan(const Problem& P, char* query, hipStream_t s, sdgr_plan* plan
     unsigned long long* slots = a.take<unsigned long long>(2 * TOTAL_SLOTS);
     DevView* dviews = a.take<DevView>(P.nv);
     DevScene* dscenes = a.take<DevScene>(P.ns);
-    SDGR_HIP(launch_upload(dviews, P.views.data(), sizeof(DevView) * P.nv, s));
-    SDGR_HIP(launch_upload(dscenes, P.scenes.data(), sizeof(DevScene) * P.ns, s));
-    SDGR_HIP(launch_fill_u32((uint32_t*)totals, 0u, 16, s));
+    Setup setup;
+    setup.table(dviews, P.views.data(), sizeof(DevView) * P.nv);
+    setup.table(dscenes, P.scenes.data(), sizeof(DevScene) * P.ns);
+    setup.fill((uint32_t*)totals, 0u, 16);
+    setup.fill((uint32_t*)slots, 0u, 4 * TOTAL_SLOTS);
+    SDGR_HIP(setup.launch(s));
     {
         StageTimer t(SG_QUERY, s);
         SDGR_HIP(launch_preprocess(dviews, dscenes, P.nv, P.ns, P.items, P.rp, false, nullptr,
@@ -891,14 +899,19 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
     layout(P, plan->pairs_c, plan->pairs_i, FWD, (char*)state, (char*)scratch, b, nullptr,
            nullptr);
     if (g_count_work) P.rp.work = reinterpret_cast<unsigned long long*>(b.status + WORK_WORD);
-    if ((rc = upload_tables(P, b, s, state, true))) return rc;
-    SDGR_HIP(launch_fill_u32(b.status + ST_PAIRS_I, 0u, 1, s));
-    SDGR_HIP(launch_fill_u32(b.status + WORK_WORD, 0u, STATUS_WORDS - WORK_WORD, s));
+    Setup setup;
+    upload_tables(P, b, setup, state, true);
+    setup_lists_c(P, b, setup);
+    setup.fill(b.status + ST_PAIRS_I, 0u, 1);
+    setup.fill(b.status + WORK_WORD, 0u, WL_BINS - WORK_WORD);
+    // one fill from tau to the end of nlast: rays of empty tiles have none
+    setup.fill((uint32_t*)b.tau, 0u, (int64_t)(b.nlast - (uint32_t*)b.tau) + P.rays);
+    if (b.hits) setup.fill((uint32_t*)b.hit_tops, 0u, 2 * HIT_SUBS * HIT_TOP_STRIDE);
+    if (P.det) setup.fill((uint32_t*)b.part_a, 0u, plan->pairs_c);
+    SDGR_HIP(setup.launch(s));
     // the projection also clears A for pass A's sums
     if ((rc = build_lists_c(P, plan, b, true, s))) return rc;
     const int pw = final_buffer_c(P);
-    SDGR_HIP(launch_fill_u32((uint32_t*)b.tau, 0u, P.rays, s));   // rays of empty tiles
-    SDGR_HIP(launch_fill_u32(b.nlast, 0u, P.rays, s));
     {
         StageTimer t(SG_RASTER_A_FWD, s);
         RasterParams rp = P.rp;
@@ -910,12 +923,9 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
             rp.hit_subs = (uint32_t)std::min<int64_t>(
                 std::max<int64_t>(P.hit_units / HIT_SUB_MIN, 1), HIT_SUBS);
             rp.hit_sub_cap = rp.hit_cap / rp.hit_subs;
-            SDGR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(b.hit_tops), 0u,
-                                     2 * HIT_SUBS * HIT_TOP_STRIDE, s));
         }
         if (P.det) {
             // one partial per (tile, record) pair, summed per record in list order
-            SDGR_HIP(launch_fill_u32((uint32_t*)b.part_a, 0u, plan->pairs_c, s));
             rp.ppos = b.ppos[pw];
             rp.part = b.part_a;
         }
@@ -987,7 +997,12 @@ int sdgr_backward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
     layout(P, plan->pairs_c, plan->pairs_i, BWD, (char*)state, (char*)scratch, b, nullptr,
            nullptr);
     if (g_count_work) P.rp.work = reinterpret_cast<unsigned long long*>(b.status + WORK_WORD);
-    if ((rc = upload_tables(P, b, s, state, false))) return rc;
+    Setup setup;
+    upload_tables(P, b, setup, state, false);
+    if (P.recompute) setup_lists_c(P, b, setup);
+    if (b.hits) setup.fill((uint32_t*)b.hit_touched, 0u, (plan->pairs_c + 3) / 4);
+    if (P.det) setup.fill((uint32_t*)b.part_g, 0u, 6 * plan->pairs_c);
+    SDGR_HIP(setup.launch(s));
     if (P.recompute) {
         // the forward's lists are gone: rebuild them (identical, the sorts
         // are deterministic) and refill the intensities from the kept A
@@ -1014,11 +1029,8 @@ int sdgr_backward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
             rp.hit_ppos = b.ppos[pw];
             rp.hit_part = b.hit_part;
             rp.hit_touched = b.hit_touched;
-            SDGR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(b.hit_touched), 0u,
-                                     (plan->pairs_c + 3) / 4, s));
         }
         if (P.det) {
-            SDGR_HIP(launch_fill_u32((uint32_t*)b.part_g, 0u, 6 * plan->pairs_c, s));
             rp.ppos = b.ppos[pw];
             rp.part = b.part_g;
             rp.part_stride = plan->pairs_c;

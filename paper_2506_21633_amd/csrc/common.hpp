@@ -153,8 +153,7 @@ enum StatusSlot : int {
     ST_PAIRS_C = 1,    // computation-plane pairs of the last projection (sort length)
     ST_PAIRS_I = 2,    // imaging-plane pairs of records with nonzero intensity
     ST_WORK_TILES = 4, // non-empty computation-plane tiles in the worklist
-    ST_ACTIVE = 5,     // records pass A used (backward list length)
-    ST_COUNT = 8       // u64 pair totals of the projection at status + 8
+    ST_ACTIVE = 5      // records pass A used (backward list length)
 };
 
 // Index of the view a global record / bucket belongs to: the last v with
@@ -378,8 +377,9 @@ __device__ inline uint64_t footprint_mask(float cx, float cy, float a, float b, 
 namespace sdgr {
 
 
-// Pair totals of the projection are accumulated in 2 x TOTAL_SLOTS u64
-// slots (spread atomics) and summed into totals[0..1].
+// Optional (slots): the pair totals of the projection, accumulated in
+// 2 x TOTAL_SLOTS u64 slots (spread atomics, from zero) and summed into
+// totals[0..1].
 constexpr int TOTAL_SLOTS = 1024;
 hipError_t launch_preprocess(const DevView* views, const DevScene* scenes, int nv, int nscenes,
                              int64_t items, const RasterParams& rp,
@@ -450,8 +450,6 @@ hipError_t launch_gather_rects(const uint32_t* order, const uint2* rect, int64_t
 // cap as an overflow.
 hipError_t launch_scan_blocks(uint32_t* bsum, int64_t n, int64_t cap, uint32_t* status,
                               int status_slot, hipStream_t s);
-// overflow check and actual pair counts from the projection's u64 totals
-hipError_t launch_pair_total_c(int64_t cap_c, uint32_t* status, hipStream_t s);
 // (dord, poff optional: the record at each depth rank and its first pair)
 hipError_t launch_emit_pairs_c(const DevView* views, int nv, int64_t records,
                                const uint32_t* dval_sorted, const uint2* rect_sorted,
@@ -495,11 +493,36 @@ hipError_t launch_view_lists(const DevView* views, int nv, int64_t max_records, 
                              unsigned long long* vtot, uint32_t* status, uint2* ranges,
                              uint32_t* pkey, uint32_t* pval, uint32_t* ppos, uint32_t* dord,
                              uint32_t* poff, hipStream_t s);
+// (ranges start at zero)
 hipError_t launch_tile_ranges(const uint32_t* keys, int64_t cap, const uint32_t* n_dev,
                               int64_t buckets, uint2* ranges, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_or_word(const uint32_t* src, uint32_t* dst, hipStream_t s);
-hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t s);
+
+// Word fills and small host tables (a multiple of 4 bytes each) that a call
+// starts with, in as few launches as the tables' size allows. The fills and
+// tables must not overlap.
+struct SetupFill {
+    uint32_t* p;
+    int64_t n;
+    uint32_t v;
+};
+struct Setup {
+    static constexpr int FILLS = 10, TABLES = 4;
+    void fill(uint32_t* p, uint32_t v, int64_t n);
+    void table(void* dst, const void* src, size_t bytes);
+    hipError_t launch(hipStream_t s) const;
+
+private:
+    struct Table {
+        void* dst;
+        const void* src;
+        size_t bytes;
+    };
+    SetupFill fills[FILLS];
+    Table tables[TABLES];
+    int nfill = 0, ntable = 0;
+};
 
 // tight: the masks whose hits the re-deriving backward and the deterministic
 // sums go by (see footprint_mask)
@@ -508,6 +531,7 @@ hipError_t launch_pair_masks(const DevView* views, int nv, int64_t cap_c, const 
                              const uint32_t* status, const uint32_t* pkey,
                              const uint32_t* pvals, const CRec* crec,
                              uint64_t* pmask, uint64_t* psum, hipStream_t s);
+// (bins start at zero)
 hipError_t launch_tile_worklist(const uint2* ranges, int64_t tiles_c, uint32_t* worklist,
                                 uint32_t* bins, uint32_t* status, hipStream_t s);
 hipError_t launch_raster_a_fwd(const DevView* views, int nv, int64_t tiles_c,

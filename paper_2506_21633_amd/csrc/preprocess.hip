@@ -203,9 +203,6 @@ k_preprocess(const DevView* __restrict__ views, const DevScene* __restrict__ sce
              uint32_t* __restrict__ dkey, float* __restrict__ A_zero,
              float* __restrict__ prec, unsigned long long* __restrict__ totals)
 {
-    __shared__ unsigned long long part[2];
-    if (threadIdx.x < 2) part[threadIdx.x] = 0;
-    __syncthreads();
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint32_t nc = 0, ni = 0;
     if (t < items) {
@@ -305,6 +302,10 @@ k_preprocess(const DevView* __restrict__ views, const DevScene* __restrict__ sce
             }
         }
     }
+    if (!totals) return;
+    __shared__ unsigned long long part[2];
+    if (threadIdx.x < 2) part[threadIdx.x] = 0;
+    __syncthreads();
     // wave sums first: 256 same-address LDS atomics would serialise
     unsigned long long wc = nc, wi = ni;
 #pragma unroll
@@ -326,14 +327,23 @@ k_preprocess(const DevView* __restrict__ views, const DevScene* __restrict__ sce
 __global__ void __launch_bounds__(1024)
 k_sum_slots(const unsigned long long* __restrict__ slots, unsigned long long* __restrict__ out)
 {
-    __shared__ unsigned long long acc[2];
-    if (threadIdx.x < 2) acc[threadIdx.x] = 0;
+    __shared__ unsigned long long s_sum[TOTAL_SLOTS / WAVE][2];
+    unsigned long long c = slots[2 * threadIdx.x], i = slots[2 * threadIdx.x + 1];
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        c += (unsigned long long)__shfl_xor((long long)c, d, WAVE);
+        i += (unsigned long long)__shfl_xor((long long)i, d, WAVE);
+    }
+    if (lane_id() == 0) {
+        s_sum[threadIdx.x / WAVE][0] = c;
+        s_sum[threadIdx.x / WAVE][1] = i;
+    }
     __syncthreads();
-    const unsigned long long c = slots[2 * threadIdx.x], i = slots[2 * threadIdx.x + 1];
-    if (c) atomicAdd(&acc[0], c);
-    if (i) atomicAdd(&acc[1], i);
-    __syncthreads();
-    if (threadIdx.x < 2) out[threadIdx.x] = acc[threadIdx.x];
+    if (threadIdx.x < 2) {
+        unsigned long long sum = 0ull;
+        for (int k = 0; k < TOTAL_SLOTS / WAVE; ++k) sum += s_sum[k][threadIdx.x];
+        out[threadIdx.x] = sum;
+    }
 }
 
 // I = P A into the imaging record (incident intensity 1, Sec. II-A; P the
@@ -644,12 +654,6 @@ k_params_reduce(const DevScene* __restrict__ scenes, int nscenes, int64_t items,
 
 inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-__global__ void __launch_bounds__(256) k_fill_u64(unsigned long long* p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
-}
-
 }  // namespace
 
 hipError_t launch_preprocess(const DevView* views, const DevScene* scenes, int nv, int nscenes,
@@ -659,8 +663,6 @@ hipError_t launch_preprocess(const DevView* views, const DevScene* scenes, int n
                              unsigned long long* slots, unsigned long long* totals,
                              hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fill_u64, dim3(2 * TOTAL_SLOTS / 256), dim3(256), 0, s, slots,
-                       2 * TOTAL_SLOTS);
     if (items > 0 && nv > 0)
         hipLaunchKernelGGL(k_preprocess,
                            dim3(blocks_for(items, 256), (unsigned)((nv + PRE_VIEWS - 1) / PRE_VIEWS)),
@@ -668,7 +670,8 @@ hipError_t launch_preprocess(const DevView* views, const DevScene* scenes, int n
                            write_records ? 1 : 0, crec, iq, iw, rect_c, rect_i, dkey,
                            write_records ? A_zero : nullptr, write_records ? prec : nullptr,
                            slots);
-    hipLaunchKernelGGL(k_sum_slots, dim3(1), dim3(TOTAL_SLOTS), 0, s, slots, totals);
+    if (slots)
+        hipLaunchKernelGGL(k_sum_slots, dim3(1), dim3(TOTAL_SLOTS), 0, s, slots, totals);
     return hipGetLastError();
 }
 

@@ -2209,8 +2209,6 @@ hipError_t launch_tile_worklist(const uint2* ranges, int64_t tiles_c, uint32_t* 
                            tiles_c, bins, status, worklist);
         return hipGetLastError();
     }
-    hipError_t e = launch_fill_u32(bins, 0u, 66, s);
-    if (e != hipSuccess) return e;
     const unsigned wl_grid = (unsigned)((tiles_c + WL_TILES - 1) / WL_TILES);
     if (tiles_c > 0)
         hipLaunchKernelGGL(k_worklist_count, dim3(wl_grid), dim3(256), 0, s, ranges, tiles_c,

@@ -262,3 +262,10 @@ def test_images_without_lists(cuda, n, deterministic):
         plan = r.plan_for(r.plan().pairs_c, 100)
         with pytest.raises(C.SDGRError):
             r.status(r.forward(plan))
+
+
+@pytest.mark.parametrize("nv", [9, 11, 12, 25])
+def test_tables_over_launches(cuda, nv):
+    """View tables that end in, at and after the first setup launch's data."""
+    views = [grid_view(2, 1 + k % 3, azimuth=13.0 * k) for k in range(nv)]
+    check(spread_scene(nv, 90, (1.0, 2.0, 2.0), 0.15, 0.5), views, cuda)
