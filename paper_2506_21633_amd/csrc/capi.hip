@@ -468,7 +468,7 @@ void layout(const Problem& P, int64_t cap_c, int64_t cap_i, Phase ph, char* stat
         b.grad_c = sc.take<float>(GC_STRIDE * R);   // record-major, see launch_params_backward
         b.grad_i = sc.take<float>(GC_STRIDE * R);   // record-major, as grad_c
         b.pgrad = sc.take<float>((int64_t)params_part_floats(P.nv, P.items, P.shc));
-        if (P.det) b.part_g = sc.take<float>(6 * cap_c);
+        if (P.det) b.part_g = sc.take<float>(PART_G * cap_c);
         if (P.hit_units > 0) {
             b.hit_part = sc.take<float>(HIT_PART_STRIDE * cap_c);
             b.hit_touched = sc.take<unsigned char>(cap_c + 4);
@@ -933,8 +933,8 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
                                      b.ranges, b.pval[pw], b.pmask, b.psum, b.crec, b.A,
                                      b.tau, b.nlast, s));
         if (P.det)
-            SDGR_HIP(launch_reduce_pairs(b.dord, b.poff, P.records, b.status, b.part_a, 1,
-                                         plan->pairs_c, b.A, 0, 1, s));
+            SDGR_HIP(launch_reduce_pairs(b.dord, b.poff, P.records, b.status, b.part_a, 1, b.A,
+                                         1, s));
     }
     {
         StageTimer t(SG_INTENSITY, s);
@@ -1001,7 +1001,7 @@ int sdgr_backward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
     upload_tables(P, b, setup, state, false);
     if (P.recompute) setup_lists_c(P, b, setup);
     if (b.hits) setup.fill((uint32_t*)b.hit_touched, 0u, (plan->pairs_c + 3) / 4);
-    if (P.det) setup.fill((uint32_t*)b.part_g, 0u, 6 * plan->pairs_c);
+    if (P.det) setup.fill((uint32_t*)b.part_g, 0u, PART_G * plan->pairs_c);
     SDGR_HIP(setup.launch(s));
     if (P.recompute) {
         // the forward's lists are gone: rebuild them (identical, the sorts
@@ -1033,7 +1033,6 @@ int sdgr_backward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
         if (P.det) {
             rp.ppos = b.ppos[pw];
             rp.part = b.part_g;
-            rp.part_stride = plan->pairs_c;
         }
         // stored hits first (their sums are stored, not added), then the
         // tiles whose hits are re-derived (atomics)
@@ -1046,8 +1045,8 @@ int sdgr_backward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
                                      b.ranges, b.pval[pw], b.pmask, b.psum, b.crec, b.tau,
                                      b.nlast, b.grad_c, P.records, s));
         if (P.det)
-            SDGR_HIP(launch_reduce_pairs(b.dord, b.poff, P.records, b.status, b.part_g, 6,
-                                         plan->pairs_c, b.grad_c, 1, GC_STRIDE, s));
+            SDGR_HIP(launch_reduce_pairs(b.dord, b.poff, P.records, b.status, b.part_g,
+                                         PART_G, b.grad_c, GC_STRIDE, s));
     }
     StageTimer t(SG_PARAMS_BWD, s);
     SDGR_HIP(launch_params_backward(b.views, b.scenes, P.nv, P.ns, P.items, P.rp, b.A,

@@ -85,11 +85,11 @@ struct RasterParams {
     unsigned long long* work = nullptr;
     // deterministic mode (null = off): every computation-plane pair's
     // position before the pair sort; pass A writes its per-(tile, record)
-    // sums there, in `part` (component k at k * part_stride), instead of
-    // adding them into the records' sums with float atomics
+    // sums there, in `part` (one float in the forward, a row of PART_G in
+    // the backward), instead of adding them into the records' sums with
+    // float atomics
     const uint32_t* ppos = nullptr;
     float* part = nullptr;
-    int64_t part_stride = 0;
     // stored hits (null = off): pass A's forward keeps the hits each tile's
     // rays processed, hit group by hit group, in `hits` (hit_cap 16-byte
     // units in hit_subs equal parts of hit_sub_cap, taken in blocks through
@@ -132,6 +132,7 @@ constexpr int HIT_SUBS = 64;
 constexpr int HIT_TOP_STRIDE = 16;
 constexpr int64_t HIT_SUB_MIN = 16384;   // 256 KB
 constexpr int HIT_TRIES = 3;
+constexpr int PART_G = 6;      // floats per pair of the deterministic backward's sums
 constexpr int GC_STRIDE = 8;   // floats per record in grad_c and grad_i
 constexpr int HIT_PART_STRIDE = 8;   // floats per pair partial: six sums, the record, spare
 
@@ -456,12 +457,12 @@ hipError_t launch_emit_pairs_c(const DevView* views, int nv, int64_t records,
                                const uint32_t* bscan_c, int64_t cap_c, const uint32_t* status,
                                uint32_t* pkey, uint32_t* pval, uint32_t* seg, uint32_t* dord,
                                uint32_t* poff, hipStream_t s);
-// out[k * out_comp + dord[p] * out_rec] = sum of part[k * part_stride + i]
-// over the pairs i in [poff[p], poff[p + 1]) in order (the last record's end
-// is status[ST_PAIRS_C]), for every depth rank p < records and k < ncomp.
+// Sums of the rows of ncomp floats (1 or PART_G) in part over the pairs
+// [poff[p], poff[p + 1]) in order (the last record's end is
+// status[ST_PAIRS_C]), for every depth rank p < records, to
+// out[dord[p] * out_rec].
 hipError_t launch_reduce_pairs(const uint32_t* dord, const uint32_t* poff, int64_t records,
-                               const uint32_t* status, const float* part, int ncomp,
-                               int64_t part_stride, float* out, int64_t out_comp,
+                               const uint32_t* status, const float* part, int ncomp, float* out,
                                int64_t out_rec, hipStream_t s);
 // Sums of the per-pair partials the stored-hit pass A backward wrote: the
 // rows part[i * HIT_PART_STRIDE ..] of the pair positions i < min(cap,

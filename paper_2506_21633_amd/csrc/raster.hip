@@ -341,6 +341,20 @@ __device__ __forceinline__ RecPair load_rec_pair(const CRec* __restrict__ crec, 
     return RecPair{base[2u * (uint64_t)ie + half], base[2u * (uint64_t)io + half]};
 }
 
+// The records of the lanes' ids straight into LDS, both halves of lane i's at
+// dst[2 i] and dst[2 i + 1]: a pair of lanes loads the halves of one record,
+// so each line is touched by one instruction.
+__device__ __forceinline__ void load_recs_to_lds(const CRec* __restrict__ crec, uint32_t id,
+                                                 float4* dst)
+{
+    const int lane = lane_id();
+    const float4* base = reinterpret_cast<const float4*>(crec);
+    const uint32_t lo = (uint32_t)__shfl((int)id, lane / 2, WAVE);
+    const uint32_t hi = (uint32_t)__shfl((int)id, WAVE / 2 + lane / 2, WAVE);
+    load16_to_lds(&base[2u * (uint64_t)lo + (lane & 1)], dst);
+    load16_to_lds(&base[2u * (uint64_t)hi + (lane & 1)], dst + WAVE);
+}
+
 __device__ __forceinline__ CRec own_rec(const RecPair& p)
 {
     const bool odd = (lane_id() & 1) != 0;
@@ -1264,11 +1278,19 @@ k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scen
 // when long lists are the majority the first variant runs every tile):
 //   FLUSHER (lists of at least 2^(LONG_LIST_BITS - 1) entries): a second wave
 //     of the workgroup sends each batch's atomics while the first goes on,
-//     so a long chain of batches never waits on them; two sum buffers and
-//     two copies picked by ray (fewer same-address LDS atomics);
-//   short lists: one wave sends its own atomics, one buffer and one copy:
-//     less than half the LDS, so more tiles run per CU.
+//     so a long chain of batches never waits on them; two sum buffers;
+//   short lists: one wave sends its own atomics, one buffer: less LDS, so
+//     more tiles run per CU.
+// The short lists are bound by the float atomics, which every XCD sends on to
+// memory: a request per entry and sum was 148M requests and 9.1 ms of the
+// 16-view block of 2M Gaussians (10.6 ms both variants); eight entries to an
+// instruction, the six sums of one in one request, and batches of 4 chunks
+// (24 KB of LDS instead of 48) made both variants 5.0 ms.
 constexpr int LONG_LIST_BITS = 12;
+
+// Hits of a compaction group of the backward: all of a batch's when at most
+// BG_HITS are left, else each ray's next BG_RAY.
+constexpr uint32_t BG_RAY = 32, BG_HITS = WAVE * BG_RAY;
 
 template <bool FLUSHER, bool DET>
 __global__ void __launch_bounds__(FLUSHER ? 2 * WAVE : WAVE) __attribute__((amdgpu_waves_per_eu(1, 2)))
@@ -1280,26 +1302,22 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                const float* __restrict__ tau, const uint32_t* __restrict__ nlast,
                float* __restrict__ grad_c, int64_t stride)
 {
-    constexpr int NB = 2 * A_BATCH;
-    constexpr int HKB = NB <= 8 ? 3 : 4;   // bits of a hit's chunk index
-    constexpr int HRS = 6 + HKB;           // shift of a hit's ray index
-    static_assert(NB <= 16, "hits are packed in 16 bits");
-    __shared__ float4 s_q[NB][WAVE];
-    __shared__ float s_wc[NB][WAVE], s_wk[NB][WAVE];   // conic c and extinction
-    __shared__ float s_c[NB][WAVE];                    // c = P dL/dI of the entry
-    // per-entry gradient sums in GC copies, picked by ray so that the hits
-    // of one entry from neighbouring rays in a round add to different
-    // addresses (rows padded by one word: copies and rows differ in bank)
-    constexpr int GC = 1;
+    constexpr int NB = A_BATCH;
+    constexpr int HKB = 2;         // bits of a hit's chunk index
+    constexpr int HRS = 6 + HKB;   // shift of a hit's ray index
+    static_assert(NB == 1 << HKB, "chunk index bits");
+    __shared__ float4 s_rec[NB][2 * WAVE];   // both halves of each entry's record
+    // per-entry gradient sums (rows padded by one: they differ in bank), in
     // two buffers with the flusher: the second wave of the workgroup sends
     // one batch's sums with atomics while the first accumulates the next
     // batch in the other
     constexpr int GB = FLUSHER ? 2 : 1;
-    __shared__ double s_G[GB][GC][NB][6][WAVE + 1];
+    __shared__ double s_G[GB][NB][6][WAVE + 1];
     __shared__ uint32_t s_rf[GB][FLUSHER ? NB : 1][WAVE];   // records of the handed-off entries
+    __shared__ uint2 s_list[WAVE];            // entries being sent: lane, destination
     __shared__ uint32_t s_cmd[GB][WAVE];      // per entry lane: chunks gathered (bits), last flag
     __shared__ uint32_t s_chk[NB];
-    __shared__ uint16_t s_hit[WAVE * WAVE];   // (ray, chunk, entry) packed, ray-major, back to front
+    __shared__ uint16_t s_hit[BG_HITS];    // (ray, chunk, entry) packed, ray-major, back to front
     // per ray during a chunk: first hit in s_hit, optical depth, U
     struct alignas(16) RayB { uint32_t o; float t, U, pad; };
     __shared__ RayB s_ray[WAVE];
@@ -1314,6 +1332,34 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
     // tiles whose hits the forward stored run in k_raster_a_bwd_hits
     if (!DET && rp.hits != nullptr && rp.hit_tail[worklist[wi]] != HIT_OVERFLOW) return;
     constexpr uint32_t LAST = 1u << 31;
+    // The six sums of a batch's touched entries (cmd: their chunks per lane,
+    // rec: where each lane's go) leave with one atomic each, eight entries to
+    // an instruction: the lanes of one entry add to one 32-byte row, which is
+    // one request to memory instead of six. The sums are cleared for reuse.
+    auto send = [&](int hb, uint32_t cmd, const uint32_t (&rec)[NB]) {
+        const int lane = lane_id();
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const uint64_t m = __ballot((cmd >> k) & 1u);
+            if (m == 0ull) continue;
+            if ((cmd >> k) & 1u) {
+                const uint32_t at = lanes_below(m);
+                s_list[at] = make_uint2((uint32_t)lane, rec[k]);
+            }
+            wave_lds_sync();
+            const int n = __popcll(m), c = lane & 7;
+            for (int e = lane >> 3; e < n; e += WAVE / 8) {
+                if (c >= 6) continue;
+                const uint2 el = s_list[e];
+                const float v = (float)s_G[hb][k][c][el.x];
+                s_G[hb][k][c][el.x] = 0.0;
+                if (v == 0.0f) continue;
+                if constexpr (DET) rp.part[(int64_t)el.y * PART_G + c] = v;
+                else unsafeAtomicAdd(&grad_c[(int64_t)el.y * GC_STRIDE + c], v);
+            }
+            wave_lds_sync();
+        }
+    };
     if (FLUSHER && threadIdx.x >= WAVE) {
         // the flusher: per hand-off, the six sums of every handed-off entry
         // leave with one atomic each, and the buffer is cleared for reuse
@@ -1321,24 +1367,10 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
         for (int hb = 0;; hb ^= 1) {
             __syncthreads();
             const uint32_t cmd = s_cmd[hb][fl];
+            uint32_t rec[NB];
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                if (!(cmd & (1u << k))) continue;
-                const uint32_t rk = s_rf[hb][k][fl];
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    double sum = 0.0;
-#pragma unroll
-                    for (int g = 0; g < GC; ++g) {
-                        sum += s_G[hb][g][k][c][fl];
-                        s_G[hb][g][k][c][fl] = 0.0;
-                    }
-                    const float v = (float)sum;
-                    if (v == 0.0f) continue;
-                    if constexpr (DET) rp.part[c * rp.part_stride + rk] = v;
-                    else unsafeAtomicAdd(&grad_c[(int64_t)rk * GC_STRIDE + c], v);
-                }
-            }
+            for (int k = 0; k < NB; ++k) rec[k] = s_rf[hb][k][fl];
+            send(hb, cmd, rec);
             if (cmd & LAST) return;
         }
     }
@@ -1356,13 +1388,11 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
 #pragma unroll
     for (int b = 0; b < GB; ++b)
 #pragma unroll
-        for (int g = 0; g < GC; ++g)
+        for (int k = 0; k < NB; ++k)
 #pragma unroll
-            for (int k = 0; k < NB; ++k)
-#pragma unroll
-                for (int c = 0; c < 6; ++c) s_G[b][g][k][c][lane] = 0.0;
+            for (int c = 0; c < 6; ++c) s_G[b][k][c][lane] = 0.0;
     unsigned long long n_iter = 0, n_hits = 0;   // work counters
-    unsigned long long n_batch = 0, n_group = 0;
+    unsigned long long n_batch = 0, n_extra = 0;
     const uint32_t n_max = wave_max_u32(n_mine);
     const uint32_t e_end = rg.x + n_max;           // exclusive end of the used entries
     // the six per-entry sums of the last processed batch leave once the next
@@ -1382,19 +1412,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             __syncthreads();
             hb ^= 1;
         } else {
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                if (!(got_prev & (1u << k))) continue;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    const float v = (float)s_G[0][0][k][c][lane];
-                    s_G[0][0][k][c][lane] = 0.0;
-                    if (v == 0.0f) continue;
-                    if constexpr (DET) rp.part[c * rp.part_stride + r_prev[k]] = v;
-                    else unsafeAtomicAdd(&grad_c[(int64_t)r_prev[k] * GC_STRIDE + c], v);
-                }
-            }
-            wave_lds_sync();
+            send(0, got_prev, r_prev);
         }
         got_prev = 0u;
     };
@@ -1406,9 +1424,8 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
     auto hit_round = [&](const uint32_t hv, const bool valid, const bool head, const RayB rs) {
         const int rr = (int)(hv >> HRS), k = (int)((hv >> 6) & ((1u << HKB) - 1u)),
                   j = (int)(hv & 63u);
-        const float4 g = s_q[k][j];
-        const float2 g2 = make_float2(s_wc[k][j], s_wk[k][j]);
-        const float cj = s_c[k][j];
+        const float4 g = s_rec[k][2 * j], g2 = s_rec[k][2 * j + 1];
+        const float cj = g2.w;
         bool real = false;
         float x = 0.0f, E = 1.0f, ex = 0.0f, f = 0.0f, dx = 0.0f, dy = 0.0f;
         float c = 0.0f;
@@ -1446,13 +1463,12 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             }
             const float dxx = dalpha * E;   // d alpha / d x = exp(-x)
             const float dq = dxx * g2.y * (-0.5f * ex * rp.inv1meps);
-            const int gc = (rr + (rr >> 3)) & (GC - 1);
-            atomicAdd(&s_G[hb][gc][k][0][j], (double)(-2.0f * dq * (g.z * dx + g.w * dy)));
-            atomicAdd(&s_G[hb][gc][k][1][j], (double)(-2.0f * dq * (g.w * dx + g2.x * dy)));
-            atomicAdd(&s_G[hb][gc][k][2][j], (double)(dq * dx * dx));
-            atomicAdd(&s_G[hb][gc][k][3][j], (double)(2.0f * dq * dx * dy));
-            atomicAdd(&s_G[hb][gc][k][4][j], (double)(dq * dy * dy));
-            atomicAdd(&s_G[hb][gc][k][5][j], (double)(dxx * f));
+            atomicAdd(&s_G[hb][k][0][j], (double)(-2.0f * dq * (g.z * dx + g.w * dy)));
+            atomicAdd(&s_G[hb][k][1][j], (double)(-2.0f * dq * (g.w * dx + g2.x * dy)));
+            atomicAdd(&s_G[hb][k][2][j], (double)(dq * dx * dx));
+            atomicAdd(&s_G[hb][k][3][j], (double)(2.0f * dq * dx * dy));
+            atomicAdd(&s_G[hb][k][4][j], (double)(dq * dy * dy));
+            atomicAdd(&s_G[hb][k][5][j], (double)(dxx * f));
         }
         const uint64_t hbits = __ballot(real);
         if (lane == 0) n_hits += (unsigned long long)__popcll(hbits);
@@ -1533,12 +1549,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                 for (int k = 0; k < NB; ++k) {
                     const bool need = (m[k] & lv[k]) != 0ull;
                     got |= need ? 1u << k : 0u;
-                    const uint32_t rk = need ? rec[k] : (uint32_t)V.rec_off;
-                    const float* w = reinterpret_cast<const float*>(&crec[rk].w);
-                    load16_to_lds(&crec[rk].q, &s_q[k][0]);
-                    load4_to_lds(w, &s_wc[k][0]);
-                    load4_to_lds(w + 1, &s_wk[k][0]);
-                    load4_to_lds(w + 3, &s_c[k][0]);
+                    load_recs_to_lds(crec, need ? rec[k] : (uint32_t)V.rec_off, &s_rec[k][0]);
                 }
 #pragma unroll
                 for (int k = 0; k < NB; ++k)
@@ -1553,11 +1564,8 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             for (int k = 0; k < NB; ++k) r_prev[k] = r_cur[k];
             // the batch's chunks, transposed: bit j of col[k] is entry j of
             // chunk k covering my cell that my ray used in the forward
-            // (all eight transposed together, as in the forward; the hit
-            // totals summed two to a word)
-            static_assert(NB % 2 == 0, "hit totals are summed in pairs");
+            // (all transposed together, as in the forward)
             uint64_t col[NB];
-            uint32_t hk[NB];   // hits of each chunk over the wave
 #pragma unroll
             for (int k = 0; k < NB; ++k) col[k] = m[k];
             transpose64_n(col, tl);
@@ -1571,53 +1579,42 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                 }
                 col[k] &= used;
             }
-            {
-                uint32_t tot[NB / 2];
-#pragma unroll
-                for (int i = 0; i < NB / 2; ++i)
-                    tot[i] = (uint32_t)__popcll(col[2 * i]) |
-                             ((uint32_t)__popcll(col[2 * i + 1]) << 16);
-                wave_total_u32_n(tot);
-#pragma unroll
-                for (int i = 0; i < NB / 2; ++i) {
-                    hk[2 * i] = tot[i] & 0xFFFFu;
-                    hk[2 * i + 1] = tot[i] >> 16;
-                }
-            }
-            // groups of consecutive chunks whose hits fit s_hit; each group's
-            // hits are compacted ray-major, back to front (the batch's chunks
-            // come back to front), and taken 64 per round
-            for (int g0 = 0; g0 < nb;) {
-                ++n_group;
-                int g1 = g0;
-                uint32_t H = 0;
-                bool open = true;
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    if (k < g0 || k >= nb || !open) continue;
-                    if (H + hk[k] <= (uint32_t)(WAVE * WAVE)) {
-                        H += hk[k];
-                        g1 = k + 1;
-                    } else {
-                        open = false;
-                    }
-                }
+            // the batch's hits in groups, compacted ray-major, back to front
+            // (the batch's chunks come back to front), and taken 64 per
+            // round: all that are left when they are few, else each ray's
+            // next BG_RAY
+            for (bool more = false;; more = true) {
                 uint32_t nr = 0;
 #pragma unroll
-                for (int k = 0; k < NB; ++k)
-                    if (k >= g0 && k < g1) nr += (uint32_t)__popcll(col[k]);
-                const uint32_t o = wave_excl_scan_u32(nr);
-                if (H > 0u) {
+                for (int k = 0; k < NB; ++k) nr += (uint32_t)__popcll(col[k]);
+                if (__ballot(nr != 0u) == 0ull) break;
+                n_extra += more ? 1u : 0u;
+                // hits left and hits of a limited group, scanned together
+                // (at most 64 x 512 and 64 x BG_RAY: two to a word)
+                const uint32_t lim = min(nr, BG_RAY);
+                const uint32_t both = nr | (lim << 16);
+                const uint32_t excl = wave_excl_scan_u32(both);
+                const uint32_t tot =
+                    (uint32_t)__builtin_amdgcn_readlane((int)(excl + both), WAVE - 1);
+                const bool few = (tot & 0xFFFFu) <= BG_HITS;
+                const uint32_t H = few ? (tot & 0xFFFFu) : (tot >> 16);
+                const uint32_t o = few ? (excl & 0xFFFFu) : (excl >> 16);
+                const uint32_t o_end = o + (few ? nr : lim);
+                {
                     uint32_t w = o;
 #pragma unroll
                     for (int k = 0; k < NB; ++k) {
-                        if (k < g0 || k >= g1) continue;
-                        uint64_t c = col[k];
-                        while (c != 0ull) {
-                            const int j = 63 - __builtin_clzll(c);
-                            c &= ~(1ull << j);
-                            s_hit[w++] = (uint16_t)((lane << HRS) | (k << 6) | j);
+                        uint32_t half[2] = {(uint32_t)col[k], (uint32_t)(col[k] >> 32)};
+#pragma unroll
+                        for (int q = 1; q >= 0; --q) {
+                            const uint32_t tag = (uint32_t)((lane << HRS) | (k << 6) | (q << 5));
+                            while (half[q] != 0u && w < o_end) {
+                                const uint32_t j = 31u - (uint32_t)__builtin_clz(half[q]);
+                                half[q] &= ~(1u << j);
+                                s_hit[w++] = (uint16_t)(tag | j);
+                            }
                         }
+                        col[k] = ((uint64_t)half[1] << 32) | half[0];
                     }
                     s_ray[lane] = RayB{o, t, U, 0.0f};
                     wave_lds_sync();
@@ -1638,7 +1635,6 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                     }
                     wave_lds_sync();
                 }
-                g0 = g1;
             }
             wave_lds_sync();
         }
@@ -1650,7 +1646,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             atomicAdd(&rp.work[5], n_iter);
             atomicAdd(&rp.work[1], n_hits);
             atomicMax(&rp.work[9], n_batch);
-            atomicAdd(&rp.work[11], n_group - n_batch);
+            atomicAdd(&rp.work[11], n_extra);
             atomicAdd(&rp.work[FLUSHER ? 14 : 15], 1ull);
             atomicAdd(&rp.work[17], 1ull);
         }

@@ -803,27 +803,41 @@ k_emit_c(const DevView* __restrict__ views, int nv, int64_t records,
 
 // Deterministic sums over the computation-plane pairs: thread = depth rank
 // p, its record's pairs are [poff[p], next) before the pair sort (one
-// record's tiles, row by row); their partials are added in that order.
-// After a pair overflow the lists are empty and no partial was written:
-// nothing is summed (the call's results are void anyway).
+// record's tiles, row by row); their rows of NC partials are added in that
+// order. Bound by the rows' bytes. (One array per component, read one after
+// the other: 132 us for both sums of 24 views of 60k Gaussians.) After a
+// pair overflow the lists are empty and no partial was written: nothing is
+// summed (the call's results are void anyway).
+template <int NC>
 __global__ void __launch_bounds__(256)
 k_reduce_pairs(const uint32_t* __restrict__ dord, const uint32_t* __restrict__ poff,
                int64_t records, const uint32_t* __restrict__ status,
-               const float* __restrict__ part, int ncomp, int64_t part_stride,
-               float* __restrict__ out, int64_t out_comp, int64_t out_rec)
+               const float* __restrict__ part, float* __restrict__ out, int64_t out_rec)
 {
+    static_assert(NC == 1 || NC % 2 == 0, "rows are read two floats at a time");
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= records || status[ST_OVERFLOW]) return;
     const uint32_t kc = status[ST_PAIRS_C];
     const uint32_t lo = min(poff[p], kc);
     const uint32_t hi = p + 1 < records ? min(poff[p + 1], kc) : kc;
     const uint32_t r = dord[p];
-    for (int k = 0; k < ncomp; ++k) {
-        const float* src = part + (int64_t)k * part_stride;
-        float acc = 0.0f;
-        for (uint32_t i = lo; i < hi; ++i) acc += src[i];
-        out[(int64_t)k * out_comp + (int64_t)r * out_rec] = acc;
+    float acc[NC] = {};
+    for (uint32_t i = lo; i < hi; ++i) {
+        const float* row = part + (uint64_t)i * NC;
+        if constexpr (NC == 1) {
+            acc[0] += row[0];
+        } else {
+#pragma unroll
+            for (int k = 0; k < NC; k += 2) {
+                const float2 v = *reinterpret_cast<const float2*>(row + k);
+                acc[k] += v.x;
+                acc[k + 1] += v.y;
+            }
+        }
     }
+    float* o = out + (int64_t)r * out_rec;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) o[k] = acc[k];
 }
 
 // The stored-hit pass A backward's per-pair partials, summed per record.
@@ -1589,13 +1603,18 @@ hipError_t launch_emit_pairs_c(const DevView* views, int nv, int64_t records,
 }
 
 hipError_t launch_reduce_pairs(const uint32_t* dord, const uint32_t* poff, int64_t records,
-                               const uint32_t* status, const float* part, int ncomp,
-                               int64_t part_stride, float* out, int64_t out_comp,
+                               const uint32_t* status, const float* part, int ncomp, float* out,
                                int64_t out_rec, hipStream_t s)
 {
     if (records <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce_pairs, dim3(grid256(records)), dim3(256), 0, s, dord, poff,
-                       records, status, part, ncomp, part_stride, out, out_comp, out_rec);
+    if (ncomp == 1)
+        hipLaunchKernelGGL(k_reduce_pairs<1>, dim3(grid256(records)), dim3(256), 0, s, dord, poff,
+                           records, status, part, out, out_rec);
+    else if (ncomp == PART_G)
+        hipLaunchKernelGGL(k_reduce_pairs<PART_G>, dim3(grid256(records)), dim3(256), 0, s, dord,
+                           poff, records, status, part, out, out_rec);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
