@@ -212,6 +212,13 @@ __device__ __forceinline__ float wave_sum(float v)
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Value of the lane a DPP row shift or row broadcast names, 0 where there
 // is none (bound control) or the row is masked off.
 template <int CTRL, int ROWS>

@@ -549,7 +549,6 @@ k_gather_rects(const uint32_t* __restrict__ order, const uint2* __restrict__ rec
                uint2* __restrict__ rect_sorted, uint32_t* __restrict__ bsum)
 {
     __shared__ uint32_t s_w[GATHER_BLOCKS][4];
-    __shared__ unsigned long long s_big;
     // each XCD walks a contiguous part of the order: in view-major order its
     // reads stay inside a view or two, which its L2 holds
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
@@ -567,23 +566,30 @@ k_gather_rects(const uint32_t* __restrict__ order, const uint2* __restrict__ rec
     }
 #pragma unroll
     for (int k = 0; k < GATHER_BLOCKS; ++k) {
-        const int64_t b0 = ((int64_t)blk * GATHER_BLOCKS + k) * 256;
-        const int64_t i = b0 + threadIdx.x;
+        const int64_t i = ((int64_t)blk * GATHER_BLOCKS + k) * 256 + threadIdx.x;
         if (i < n) rect_sorted[i] = rc[k];
         const uint32_t c = ((rc[k].x >> 16) - (rc[k].x & 0xFFFF)) *
                            ((rc[k].y >> 16) - (rc[k].y & 0xFFFF));
-        uint32_t tot;
-        (void)block_excl_scan_256(c, s_w[k], tot);
-        // 256 counts of under 2^24 cannot wrap; beyond, the sum saturates (it
-        // is above every capacity)
-        if (__syncthreads_or(c >> 24)) {
-            if (threadIdx.x == 0) s_big = 0ull;
-            __syncthreads();
-            atomicAdd(&s_big, (unsigned long long)c);
-            __syncthreads();
-            tot = (uint32_t)min(s_big, 0xFFFFFFFFull);
+        uint32_t sum = c;
+#pragma unroll
+        for (int d = 1; d < WAVE; d <<= 1) sum += (uint32_t)__shfl_xor((int)sum, d, WAVE);
+        // 64 counts of under 2^24 cannot wrap; larger ones saturate (a sum
+        // above every capacity)
+        if (__ballot(c >> 24) != 0ull) {
+            unsigned long long all = c;
+#pragma unroll
+            for (int d = 1; d < WAVE; d <<= 1)
+                all += (unsigned long long)__shfl_xor((long long)all, d, WAVE);
+            sum = (uint32_t)min(all, 0xFFFFFFFFull);
         }
-        if (threadIdx.x == 0 && b0 < n) bsum[blk * GATHER_BLOCKS + k] = tot;
+        if (lane_id() == 0) s_w[k][threadIdx.x / WAVE] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x < GATHER_BLOCKS) {
+        const int64_t b = (int64_t)blk * GATHER_BLOCKS + threadIdx.x;
+        unsigned long long sum = 0ull;
+        for (int w = 0; w < 4; ++w) sum += s_w[threadIdx.x][w];
+        if (b * 256 < n) bsum[b] = (uint32_t)min(sum, 0xFFFFFFFFull);
     }
 }
 
@@ -667,8 +673,9 @@ k_scan_blocks(uint32_t* __restrict__ a, int64_t n, int64_t cap, uint32_t* __rest
 // segmented by view).
 constexpr int LDS_VIEWS = 512;
 
-// Pair writes of one wave's records (imaging plane: few records have pairs,
-// and a loop per record would leave most lanes idle). Record (lane) l
+// Pair writes of one wave's records (a loop per record would leave most lanes
+// idle and store single words: the computation plane's pairs of 16 views of
+// 2M Gaussians took 831 us instead of 374). Record (lane) l
 // owns the wave's pairs [ex[l], ex[l] + cnt_l) in row-major order over its
 // tile rectangle (width w, first tile local0, tile row stride txn); the key
 // is kadd + local, or (local << 8) | kadd for view-major imaging keys. The
@@ -727,9 +734,17 @@ __device__ __forceinline__ uint32_t stage_wave_records(EmitWaves& L, int w, uint
     return total;
 }
 
-// Computation-plane pairs, one thread per record in depth order: the
-// record emits (tile bucket, record) for every tile of its rectangle at its
-// scanned offset, so each tile's pairs leave in depth order.
+// Computation-plane pairs of the records in depth order: each record's
+// (tile bucket, record) for every tile of its rectangle at its scanned
+// offset, so each tile's pairs leave in depth order. A wave writes its
+// records' pairs 64 at a time (see EmitWaves).
+// A workgroup takes EMIT_BLOCKS blocks of 256 records, their loads in flight
+// together: 4 from EMIT_LARGE records on (72 views of 200k Gaussians 107 us
+// instead of 132 with one, 16 views of 2M 374 instead of 480), one below (one
+// view of 500k 12 us, with 4 it is 18).
+constexpr int64_t EMIT_LARGE = 2000000;
+
+template <int EMIT_BLOCKS>
 __global__ void __launch_bounds__(256)
 k_emit_c(const DevView* __restrict__ views, int nv, int64_t records,
          const uint32_t* __restrict__ dval, const uint2* __restrict__ rect_sorted,
@@ -737,68 +752,74 @@ k_emit_c(const DevView* __restrict__ views, int nv, int64_t records,
          uint32_t* __restrict__ pkey, uint32_t* __restrict__ pval, uint32_t* __restrict__ seg,
          uint32_t* __restrict__ dord, uint32_t* __restrict__ poff)
 {
-    __shared__ uint32_t s_w[4];
+    __shared__ uint32_t s_w[EMIT_BLOCKS][4];
+    __shared__ EmitWaves L;
     __shared__ int64_t s_off[LDS_VIEWS];
     __shared__ int32_t s_tile[LDS_VIEWS], s_tx[LDS_VIEWS];
     const bool cached = nv <= LDS_VIEWS;
+    const uint32_t lane = lane_id();
+    const int w = threadIdx.x / WAVE;
+    const int64_t b0 = (int64_t)blockIdx.x * EMIT_BLOCKS;
+    uint2 rc[EMIT_BLOCKS];
+    uint32_t rec[EMIT_BLOCKS], first[EMIT_BLOCKS];
+#pragma unroll
+    for (int k = 0; k < EMIT_BLOCKS; ++k) {
+        const int64_t p = (b0 + k) * 256 + threadIdx.x;
+        rc[k] = p < records ? rect_sorted[p] : make_uint2(0u, 0u);
+        rec[k] = p < records ? dval[p] : 0u;
+        first[k] = (b0 + k) * 256 < records ? bscan[b0 + k] : 0u;
+    }
     if (cached)
         for (int k = threadIdx.x; k < nv; k += blockDim.x) {
             s_off[k] = views[k].rec_off;
             s_tile[k] = views[k].tile_c;
             s_tx[k] = views[k].txc;
         }
+    const uint64_t lim = min((uint64_t)status[ST_PAIRS_C], (uint64_t)cap_c);
+    const bool over = status[ST_OVERFLOW] != 0u;
     __syncthreads();
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint2 rc = p < records ? rect_sorted[p] : make_uint2(0u, 0u);
-    const uint32_t tx0 = rc.x & 0xFFFF, tx1 = rc.x >> 16, ty0 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
-    // offset: the block's prefix plus the counts of the block's records before
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan_256((tx1 - tx0) * (ty1 - ty0), s_w, tot);
-    if (p >= records) return;
-    // the first pair of this depth rank's record and the record
-    // (deterministic mode)
-    if (poff) poff[p] = bscan[blockIdx.x] + ex;
-    if (dord) dord[p] = dval[p];
-    int vp = -1;   // the view of position p, when the order is view-major
-    if (seg && cached) {
-        // view-major order (segmented depth sort): the first record of each
-        // view marks where the view's pairs start
+    auto view_of = [&](int64_t x) {
         int lo = 0, hi = nv - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (s_off[mid] <= p) lo = mid; else hi = mid - 1;
+            if (s_off[mid] <= x) lo = mid; else hi = mid - 1;
         }
-        if (s_off[lo] == p) seg[lo] = bscan[blockIdx.x] + ex;
-        vp = lo;
-    }
-    const uint32_t kc = status[ST_PAIRS_C];
-    if (status[ST_OVERFLOW]) return;
-    if (tx0 >= tx1 || ty0 >= ty1) return;
-    const uint32_t r = dval[p];
-    uint32_t tile0, txc;
-    if (vp >= 0) {   // the record at p is one of that view's
-        tile0 = (uint32_t)s_tile[vp];
-        txc = (uint32_t)s_tx[vp];
-    } else if (cached) {
-        int lo = 0, hi = nv - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_off[mid] <= (int64_t)r) lo = mid; else hi = mid - 1;
+        return lo;
+    };
+#pragma unroll
+    for (int k = 0; k < EMIT_BLOCKS; ++k) {
+        const int64_t p = (b0 + k) * 256 + threadIdx.x;
+        const bool in = p < records;
+        const uint32_t cnt = ((rc[k].x >> 16) - (rc[k].x & 0xFFFFu)) *
+                             ((rc[k].y >> 16) - (rc[k].y & 0xFFFFu));
+        // offset: the block's prefix plus the counts of its records before
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan_256(cnt, s_w[k], tot);
+        // the first pair of this depth rank's record and the record
+        // (deterministic mode)
+        if (in && poff) poff[p] = first[k] + ex;
+        if (in && dord) dord[p] = rec[k];
+        uint32_t tile0 = 0u, txc = 0u;
+        if (cached) {
+            // view-major order (segmented depth sort): the first record of
+            // each view marks where the view's pairs start
+            const int v = in ? view_of(seg ? p : (int64_t)rec[k]) : 0;
+            if (in && seg && s_off[v] == p) seg[v] = first[k] + ex;
+            tile0 = (uint32_t)s_tile[v];
+            txc = (uint32_t)s_tx[v];
+        } else if (in && cnt) {
+            const int v = find_view(nv, (int64_t)rec[k], [&](int j) { return views[j].rec_off; });
+            tile0 = (uint32_t)views[v].tile_c;
+            txc = (uint32_t)views[v].txc;
         }
-        tile0 = (uint32_t)s_tile[lo];
-        txc = (uint32_t)s_tx[lo];
-    } else {
-        const int v = find_view(nv, (int64_t)r, [&](int k) { return views[k].rec_off; });
-        tile0 = (uint32_t)views[v].tile_c;
-        txc = (uint32_t)views[v].txc;
+        if (over) continue;
+        uint32_t ex0;
+        const uint32_t total =
+            stage_wave_records(L, w, lane, ex, cnt, rc[k], txc, tile0, rec[k], &ex0);
+        wave_lds_sync();
+        emit_wave_pairs(L, w, lane, (uint64_t)first[k] + ex0, total, lim, false, pkey, pval);
+        wave_lds_sync();
     }
-    uint64_t o = (uint64_t)bscan[blockIdx.x] + ex;
-    for (uint32_t ty = ty0; ty < ty1; ++ty)
-        for (uint32_t tx = tx0; tx < tx1; ++tx, ++o)
-            if (o < kc && o < (uint64_t)cap_c) {
-                pkey[o] = tile0 + ty * txc + tx;
-                pval[o] = r;
-            }
 }
 
 // Deterministic sums over the computation-plane pairs: thread = depth rank
@@ -1596,9 +1617,11 @@ hipError_t launch_emit_pairs_c(const DevView* views, int nv, int64_t records,
 {
     if (records <= 0) return hipSuccess;
     if (seg && nv > LDS_VIEWS) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_emit_c, dim3(grid256(records)), dim3(256), 0, s, views, nv, records,
-                       dval_sorted, rect_sorted, bscan_c, cap_c, status, pkey, pval, seg, dord,
-                       poff);
+    const bool large = records >= EMIT_LARGE;
+    const int64_t per = large ? 4 : 1;
+    hipLaunchKernelGGL(large ? k_emit_c<4> : k_emit_c<1>, dim3(grid256((records + per - 1) / per)),
+                       dim3(256), 0, s, views, nv, records, dval_sorted, rect_sorted, bscan_c,
+                       cap_c, status, pkey, pval, seg, dord, poff);
     return hipGetLastError();
 }
 
