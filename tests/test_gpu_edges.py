@@ -271,22 +271,23 @@ def test_tables_over_launches(cuda, nv):
     check(spread_scene(nv, 90, (1.0, 2.0, 2.0), 0.15, 0.5), views, cuda)
 
 
-@pytest.mark.parametrize("nv", [49, 50])
-def test_emission_of_many_records(cuda, nv):
+def test_emission_of_many_records(cuda):
     """Record counts below and at where the pair emission takes four blocks at
-    a time: in deterministic mode each view's A is, bit for bit, that of a
-    call with the view alone."""
+    a time, and one view further: in deterministic mode the common views' A
+    agree bit for bit (their pairs have the same places), the images within
+    the rounding of FP32 sums."""
     from paper_2506_21633_amd import api
     scene = spread_scene(5, 40000, (1.0, 3.0, 3.0), 0.03, 0.1)
-    views = [grid_view(3 + k % 2, 4, azimuth=7.0 * k) for k in range(nv)]
+    views = [grid_view(3 + k % 2, 4, azimuth=7.0 * k) for k in range(51)]
     g = api.GaussianTensors.from_numpy(scene, cuda)
-    options = api.RenderOptions(deterministic=True)
-    r = api.Renderer([g], views, options)
-    res = r.forward()
-    r.status(res)
-    A = r.intensity_shares(res).reshape(nv, scene.n)
-    for v in (0, 1, nv // 2, nv - 1):
-        one = api.Renderer([g], views[v:v + 1], options)
-        alone = one.forward()
-        assert torch.equal(one.intensity_shares(alone), A[v])
-        assert elem_err(res.image(v).cpu().numpy(), alone.image(0).cpu().numpy()) <= 1e-6
+    A, images = [], []
+    for nv in (49, 50, 51):
+        r = api.Renderer([g], views[:nv], api.RenderOptions(deterministic=True))
+        res = r.forward()
+        r.status(res)
+        A.append(r.intensity_shares(res)[:49 * scene.n])
+        images.append([res.image(v).cpu().numpy() for v in (0, 24, 48)])
+    assert torch.equal(A[0], A[1]) and torch.equal(A[0], A[2])
+    for got in images[1:]:
+        for a, b in zip(got, images[0]):
+            assert elem_err(a, b) <= 1e-6
