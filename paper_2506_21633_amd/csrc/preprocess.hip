@@ -360,8 +360,13 @@ k_sum_slots(const unsigned long long* __restrict__ slots, unsigned long long* __
 // the listed records only. A wave takes 8 groups of 64 consecutive records
 // (16 was 0.137 ms on the 72-view vehicle, 8 is 0.124).
 constexpr int INT_GROUPS = 8;
+// The list's length is one counter, whose updates take about 4 ns each one
+// after the other: 16 waves to a workgroup from INT_LARGE records on (72
+// views of 200k 122 -> 101 us), 4 below (8 views of 20k 11 us, with 16 13).
+constexpr int64_t INT_LARGE = 1000000;
 
-__global__ void __launch_bounds__(256)
+template <int INT_WAVES>
+__global__ void __launch_bounds__(INT_WAVES * WAVE)
 k_set_intensity(const DevView* __restrict__ views, const DevScene* __restrict__ scenes, int nv,
                 int64_t records, const float* __restrict__ A,
                 const float* __restrict__ prec, float2* __restrict__ iw,
@@ -369,10 +374,10 @@ k_set_intensity(const DevView* __restrict__ views, const DevScene* __restrict__ 
                 uint32_t* __restrict__ bsum_i, uint32_t* __restrict__ status,
                 uint32_t* __restrict__ active)
 {
-    __shared__ uint32_t s_cnt[4];
+    __shared__ uint32_t s_cnt[INT_WAVES];
     __shared__ uint32_t s_base;
     const int lane = lane_id(), w = threadIdx.x / WAVE;
-    const int64_t wave0 = ((int64_t)blockIdx.x * 4 + w) * (INT_GROUPS * WAVE);
+    const int64_t wave0 = ((int64_t)blockIdx.x * INT_WAVES + w) * (INT_GROUPS * WAVE);
     uint64_t m[INT_GROUPS];
     uint32_t n = 0, quarter = 0;
     // the wave's records mostly lie in one view: look it up once
@@ -435,7 +440,8 @@ k_set_intensity(const DevView* __restrict__ views, const DevScene* __restrict__ 
     if (lane == 0) s_cnt[w] = n;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t tot = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+        uint32_t tot = 0u;
+        for (int k = 0; k < INT_WAVES; ++k) tot += s_cnt[k];
         s_base = tot ? atomicAdd(&status[ST_ACTIVE], tot) : 0u;
     }
     __syncthreads();
@@ -682,9 +688,12 @@ hipError_t launch_set_intensity(const DevView* views, const DevScene* scenes, in
                                 hipStream_t s)
 {
     if (records <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_set_intensity, dim3(blocks_for(records, 4 * INT_GROUPS * WAVE)),
-                       dim3(256), 0, s, views, scenes, nv, records, A, prec, iw, rect_i, cnt_i,
-                       bsum_i, status, active);
+    const bool large = records >= INT_LARGE;
+    const int waves = large ? 16 : 4;
+    hipLaunchKernelGGL(large ? k_set_intensity<16> : k_set_intensity<4>,
+                       dim3(blocks_for(records, waves * INT_GROUPS * WAVE)), dim3(waves * WAVE), 0,
+                       s, views, scenes, nv, records, A, prec, iw, rect_i, cnt_i, bsum_i, status,
+                       active);
     return hipGetLastError();
 }
 
