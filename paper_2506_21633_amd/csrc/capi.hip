@@ -137,6 +137,7 @@ struct Problem {
     bool view_lists = false;   // lists of small views, see launch_view_lists
     int64_t max_n = 0;         // most records of a view
     bool images_apart = false; // the views' images follow one another
+    bool images_packed = false;   // and leave no gaps
     int64_t reads_i = 0;       // records of the view, summed over the imaging tiles
     int64_t hit_units = 0;  // 16-byte units of the stored-hit stream (0: none)
 };
@@ -310,10 +311,11 @@ int build_problem(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vi
         pairs += (int64_t)V.n * V.n;
     }
     P.view_lists = fits && P.max_n <= VL_MAX && reads <= VL_READS && pairs <= VL_PAIRS;
-    P.images_apart = true;
+    P.images_apart = P.images_packed = true;
     int64_t end = 0;
     for (const DevView& V : P.views) {
         P.images_apart = P.images_apart && V.img_off >= end;
+        P.images_packed = P.images_packed && V.img_off == V.pix_off;
         end = V.img_off + (int64_t)V.W * V.H;
         P.reads_i += (int64_t)V.txi * V.tyi * V.n;
     }
@@ -908,6 +910,8 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
     setup.fill((uint32_t*)b.tau, 0u, (int64_t)(b.nlast - (uint32_t*)b.tau) + P.rays);
     if (b.hits) setup.fill((uint32_t*)b.hit_tops, 0u, 2 * HIT_SUBS * HIT_TOP_STRIDE);
     if (P.det) setup.fill((uint32_t*)b.part_a, 0u, plan->pairs_c);
+    const bool direct_i = without_lists_i(P, plan);
+    if (!direct_i && P.images_packed) setup.fill((uint32_t*)images, 0u, P.pixels);
     SDGR_HIP(setup.launch(s));
     // the projection also clears A for pass A's sums
     if ((rc = build_lists_c(P, plan, b, true, s))) return rc;
@@ -941,7 +945,7 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
         SDGR_HIP(launch_set_intensity(b.views, b.scenes, P.nv, P.records, b.A, b.prec, b.iw,
                                       b.rect_i, b.cnt_i, b.bsum_i, b.status, b.active, s));
     }
-    if (without_lists_i(P, plan)) {
+    if (direct_i) {
         StageTimer t(SG_RASTER_B_FWD, s);
         SDGR_HIP(launch_raster_b_direct(b.views, P.nv, P.tiles_c, P.tiles_i, P.records,
                                         plan->pairs_i, P.rp, b.bsum_i, b.status, b.rect_i, b.iq,
@@ -954,12 +958,12 @@ int sdgr_forward(const sdgr_scene* scenes, int32_t nscenes, const sdgr_view* vie
     if (P.det)
         SDGR_HIP(launch_raster_b_tiles(b.views, P.nv, P.pixels, plan->pairs_c, plan->pairs_i,
                                        P.tiles_c, P.tiles_i, P.rp, b.status, b.pkey[pwi],
-                                       b.pval[pwi], b.iq, b.iw, b.ranges_i, images, P.ikey_vm,
-                                       s));
+                                       b.pval[pwi], b.iq, b.iw, b.ranges_i, images,
+                                       P.images_packed, P.ikey_vm, s));
     else
         SDGR_HIP(launch_raster_b_fwd(b.views, P.nv, P.pixels, plan->pairs_c, plan->pairs_i, P.rp,
                                      b.status, b.pkey[pwi], b.pval[pwi], b.iq, b.iw, images,
-                                     P.ikey_vm, s));
+                                     P.images_packed, P.ikey_vm, s));
     return SDGR_OK;
 }
 

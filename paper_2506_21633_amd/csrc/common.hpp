@@ -516,7 +516,7 @@ struct SetupFill {
     uint32_t v;
 };
 struct Setup {
-    static constexpr int FILLS = 10, TABLES = 4;
+    static constexpr int FILLS = 12, TABLES = 4;
     void fill(uint32_t* p, uint32_t v, int64_t n);
     void table(void* dst, const void* src, size_t bytes);
     hipError_t launch(hipStream_t s) const;
@@ -551,7 +551,8 @@ hipError_t launch_raster_a_fwd(const DevView* views, int nv, int64_t tiles_c,
 hipError_t launch_raster_b_fwd(const DevView* views, int nv, int64_t pixels, int64_t cap_c,
                                int64_t cap_i, const RasterParams& rp, const uint32_t* status,
                                const uint32_t* pkey, const uint32_t* pvals, const float4* iq,
-                               const float2* iw, float* images, bool vm, hipStream_t s);
+                               const float2* iw, float* images, bool zeroed, bool vm,
+                               hipStream_t s);
 // Pass B over the views' records themselves, without imaging-plane lists:
 // stores every pixel, sets the pair count in status (bsum: counts per 256
 // records).
@@ -569,8 +570,8 @@ hipError_t launch_raster_b_tiles(const DevView* views, int nv, int64_t pixels, i
                                  int64_t cap_i, int64_t tiles_c, int64_t tiles_i,
                                  const RasterParams& rp, const uint32_t* status,
                                  const uint32_t* pkey, const uint32_t* pvals, const float4* iq,
-                                 const float2* iw, uint2* ranges_i, float* images, bool vm,
-                                 hipStream_t s);
+                                 const float2* iw, uint2* ranges_i, float* images, bool zeroed,
+                                 bool vm, hipStream_t s);
 hipError_t launch_image_bwd(const DevView* views, const DevScene* scenes, int nv,
                             int64_t records, const RasterParams& rp, const uint32_t* status,
                             const uint32_t* active, const float4* iq, const float2* iw,

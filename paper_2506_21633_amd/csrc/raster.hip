@@ -1308,6 +1308,11 @@ constexpr int LONG_LIST_BITS = 12;
 // BG_HITS are left, else each ray's next BG_RAY.
 constexpr uint32_t BG_RAY = 32, BG_HITS = WAVE * BG_RAY;
 
+// Tiles a workgroup looks at for one without stored hits (none has them in
+// most calls: a workgroup per tile that only finds its own stored took the
+// two launches 38 us for the 74k tiles of 72 views).
+constexpr int BWD_TILES = 8;
+
 template <bool FLUSHER, bool DET>
 __global__ void __launch_bounds__(FLUSHER ? 2 * WAVE : WAVE) __attribute__((amdgpu_waves_per_eu(1, 2)))
 k_raster_a_bwd(const DevView* __restrict__ views, int nv,
@@ -1343,10 +1348,15 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
     const uint32_t ntiles = status[ST_WORK_TILES];
     uint32_t nlong = status[WL_BINS_WORD + 33 + LONG_LIST_BITS];
     if (2u * nlong >= ntiles) nlong = ntiles;
-    const uint32_t wi = FLUSHER ? blockIdx.x : nlong + blockIdx.x;
-    if (wi >= (FLUSHER ? nlong : ntiles)) return;
-    // tiles whose hits the forward stored run in k_raster_a_bwd_hits
-    if (!DET && rp.hits != nullptr && rp.hit_tail[worklist[wi]] != HIT_OVERFLOW) return;
+    const uint32_t w0 = FLUSHER ? 0u : nlong, w1 = FLUSHER ? nlong : ntiles;
+    // tiles whose hits the forward stored run in k_raster_a_bwd_hits, mostly
+    // all of them: a workgroup then looks at BWD_TILES tiles for one without
+    uint64_t todo_tiles = w0 + blockIdx.x < w1 ? 1ull : 0ull;
+    if (!DET && rp.hits != nullptr) {
+        const uint32_t wi = w0 + blockIdx.x + (uint32_t)lane_id() * gridDim.x;
+        todo_tiles = __ballot(lane_id() < BWD_TILES && wi < w1 &&
+                              rp.hit_tail[worklist[min(wi, w1 - 1u)]] == HIT_OVERFLOW);
+    }
     constexpr uint32_t LAST = 1u << 31;
     // The six sums of a batch's touched entries (cmd: their chunks per lane,
     // rec: where each lane's go) leave with one atomic each, eight entries to
@@ -1376,296 +1386,305 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
             wave_lds_sync();
         }
     };
-    if (FLUSHER && threadIdx.x >= WAVE) {
-        // the flusher: per hand-off, the six sums of every handed-off entry
-        // leave with one atomic each, and the buffer is cleared for reuse
-        const int fl = threadIdx.x - WAVE;
-        for (int hb = 0;; hb ^= 1) {
-            __syncthreads();
-            const uint32_t cmd = s_cmd[hb][fl];
-            uint32_t rec[NB];
-#pragma unroll
-            for (int k = 0; k < NB; ++k) rec[k] = s_rf[hb][k][fl];
-            send(hb, cmd, rec);
-            if (cmd & LAST) return;
-        }
-    }
-    const int lane = threadIdx.x;
-    const TransposeLane tl = transpose_lane();
-    const int64_t bucket = worklist[wi];
-    const TileCell tc = tile_cell(views, nv, bucket, true);
-    const DevView& V = views[tc.v];
-    const float x0 = (float)(tc.tx * TILE) + 0.5f, y0 = (float)(tc.ty * TILE) + 0.5f;
-    const uint2 rg = ranges[bucket];
-    const int64_t ray = V.ray_off + (int64_t)tc.row * V.Wc + tc.col;
-    const uint32_t n_mine = tc.inside ? nlast[ray] : 0u;   // entries [0, n_mine) were used
-    float t = tc.inside ? tau[ray] : 0.0f;
-    float U = 0.0f;
-#pragma unroll
-    for (int b = 0; b < GB; ++b)
-#pragma unroll
-        for (int k = 0; k < NB; ++k)
-#pragma unroll
-            for (int c = 0; c < 6; ++c) s_G[b][k][c][lane] = 0.0;
-    unsigned long long n_iter = 0, n_hits = 0;   // work counters
-    unsigned long long n_batch = 0, n_extra = 0;
-    const uint32_t n_max = wave_max_u32(n_mine);
-    const uint32_t e_end = rg.x + n_max;           // exclusive end of the used entries
-    // the six per-entry sums of the last processed batch leave once the next
-    // batch's loads have landed: handed to the flusher wave (the barrier also
-    // returns the buffer it emptied last), or sent by this wave before the
-    // next batch accumulates into the same buffer
-    uint32_t got_prev = 0u;
-    // where each entry's sums go: its record, or in deterministic mode its
-    // pair's position before the sort
-    uint32_t r_prev[NB], r_cur[NB];
-    int hb = 0;                        // buffer the current batch accumulates in
-    auto flush = [&](bool last) {
-        if constexpr (FLUSHER) {
-#pragma unroll
-            for (int k = 0; k < NB; ++k) s_rf[hb][k][lane] = r_prev[k];
-            s_cmd[hb][lane] = got_prev | (last ? LAST : 0u);
-            __syncthreads();
-            hb ^= 1;
-        } else {
-            send(0, got_prev, r_prev);
-        }
-        got_prev = 0u;
-    };
-    // One round of up to 64 hits, lane = hit (each ray's hits contiguous,
-    // back to front; `head` marks a ray's first hit in the round, rs is its
-    // state before the round): optical depths and U by segmented scans, the
-    // per-entry gradient sums into LDS, each ray's state after its last hit
-    // back to s_ray.
-    auto hit_round = [&](const uint32_t hv, const bool valid, const bool head, const RayB rs) {
-        const int rr = (int)(hv >> HRS), k = (int)((hv >> 6) & ((1u << HKB) - 1u)),
-                  j = (int)(hv & 63u);
-        const float4 g = s_rec[k][2 * j], g2 = s_rec[k][2 * j + 1];
-        const float cj = g2.w;
-        bool real = false;
-        float x = 0.0f, E = 1.0f, ex = 0.0f, f = 0.0f, dx = 0.0f, dy = 0.0f;
-        float c = 0.0f;
-        if (valid) {
-            dx = x0 + (float)(rr & (TILE - 1)) - g.x;
-            dy = y0 + (float)(rr / TILE) - g.y;
-            const float q = quadform(g, g2.x, dx, dy);
-            if (q < rp.q_max) {
-                real = true;
-                c = cj;
-                ex = __expf(-0.5f * q);
-                f = (ex - rp.eps) * rp.inv1meps;
-                x = g2.y * f;
-                E = __expf(-x);
-            }
-        }
-        const float sx = seg_incl_scan(x, head);   // this and the later hits
-        float sa = E, sb = real ? c * (1.0f - E) : 0.0f;
-        seg_incl_affine(sa, sb, head);
-        float ea = __int_as_float(from_lane_below(__float_as_int(sa)));
-        float eb = __int_as_float(from_lane_below(__float_as_int(sb)));
-        if (head) {
-            ea = 1.0f;
-            eb = 0.0f;
-        }
-        const float tr = valid ? rs.t : 0.0f;
-        const float Ur = valid ? rs.U : 0.0f;
-        if (real) {
-            float dalpha;
-            if (rp.shadowing) {
-                const float Tn = __expf(-fmaxf(tr - sx, 0.0f));
-                dalpha = Tn * (c - (ea * Ur + eb));
-            } else {
-                dalpha = c;
-            }
-            const float dxx = dalpha * E;   // d alpha / d x = exp(-x)
-            const float dq = dxx * g2.y * (-0.5f * ex * rp.inv1meps);
-            atomicAdd(&s_G[hb][k][0][j], (double)(-2.0f * dq * (g.z * dx + g.w * dy)));
-            atomicAdd(&s_G[hb][k][1][j], (double)(-2.0f * dq * (g.w * dx + g2.x * dy)));
-            atomicAdd(&s_G[hb][k][2][j], (double)(dq * dx * dx));
-            atomicAdd(&s_G[hb][k][3][j], (double)(2.0f * dq * dx * dy));
-            atomicAdd(&s_G[hb][k][4][j], (double)(dq * dy * dy));
-            atomicAdd(&s_G[hb][k][5][j], (double)(dxx * f));
-        }
-        const uint64_t hbits = __ballot(real);
-        if (lane == 0) n_hits += (unsigned long long)__popcll(hbits);
-        const int nxt = from_lane_above(valid ? (int)hv : -1);
-        const bool endseg = valid && (lane == WAVE - 1 || (nxt >> HRS) != rr);
-        wave_lds_sync();
-        if (endseg && rp.shadowing) s_ray[rr] = RayB{rs.o, tr - sx, sa * Ur + sb, 0.0f};
-        wave_lds_sync();
-    };
-    const int64_t c_first = rg.x / WAVE, c_end = (int64_t)(e_end + WAVE - 1) / WAVE;
-    for (int64_t g1 = c_end; g1 > c_first && n_max > 0u; g1 -= WAVE) {
-        const int64_t g0 = max(c_first, g1 - (int64_t)WAVE);
-        // lane = chunk g0 + lane: the rays that used an entry at or past its start
-        const int64_t cpos = (g0 + lane) * WAVE - (int64_t)rg.x;
-        uint64_t live_c = 0ull;
-        for (int rr = 0; rr < WAVE; ++rr) {
-            const uint32_t nm = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, rr);
-            if ((int64_t)nm > cpos) live_c |= 1ull << rr;
-        }
-        const uint64_t sm = g0 + lane < g1 ? psum[g0 + lane] : 0ull;
-        uint64_t todo = __ballot((sm & live_c) != 0ull);   // chunks to read, back to front
-        // up to NB chunks per batch: their masks and values are fetched one
-        // batch ahead (in flight while the current batch's hits are
-        // processed), then the records the rays need
-        uint32_t chk_n[NB], rec_n[NB], r_n[NB];
-        uint64_t lv_n[NB], m_n[NB];
-        int nb_n = 0;
-        auto fetch = [&]() {
-            nb_n = 0;
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                chk_n[k] = 0u;
-                lv_n[k] = 0ull;
-                if (todo != 0ull) {
-                    const int hi = 63 - __builtin_clzll(todo);
-                    todo &= ~(1ull << hi);
-                    chk_n[k] = (uint32_t)g0 + (uint32_t)hi;
-                    const uint32_t l0 =
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)live_c, hi);
-                    const uint32_t l1 =
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(live_c >> 32), hi);
-                    lv_n[k] = ((uint64_t)l1 << 32) | l0;
-                    nb_n = k + 1;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const uint32_t e = chk_n[k] * WAVE + lane;
-                const bool in = k < nb_n && e >= rg.x && e < e_end;
-                m_n[k] = in ? pmask[e] : 0ull;
-                rec_n[k] = in ? pvals[e] : 0u;
-                if constexpr (DET) r_n[k] = in ? rp.ppos[e] : 0u;
-                else r_n[k] = rec_n[k];
-            }
-        };
-        fetch();
-        while (nb_n > 0) {
-            ++n_batch;
-            uint32_t got = 0u;
-            const int nb = nb_n;
-            uint64_t m[NB];   // lane = entry: the cells it covers
-            {
-                uint32_t chk[NB];
-                uint64_t lv[NB];
-                uint32_t* r = r_cur;
+    while (todo_tiles != 0ull) {   // the same for both waves
+        const uint32_t wi = w0 + blockIdx.x + (uint32_t)__builtin_ctzll(todo_tiles) * gridDim.x;
+        todo_tiles &= todo_tiles - 1ull;
+        if (FLUSHER && threadIdx.x >= WAVE) {
+            // the flusher: per hand-off, the six sums of every handed-off entry
+            // leave with one atomic each, and the buffer is cleared for reuse
+            const int fl = threadIdx.x - WAVE;
+            for (int hb = 0;; hb ^= 1) {
+                __syncthreads();
+                const uint32_t cmd = s_cmd[hb][fl];
                 uint32_t rec[NB];
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    chk[k] = chk_n[k];
-                    lv[k] = lv_n[k];
-                    m[k] = m_n[k];
-                    rec[k] = rec_n[k];
-                    r[k] = r_n[k];
-                }
-                // records straight into LDS, all in flight together (entries
-                // no ray needs read record 0 of the view, one shared line)
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const bool need = (m[k] & lv[k]) != 0ull;
-                    got |= need ? 1u << k : 0u;
-                    load_recs_to_lds(crec, need ? rec[k] : (uint32_t)V.rec_off, &s_rec[k][0]);
-                }
-#pragma unroll
-                for (int k = 0; k < NB; ++k)
-                    if (lane == k) s_chk[k] = chk[k];
+                for (int k = 0; k < NB; ++k) rec[k] = s_rf[hb][k][fl];
+                send(hb, cmd, rec);
+                if (cmd & LAST) break;
             }
-            wait_all_memory();
+            __syncthreads();
+            continue;
+        }
+        const int lane = threadIdx.x;
+        const TransposeLane tl = transpose_lane();
+        const int64_t bucket = worklist[wi];
+        const TileCell tc = tile_cell(views, nv, bucket, true);
+        const DevView& V = views[tc.v];
+        const float x0 = (float)(tc.tx * TILE) + 0.5f, y0 = (float)(tc.ty * TILE) + 0.5f;
+        const uint2 rg = ranges[bucket];
+        const int64_t ray = V.ray_off + (int64_t)tc.row * V.Wc + tc.col;
+        const uint32_t n_mine = tc.inside ? nlast[ray] : 0u;   // entries [0, n_mine) were used
+        float t = tc.inside ? tau[ray] : 0.0f;
+        float U = 0.0f;
+#pragma unroll
+        for (int b = 0; b < GB; ++b)
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+#pragma unroll
+                for (int c = 0; c < 6; ++c) s_G[b][k][c][lane] = 0.0;
+        unsigned long long n_iter = 0, n_hits = 0;   // work counters
+        unsigned long long n_batch = 0, n_extra = 0;
+        const uint32_t n_max = wave_max_u32(n_mine);
+        const uint32_t e_end = rg.x + n_max;           // exclusive end of the used entries
+        // the six per-entry sums of the last processed batch leave once the next
+        // batch's loads have landed: handed to the flusher wave (the barrier also
+        // returns the buffer it emptied last), or sent by this wave before the
+        // next batch accumulates into the same buffer
+        uint32_t got_prev = 0u;
+        // where each entry's sums go: its record, or in deterministic mode its
+        // pair's position before the sort
+        uint32_t r_prev[NB], r_cur[NB];
+        int hb = 0;                        // buffer the current batch accumulates in
+        auto flush = [&](bool last) {
+            if constexpr (FLUSHER) {
+#pragma unroll
+                for (int k = 0; k < NB; ++k) s_rf[hb][k][lane] = r_prev[k];
+                s_cmd[hb][lane] = got_prev | (last ? LAST : 0u);
+                __syncthreads();
+                hb ^= 1;
+            } else {
+                send(0, got_prev, r_prev);
+            }
+            got_prev = 0u;
+        };
+        // One round of up to 64 hits, lane = hit (each ray's hits contiguous,
+        // back to front; `head` marks a ray's first hit in the round, rs is its
+        // state before the round): optical depths and U by segmented scans, the
+        // per-entry gradient sums into LDS, each ray's state after its last hit
+        // back to s_ray.
+        auto hit_round = [&](const uint32_t hv, const bool valid, const bool head, const RayB rs) {
+            const int rr = (int)(hv >> HRS), k = (int)((hv >> 6) & ((1u << HKB) - 1u)),
+                      j = (int)(hv & 63u);
+            const float4 g = s_rec[k][2 * j], g2 = s_rec[k][2 * j + 1];
+            const float cj = g2.w;
+            bool real = false;
+            float x = 0.0f, E = 1.0f, ex = 0.0f, f = 0.0f, dx = 0.0f, dy = 0.0f;
+            float c = 0.0f;
+            if (valid) {
+                dx = x0 + (float)(rr & (TILE - 1)) - g.x;
+                dy = y0 + (float)(rr / TILE) - g.y;
+                const float q = quadform(g, g2.x, dx, dy);
+                if (q < rp.q_max) {
+                    real = true;
+                    c = cj;
+                    ex = __expf(-0.5f * q);
+                    f = (ex - rp.eps) * rp.inv1meps;
+                    x = g2.y * f;
+                    E = __expf(-x);
+                }
+            }
+            const float sx = seg_incl_scan(x, head);   // this and the later hits
+            float sa = E, sb = real ? c * (1.0f - E) : 0.0f;
+            seg_incl_affine(sa, sb, head);
+            float ea = __int_as_float(from_lane_below(__float_as_int(sa)));
+            float eb = __int_as_float(from_lane_below(__float_as_int(sb)));
+            if (head) {
+                ea = 1.0f;
+                eb = 0.0f;
+            }
+            const float tr = valid ? rs.t : 0.0f;
+            const float Ur = valid ? rs.U : 0.0f;
+            if (real) {
+                float dalpha;
+                if (rp.shadowing) {
+                    const float Tn = __expf(-fmaxf(tr - sx, 0.0f));
+                    dalpha = Tn * (c - (ea * Ur + eb));
+                } else {
+                    dalpha = c;
+                }
+                const float dxx = dalpha * E;   // d alpha / d x = exp(-x)
+                const float dq = dxx * g2.y * (-0.5f * ex * rp.inv1meps);
+                atomicAdd(&s_G[hb][k][0][j], (double)(-2.0f * dq * (g.z * dx + g.w * dy)));
+                atomicAdd(&s_G[hb][k][1][j], (double)(-2.0f * dq * (g.w * dx + g2.x * dy)));
+                atomicAdd(&s_G[hb][k][2][j], (double)(dq * dx * dx));
+                atomicAdd(&s_G[hb][k][3][j], (double)(2.0f * dq * dx * dy));
+                atomicAdd(&s_G[hb][k][4][j], (double)(dq * dy * dy));
+                atomicAdd(&s_G[hb][k][5][j], (double)(dxx * f));
+            }
+            const uint64_t hbits = __ballot(real);
+            if (lane == 0) n_hits += (unsigned long long)__popcll(hbits);
+            const int nxt = from_lane_above(valid ? (int)hv : -1);
+            const bool endseg = valid && (lane == WAVE - 1 || (nxt >> HRS) != rr);
             wave_lds_sync();
-            fetch();   // the next batch's masks and values
-            flush(false);
-            got_prev = got;
-#pragma unroll
-            for (int k = 0; k < NB; ++k) r_prev[k] = r_cur[k];
-            // the batch's chunks, transposed: bit j of col[k] is entry j of
-            // chunk k covering my cell that my ray used in the forward
-            // (all transposed together, as in the forward)
-            uint64_t col[NB];
-#pragma unroll
-            for (int k = 0; k < NB; ++k) col[k] = m[k];
-            transpose64_n(col, tl);
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                uint64_t used = 0ull;
-                if (k < nb) {
-                    const int64_t pos0 = (int64_t)s_chk[k] * WAVE - rg.x;
-                    const int64_t nu = (int64_t)n_mine - pos0;   // used: positions < n_mine
-                    used = nu >= WAVE ? ~0ull : (nu <= 0 ? 0ull : ((1ull << nu) - 1ull));
-                }
-                col[k] &= used;
+            if (endseg && rp.shadowing) s_ray[rr] = RayB{rs.o, tr - sx, sa * Ur + sb, 0.0f};
+            wave_lds_sync();
+        };
+        const int64_t c_first = rg.x / WAVE, c_end = (int64_t)(e_end + WAVE - 1) / WAVE;
+        for (int64_t g1 = c_end; g1 > c_first && n_max > 0u; g1 -= WAVE) {
+            const int64_t g0 = max(c_first, g1 - (int64_t)WAVE);
+            // lane = chunk g0 + lane: the rays that used an entry at or past its start
+            const int64_t cpos = (g0 + lane) * WAVE - (int64_t)rg.x;
+            uint64_t live_c = 0ull;
+            for (int rr = 0; rr < WAVE; ++rr) {
+                const uint32_t nm = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, rr);
+                if ((int64_t)nm > cpos) live_c |= 1ull << rr;
             }
-            // the batch's hits in groups, compacted ray-major, back to front
-            // (the batch's chunks come back to front), and taken 64 per
-            // round: all that are left when they are few, else each ray's
-            // next BG_RAY
-            for (bool more = false;; more = true) {
-                uint32_t nr = 0;
+            const uint64_t sm = g0 + lane < g1 ? psum[g0 + lane] : 0ull;
+            uint64_t todo = __ballot((sm & live_c) != 0ull);   // chunks to read, back to front
+            // up to NB chunks per batch: their masks and values are fetched one
+            // batch ahead (in flight while the current batch's hits are
+            // processed), then the records the rays need
+            uint32_t chk_n[NB], rec_n[NB], r_n[NB];
+            uint64_t lv_n[NB], m_n[NB];
+            int nb_n = 0;
+            auto fetch = [&]() {
+                nb_n = 0;
 #pragma unroll
-                for (int k = 0; k < NB; ++k) nr += (uint32_t)__popcll(col[k]);
-                if (__ballot(nr != 0u) == 0ull) break;
-                n_extra += more ? 1u : 0u;
-                // hits left and hits of a limited group, scanned together
-                // (at most 64 x 512 and 64 x BG_RAY: two to a word)
-                const uint32_t lim = min(nr, BG_RAY);
-                const uint32_t both = nr | (lim << 16);
-                const uint32_t excl = wave_excl_scan_u32(both);
-                const uint32_t tot =
-                    (uint32_t)__builtin_amdgcn_readlane((int)(excl + both), WAVE - 1);
-                const bool few = (tot & 0xFFFFu) <= BG_HITS;
-                const uint32_t H = few ? (tot & 0xFFFFu) : (tot >> 16);
-                const uint32_t o = few ? (excl & 0xFFFFu) : (excl >> 16);
-                const uint32_t o_end = o + (few ? nr : lim);
+                for (int k = 0; k < NB; ++k) {
+                    chk_n[k] = 0u;
+                    lv_n[k] = 0ull;
+                    if (todo != 0ull) {
+                        const int hi = 63 - __builtin_clzll(todo);
+                        todo &= ~(1ull << hi);
+                        chk_n[k] = (uint32_t)g0 + (uint32_t)hi;
+                        const uint32_t l0 =
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)live_c, hi);
+                        const uint32_t l1 =
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(live_c >> 32), hi);
+                        lv_n[k] = ((uint64_t)l1 << 32) | l0;
+                        nb_n = k + 1;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const uint32_t e = chk_n[k] * WAVE + lane;
+                    const bool in = k < nb_n && e >= rg.x && e < e_end;
+                    m_n[k] = in ? pmask[e] : 0ull;
+                    rec_n[k] = in ? pvals[e] : 0u;
+                    if constexpr (DET) r_n[k] = in ? rp.ppos[e] : 0u;
+                    else r_n[k] = rec_n[k];
+                }
+            };
+            fetch();
+            while (nb_n > 0) {
+                ++n_batch;
+                uint32_t got = 0u;
+                const int nb = nb_n;
+                uint64_t m[NB];   // lane = entry: the cells it covers
                 {
-                    uint32_t w = o;
+                    uint32_t chk[NB];
+                    uint64_t lv[NB];
+                    uint32_t* r = r_cur;
+                    uint32_t rec[NB];
 #pragma unroll
                     for (int k = 0; k < NB; ++k) {
-                        uint32_t half[2] = {(uint32_t)col[k], (uint32_t)(col[k] >> 32)};
+                        chk[k] = chk_n[k];
+                        lv[k] = lv_n[k];
+                        m[k] = m_n[k];
+                        rec[k] = rec_n[k];
+                        r[k] = r_n[k];
+                    }
+                    // records straight into LDS, all in flight together (entries
+                    // no ray needs read record 0 of the view, one shared line)
 #pragma unroll
-                        for (int q = 1; q >= 0; --q) {
-                            const uint32_t tag = (uint32_t)((lane << HRS) | (k << 6) | (q << 5));
-                            while (half[q] != 0u && w < o_end) {
-                                const uint32_t j = 31u - (uint32_t)__builtin_clz(half[q]);
-                                half[q] &= ~(1u << j);
-                                s_hit[w++] = (uint16_t)(tag | j);
-                            }
-                        }
-                        col[k] = ((uint64_t)half[1] << 32) | half[0];
+                    for (int k = 0; k < NB; ++k) {
+                        const bool need = (m[k] & lv[k]) != 0ull;
+                        got |= need ? 1u << k : 0u;
+                        load_recs_to_lds(crec, need ? rec[k] : (uint32_t)V.rec_off, &s_rec[k][0]);
                     }
-                    s_ray[lane] = RayB{o, t, U, 0.0f};
-                    wave_lds_sync();
-                    for (uint32_t base = 0; base < H; base += WAVE) {
-                        ++n_iter;
-                        const uint32_t L = base + lane;
-                        const bool valid = L < H;
-                        const uint32_t hv = valid ? (uint32_t)s_hit[L] : 0u;
-                        // ray state (lanes past the last hit read ray 0 and ignore it)
-                        const RayB rs = s_ray[hv >> HRS];
-                        const int seg0 = valid ? max((int)rs.o - (int)base, 0) : lane;
-                        hit_round(hv, valid, lane == seg0, rs);
-                    }
-                    {
-                        const RayB rs = s_ray[lane];
-                        t = rs.t;
-                        U = rs.U;
-                    }
-                    wave_lds_sync();
+#pragma unroll
+                    for (int k = 0; k < NB; ++k)
+                        if (lane == k) s_chk[k] = chk[k];
                 }
+                wait_all_memory();
+                wave_lds_sync();
+                fetch();   // the next batch's masks and values
+                flush(false);
+                got_prev = got;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) r_prev[k] = r_cur[k];
+                // the batch's chunks, transposed: bit j of col[k] is entry j of
+                // chunk k covering my cell that my ray used in the forward
+                // (all transposed together, as in the forward)
+                uint64_t col[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) col[k] = m[k];
+                transpose64_n(col, tl);
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    uint64_t used = 0ull;
+                    if (k < nb) {
+                        const int64_t pos0 = (int64_t)s_chk[k] * WAVE - rg.x;
+                        const int64_t nu = (int64_t)n_mine - pos0;   // used: positions < n_mine
+                        used = nu >= WAVE ? ~0ull : (nu <= 0 ? 0ull : ((1ull << nu) - 1ull));
+                    }
+                    col[k] &= used;
+                }
+                // the batch's hits in groups, compacted ray-major, back to front
+                // (the batch's chunks come back to front), and taken 64 per
+                // round: all that are left when they are few, else each ray's
+                // next BG_RAY
+                for (bool more = false;; more = true) {
+                    uint32_t nr = 0;
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) nr += (uint32_t)__popcll(col[k]);
+                    if (__ballot(nr != 0u) == 0ull) break;
+                    n_extra += more ? 1u : 0u;
+                    // hits left and hits of a limited group, scanned together
+                    // (at most 64 x 512 and 64 x BG_RAY: two to a word)
+                    const uint32_t lim = min(nr, BG_RAY);
+                    const uint32_t both = nr | (lim << 16);
+                    const uint32_t excl = wave_excl_scan_u32(both);
+                    const uint32_t tot =
+                        (uint32_t)__builtin_amdgcn_readlane((int)(excl + both), WAVE - 1);
+                    const bool few = (tot & 0xFFFFu) <= BG_HITS;
+                    const uint32_t H = few ? (tot & 0xFFFFu) : (tot >> 16);
+                    const uint32_t o = few ? (excl & 0xFFFFu) : (excl >> 16);
+                    const uint32_t o_end = o + (few ? nr : lim);
+                    {
+                        uint32_t w = o;
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) {
+                            uint32_t half[2] = {(uint32_t)col[k], (uint32_t)(col[k] >> 32)};
+#pragma unroll
+                            for (int q = 1; q >= 0; --q) {
+                                const uint32_t tag =
+                                    (uint32_t)((lane << HRS) | (k << 6) | (q << 5));
+                                while (half[q] != 0u && w < o_end) {
+                                    const uint32_t j = 31u - (uint32_t)__builtin_clz(half[q]);
+                                    half[q] &= ~(1u << j);
+                                    s_hit[w++] = (uint16_t)(tag | j);
+                                }
+                            }
+                            col[k] = ((uint64_t)half[1] << 32) | half[0];
+                        }
+                        s_ray[lane] = RayB{o, t, U, 0.0f};
+                        wave_lds_sync();
+                        for (uint32_t base = 0; base < H; base += WAVE) {
+                            ++n_iter;
+                            const uint32_t L = base + lane;
+                            const bool valid = L < H;
+                            const uint32_t hv = valid ? (uint32_t)s_hit[L] : 0u;
+                            // ray state (lanes past the last hit read ray 0 and ignore it)
+                            const RayB rs = s_ray[hv >> HRS];
+                            const int seg0 = valid ? max((int)rs.o - (int)base, 0) : lane;
+                            hit_round(hv, valid, lane == seg0, rs);
+                        }
+                        {
+                            const RayB rs = s_ray[lane];
+                            t = rs.t;
+                            U = rs.U;
+                        }
+                        wave_lds_sync();
+                    }
+                }
+                wave_lds_sync();
             }
-            wave_lds_sync();
         }
-    }
-    flush(true);
-    if (rp.work) {
-        n_hits = wave_sum_u64(n_hits);
-        if (lane == 0) {
-            atomicAdd(&rp.work[5], n_iter);
-            atomicAdd(&rp.work[1], n_hits);
-            atomicMax(&rp.work[9], n_batch);
-            atomicAdd(&rp.work[11], n_extra);
-            atomicAdd(&rp.work[FLUSHER ? 14 : 15], 1ull);
-            atomicAdd(&rp.work[17], 1ull);
+        flush(true);
+        if (rp.work) {
+            n_hits = wave_sum_u64(n_hits);
+            if (lane == 0) {
+                atomicAdd(&rp.work[5], n_iter);
+                atomicAdd(&rp.work[1], n_hits);
+                atomicMax(&rp.work[9], n_batch);
+                atomicAdd(&rp.work[11], n_extra);
+                atomicAdd(&rp.work[FLUSHER ? 14 : 15], 1ull);
+                atomicAdd(&rp.work[17], 1ull);
+            }
         }
+        if constexpr (FLUSHER) __syncthreads();
+        else wave_lds_sync();
     }
 }
 
@@ -2070,23 +2089,23 @@ __device__ __forceinline__ int list_bin(const uint2* __restrict__ ranges, int64_
     return rg.y > rg.x ? 32 - __clz(rg.y - rg.x) : 0;   // 0: nothing to do
 }
 
-// Adds the wave's tiles to the block's counts, one LDS atomic per bin among
-// them; returns the tile's place among the block's tiles of its bin.
+// Adds the wave's tiles to the block's counts, one LDS atomic for the lanes
+// of each bin (a loop over the bins among them waits for one atomic after
+// the other: 21 us for 9216 tiles in one workgroup); returns the tile's place
+// among the block's tiles of its bin.
 __device__ __forceinline__ uint32_t bin_rank(uint32_t* s_cnt, int bin)
 {
-    uint32_t rank = 0u;
-    uint64_t todo = __ballot(bin != 0);
-    while (todo != 0ull) {
-        const int b = __builtin_amdgcn_readlane(bin, __builtin_ctzll(todo));
-        const uint64_t same = __ballot(bin == b);
-        uint32_t first = 0u;
-        if (lane_id() == __builtin_ctzll(same))
-            first = atomicAdd(&s_cnt[b], (uint32_t)__popcll(same));
-        first = (uint32_t)__builtin_amdgcn_readlane((int)first, __builtin_ctzll(same));
-        if (bin == b) rank = first + lanes_below(same);
-        todo &= ~same;
+    uint64_t same = __ballot(bin != 0);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        const uint64_t bit = __ballot((bin >> b) & 1);
+        same &= ((bin >> b) & 1) ? bit : ~bit;
     }
-    return rank;
+    uint32_t first = 0u;
+    if (bin != 0 && lanes_below(same) == 0u)
+        first = atomicAdd(&s_cnt[bin], (uint32_t)__popcll(same));
+    const int lead = same ? __builtin_ctzll(same) : 0;   // (no bin: any lane)
+    return (uint32_t)__shfl((int)first, lead, WAVE) + lanes_below(same);
 }
 
 __global__ void __launch_bounds__(256)
@@ -2141,10 +2160,10 @@ k_worklist_place(const uint2* __restrict__ ranges, int64_t tiles_c, uint32_t* __
         if (bin[k]) worklist[s_base[bin[k]] + rank[k]] = (uint32_t)(t0 + k * 256);
 }
 
-// The three steps in one workgroup, for at most WL_SMALL tiles (three
-// launches of 4 us each otherwise).
+// The three steps in one workgroup, for at most WL_SMALL tiles (64 tiles in 3
+// us, 9216 in 13, 16384 in 16; the three launches take 12, 18 and 18).
 constexpr int WL_SMALL_THREADS = 1024;
-constexpr int WL_SMALL_PER = 8;
+constexpr int WL_SMALL_PER = 16;
 constexpr int64_t WL_SMALL = WL_SMALL_THREADS * WL_SMALL_PER;
 
 __global__ void __launch_bounds__(WL_SMALL_THREADS)
@@ -2160,7 +2179,8 @@ k_worklist_small(const uint2* __restrict__ ranges, int64_t tiles_c, uint32_t* __
     for (int k = 0; k < WL_SMALL_PER; ++k)
         bin[k] = list_bin(ranges, (int64_t)(k * WL_SMALL_THREADS) + threadIdx.x, tiles_c);
 #pragma unroll
-    for (int k = 0; k < WL_SMALL_PER; ++k) rank[k] = bin_rank(s_cnt, bin[k]);
+    for (int k = 0; k < WL_SMALL_PER; ++k)
+        rank[k] = k * WL_SMALL_THREADS < tiles_c ? bin_rank(s_cnt, bin[k]) : 0u;
     __syncthreads();
     if (threadIdx.x < WAVE) {
         // bins in descending order of length: lane l holds bin 32 - l
@@ -2254,11 +2274,13 @@ hipError_t launch_raster_a_fwd(const DevView* views, int nv, int64_t tiles_c,
 hipError_t launch_raster_b_fwd(const DevView* views, int nv, int64_t pixels, int64_t cap_c,
                                int64_t cap_i, const RasterParams& rp, const uint32_t* status,
                                const uint32_t* pkey, const uint32_t* pvals, const float4* iq,
-                               const float2* iw, float* images, bool vm, hipStream_t s)
+                               const float2* iw, float* images, bool zeroed, bool vm,
+                               hipStream_t s)
 {
     if (pixels <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_images, dim3(grid256(pixels)), dim3(256), 0, s, views, nv, pixels,
-                       images);
+    if (!zeroed)
+        hipLaunchKernelGGL(k_zero_images, dim3(grid256(pixels)), dim3(256), 0, s, views, nv,
+                           pixels, images);
     if (cap_i <= 0) return hipGetLastError();
     const int64_t segs = (cap_i + B_SEGMENT - 1) / B_SEGMENT;
     hipLaunchKernelGGL(k_raster_b_fwd, dim3(raster_grid(segs)), dim3(RASTER_THREADS), 0, s, views,
@@ -2283,12 +2305,13 @@ hipError_t launch_raster_b_tiles(const DevView* views, int nv, int64_t pixels, i
                                  int64_t cap_i, int64_t tiles_c, int64_t tiles_i,
                                  const RasterParams& rp, const uint32_t* status,
                                  const uint32_t* pkey, const uint32_t* pvals, const float4* iq,
-                                 const float2* iw, uint2* ranges_i, float* images, bool vm,
-                                 hipStream_t s)
+                                 const float2* iw, uint2* ranges_i, float* images, bool zeroed,
+                                 bool vm, hipStream_t s)
 {
     if (pixels <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_images, dim3(grid256(pixels)), dim3(256), 0, s, views, nv, pixels,
-                       images);
+    if (!zeroed)
+        hipLaunchKernelGGL(k_zero_images, dim3(grid256(pixels)), dim3(256), 0, s, views, nv,
+                           pixels, images);
     if (cap_i <= 0 || tiles_i <= 0) return hipGetLastError();
     hipError_t e = launch_ranges_i(views, pkey + cap_c, status, cap_i, tiles_c, tiles_i, vm,
                                    ranges_i, s);
@@ -2334,12 +2357,14 @@ hipError_t launch_raster_a_bwd(const DevView* views, int nv, int64_t tiles_c,
     // long lists (the front of the worklist), then the short ones
     auto two = [&](auto det) {
         constexpr bool D = decltype(det)::value;
-        hipLaunchKernelGGL((k_raster_a_bwd<true, D>), dim3((unsigned)tiles_c), dim3(2 * WAVE), 0,
-                           s, views, nv, rp, status, worklist, ranges, pvals, pmask, psum, crec,
-                           tau, nlast, grad_c, stride);
-        hipLaunchKernelGGL((k_raster_a_bwd<false, D>), dim3((unsigned)tiles_c), dim3(WAVE), 0, s,
-                           views, nv, rp, status, worklist, ranges, pvals, pmask, psum, crec,
-                           tau, nlast, grad_c, stride);
+        const int64_t per = !D && rp.hits ? BWD_TILES : 1;
+        const unsigned grid = (unsigned)((tiles_c + per - 1) / per);
+        hipLaunchKernelGGL((k_raster_a_bwd<true, D>), dim3(grid), dim3(2 * WAVE), 0, s, views, nv,
+                           rp, status, worklist, ranges, pvals, pmask, psum, crec, tau, nlast,
+                           grad_c, stride);
+        hipLaunchKernelGGL((k_raster_a_bwd<false, D>), dim3(grid), dim3(WAVE), 0, s, views, nv,
+                           rp, status, worklist, ranges, pvals, pmask, psum, crec, tau, nlast,
+                           grad_c, stride);
     };
     if (rp.ppos)
         two(std::true_type{});
