@@ -27,6 +27,7 @@
 //                    the image at tile boundaries.
 //   pass B backward: one thread per record walks its footprint ellipse and
 //                    gathers dL/dS (no atomics).
+#include <algorithm>
 #include <cfloat>
 #include <type_traits>
 
@@ -479,6 +480,13 @@ constexpr int HB_SLOTS = HB_CHUNKS * WAVE;
 constexpr int HB_CHUNK_BITS = 2, HB_RAY_SHIFT = 6 + HB_CHUNK_BITS;
 static_assert(HB_CHUNKS == 1 << HB_CHUNK_BITS, "chunk index bits of a stored hit");
 
+// Where hits are stored, up to this many tiles go to k_raster_a_fwd_hits, nine
+// waves to a tile, which halves the chain of a long list: 8 views of 20k
+// Gaussians in 88 tiles 100 -> 63 us, 20 views of 80k in 718 tiles 142 -> 91.
+// More tiles fill the device with a wave each: 72 views of 200k in 2601 tiles
+// 375 against 453, 36 views of 50k in 6360 shorter ones 145 against 341.
+constexpr uint32_t HF_TILES = 1536;
+
 // DET: deterministic mode (per-pair partials at their pre-sort positions).
 // HITS: the hits are stored for the backward. Only then may a group be cut by
 // ray: without stored hits the backward takes a ray's hits to be those in
@@ -513,7 +521,8 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     __shared__ RayF s_ray[WAVE];
     const int lane = threadIdx.x;
     const TransposeLane tl = transpose_lane();
-    if (blockIdx.x >= status[ST_WORK_TILES]) return;
+    const uint32_t ntiles = status[ST_WORK_TILES];
+    if (blockIdx.x >= ntiles || (HITS && ntiles <= HF_TILES)) return;
     const int64_t bucket = worklist[blockIdx.x];
     const TileCell tc = tile_cell(views, nv, bucket, true);
     const DevView& V = views[tc.v];
@@ -865,6 +874,470 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
         const int64_t ray = V.ray_off + (int64_t)tc.row * V.Wc + tc.col;
         tau[ray] = t;
         nlast[ray] = last;
+    }
+}
+
+// Pass A forward with the hits stored for the backward, for few tiles: a
+// workgroup of nine waves takes a tile. The list is walked in the same batches
+// of four chunks, in three stages a step apart (a step is a group of hits):
+//   four waves prepare the next group: load and transpose a chunk each and
+//     compact the hits ray-major together. Masks and record ids are loaded two
+//     batches ahead, records one batch ahead. Which rays are in play is known
+//     up to the group before the current one; hits of rays that stop in that
+//     are evaluated in vain;
+//   four waves evaluate the current group, 256 hits at a time, 64 to a wave:
+//     the segmented prefix sums along the rays run in each wave, and the one
+//     ray that crosses from a wave into the next is carried over through LDS;
+//   the last wave sends the per-entry sums of the group before and copies its
+//     hits to the stream (memory operations complete in order, so a wave that
+//     also stored would wait for its atomics whenever it waits for a load).
+// Bound by the chain of batches of the longest lists, most of it dependent
+// instructions and LDS accesses: a single wave that does all of it takes 4 us
+// a batch (k_raster_a_fwd, the better one where tiles fill the device).
+constexpr int HF_THREADS = (2 * HB_CHUNKS + 1) * WAVE;
+
+// One group of hits, from the preparing waves.
+struct HitGroup {
+    uint32_t H, base, off;   // hits; chunk k of the batch is base + byte k of off
+    uint32_t flags;          // 1: no group, the list is done, 2: first of its batch
+    int par, buf;            // buffers of its batch's records (of two, of three)
+};
+
+// What a wave of the evaluation tells the others about its 64 hits.
+struct HitFwdInfo {
+    uint32_t kept, kept0;   // hits processed, and those of its first lane's ray
+    uint32_t bits;          // 1: first lane processed, 2: its last ray stopped, 4: one ray only
+};
+
+__global__ void __launch_bounds__(HF_THREADS)
+k_raster_a_fwd_hits(const DevView* __restrict__ views, int nv, RasterParams rp,
+                    const uint32_t* __restrict__ status, const uint32_t* __restrict__ worklist,
+                    const uint2* __restrict__ ranges, const uint32_t* __restrict__ pvals,
+                    const uint64_t* __restrict__ pmask, const uint64_t* __restrict__ psum,
+                    const CRec* __restrict__ crec, float* __restrict__ A,
+                    float* __restrict__ tau, uint32_t* __restrict__ nlast)
+{
+    constexpr int NB = HB_CHUNKS, HRS = HB_RAY_SHIFT;
+    static_assert(NB <= 4 * ((int)HIT_HEADER_UNITS - 1), "chunk ids of a stored-hit record");
+    __shared__ float4 s_q[2][NB][WAVE];
+    __shared__ float2 s_w[2][NB][WAVE];       // conic c and extinction
+    __shared__ uint32_t s_rec[3][NB][WAVE];   // record of each entry
+    __shared__ double s_A[NB][WAVE + 1];      // per-entry sums
+    __shared__ uint32_t s_cnt[NB][WAVE];      // hits per chunk and ray
+    __shared__ uint16_t s_hit[2][GROUP_HITS]; // (ray, chunk, entry) packed, ray-major
+    __shared__ uint32_t s_o[2][WAVE];         // per ray: its first hit in s_hit
+    __shared__ HitGroup s_group[2];
+    // per ray: optical depth, transmittance, last list position used
+    struct alignas(16) RayF { float t, T; uint32_t last, pad; };
+    __shared__ RayF s_ray[WAVE];
+    __shared__ float s_tail[NB];              // sum of the last ray's hits in each wave's round
+    __shared__ HitFwdInfo s_info[NB];
+    __shared__ uint4 s_out[GROUP_HITS / 8];   // the group's processed hits, in order
+    const uint32_t ntiles = status[ST_WORK_TILES];
+    if (blockIdx.x >= ntiles || ntiles > HF_TILES) return;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+    const int w = wave & (NB - 1);
+    const int64_t bucket = worklist[blockIdx.x];
+    const TileCell tc = tile_cell(views, nv, bucket, true);
+    const DevView& V = views[tc.v];
+    const uint2 rg = ranges[bucket];
+    if (wave < NB) s_A[w][lane] = 0.0;
+    if (wave == 0) s_ray[lane] = RayF{0.0f, 1.0f, 0u, 0u};
+    __syncthreads();
+    // Every wave meets the same barriers: three per 256 hits of a group, at
+    // least three per group, and three before the first.
+    auto rounds = [](uint32_t H) { return max(1u, (H + NB * WAVE - 1) / (NB * WAVE)); };
+
+    if (wave < NB) {   // ---- the next group
+        const TransposeLane tl = transpose_lane();
+        const uint32_t c_first = rg.x / WAVE, c_end = (rg.y + WAVE - 1) / WAVE;
+        bool alive = tc.inside;
+        uint64_t live = __ballot(alive);
+        // a batch: up to NB chunks whose footprint summary meets a ray in
+        // play, from one group of 64 chunks (loads are unconditional, so that
+        // waiting for one waits for no other)
+        struct Batch {
+            uint32_t base, off;
+            int nb;
+            __device__ uint32_t chunk(int k) const { return base + ((off >> (8 * k)) & 0xFFu); }
+        };
+        uint32_t g0 = c_first;
+        auto summary = [&](uint32_t g) { return psum[min(g + lane, c_end - 1u)]; };
+        auto meets = [&](uint64_t sm) {
+            return __ballot(g0 + lane < c_end && (sm & live) != 0ull);
+        };
+        uint64_t ahead = summary(g0);
+        uint64_t todo = meets(ahead);
+        ahead = summary(g0 + WAVE);
+        auto next = [&]() {
+            while (todo == 0ull && g0 + WAVE < c_end) {
+                g0 += WAVE;
+                todo = meets(ahead);
+                ahead = summary(g0 + WAVE);
+            }
+            Batch b{g0, 0u, 0};
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (todo != 0ull) {
+                    b.off |= (uint32_t)__builtin_ctzll(todo) << (8 * k);
+                    todo &= todo - 1ull;
+                    b.nb = k + 1;
+                }
+            return b;
+        };
+        // the wave's chunk of a batch: cells covered and record of the lane's entry
+        struct Entry {
+            uint64_t m;
+            uint32_t rec;
+            bool in;
+            __device__ uint64_t cells() const { return in ? m : 0ull; }
+        };
+        auto fetch = [&](const Batch& b) {
+            const uint32_t e = b.chunk(w) * WAVE + lane;
+            const bool in = w < b.nb && e >= rg.x && e < rg.y;
+            const uint32_t at = in ? e : rg.x;
+            return Entry{pmask[at], pvals[at], in};
+        };
+        // (entries no ray in play needs read record 0, one shared line)
+        auto gather = [&](const Entry& e) {
+            return load_rec_pair(crec, (e.cells() & live) != 0ull ? e.rec : 0u);
+        };
+        Batch cur = next(), nx = next();
+        Entry e_cur = fetch(cur), e_nx = fetch(nx);
+        RecPair rec = gather(e_cur);
+        uint32_t N = 0u, done = 0u, idx = 0u;   // the ray's hits in the batch, those taken, and
+                                                // the index of the wave's next one
+        uint32_t half[2] = {0u, 0u};            // the wave's entries left that cover the ray
+        int par = 0, buf = 0;
+        uint32_t b_base = 0u, b_off = 0u;   // the batch's chunks
+        uint32_t n_batch = 0, n_extra = 0;   // work counters
+        uint32_t H = 0u;   // of the group being evaluated
+        for (int p = 1;; p ^= 1) {
+            // rays that reached tau_max drop their remaining hits
+            if (rp.shadowing && s_ray[lane].t >= rp.tau_max) {
+                alive = false;
+                done = N;
+                half[0] = half[1] = 0u;
+            }
+            live = __ballot(alive);
+            const bool fresh = __ballot(done != N) == 0ull;
+            const bool end = fresh && (cur.nb == 0 || live == 0ull);
+            const uint32_t base = cur.base, off = cur.off;
+            if (fresh && !end) {
+                if (n_batch > 0u) {
+                    par ^= 1;
+                    buf = buf == 2 ? 0 : buf + 1;
+                }
+                ++n_batch;
+                const Batch nn = next();
+                const Entry e_nn = fetch(nn);
+                const CRec own = own_rec(rec);
+                s_q[par][w][lane] = own.q;
+                s_w[par][w][lane] = make_float2(own.w.x, own.w.y);
+                s_rec[buf][w][lane] = e_cur.rec;
+                rec = gather(e_nx);
+                // lane = ray: the entries of the wave's chunk covering it
+                uint64_t col = transpose64(e_cur.cells(), tl);
+                if (!alive) col = 0ull;
+                s_cnt[w][lane] = (uint32_t)__popcll(col);
+                half[0] = (uint32_t)col;
+                half[1] = (uint32_t)(col >> 32);
+                cur = nx;
+                nx = nn;
+                e_cur = e_nx;
+                e_nx = e_nn;
+            } else {
+                n_extra += end ? 0u : 1u;
+            }
+            __syncthreads();
+            HitGroup g{0u, 0u, 0u, 1u, par, buf};
+            if (!end) {
+                if (fresh) {
+                    N = done = idx = 0u;
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) {
+                        const uint32_t c = s_cnt[k][lane];
+                        if (k < w) idx += c;
+                        N += c;
+                    }
+                    b_base = base;
+                    b_off = off;
+                }
+                // all hits that are left when they are few, else each ray's
+                // next GROUP_RAY (both scanned together: at most 64 x 256 and
+                // 64 x GROUP_RAY, two to a word)
+                const uint32_t left = N - done, lim = min(left, GROUP_RAY);
+                const uint32_t both = left | (lim << 16);
+                const uint32_t ex = wave_excl_scan_u32(both);
+                const uint32_t tot =
+                    (uint32_t)__builtin_amdgcn_readlane((int)(ex + both), WAVE - 1);
+                const bool few = (tot & 0xFFFFu) <= GROUP_HITS / 2;
+                const uint32_t o = few ? (ex & 0xFFFFu) : (ex >> 16);
+                const uint32_t to = done + (few ? left : lim);
+                g = HitGroup{few ? (tot & 0xFFFFu) : (tot >> 16), b_base, b_off, fresh ? 2u : 0u,
+                             par, buf};
+                if (w == 0) s_o[p ^ 1][lane] = o;
+                uint16_t* out = s_hit[p ^ 1] + o;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const uint32_t tag = (uint32_t)((lane << HRS) | (w << 6) | (q << 5));
+                    while (half[q] != 0u && idx < to) {
+                        const uint32_t j = (uint32_t)__builtin_ctz(half[q]);
+                        half[q] &= half[q] - 1u;
+                        out[idx - done] = (uint16_t)(tag | j);
+                        ++idx;
+                    }
+                }
+                done = to;
+            }
+            if (w == 0 && lane == 0) s_group[p ^ 1] = g;
+            __syncthreads();
+            __syncthreads();
+            for (uint32_t k = rounds(H); k > 1u; --k) {
+                __syncthreads();
+                __syncthreads();
+                __syncthreads();
+            }
+            if (end) break;
+            H = g.H;
+        }
+        if (rp.work && w == 0 && lane == 0) {
+            atomicMax(&rp.work[8], (unsigned long long)n_batch);
+            atomicAdd(&rp.work[10], (unsigned long long)n_extra);
+        }
+    } else if (wave < 2 * NB) {   // ---- the current group
+        const float x0 = (float)(tc.tx * TILE) + 0.5f, y0 = (float)(tc.ty * TILE) + 0.5f;
+        uint32_t n_iter = 0, n_hits = 0;   // work counters
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+        for (int p = 0;; p ^= 1) {
+            const HitGroup G = s_group[p];
+            if (G.flags & 1u) break;
+            uint32_t kept = 0u;   // hits of the group processed so far
+            for (uint32_t base = 0; base == 0u || base < G.H; base += NB * WAVE) {
+                const uint32_t b0 = base + (uint32_t)w * WAVE, L = b0 + lane;
+                n_iter += b0 < G.H ? 1u : 0u;
+                const bool valid = L < G.H;
+                const uint32_t hv = valid ? (uint32_t)s_hit[p][L] : 0u;
+                const int rr = (int)(hv >> HRS), k = (int)((hv >> 6) & (NB - 1u)),
+                          j = (int)(hv & 63u);
+                // ray state and entry record, read together (lanes past the
+                // last hit read entry 0 of ray 0 and ignore it)
+                const RayF rs = s_ray[rr];
+                const uint32_t ro = s_o[p][rr];
+                const float4 g = s_q[G.par][k][j];
+                const float2 g2 = s_w[G.par][k][j];
+                // the ray of the next hit, the next wave's first for lane 63
+                const int fol = L + 1u < G.H ? (int)((uint32_t)s_hit[p][L + 1u] >> HRS) : -1;
+                const int seg0 = valid ? max((int)ro - (int)b0, 0) : lane;
+                bool real = false;
+                float x = 0.0f, E = 1.0f;
+                if (valid) {
+                    const float dx = x0 + (float)(rr & (TILE - 1)) - g.x;
+                    const float dy = y0 + (float)(rr / TILE) - g.y;
+                    const float q = quadform(g, g2.x, dx, dy);
+                    if (q < rp.q_max) {
+                        real = true;
+                        x = g2.y * ((__expf(-0.5f * q) - rp.eps) * rp.inv1meps);
+                        E = __expf(-x);
+                    }
+                }
+                float incl = seg_incl_scan(x, lane == seg0);
+                if (lane == WAVE - 1) s_tail[w] = incl;
+                __syncthreads();
+                // the lanes whose ray began in a wave before
+                const bool crossed = valid && ro < b0;
+                {
+                    const uint32_t o0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)ro);
+                    float carry = 0.0f;
+                    for (int v = w - 1; v >= 0 && o0 < base + (uint32_t)(v + 1) * WAVE; --v)
+                        carry += s_tail[v];
+                    if (crossed) incl += carry;
+                }
+                const float excl = incl - x;
+                const float tr = valid ? rs.t : 0.0f;
+                const float Tr = valid ? rs.T : 1.0f;
+                // a ray's hits are processed up to the first one reached with
+                // an optical depth of tau_max (a prefix of its segment)
+                const uint64_t stop = __ballot(valid && rp.shadowing && !(tr + excl < rp.tau_max));
+                const uint64_t after = stop & (~0ull << seg0);
+                bool proc = valid && (after == 0ull || lane < __builtin_ctzll(after));
+                {
+                    const uint64_t kb = __ballot(proc), cr = __ballot(crossed);
+                    const int s63 = __builtin_amdgcn_readlane(seg0, WAVE - 1);
+                    if (lane == 0)
+                        s_info[w] = HitFwdInfo{(uint32_t)__popcll(kb), (uint32_t)__popcll(kb & cr),
+                                               (uint32_t)(kb & 1ull) |
+                                                   ((stop & (~0ull << s63)) != 0ull ? 2u : 0u) |
+                                                   (cr == ~0ull ? 4u : 0u)};
+                }
+                __syncthreads();
+                // hits kept by the waves before, and whether the ray that
+                // crosses into this wave, or into the next, was stopped before
+                uint32_t at = kept;
+                bool dead = false, dead_in = false, next_first = false;
+#pragma unroll
+                for (int v = 0; v < NB; ++v) {
+                    const HitFwdInfo f = s_info[v];
+                    if (v == w) dead_in = dead;
+                    if (v == w + 1) next_first = !dead && (f.bits & 1u) != 0u;
+                    const uint32_t n = f.kept - (dead ? f.kept0 : 0u);
+                    if (v < w) at += n;
+                    kept += n;
+                    dead = (f.bits & 2u) != 0u || (dead && (f.bits & 4u) != 0u);
+                }
+                if (crossed && dead_in) proc = false;
+                {
+                    const uint64_t kb = __ballot(proc);
+                    if (proc)
+                        reinterpret_cast<uint16_t*>(s_out)[at + lanes_below(kb)] = (uint16_t)hv;
+                }
+                if (proc && real) {
+                    // at least FLT_MIN, so that A > 0 marks exactly the
+                    // records some ray used (the exact alpha T is > 0 for
+                    // every footprint hit)
+                    const float a = fmaxf(
+                        (1.0f - E) * (rp.shadowing ? Tr * __expf(-excl) : 1.0f), FLT_MIN);
+                    atomicAdd(&s_A[k][j], (double)a);
+                }
+                n_hits += (uint32_t)__popcll(__ballot(proc && real));
+                // the last processed hit of each ray updates the ray; a ray
+                // stopped in front of a further hit of its own is done, also
+                // where its sum rounds to just below tau_max
+                const int nxt = from_lane_above(proc ? rr : -1);
+                const bool own_next = fol == rr;
+                const bool goes_on = lane == WAVE - 1 ? own_next && next_first : nxt == rr;
+                if (proc && !goes_on) {
+                    float tn = tr + incl;
+                    if (own_next && rp.shadowing && (lane < WAVE - 1 || w < NB - 1))
+                        tn = fmaxf(tn, rp.tau_max);
+                    const uint32_t chunk = G.base + ((G.off >> (8 * k)) & 0xFFu);
+                    s_ray[rr] = RayF{tn, rp.shadowing ? Tr * __expf(-incl) : Tr,
+                                     chunk * WAVE + (uint32_t)j - rg.x + 1u, 0u};
+                }
+                __syncthreads();
+            }
+        }
+        if (rp.work && lane == 0) {
+            atomicAdd(&rp.work[4], (unsigned long long)n_iter);
+            atomicAdd(&rp.work[0], (unsigned long long)n_hits);
+        }
+    } else {   // ---- what the group before leaves to store
+        // this tile's chain of records (h_on while the stream has room; h_prev
+        // becomes HIT_OVERFLOW when it runs out), the block of the stream the
+        // tile writes into [h_top, h_end) and the block size it takes next
+        bool h_on = true;
+        uint32_t h_top = 0u, h_end = 0u, h_blk = 128u, h_prev = HIT_NONE, h_prev2 = HIT_NONE;
+        uint32_t h_sub = blockIdx.x % rp.hit_subs;   // part of the stream
+        HitGroup G{0u, 0u, 0u, 1u, 0, 0};
+        uint32_t kept = 0u;   // hits of it processed
+        bool fresh = true;    // no record of its batch is stored yet
+        auto store_hits = [&]() {
+            if (G.flags & 1u) return;
+            if (G.flags & 2u) fresh = true;
+            if (h_on && kept > 0u) {
+                // room for the group's record; a new block when the tile's is
+                // short (sizes doubling up to 16 KB, so short tiles waste
+                // little and long ones seldom ask), from the tile's part of
+                // the stream or one of the next ones (never an earlier one: a
+                // tile's records lie in increasing order)
+                const uint32_t words = (kept + 7u) / 8u, units = HIT_HEADER_UNITS + words;
+                if (h_end - h_top < units) {
+                    const uint32_t take = max(units, h_blk);
+                    h_blk = min(2u * h_blk, 1024u);
+                    h_on = false;
+                    for (int k = 0; k < HIT_TRIES && h_sub < rp.hit_subs; ++k, ++h_sub) {
+                        unsigned long long at = 0ull;
+                        if (lane == 0)
+                            at = atomicAdd(&rp.hit_tops[h_sub * HIT_TOP_STRIDE],
+                                           (unsigned long long)take);
+                        at = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
+                                  (int)(uint32_t)(at >> 32)) << 32) |
+                             (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+                        if (at + take <= rp.hit_sub_cap) {
+                            h_on = true;
+                            h_top = h_sub * rp.hit_sub_cap + (uint32_t)at;
+                            h_end = h_top + take;
+                            break;
+                        }
+                    }
+                    if (!h_on) h_prev = HIT_OVERFLOW;
+                }
+                if (h_on) {
+                    uint4* to = rp.hits + h_top;
+                    for (uint32_t i = lane; i < words; i += WAVE) to[HIT_HEADER_UNITS + i] = s_out[i];
+                    if (lane == 0) to[0] = make_uint4(h_prev, kept, fresh ? 1u : 0u, h_prev2);
+                    if (lane == 1)
+                        to[1] = make_uint4(G.base + (G.off & 0xFFu), G.base + ((G.off >> 8) & 0xFFu),
+                                           G.base + ((G.off >> 16) & 0xFFu), G.base + (G.off >> 24));
+                    h_prev2 = h_prev;
+                    h_prev = h_top;
+                    h_top += units;
+                }
+            }
+            if (kept > 0u) fresh = false;
+        };
+        auto store_sums = [&]() {
+            if (G.flags & 1u) return;
+            // (a nonzero sum means that a ray in play hit the entry)
+            double a[NB];
+            uint32_t r[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                a[k] = s_A[k][lane];
+                r[k] = s_rec[G.buf][k][lane];
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) s_A[k][lane] = 0.0;
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if ((float)a[k] != 0.0f) unsafeAtomicAdd(&A[r[k]], (float)a[k]);
+        };
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+        for (int p = 0;; p ^= 1) {
+            const HitGroup next = s_group[p];
+            if (next.flags & 1u) break;
+            store_hits();
+            uint32_t n = 0u;
+            for (uint32_t k = rounds(next.H), k0 = k; k > 0u; --k) {
+                __syncthreads();
+                if (k == k0) store_sums();
+                __syncthreads();
+                bool dead = false;
+#pragma unroll
+                for (int v = 0; v < NB; ++v) {
+                    const HitFwdInfo f = s_info[v];
+                    n += f.kept - (dead ? f.kept0 : 0u);
+                    dead = (f.bits & 2u) != 0u || (dead && (f.bits & 4u) != 0u);
+                }
+                __syncthreads();
+            }
+            G = next;
+            kept = n;
+        }
+        store_hits();
+        store_sums();
+        const RayF rs = s_ray[lane];
+        if (lane == 0) rp.hit_tail[bucket] = h_prev;
+        if (tc.inside) {
+            const int64_t ray = V.ray_off + (int64_t)tc.row * V.Wc + tc.col;
+            tau[ray] = rs.t;
+            nlast[ray] = rs.last;
+        }
+        if (rp.work) {
+            const uint32_t used = wave_max_u32(rs.last);   // list prefix any ray used
+            const uint64_t stopped =
+                __ballot(tc.inside && rp.shadowing && rs.t >= rp.tau_max);
+            if (lane == 0) {
+                atomicAdd(&rp.work[7], (unsigned long long)used);
+                atomicAdd(&rp.work[12], (unsigned long long)__popcll(stopped));
+                atomicMax(&rp.work[13], (unsigned long long)used);
+            }
+        }
     }
 }
 
@@ -2265,9 +2738,18 @@ hipError_t launch_raster_a_fwd(const DevView* views, int nv, int64_t tiles_c,
                            dim3((unsigned)tiles_c), dim3(WAVE), 0, s, views, nv, rp, status,
                            worklist, ranges, pvals, pmask, psum, crec, A, tau, nlast);
     };
-    if (rp.ppos) run(std::true_type{}, std::false_type{});
-    else if (rp.hits) run(std::false_type{}, std::true_type{});
-    else run(std::false_type{}, std::false_type{});
+    if (rp.ppos) {
+        run(std::true_type{}, std::false_type{});
+    } else if (rp.hits) {
+        // (the number of tiles with lists is known on the device only)
+        hipLaunchKernelGGL(k_raster_a_fwd_hits,
+                           dim3((unsigned)std::min<int64_t>(tiles_c, HF_TILES)),
+                           dim3(HF_THREADS), 0, s, views, nv, rp, status, worklist, ranges, pvals,
+                           pmask, psum, crec, A, tau, nlast);
+        if (tiles_c > (int64_t)HF_TILES) run(std::false_type{}, std::true_type{});
+    } else {
+        run(std::false_type{}, std::false_type{});
+    }
     return hipGetLastError();
 }
 

@@ -291,3 +291,19 @@ def test_emission_of_many_records(cuda):
     for got in images[1:]:
         for a, b in zip(got, images[0]):
             assert elem_err(a, b) <= 1e-6
+
+
+@pytest.mark.parametrize("shadowing", [True, False], ids=["shadows", "none"])
+@pytest.mark.parametrize("tiles", [(38, 40), (32, 48), (39, 41)], ids=lambda t: str(t[0] * t[1]))
+def test_pass_a_by_number_of_tiles(cuda, tiles, shadowing):
+    """Pass A around the number of tiles that changes its form (1536), with
+    lists of a few entries to thousands, rays that stop early, and many hits
+    of one ray in a batch."""
+    from paper_2506_21633_amd import api
+    a, b = tiles
+    wide = (0.5, 0.8 * a, 0.8 * b / math.cos(math.radians(45.0)))
+    scene = spread_scene(a, 15000, wide, 0.15, 0.6)
+    scene.means[12000:] *= np.float32(0.03)                # a few crowded tiles
+    scene.ext[13500:] *= np.float32(0.01)                  # that rays see far into
+    check(scene, [grid_view(a, b)], cuda, api.RenderOptions(shadowing=shadowing),
+          shadowing=shadowing)
