@@ -1456,57 +1456,118 @@ k_raster_b_fwd(const DevView* __restrict__ views, int nv, RasterParams rp, int64
     }
 }
 
-// Deterministic pass B: one wave per imaging tile (bucket tiles_c + t) walks
-// its whole list, 64 entries at a time: lane = entry while the records load
-// and the footprint masks form, then lane = pixel adding the entries that
-// cover it in list order. Every pixel is written once, by a plain store on
-// the zeroed image, so repeated runs agree bit for bit.
-__global__ void __launch_bounds__(RASTER_THREADS)
-k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int64_t cap_c,
-                int64_t tiles_c, int64_t tiles_i, const uint2* __restrict__ ranges_i,
-                const uint32_t* __restrict__ pvals, const float4* __restrict__ iq,
-                const float2* __restrict__ iw, float* __restrict__ images)
-{
-    __shared__ float4 s_q[RASTER_WAVES][WAVE];
-    __shared__ float2 s_w[RASTER_WAVES][WAVE];
-    const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const TransposeLane tl = transpose_lane();
-    const int64_t t = (int64_t)blockIdx.x * RASTER_WAVES + w;
-    if (t >= tiles_i) return;
-    const uint2 rg = ranges_i[t];
-    if (rg.y <= rg.x) return;
-    const TileCell tc = tile_cell(views, nv, tiles_c + t, false);
-    const DevView& V = views[tc.v];
-    const float px = tc.col + 0.5f, py = tc.row + 0.5f;
+// Sum of the first cnt (up to 64) of a wave's records on the lane's pixel, for
+// the kernels where a workgroup has a tile of the image.
+struct TileSum {
     float acc = 0.0f;
-    for (uint32_t b0 = rg.x; b0 < rg.y; b0 += WAVE) {
-        const uint32_t e = b0 + lane;
+    unsigned long long n_iter = 0, n_hits = 0;   // work counters
+
+    __device__ __forceinline__ void add(const float4* q4, const float2* w2, uint32_t cnt,
+                                        const TileCell& tc, const RasterParams& rp,
+                                        const TransposeLane& tl)
+    {
+        const int lane = lane_id();
+        const float px = tc.col + 0.5f, py = tc.row + 0.5f;
         uint64_t m = 0ull;
-        if (e < rg.y) {
-            const uint32_t r = pvals[cap_c + e];
-            const float4 g = iq[r];
-            const float2 g2 = iw[r];
-            s_q[w][lane] = g;
-            s_w[w][lane] = g2;
+        if ((uint32_t)lane < cnt) {
+            const float4 g = q4[lane];
+            const float2 g2 = w2[lane];
             if (g2.y != 0.0f)   // zero intensity adds nothing
                 m = footprint_mask<false>(g.x, g.y, g.z, g.w, g2.x, rp.q_max, tc.tx, tc.ty);
         }
-        wave_lds_sync();
         // the transpose exchanges bits between lanes: every lane takes part,
         // pixels outside the image drop their column afterwards
         uint64_t col = transpose64(m, tl);
         if (!tc.inside) col = 0ull;
-        while (col != 0ull) {
-            const int j = __builtin_ctzll(col);
-            col &= col - 1ull;
-            const float4 g = s_q[w][j];
-            const float2 g2 = s_w[w][j];
-            const float q = quadform(g, g2.x, px - g.x, py - g.y);
-            if (q < rp.q_max) acc += (__expf(-0.5f * q) - rp.eps) * rp.inv1meps * g2.y;
+        while (__ballot(col != 0ull) != 0ull) {
+            ++n_iter;
+            if (col != 0ull) {
+                const int j = __builtin_ctzll(col);
+                col &= col - 1ull;
+                const float4 g = q4[j];
+                const float2 g2 = w2[j];
+                const float q = quadform(g, g2.x, px - g.x, py - g.y);
+                if (q < rp.q_max) {
+                    ++n_hits;
+                    acc += (__expf(-0.5f * q) - rp.eps) * rp.inv1meps * g2.y;
+                }
+            }
         }
+    }
+
+    __device__ __forceinline__ void count(const RasterParams& rp) const
+    {
+        if (!rp.work) return;
+        const unsigned long long hits = wave_sum_u64(n_hits);
+        if (lane_id() == 0) {
+            atomicAdd(&rp.work[6], n_iter);
+            atomicAdd(&rp.work[2], hits);
+        }
+    }
+};
+
+constexpr int BT_WAVES = 8;
+
+// The waves' sums in wave order, stored once per pixel.
+__device__ __forceinline__ void store_tile(float (*s_acc)[WAVE], int w, float acc,
+                                           const TileCell& tc, const DevView& V,
+                                           float* __restrict__ images)
+{
+    const int lane = lane_id();
+    s_acc[w][lane] = acc;
+    __syncthreads();
+    if (w != 0 || !tc.inside) return;
+    float sum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < BT_WAVES; ++k) sum += s_acc[k][lane];
+    images[V.img_off + (int64_t)tc.row * V.W + tc.col] = sum;
+}
+
+// Deterministic pass B: a workgroup per imaging tile (bucket tiles_c + t), its
+// list in equal runs of whole chunks over the waves, which take 64 entries at
+// a time: lane = entry while the records load and the footprint masks form,
+// then lane = pixel adding the entries that cover it in list order. Every
+// pixel is written once, by a plain store on the zeroed image, from the
+// waves' sums in their order, so repeated runs agree bit for bit. Bound by
+// the longest list's chain of chunks (a wave per tile took 183 us for 24 views
+// of 60k Gaussians).
+__global__ void __launch_bounds__(BT_WAVES * WAVE)
+k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int64_t cap_c,
+                int64_t tiles_c, const uint2* __restrict__ ranges_i,
+                const uint32_t* __restrict__ pvals, const float4* __restrict__ iq,
+                const float2* __restrict__ iw, float* __restrict__ images)
+{
+    __shared__ float4 s_q[BT_WAVES][WAVE];
+    __shared__ float2 s_w[BT_WAVES][WAVE];
+    __shared__ float s_acc[BT_WAVES][WAVE];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), lane = lane_id();
+    const uint2 rg = ranges_i[blockIdx.x];
+    if (rg.y <= rg.x) return;
+    const TransposeLane tl = transpose_lane();
+    const TileCell tc = tile_cell(views, nv, tiles_c + blockIdx.x, false);
+    const DevView& V = views[tc.v];
+    const uint32_t chunks = (rg.y - rg.x + WAVE - 1) / WAVE;
+    const uint32_t per = (chunks + BT_WAVES - 1) / BT_WAVES;
+    const uint32_t e0 = min(rg.y, rg.x + (uint32_t)w * per * WAVE);
+    const uint32_t e1 = min(rg.y, e0 + per * WAVE);
+    TileSum sum;
+    // records one chunk ahead, their ids two
+    auto id = [&](uint32_t b) { return b + lane < e1 ? pvals[cap_c + b + lane] : 0u; };
+    uint32_t r_n = id(e0);
+    float4 g_n = iq[r_n];
+    float2 g2_n = iw[r_n];
+    r_n = id(e0 + WAVE);
+    for (uint32_t b = e0; b < e1; b += WAVE) {
+        s_q[w][lane] = g_n;
+        s_w[w][lane] = g2_n;
+        g_n = iq[r_n];
+        g2_n = iw[r_n];
+        r_n = id(b + 2 * WAVE);
+        wave_lds_sync();
+        sum.add(s_q[w], s_w[w], min(e1 - b, (uint32_t)WAVE), tc, rp, tl);
         wave_lds_sync();
     }
-    if (tc.inside) images[V.img_off + (int64_t)tc.row * V.W + tc.col] = acc;
+    store_tile(s_acc, w, sum.acc, tc, V, images);
 }
 
 // Pass B without lists, for few records per tile: a workgroup takes a tile
@@ -1517,54 +1578,47 @@ k_raster_b_tile(const DevView* __restrict__ views, int nv, RasterParams rp, int6
 // the place of the scan, the emission, the sort (3 to 6 launches), the
 // zeroing and the tile sums, which were bound by their launches. Also counts
 // the pairs the lists would have (for the overflow flag).
-constexpr int BD_WAVES = 8;
-
-__global__ void __launch_bounds__(BD_WAVES * WAVE)
+__global__ void __launch_bounds__(BT_WAVES * WAVE)
 k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, int64_t tiles_c,
                   int64_t cap_i, const uint32_t* __restrict__ bsum, int64_t nbsum,
                   uint32_t* __restrict__ status, const uint2* __restrict__ rect,
                   const float4* __restrict__ iq, const float2* __restrict__ iw,
                   float* __restrict__ images)
 {
-    __shared__ float4 s_q[BD_WAVES][2 * WAVE];
-    __shared__ float2 s_w[BD_WAVES][2 * WAVE];
-    __shared__ float s_acc[BD_WAVES][WAVE];
+    __shared__ float4 s_q[BT_WAVES][2 * WAVE];
+    __shared__ float2 s_w[BT_WAVES][2 * WAVE];
+    __shared__ float s_acc[BT_WAVES][WAVE];
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), lane = lane_id();
     const TransposeLane tl = transpose_lane();
     const TileCell tc = tile_cell(views, nv, tiles_c + blockIdx.x, false);
     const DevView& V = views[tc.v];
     const int64_t rec0 = V.rec_off;
-    const int n = V.n, chunks = (n + WAVE - 1) / WAVE, per = (chunks + BD_WAVES - 1) / BD_WAVES;
+    const int n = V.n, chunks = (n + WAVE - 1) / WAVE, per = (chunks + BT_WAVES - 1) / BT_WAVES;
     const int c0 = w * per, c1 = min(chunks, c0 + per);
     const uint32_t tx = (uint32_t)tc.tx, ty = (uint32_t)tc.ty;
-    const float px = tc.col + 0.5f, py = tc.row + 0.5f;
-    float acc = 0.0f;
-    unsigned long long n_iter = 0, n_hits = 0;   // work counters
-    // the first cnt (up to 64) records kept
-    auto add = [&](uint32_t cnt) {
-        uint64_t m = 0ull;
-        if ((uint32_t)lane < cnt) {
-            const float4 g = s_q[w][lane];
-            m = footprint_mask<false>(g.x, g.y, g.z, g.w, s_w[w][lane].x, rp.q_max, tc.tx, tc.ty);
-        }
-        uint64_t col = transpose64(m, tl);
-        if (!tc.inside) col = 0ull;
-        while (__ballot(col != 0ull) != 0ull) {
-            ++n_iter;
-            if (col != 0ull) {
-                const int j = __builtin_ctzll(col);
-                col &= col - 1ull;
-                const float4 g = s_q[w][j];
-                const float2 g2 = s_w[w][j];
-                const float q = quadform(g, g2.x, px - g.x, py - g.y);
-                if (q < rp.q_max) {
-                    ++n_hits;
-                    acc += (__expf(-0.5f * q) - rp.eps) * rp.inv1meps * g2.y;
-                }
-            }
-        }
-    };
+    TileSum sum;
     uint32_t kept = 0u;
+    auto put = [&](const float4& g, const float2& g2) {
+        const bool hit = g2.y != 0.0f;   // zero intensity adds nothing
+        const uint64_t m = __ballot(hit);
+        if (m == 0ull) return;
+        if (hit) {
+            const uint32_t at = kept + lanes_below(m);
+            s_q[w][at] = g;
+            s_w[w][at] = g2;
+        }
+        kept += (uint32_t)__popcll(m);
+        wave_lds_sync();
+        if (kept < WAVE) return;
+        sum.add(s_q[w], s_w[w], WAVE, tc, rp, tl);
+        kept -= WAVE;
+        wave_lds_sync();
+        if ((uint32_t)lane < kept) {
+            s_q[w][lane] = s_q[w][WAVE + lane];
+            s_w[w][lane] = s_w[w][WAVE + lane];
+        }
+        wave_lds_sync();
+    };
     constexpr int AHEAD = 4;   // chunks whose loads are in flight together
     for (int cb = c0; cb < c1; cb += AHEAD) {
         uint2 rc[AHEAD];
@@ -1585,39 +1639,13 @@ k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, in
                 g2[k] = iw[r];
             }
         }
-#pragma unroll
-        for (int k = 0; k < AHEAD; ++k) {
-            const bool hit = g2[k].y != 0.0f;   // zero intensity adds nothing
-            const uint64_t m = __ballot(hit);
-            if (m == 0ull) continue;
-            if (hit) {
-                const uint32_t at = kept + lanes_below(m);
-                s_q[w][at] = g[k];
-                s_w[w][at] = g2[k];
-            }
-            kept += (uint32_t)__popcll(m);
-            wave_lds_sync();
-            if (kept >= WAVE) {
-                add(WAVE);
-                kept -= WAVE;
-                wave_lds_sync();
-                if ((uint32_t)lane < kept) {
-                    s_q[w][lane] = s_q[w][WAVE + lane];
-                    s_w[w][lane] = s_w[w][WAVE + lane];
-                }
-                wave_lds_sync();
-            }
-        }
+        put(g[0], g2[0]);
+        put(g[1], g2[1]);
+        put(g[2], g2[2]);
+        put(g[3], g2[3]);
     }
-    if (kept) add(kept);
-    s_acc[w][lane] = acc;
-    __syncthreads();
-    if (w == 0 && tc.inside) {
-        float sum = 0.0f;
-#pragma unroll
-        for (int k = 0; k < BD_WAVES; ++k) sum += s_acc[k][lane];
-        images[V.img_off + (int64_t)tc.row * V.W + tc.col] = sum;
-    }
+    if (kept) sum.add(s_q[w], s_w[w], kept, tc, rp, tl);
+    store_tile(s_acc, w, sum.acc, tc, V, images);
     if (blockIdx.x == 0 && w == 1) {
         unsigned long long pairs = 0ull;
         for (int64_t k = lane; k < nbsum; k += WAVE) pairs += bsum[k];
@@ -1628,13 +1656,7 @@ k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, in
             status[ST_PAIRS_I] = over ? 0u : (uint32_t)pairs;
         }
     }
-    if (rp.work) {
-        n_hits = wave_sum_u64(n_hits);
-        if (lane == 0) {
-            atomicAdd(&rp.work[6], n_iter);
-            atomicAdd(&rp.work[2], n_hits);
-        }
-    }
+    sum.count(rp);
 }
 
 struct __attribute__((packed, aligned(4))) Float4Unaligned { float v[4]; };
@@ -2777,7 +2799,7 @@ hipError_t launch_raster_b_direct(const DevView* views, int nv, int64_t tiles_c,
                                   hipStream_t s)
 {
     if (tiles_i <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_raster_b_direct, dim3((unsigned)tiles_i), dim3(BD_WAVES * WAVE), 0, s,
+    hipLaunchKernelGGL(k_raster_b_direct, dim3((unsigned)tiles_i), dim3(BT_WAVES * WAVE), 0, s,
                        views, nv, rp, tiles_c, cap_i, bsum, (records + 255) / 256, status, rect,
                        iq, iw, images);
     return hipGetLastError();
@@ -2798,8 +2820,8 @@ hipError_t launch_raster_b_tiles(const DevView* views, int nv, int64_t pixels, i
     hipError_t e = launch_ranges_i(views, pkey + cap_c, status, cap_i, tiles_c, tiles_i, vm,
                                    ranges_i, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_raster_b_tile, dim3(raster_grid(tiles_i)), dim3(RASTER_THREADS), 0, s,
-                       views, nv, rp, cap_c, tiles_c, tiles_i, ranges_i, pvals, iq, iw, images);
+    hipLaunchKernelGGL(k_raster_b_tile, dim3((unsigned)tiles_i), dim3(BT_WAVES * WAVE), 0, s,
+                       views, nv, rp, cap_c, tiles_c, ranges_i, pvals, iq, iw, images);
     return hipGetLastError();
 }
 
