@@ -1598,7 +1598,7 @@ k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, in
     const uint32_t tx = (uint32_t)tc.tx, ty = (uint32_t)tc.ty;
     TileSum sum;
     uint32_t kept = 0u;
-    auto put = [&](const float4& g, const float2& g2) {
+    auto put = [&](float4 g, float2 g2) {
         const bool hit = g2.y != 0.0f;   // zero intensity adds nothing
         const uint64_t m = __ballot(hit);
         if (m == 0ull) return;
@@ -1632,6 +1632,7 @@ k_raster_b_direct(const DevView* __restrict__ views, int nv, RasterParams rp, in
 #pragma unroll
         for (int k = 0; k < AHEAD; ++k) {
             const int64_t r = rec0 + (cb + k) * WAVE + lane;
+            g[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             g2[k] = make_float2(0.0f, 0.0f);
             if (tx >= (rc[k].x & 0xFFFFu) && tx < rc[k].x >> 16 && ty >= (rc[k].y & 0xFFFFu) &&
                 ty < rc[k].y >> 16) {
