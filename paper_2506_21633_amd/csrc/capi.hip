@@ -627,8 +627,8 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
         // below reads one view's records at a time (the per-tile lists are
         // the same either way)
         if (P.seg)
-            SDGR_HIP(launch_seg_setup(b.views, P.nv, R, b.status + ST_RECORDS, false, &b.segt[0],
-                                      s));
+            SDGR_HIP(launch_seg_setup(b.views, P.nv, R, b.status + ST_RECORDS, R, 32, false,
+                                      false, &b.segt[0], s));
         SDGR_HIP(launch_radix_sort_u32(dk, dv, R, b.status + ST_RECORDS, 32, true, b.hist,
                                        &which, s, 0, P.seg ? &b.segt[0] : nullptr, P.nv,
                                        false));
@@ -648,8 +648,9 @@ int build_lists_c(const Problem& P, const sdgr_plan* plan, const Bufs& b, bool z
     {
         StageTimer t(SG_PAIR_SORT, s);
         if (P.seg)
-            SDGR_HIP(launch_seg_setup(b.views, P.nv, R, b.status + ST_PAIRS_C, true, &b.segt[1],
-                                      s, PAIR_SORT_BLOCKS));
+            SDGR_HIP(launch_seg_setup(b.views, P.nv, R, b.status + ST_PAIRS_C, plan->pairs_c,
+                                      bits_pairs_c(P), true, b.ppos[0] != nullptr, &b.segt[1], s,
+                                      PAIR_SORT_BLOCKS));
         uint32_t* pp[2] = {b.ppos[0], b.ppos[1]};
         SDGR_HIP(launch_radix_sort_u32(pk, pv, plan->pairs_c, b.status + ST_PAIRS_C,
                                        bits_pairs_c(P), false, b.hist, &pw, s, 0,

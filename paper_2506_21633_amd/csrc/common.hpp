@@ -444,9 +444,11 @@ hipError_t launch_radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], int64_t c
                                  unsigned max_blocks = MAX_SORT_BLOCKS);
 // Segment table of a segmented sort over the views: records (pairs = false)
 // or computation-plane pairs (pairs = true; seg[] as the emission wrote it),
-// n_dev items in all.
+// n_dev items (at most cap) in all, for a sort of `bits` key bits (positions:
+// one with vals2).
 hipError_t launch_seg_setup(const DevView* views, int nv, int64_t records, const uint32_t* n_dev,
-                            bool pairs, SegTable* segt, hipStream_t s,
+                            int64_t cap, int bits, bool pairs, bool positions, SegTable* segt,
+                            hipStream_t s,
                             unsigned max_blocks = MAX_SORT_BLOCKS);
 
 // Tile rectangles of the records in depth order, and the computation-plane

@@ -20,7 +20,8 @@
 //      ones) and the same sort groups them by tile, the order only fixing
 //      the FP32 summation order of pass B.
 //
-// Sort blocks work on runs of 4096-element tiles (256 threads x 16 items).
+// Sort blocks work on runs of tiles of 4096 items (256 threads x 16), or of
+// 2048 or 1024 where there are few.
 #include "common.hpp"
 
 #include <algorithm>
@@ -30,11 +31,12 @@ namespace sdgr {
 namespace {
 
 constexpr int SB = 256;          // threads per sort/scan block
-constexpr int SI = 16;           // items per thread
-constexpr int SN = SB * SI;      // items per block
+constexpr int SI_LARGE = 16;     // items per thread and tile
+constexpr int SI_MIDDLE = 8;
+constexpr int SI_SMALL = 4;
 constexpr int MAX_RADIX = 1 << 10;
 
-inline unsigned nblocks(int64_t n) { return (unsigned)((n + SN - 1) / SN); }
+inline unsigned nblocks(int64_t n, int sn) { return (unsigned)((n + sn - 1) / sn); }
 
 __global__ void __launch_bounds__(256) k_fill(uint32_t* p, uint32_t v, int64_t n)
 {
@@ -59,12 +61,28 @@ inline int digit_bits(int bits)
 }
 
 // Sort grids have at most max_blocks blocks; each takes a contiguous
-// run of 4096-item tiles of the actual item count, so the per-block digit
+// run of tiles of the actual item count, so the per-block digit
 // counts (digit-major, R x nb words) and their scan stay small however long
 // the array is.
-inline unsigned sort_grid(int64_t cap, unsigned max_blocks)
+inline unsigned sort_grid(int64_t cap, unsigned max_blocks, int sn)
 {
-    return std::min(nblocks(cap), max_blocks);
+    return std::min(nblocks(cap, sn), max_blocks);
+}
+
+// Items of a sort tile: small tiles where the large ones would be too few
+// blocks; only with 8-bit digits, whose counts fit the same space for four
+// times the blocks. The depth sort of 160k records takes 57 us with tiles of
+// 1024 items, 62 of 2048, 76 of 4096; of 500k 70, 67 and 79; of 640k 96, 83
+// and 87; of 1.6M 135, 110 and 104; the sort of 2.8M pairs with their
+// positions 43, 40 and 46.
+constexpr int64_t SORT_SMALL = int64_t(1) << 18, SORT_MIDDLE = int64_t(1) << 20,
+                  SORT_MIDDLE_PAIRS = int64_t(1) << 22;
+
+int sort_tile_items(int64_t cap, int bits, bool positions)
+{
+    if (digit_bits(bits) != 8) return SB * SI_LARGE;
+    if (cap <= SORT_SMALL) return SB * SI_SMALL;
+    return SB * (cap <= (positions ? SORT_MIDDLE_PAIRS : SORT_MIDDLE) ? SI_MIDDLE : SI_LARGE);
 }
 
 struct SortSpan {
@@ -73,11 +91,11 @@ struct SortSpan {
     uint32_t tpb;   // tiles per block
 };
 
-__device__ __forceinline__ SortSpan sort_span(const uint32_t* n_dev, uint32_t grid)
+__device__ __forceinline__ SortSpan sort_span(const uint32_t* n_dev, uint32_t grid, int sn)
 {
     SortSpan sp;
     sp.n = *n_dev;
-    const uint32_t tiles = (uint32_t)((sp.n + SN - 1) / SN);
+    const uint32_t tiles = (uint32_t)((sp.n + sn - 1) / sn);
     sp.tpb = max(1u, (tiles + grid - 1) / grid);
     sp.nb = (tiles + sp.tpb - 1) / sp.tpb;
     return sp;
@@ -92,9 +110,10 @@ struct BlockItems {
     int s;
 };
 
+template <int SN>
 __device__ __forceinline__ bool span_items(const uint32_t* n_dev, BlockItems& bi)
 {
-    const SortSpan sp = sort_span(n_dev, gridDim.x);
+    const SortSpan sp = sort_span(n_dev, gridDim.x, SN);
     if (blockIdx.x >= sp.nb) return false;
     bi.first = (int64_t)blockIdx.x * sp.tpb * SN;
     bi.end = sp.n;
@@ -107,6 +126,7 @@ __device__ __forceinline__ bool span_items(const uint32_t* n_dev, BlockItems& bi
 
 // Segment of block b: the last s with tp[s] <= b (empty segments own no
 // block, so the block lands in the non-empty one that follows them).
+template <int SN>
 __device__ __forceinline__ bool seg_items(const SegTable* t, int S, uint32_t* s_tp, BlockItems& bi)
 {
     for (int k = threadIdx.x; k <= S; k += blockDim.x) s_tp[k] = t->tp[k];
@@ -134,7 +154,7 @@ __device__ __forceinline__ bool seg_items(const SegTable* t, int S, uint32_t* s_
 // many tiles per block as keep the blocks near MAX_SORT_BLOCKS.
 __global__ void __launch_bounds__(SEG_MAX)
 k_seg_setup(const DevView* __restrict__ views, int nv, int64_t records,
-            const uint32_t* __restrict__ n_dev, int pairs, uint32_t max_blocks,
+            const uint32_t* __restrict__ n_dev, int pairs, uint32_t max_blocks, uint32_t sn,
             SegTable* __restrict__ t)
 {
     __shared__ uint32_t s_seg[SEG_MAX + 1];
@@ -162,7 +182,7 @@ k_seg_setup(const DevView* __restrict__ views, int nv, int64_t records,
     }
     __syncthreads();
     const uint32_t len = tid < nv ? s_seg[tid + 1] - s_seg[tid] : 0u;
-    const uint32_t tiles = (len + SN - 1) / SN;
+    const uint32_t tiles = (len + sn - 1) / sn;
     uint32_t all_tiles, total;
     (void)block_excl_scan_256(tiles, s_w, all_tiles);
     const uint32_t tpb = max(1u, (all_tiles + max_blocks - 1) / max_blocks);
@@ -184,19 +204,19 @@ k_seg_setup(const DevView* __restrict__ views, int nv, int64_t records,
 // (Grouping a wave's lanes by digit first, with a ballot match over the
 // digit bits, was slower for every key set here, the pair keys of a few busy
 // tiles included.)
-template <int BITS, bool SEG>
+template <int BITS, bool SEG, int SI>
 __global__ void __launch_bounds__(SB)
 k_radix_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ n_dev, int shift,
              uint32_t* __restrict__ hist, const SegTable* __restrict__ segt, int S)
 {
-    constexpr int R = 1 << BITS;
+    constexpr int R = 1 << BITS, SN = SB * SI;
     __shared__ uint32_t h[R];
     __shared__ uint32_t s_tp[SEG ? SEG_MAX + 1 : 1];
     BlockItems bi;
     if constexpr (SEG) {
-        if (!seg_items(segt, S, s_tp, bi)) return;
+        if (!seg_items<SN>(segt, S, s_tp, bi)) return;
     } else {
-        if (!span_items(n_dev, bi)) return;
+        if (!span_items<SN>(n_dev, bi)) return;
     }
     const int tid = threadIdx.x;
 #pragma unroll
@@ -228,14 +248,14 @@ k_radix_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ n_d
 // total to tot[d] (the scatter adds the prefix over digits).
 __global__ void __launch_bounds__(SB)
 k_radix_spine(uint32_t* __restrict__ hist, uint32_t* __restrict__ tot,
-              const uint32_t* __restrict__ n_dev, unsigned grid, const SegTable* __restrict__ segt,
-              int S)
+              const uint32_t* __restrict__ n_dev, unsigned grid, int sn,
+              const SegTable* __restrict__ segt, int S)
 {
     constexpr int PER = MAX_SORT_BLOCKS / SB;
     __shared__ uint32_t wtot[SB / WAVE];
     // a segmented sort's blocks (one tile each) may exceed MAX_SORT_BLOCKS:
     // the row is taken MAX_SORT_BLOCKS at a time with a running carry
-    const uint32_t nb = segt ? segt->tp[S] : sort_span(n_dev, grid).nb;
+    const uint32_t nb = segt ? segt->tp[S] : sort_span(n_dev, grid, sn).nb;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     uint32_t* row = hist + (int64_t)blockIdx.x * nb;
     uint32_t carry = 0u;
@@ -273,8 +293,8 @@ k_radix_spine(uint32_t* __restrict__ hist, uint32_t* __restrict__ tot,
     if (tid == 0) tot[blockIdx.x] = carry;
 }
 
-// Stable scatter, one 4096-item tile at a time over the block's tiles. Each
-// wave ranks its own 1024 consecutive items in 16 rounds of 64 (ballot
+// Stable scatter, one tile at a time over the block's tiles. Each wave ranks
+// its own quarter of consecutive items in SI rounds of 64 (ballot
 // match over the digit bits, per-wave digit counters in LDS, no block
 // barrier); the block then turns the per-wave counts into digit-major local
 // offsets, places the items in LDS in digit order and writes them out so
@@ -282,7 +302,7 @@ k_radix_spine(uint32_t* __restrict__ hist, uint32_t* __restrict__ tot,
 // position per digit carries over from tile to tile. With vin null the
 // values are the items' input positions. V2 moves a second value array
 // along (vin2 null: the input positions).
-template <int BITS, bool SEG, bool V2>
+template <int BITS, bool SEG, bool V2, int SI>
 __global__ void __launch_bounds__(SB)
 k_radix_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                 uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
@@ -291,7 +311,7 @@ k_radix_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
                 const SegTable* __restrict__ segt, int S,
                 const uint32_t* __restrict__ vin2, uint32_t* __restrict__ vout2)
 {
-    constexpr int R = 1 << BITS;
+    constexpr int R = 1 << BITS, SN = SB * SI;
     constexpr int NW = SB / WAVE;
     constexpr int DPT = R / SB;                  // digits per thread
     __shared__ uint32_t wc[NW][R];              // per-wave digit counters, then offsets
@@ -303,9 +323,9 @@ k_radix_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
     __shared__ uint32_t s_tp[SEG ? SEG_MAX + 1 : 1];
     BlockItems bi;
     if constexpr (SEG) {
-        if (!seg_items(segt, S, s_tp, bi)) return;
+        if (!seg_items<SN>(segt, S, s_tp, bi)) return;
     } else {
-        if (!span_items(n_dev, bi)) return;
+        if (!span_items<SN>(n_dev, bi)) return;
     }
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     const int64_t n = bi.end;
@@ -457,35 +477,35 @@ k_radix_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
 
 // Grid of a sort pass: a segmented sort's blocks take a run of tiles of
 // their segment, and every segment may end in a shorter block.
-inline unsigned pass_grid(int64_t cap, int S, bool seg, unsigned max_blocks)
+inline unsigned pass_grid(int64_t cap, int S, bool seg, unsigned max_blocks, int sn)
 {
-    return seg ? sort_grid(cap, max_blocks) + (unsigned)S : sort_grid(cap, max_blocks);
+    return sort_grid(cap, max_blocks, sn) + (seg ? (unsigned)S : 0u);
 }
 
-template <int BITS, bool SEG>
+template <int BITS, bool SEG, int SI>
 hipError_t radix_passes(uint32_t* keys[2], uint32_t* vals[2], int64_t cap, const uint32_t* n_dev,
                         int bits, bool iota_vals, uint32_t* hist, int* cur, hipStream_t s,
                         int shift0, const SegTable* segt, int S, bool keys_out,
                         uint32_t* const* vals2, unsigned max_blocks)
 {
     constexpr int R = 1 << BITS;
-    const unsigned grid = pass_grid(cap, S, SEG, max_blocks);
-    uint32_t* tot = hist + (int64_t)MAX_RADIX * grid;   // digit totals after the counts
+    const unsigned grid = pass_grid(cap, S, SEG, max_blocks, SB * SI);
+    uint32_t* tot = hist + (int64_t)R * grid;   // digit totals after the counts
     for (int shift = shift0; shift < shift0 + bits; shift += BITS) {
-        hipLaunchKernelGGL((k_radix_hist<BITS, SEG>), dim3(grid), dim3(SB), 0, s, keys[*cur],
+        hipLaunchKernelGGL((k_radix_hist<BITS, SEG, SI>), dim3(grid), dim3(SB), 0, s, keys[*cur],
                            n_dev, shift, hist, segt, S);
         hipLaunchKernelGGL(k_radix_spine, dim3(R), dim3(SB), 0, s, hist, tot, n_dev, grid,
-                           SEG ? segt : nullptr, S);
+                           SB * SI, SEG ? segt : nullptr, S);
         const uint32_t* vin = (iota_vals && shift == shift0) ? nullptr : vals[*cur];
         // the last pass writes no keys when the caller needs only the values
         uint32_t* kout = (keys_out || shift + BITS < shift0 + bits) ? keys[*cur ^ 1] : nullptr;
         if (vals2) {
             const uint32_t* vin2 = shift == shift0 ? nullptr : vals2[*cur];
-            hipLaunchKernelGGL((k_radix_scatter<BITS, SEG, true>), dim3(grid), dim3(SB), 0, s,
+            hipLaunchKernelGGL((k_radix_scatter<BITS, SEG, true, SI>), dim3(grid), dim3(SB), 0, s,
                                keys[*cur], vin, kout, vals[*cur ^ 1], n_dev, shift, hist, tot,
                                segt, S, vin2, vals2[*cur ^ 1]);
         } else {
-            hipLaunchKernelGGL((k_radix_scatter<BITS, SEG, false>), dim3(grid), dim3(SB), 0, s,
+            hipLaunchKernelGGL((k_radix_scatter<BITS, SEG, false, SI>), dim3(grid), dim3(SB), 0, s,
                                keys[*cur], vin, kout, vals[*cur ^ 1], n_dev, shift, hist, tot,
                                segt, S, nullptr, nullptr);
         }
@@ -502,14 +522,26 @@ hipError_t radix_sort_t(uint32_t* keys[2], uint32_t* vals[2], int64_t cap, const
 {
     switch (digit_bits(bits)) {
     case 8:
-        return radix_passes<8, SEG>(keys, vals, cap, n_dev, bits, iota_vals, hist, cur, s, shift0,
-                                    segt, S, keys_out, vals2, max_blocks);
+        switch (sort_tile_items(cap, bits, vals2 != nullptr)) {
+        case SB * SI_SMALL:
+            return radix_passes<8, SEG, SI_SMALL>(keys, vals, cap, n_dev, bits, iota_vals, hist,
+                                                  cur, s, shift0, segt, S, keys_out, vals2,
+                                                  max_blocks);
+        case SB * SI_MIDDLE:
+            return radix_passes<8, SEG, SI_MIDDLE>(keys, vals, cap, n_dev, bits, iota_vals, hist,
+                                                   cur, s, shift0, segt, S, keys_out, vals2,
+                                                   max_blocks);
+        default:
+            break;
+        }
+        return radix_passes<8, SEG, SI_LARGE>(keys, vals, cap, n_dev, bits, iota_vals, hist, cur,
+                                              s, shift0, segt, S, keys_out, vals2, max_blocks);
     case 9:
-        return radix_passes<9, SEG>(keys, vals, cap, n_dev, bits, iota_vals, hist, cur, s, shift0,
-                                    segt, S, keys_out, vals2, max_blocks);
+        return radix_passes<9, SEG, SI_LARGE>(keys, vals, cap, n_dev, bits, iota_vals, hist, cur,
+                                              s, shift0, segt, S, keys_out, vals2, max_blocks);
     default:
-        return radix_passes<10, SEG>(keys, vals, cap, n_dev, bits, iota_vals, hist, cur, s,
-                                     shift0, segt, S, keys_out, vals2, max_blocks);
+        return radix_passes<10, SEG, SI_LARGE>(keys, vals, cap, n_dev, bits, iota_vals, hist, cur,
+                                               s, shift0, segt, S, keys_out, vals2, max_blocks);
     }
 }
 
@@ -1536,7 +1568,7 @@ size_t radix_hist_words(int64_t cap)
 {
     // counts (up to one block per tile and a partial tile per segment),
     // digit totals
-    return (size_t)MAX_RADIX * (pass_grid(cap > 0 ? cap : 1, SEG_MAX, true, MAX_SORT_BLOCKS) + 1);
+    return (size_t)MAX_RADIX * (pass_grid(cap > 0 ? cap : 1, SEG_MAX, true, MAX_SORT_BLOCKS, SB * SI_LARGE) + 1);
 }
 
 int radix_passes_for(int bits)
@@ -1558,12 +1590,14 @@ hipError_t launch_radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], int64_t c
 }
 
 hipError_t launch_seg_setup(const DevView* views, int nv, int64_t records, const uint32_t* n_dev,
-                            bool pairs, SegTable* segt, hipStream_t s, unsigned max_blocks)
+                            int64_t cap, int bits, bool pairs, bool positions, SegTable* segt,
+                            hipStream_t s, unsigned max_blocks)
 {
     if (nv < 1 || nv > SEG_MAX) return hipErrorInvalidValue;
     if (max_blocks < SB || max_blocks > MAX_SORT_BLOCKS) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_seg_setup, dim3(1), dim3(SEG_MAX), 0, s, views, nv, records, n_dev,
-                       pairs ? 1 : 0, (uint32_t)max_blocks, segt);
+                       pairs ? 1 : 0, (uint32_t)max_blocks,
+                       (uint32_t)sort_tile_items(cap, bits, positions), segt);
     return hipGetLastError();
 }
 

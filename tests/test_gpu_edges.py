@@ -307,3 +307,11 @@ def test_pass_a_by_number_of_tiles(cuda, tiles, shadowing):
     scene.ext[13500:] *= np.float32(0.01)                  # that rays see far into
     check(scene, [grid_view(a, b)], cuda, api.RenderOptions(shadowing=shadowing),
           shadowing=shadowing)
+
+
+@pytest.mark.parametrize("n", [16500, 262144, 262145, 1048576, 1048577])
+def test_sort_tile_sizes(cuda, n):
+    """Record counts around the change of the sorts' tiles: depth order and
+    lists give the oracle's intensities."""
+    scene = spread_scene(n, n, (1.0, 6.0, 6.0), 0.02, 0.05)
+    check(scene, [grid_view(8, 8)], cuda, grads=False)
