@@ -200,17 +200,22 @@ k_seg_setup(const DevView* __restrict__ views, int nv, int64_t records,
     }
 }
 
-// Block digit histogram over the block's tiles, one LDS atomic per item.
-// (Grouping a wave's lanes by digit first, with a ballot match over the
-// digit bits, was slower for every key set here, the pair keys of a few busy
-// tiles included.)
+// Block digit histogram over the block's tiles, one LDS atomic per item, in
+// HIST_COPIES counters per digit picked by lane (the high digits of a depth
+// are few). Keys come four at a time. (Grouping a wave's lanes by digit first,
+// with a ballot match over the digit bits, was slower for every key set here,
+// the pair keys of a few busy tiles included.)
+constexpr int HIST_COPIES = 4;
+struct __attribute__((packed, aligned(4))) Key4 { uint32_t v[4]; };
+
 template <int BITS, bool SEG, int SI>
 __global__ void __launch_bounds__(SB)
 k_radix_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ n_dev, int shift,
              uint32_t* __restrict__ hist, const SegTable* __restrict__ segt, int S)
 {
     constexpr int R = 1 << BITS, SN = SB * SI;
-    __shared__ uint32_t h[R];
+    static_assert(SI % 4 == 0, "keys are loaded four at a time");
+    __shared__ uint32_t h[R * HIST_COPIES];
     __shared__ uint32_t s_tp[SEG ? SEG_MAX + 1 : 1];
     BlockItems bi;
     if constexpr (SEG) {
@@ -219,28 +224,36 @@ k_radix_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ n_d
         if (!span_items<SN>(n_dev, bi)) return;
     }
     const int tid = threadIdx.x;
-#pragma unroll
-    for (int d = tid; d < R; d += SB) h[d] = 0;
+    for (int d = tid; d < R * HIST_COPIES; d += SB) h[d] = 0;
     __syncthreads();
+    const uint32_t copy = (uint32_t)tid & (HIST_COPIES - 1);
+    auto count = [&](uint32_t key) {
+        atomicAdd(&h[(((key - bi.kb) >> shift) & (R - 1)) * HIST_COPIES + copy], 1u);
+    };
     const int64_t n = bi.end;
     for (uint32_t t = 0; t < bi.tiles; ++t) {
         const int64_t base = bi.first + (int64_t)t * SN;
         if (base >= n) break;
-        uint32_t key[SI];
+        if (base + SN <= n) {
+            Key4 key[SI / 4];
 #pragma unroll
-        for (int k = 0; k < SI; ++k) {
-            const int64_t idx = base + k * SB + tid;
-            key[k] = idx < n ? keys[idx] : 0u;
-        }
+            for (int k = 0; k < SI / 4; ++k)
+                key[k] = *reinterpret_cast<const Key4*>(keys + base + (k * SB + tid) * 4);
 #pragma unroll
-        for (int k = 0; k < SI; ++k) {
-            const int64_t idx = base + k * SB + tid;
-            if (idx < n) atomicAdd(&h[((key[k] - bi.kb) >> shift) & (R - 1)], 1u);
+            for (int k = 0; k < SI / 4; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) count(key[k].v[j]);
+        } else {
+            for (int64_t idx = base + tid; idx < n; idx += SB) count(keys[idx]);
         }
     }
     __syncthreads();
+    for (int d = tid; d < R; d += SB) {
+        uint32_t sum = 0u;
 #pragma unroll
-    for (int d = tid; d < R; d += SB) hist[(int64_t)d * bi.stride + blockIdx.x] = h[d];
+        for (int c = 0; c < HIST_COPIES; ++c) sum += h[d * HIST_COPIES + c];
+        hist[(int64_t)d * bi.stride + blockIdx.x] = sum;
+    }
 }
 
 // Spine of one pass: block d turns row d of the digit-major block counts
