@@ -353,7 +353,9 @@ struct Bufs {
     uint32_t* pkey[2] = {nullptr, nullptr};
     uint32_t* hist = nullptr;
     SegTable* segt = nullptr;       // [0] records, [1] computation-plane pairs
-    unsigned long long* slots = nullptr;   // spread pair-total accumulators
+    // 2 x TOTAL_SLOTS words: the views' pair totals of the small views' lists,
+    // and in the second half the stored-hit stream's counters (forward)
+    unsigned long long* slots = nullptr;
     // backward accumulators: 13 floats and one list slot per record
     float* grad_c = nullptr;
     float* grad_i = nullptr;
@@ -433,7 +435,6 @@ void layout(const Problem& P, int64_t cap_c, int64_t cap_i, Phase ph, char* stat
         if (P.hit_units > 0) {
             b.hits = a.take<uint4>(P.hit_units + 16);   // slack for the backward's part copies
             b.hit_tail = a.take<uint32_t>(P.tiles_c);
-            b.hit_tops = a.take<unsigned long long>(HIT_SUBS * HIT_TOP_STRIDE);
         }
     };
     auto transient = [&](Arena& a) {
@@ -453,6 +454,8 @@ void layout(const Problem& P, int64_t cap_c, int64_t cap_i, Phase ph, char* stat
         int64_t hw = (int64_t)std::max(radix_hist_words(R), radix_hist_words(K));
         b.hist = a.take<uint32_t>(hw);
         b.slots = a.take<unsigned long long>(2 * TOTAL_SLOTS);
+        b.hit_tops = b.slots ? b.slots + TOTAL_SLOTS : nullptr;
+        static_assert(HIT_SUBS * HIT_TOP_STRIDE <= TOTAL_SLOTS, "the second half of the slots");
         if (P.det) {
             b.part_a = a.take<float>(cap_c);
             b.ranges_i = a.take<uint2>(P.tiles_i);
