@@ -146,7 +146,7 @@ struct Problem {
 // forward's lists survive to the backward (not in recompute mode) and the
 // sums are unordered (not in deterministic mode, whose results must not
 // depend on which tiles found room). The default holds 8 bytes per
-// computation-plane pair plus 16 MiB (a used hit takes 8 bytes, and rays
+// computation-plane pair plus 16 MiB, room for about four hits a pair (rays
 // stop long before using every pair in their tile); a tile that finds the
 // stream full has its backward re-derive the hits from the footprint masks.
 int64_t hit_units_for(const Problem& P, int64_t pairs_c, int64_t hit_bytes)

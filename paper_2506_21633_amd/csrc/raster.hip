@@ -2,17 +2,19 @@
 // scattering intensity and imaging; Sec. II-B, their gradients).
 //
 // Computation plane (order matters: front-to-back along each ray)
-//   One wave64 (a workgroup of its own) owns one 8x8 tile: lane l handles ray
-//   (l % 8, l / 8); only non-empty tiles run, longest lists first. Every
+//   One wave64 owns one 8x8 tile, or a workgroup does where few tiles would
+//   leave the device idle: lane l handles ray (l % 8, l / 8); only non-empty
+//   tiles run, longest lists first. Every
 //   (tile, Gaussian) pair carries a 64-bit mask of the tile cells inside the
 //   footprint ellipse, and every 64 consecutive pairs of the sorted array (a
 //   chunk) the OR of their masks (k_pair_masks). The tile's depth-sorted list
 //   is walked chunk by chunk: chunks whose summary misses every ray still in
-//   play are skipped unread, the next chunk's masks are prefetched, and in a
-//   chunk that is read the 64 masks are bit-transposed so that each lane
-//   iterates only over the entries covering its own cell.
+//   play are skipped unread, the next chunks' masks are prefetched, and in
+//   those that are read the 64 masks are bit-transposed (lane = ray: which
+//   entries cover my cell) and the hits compacted, so that lane = hit.
 //   pass A forward : alpha = 1 - exp(-kappa f), A_i += alpha T, T *= exp(-kappa f);
-//                    per-entry sums in LDS (float atomics), one global atomic
+//                    per-entry sums in LDS (FP64 atomics: one takes 8 to 27
+//                    cycles for a wave, an FP32 one 192), one global atomic
 //                    per (tile, Gaussian); a ray leaves after its optical
 //                    depth reaches tau_max.
 //   pass A backward: back to front from each ray's last contributing entry:
@@ -24,7 +26,8 @@
 //                    tile's list is); footprint masks computed on the fly
 //                    and bit-transposed, so lane = pixel sums only the
 //                    entries covering it; partial pixel sums are added to
-//                    the image at tile boundaries.
+//                    the image at tile boundaries. Small calls and the
+//                    deterministic mode: a workgroup per tile.
 //   pass B backward: one thread per record walks its footprint ellipse and
 //                    gathers dL/dS (no atomics).
 #include <algorithm>
@@ -460,9 +463,10 @@ k_pair_masks(const DevView* __restrict__ views, int nv, int64_t cap, RasterParam
 // tile's 64 cells. The list is walked in 64-entry chunks aligned to the
 // global pair array; a chunk whose footprint summary misses every ray still
 // in play is skipped without reading its entries. Chunks that are read are
-// taken A_BATCH at a time: their masks are loaded together, then the
-// records of the entries any live ray needs are gathered together, so a
-// batch pays two memory latencies. Inside a chunk the 64x64 bit matrix of
+// taken in batches (of HB_CHUNKS where the hits are stored, else twice
+// A_BATCH): their masks are loaded together, then the records of the entries
+// any live ray needs are gathered together, so a batch pays two memory
+// latencies. Inside a chunk the 64x64 bit matrix of
 // footprint masks is transposed (lane = ray: which entries cover my cell),
 // the (ray, entry) hits are compacted ray-major into LDS, and the wave
 // takes them 64 at a time, lane = hit: each ray's optical depth in front of
@@ -508,10 +512,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     static_assert(!HITS || NB <= 4 * ((int)HIT_HEADER_UNITS - 1), "chunk ids of a stored-hit record");
     __shared__ float4 s_q[NB][WAVE];
     __shared__ float s_wc[NB][WAVE], s_wk[NB][WAVE];   // conic c and extinction
-    // per-entry sums in GC copies picked by ray (as in the backward; one
-    // atomic per hit conflicts little enough that one copy is fastest here)
-    constexpr int GC = 1;
-    __shared__ double s_A[GC][NB][WAVE + 1];
+    __shared__ double s_A[NB][WAVE + 1];      // per-entry sums
     __shared__ uint32_t s_chk[NB];
     constexpr uint32_t GROUP_MAX = HITS ? GROUP_HITS : WAVE * WAVE;
     __shared__ uint16_t s_hit[GROUP_MAX];     // (ray, chunk, entry) packed, ray-major
@@ -529,9 +530,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     const float x0 = (float)(tc.tx * TILE) + 0.5f, y0 = (float)(tc.ty * TILE) + 0.5f;
     const uint2 rg = ranges[bucket];
 #pragma unroll
-    for (int g = 0; g < GC; ++g)
-#pragma unroll
-        for (int k = 0; k < NB; ++k) s_A[g][k][lane] = 0.0;
+    for (int k = 0; k < NB; ++k) s_A[k][lane] = 0.0;
     float T = 1.0f, t = 0.0f;
     bool alive = tc.inside;
     uint32_t last = 0;
@@ -556,16 +555,9 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     auto flush = [&]() {
         float a[NB];
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            double sum = 0.0;
+        for (int k = 0; k < NB; ++k) a[k] = (float)s_A[k][lane];
 #pragma unroll
-            for (int g = 0; g < GC; ++g) sum += s_A[g][k][lane];
-            a[k] = (float)sum;
-        }
-#pragma unroll
-        for (int k = 0; k < NB; ++k)
-#pragma unroll
-            for (int g = 0; g < GC; ++g) s_A[g][k][lane] = 0.0;
+        for (int k = 0; k < NB; ++k) s_A[k][lane] = 0.0;
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             if (a[k] != 0.0f) {
@@ -673,7 +665,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                     for (int k = 0; k < NB; ++k) nr += (uint32_t)__popcll(col[k]);
                     if (__ballot(nr != 0u) == 0ull) break;
                     // hits left and hits of a limited group, scanned together
-                    // (at most 64 x 512 and 64 x GROUP_RAY: two to a word)
+                    // (at most 64 x 256 and 64 x GROUP_RAY: two to a word)
                     const uint32_t lim = min(nr, GROUP_RAY);
                     const uint32_t both = nr | (lim << 16);
                     const uint32_t ex = wave_excl_scan_u32(both);
@@ -805,7 +797,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                         // for every footprint hit)
                         const float a = fmaxf(
                             (1.0f - E) * (rp.shadowing ? Tr * __expf(-excl) : 1.0f), FLT_MIN);
-                        atomicAdd(&s_A[(rr + (rr >> 3)) & (GC - 1)][k][j], (double)a);
+                        atomicAdd(&s_A[k][j], (double)a);
                     }
                     n_hits += (uint32_t)__popcll(__ballot(proc && real));
                     // the last processed hit of each ray in this round updates the ray
@@ -2117,7 +2109,7 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
                     if (__ballot(nr != 0u) == 0ull) break;
                     n_extra += more ? 1u : 0u;
                     // hits left and hits of a limited group, scanned together
-                    // (at most 64 x 512 and 64 x BG_RAY: two to a word)
+                    // (at most 64 x 256 and 64 x BG_RAY: two to a word)
                     const uint32_t lim = min(nr, BG_RAY);
                     const uint32_t both = nr | (lim << 16);
                     const uint32_t excl = wave_excl_scan_u32(both);

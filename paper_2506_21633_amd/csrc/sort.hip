@@ -20,6 +20,9 @@
 //      ones) and the same sort groups them by tile, the order only fixing
 //      the FP32 summation order of pass B.
 //
+// Small views get their lists without the sorts (k_view_rank, k_view_counts,
+// k_tile_lists), and small calls no imaging-plane lists at all.
+//
 // Sort blocks work on runs of tiles of 4096 items (256 threads x 16), or of
 // 2048 or 1024 where there are few.
 #include "common.hpp"
