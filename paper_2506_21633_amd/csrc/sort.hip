@@ -1149,6 +1149,107 @@ k_emit_i(const DevView* __restrict__ views, int nv, int64_t records,
                     pkey + cap_c, pval + cap_c);
 }
 
+// The same where there are many records: a wave takes a block of 256, four to
+// a lane, and compacts the few with pairs (a fifth of the vehicle's) into one
+// table, from which it writes 64 pairs at a time. Per 64 records there were
+// two dozen pairs to write, so most of the time went into what is done once
+// per wave: with the scan, 72 views of 200k Gaussians (14.4M records) 110 us ->
+// 78, 16 views of a 2M-Gaussian block (32M) 347 -> 333. With fewer records
+// there are too few waves where records have many pairs: 3 views of the block
+// (6M) 61 against 74 with this, 5 (10M) 109 against 116, 8 (16M) 174 against
+// 177, one view of 500k 17 against 34 (26 views of the 200k, 5.2M, would take
+// 34 instead of 42).
+constexpr int64_t EMIT_I_MANY = 10000000;
+
+struct EmitTable {
+    uint32_t ex[4][256];       // first pair, relative to the wave's
+    uint32_t local0[4][256];   // first tile
+    uint32_t wr[4][256];       // rectangle width, record within the block << 16
+    uint32_t txn[4][256];      // the view's tile row stride
+    uint32_t kadd[4][256];     // the view's part of the key
+};
+
+__global__ void __launch_bounds__(256)
+k_emit_i_many(const DevView* __restrict__ views, int nv, int64_t records,
+              const uint2* __restrict__ rect_i, const uint32_t* __restrict__ cnt_i,
+              const uint32_t* __restrict__ bscan, int64_t cap_c, int64_t cap_i, int vm,
+              const uint32_t* __restrict__ status, uint32_t* __restrict__ pkey,
+              uint32_t* __restrict__ pval)
+{
+    __shared__ EmitTable L;
+    const uint32_t lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+    const int64_t block = (int64_t)blockIdx.x * 4 + w, p0 = block * 256, p = p0 + 4 * lane;
+    if (p0 >= records || status[ST_OVERFLOW]) return;
+    const uint64_t lim = min((uint64_t)status[ST_PAIRS_I], (uint64_t)cap_i);
+    uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+    if (p + 4 <= records) {
+        const uint4 c = *reinterpret_cast<const uint4*>(cnt_i + p);
+        cnt[0] = c.x;
+        cnt[1] = c.y;
+        cnt[2] = c.z;
+        cnt[3] = c.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (p + k < records) cnt[k] = cnt_i[p + k];
+    }
+    uint2 ri[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ri[k] = cnt[k] ? rect_i[p + k] : make_uint2(0u, 0u);
+    // pairs and records with pairs of the lanes below
+    const uint32_t mine = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+    const uint32_t some = (cnt[0] ? 1u : 0u) + (cnt[1] ? 1u : 0u) + (cnt[2] ? 1u : 0u) +
+                          (cnt[3] ? 1u : 0u);
+    uint32_t ex = mine, slot = some;
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        const uint32_t a = __shfl_up(ex, d, WAVE), b = __shfl_up(slot, d, WAVE);
+        if ((int)lane >= d) {
+            ex += a;
+            slot += b;
+        }
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)ex, WAVE - 1);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)slot, WAVE - 1);
+    if (total == 0u) return;
+    ex -= mine;
+    slot -= some;
+    // the wave's records mostly lie in one view: one look-up for all
+    const int v0 = find_view(nv, p0, [&](int q) { return views[q].rec_off; });
+    const int64_t v0_end = v0 + 1 < nv ? views[v0 + 1].rec_off : records;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (!cnt[k]) continue;
+        const int v = p + k < v0_end
+                          ? v0 : find_view(nv, p + k, [&](int q) { return views[q].rec_off; });
+        const uint32_t txn = (uint32_t)views[v].txi;
+        L.ex[w][slot] = ex;
+        L.local0[w][slot] = (ri[k].y & 0xFFFFu) * txn + (ri[k].x & 0xFFFFu);
+        L.wr[w][slot] = ((ri[k].x >> 16) - (ri[k].x & 0xFFFFu)) | (4u * lane + k) << 16;
+        L.txn[w][slot] = txn;
+        L.kadd[w][slot] = vm ? (uint32_t)v : (uint32_t)views[v].tile_i;
+        ex += cnt[k];
+        ++slot;
+    }
+    wave_lds_sync();
+    const uint64_t o0 = bscan[block];
+    const uint32_t top = n > 1u ? 0x80000000u >> __clz((int)(n - 1u)) : 0u;
+    for (uint32_t j = lane; j < total; j += WAVE) {
+        uint32_t l = 0u;
+        for (uint32_t step = top; step > 0u; step >>= 1)
+            if (l + step < n && L.ex[w][l + step] <= j) l += step;
+        const uint32_t t = j - L.ex[w][l], wr = L.wr[w][l], rw = wr & 0xFFFFu;
+        const uint32_t row = t / rw, col = t - row * rw;
+        const uint32_t local = L.local0[w][l] + row * L.txn[w][l] + col;
+        const uint64_t o = o0 + j;
+        if (o < lim) {
+            pkey[cap_c + o] = ikey_encode(vm != 0, (int)L.kadd[w][l], L.kadd[w][l], local);
+            pval[cap_c + o] = (uint32_t)p0 + (wr >> 16);
+        }
+    }
+}
+
 // ---- computation-plane lists of small views
 // Where every view has at most VL_MAX records, three kernels take the place
 // of the depth sort, the binning, the pair sort and the tile ranges: every
@@ -1722,8 +1823,11 @@ hipError_t launch_emit_pairs_i(const DevView* views, int nv, int64_t records,
                                hipStream_t s)
 {
     if (records <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_emit_i, dim3(grid256(records)), dim3(256), 0, s, views, nv, records,
-                       rect_i, cnt_i, bscan_i, cap_c, cap_i, vm ? 1 : 0, status, pkey, pval);
+    const bool many = records >= EMIT_I_MANY;
+    const int64_t per = many ? 4 : 1;
+    hipLaunchKernelGGL(many ? k_emit_i_many : k_emit_i, dim3(grid256((records + per - 1) / per)),
+                       dim3(256), 0, s, views, nv, records, rect_i, cnt_i, bscan_i, cap_c, cap_i,
+                       vm ? 1 : 0, status, pkey, pval);
     return hipGetLastError();
 }
 

@@ -293,6 +293,26 @@ def test_emission_of_many_records(cuda):
             assert elem_err(a, b) <= 1e-6
 
 
+def test_imaging_emission_of_many_records(cuda):
+    """Record counts below and at where the imaging plane's emission takes 256
+    records to a wave, the last block short, and views that end inside a
+    block: the images of the views all three calls share agree in deterministic
+    mode within the rounding of FP32 sums."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(8, 40003, (1.0, 3.0, 3.0), 0.03, 0.1)
+    views = [grid_view(3 + k % 2, 4, azimuth=1.4 * k) for k in range(251)]
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    images = []
+    for nv in (249, 250, 251):
+        r = api.Renderer([g], views[:nv], api.RenderOptions(deterministic=True))
+        res = r.forward()
+        r.status(res)
+        images.append(torch.cat([res.image(v).reshape(-1) for v in range(249)]))
+    assert images[0].abs().max() > 0
+    assert elem_err(images[1].cpu().numpy(), images[0].cpu().numpy()) <= 1e-6
+    assert elem_err(images[2].cpu().numpy(), images[0].cpu().numpy()) <= 1e-6
+
+
 @pytest.mark.parametrize("shadowing", [True, False], ids=["shadows", "none"])
 @pytest.mark.parametrize("tiles", [(38, 40), (32, 48), (39, 41)], ids=lambda t: str(t[0] * t[1]))
 def test_pass_a_by_number_of_tiles(cuda, tiles, shadowing):
