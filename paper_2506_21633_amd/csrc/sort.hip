@@ -55,10 +55,12 @@ __global__ void __launch_bounds__(256) k_iota(uint32_t* p, int64_t n)
 }
 
 // Digit width of a sort: the fewest passes of at most 10 bits, then the
-// narrowest digit (8 to 10 bits) that covers the key in that many passes.
+// narrowest digit (8 to 10 bits) that covers the key in that many passes. A
+// key of no bits (one bucket) has a width too: the segment table of a sort is
+// set up by it whether or not the sort makes a pass.
 inline int digit_bits(int bits)
 {
-    const int passes = (bits + 9) / 10;
+    const int passes = std::max(1, (bits + 9) / 10);
     const int d = (bits + passes - 1) / passes;
     return d < 8 ? 8 : d;
 }

@@ -335,3 +335,18 @@ def test_sort_tile_sizes(cuda, n):
     lists give the oracle's intensities."""
     scene = spread_scene(n, n, (1.0, 6.0, 6.0), 0.02, 0.05)
     check(scene, [grid_view(8, 8)], cuda, grads=False)
+
+
+MODES = {"stored": {}, "recompute": {"recompute": True}, "ordered": {"deterministic": True}}
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("n,nv", [(16385, 1), (13000, 4)])
+def test_one_tile_of_many_records(cuda, n, nv, mode):
+    """Images of one tile each where the sorts build the lists: a view past
+    the small views' record count, and views past their sum of pairs. The
+    pair sort has one bucket and makes no pass."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(n, n, (0.5, 0.7, 0.5), 0.15, 0.4)
+    views = [scenes.View.from_degrees(20.0 + 70.0 * k, 40.0, 8, 0.2) for k in range(nv)]
+    check(scene, views, cuda, api.RenderOptions(**MODES[mode]))
