@@ -648,14 +648,16 @@ k_gather_rects(const uint32_t* __restrict__ order, const uint2* __restrict__ rec
 // through LDS, each thread scanning 8 consecutive counts, the next 8192
 // loading meanwhile); the total
 // optionally becomes a pair count in status (0 and the overflow flag when
-// above the capacity).
+// above the capacity). All sums have 64 bits: 8192 counts of 256 records each
+// pass 2^32 where 262144 Gaussians have grown over 16384 tiles, and the total
+// has to show it. The offsets written have 32, unused after an overflow.
 __global__ void __launch_bounds__(1024)
 k_scan_blocks(uint32_t* __restrict__ a, int64_t n, int64_t cap, uint32_t* __restrict__ status,
               int slot)
 {
     constexpr int ITEMS = 8, NT = 1024, NWV = NT / WAVE, CH = NT * ITEMS;
     __shared__ uint32_t s_v[CH + CH / 32];   // padded: index k -> k + k / 32
-    __shared__ uint32_t s_w[NWV];
+    __shared__ unsigned long long s_w[NWV];
     __shared__ unsigned long long s_carry;
     auto pad = [](int k) { return k + (k >> 5); };
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
@@ -675,27 +677,28 @@ k_scan_blocks(uint32_t* __restrict__ a, int64_t n, int64_t cap, uint32_t* __rest
         for (int k = 0; k < ITEMS; ++k) s_v[pad(k * NT + tid)] = nx[k];
         __syncthreads();
         if (base + CH < n) load(base + CH);
-        uint32_t v[ITEMS], sum = 0u;
+        uint32_t v[ITEMS];
+        unsigned long long sum = 0ull;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             v[k] = s_v[pad(tid * ITEMS + k)];
             sum += v[k];
         }
-        uint32_t inc = sum;
+        unsigned long long inc = sum;
 #pragma unroll
         for (int d = 1; d < WAVE; d <<= 1) {
-            const uint32_t t = __shfl_up(inc, d, WAVE);
+            const unsigned long long t = __shfl_up(inc, d, WAVE);
             if (lane >= d) inc += t;
         }
         if (lane == WAVE - 1) s_w[w] = inc;
         __syncthreads();
-        uint32_t off = 0u, total = 0u;
+        unsigned long long off = 0ull, total = 0ull;
 #pragma unroll
         for (int k = 0; k < NWV; ++k) {
             if (k < w) off += s_w[k];
             total += s_w[k];
         }
-        uint32_t run = (uint32_t)s_carry + off + inc - sum;
+        uint32_t run = (uint32_t)(s_carry + off + inc - sum);
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             s_v[pad(tid * ITEMS + k)] = run;

@@ -350,3 +350,31 @@ def test_one_tile_of_many_records(cuda, n, nv, mode):
     scene = spread_scene(n, n, (0.5, 0.7, 0.5), 0.15, 0.4)
     views = [scenes.View.from_degrees(20.0 + 70.0 * k, 40.0, 8, 0.2) for k in range(nv)]
     check(scene, views, cuda, api.RenderOptions(**MODES[mode]))
+
+
+@pytest.mark.parametrize("plane", ["computation", "imaging"])
+@pytest.mark.parametrize("n", [262144, 262145])
+def test_pairs_past_32_bits_overflow(cuda, n, plane):
+    """Gaussians that have grown until each covers all 16384 tiles of a plane
+    under a plan made for small ones: 2^32 pairs and 16384 more, which in 32
+    bits would be none and few, are both reported."""
+    from paper_2506_21633_amd import _capi as C
+    from paper_2506_21633_amd import api
+    scene = spread_scene(3, n, (1.0, 60.0, 60.0), 0.05, 0.1)
+    scene.ext[:] = np.float32(1e-6)
+    view = grid_view(128, 128)
+    if plane == "imaging":   # one tile of rays, through every Gaussian
+        view.comp_w = view.comp_h = 8
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    r = api.Renderer([g], [view], api.RenderOptions(shadowing=False))
+    if plane == "computation":
+        plan = r.plan()
+    else:
+        plan = r.plan_for(n, 20000)
+    g.scales.fill_(300.0)
+    res = r.forward(plan)
+    with pytest.raises(C.SDGRError) as err:
+        r.status(res)
+    assert err.value.code == C.SDGR_EOVERFLOW
+    if plane == "imaging":
+        assert int((r.intensity_shares(res) > 0).sum()) == n   # all had pairs
