@@ -154,10 +154,13 @@ typedef struct sdgr_options {
                             covariance, in pixels^2 (0 = none) */
     int32_t deterministic;  /* 1: repeated calls on the same inputs give
                             bitwise identical images and gradients: every
-                            sum over tiles or list segments runs in a fixed
-                            order (per-pair partials reduced per Gaussian in
-                            list order, one wave per image tile) instead of
-                            float atomics; costs extra memory and time */
+                            sum over tiles or list segments runs in an
+                            order fixed by the inputs, whatever the plan's
+                            capacities (per-pair partials reduced per
+                            Gaussian in list order, a workgroup per image
+                            tile whose waves take equal runs of its
+                            Gaussians) instead of float atomics; costs extra
+                            memory and time */
     int32_t tile;        /* tile side in cells: 0 (default) or 8, the one
                             size built; other values give SDGR_EUNSUPPORTED */
     int32_t cell_area;   /* 1: I = P A times the computation-plane cell area

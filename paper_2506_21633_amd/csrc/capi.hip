@@ -568,7 +568,7 @@ int final_buffer_c(const Problem& P) { return radix_passes_for(bits_pairs_c(P)) 
 int final_buffer_i(const Problem& P) { return radix_passes_for(bits_pairs_i(P)) & 1; }
 
 // Whether pass B goes without imaging-plane lists: where its longer time is
-// less than the launches it saves (about 6.5 us each with what they do).
+// less than the launches it saves (taken at 5.5 us each with what they do).
 // That time, fitted in us over 1 to 36 views of 64 to 700 pixels and 100 to
 // 64k Gaussians: 0.65 per million rectangles read, 73 per million pairs, 0.55
 // per thousand records of a view (a wave's chain), 1.9 per thousand tiles. A
@@ -577,10 +577,20 @@ int final_buffer_i(const Problem& P) { return radix_passes_for(bits_pairs_i(P)) 
 // 323 and 328; 4000 on 4096 tiles (two sort passes) 204 and 122, 1000 on 65k
 // tiles 381 and 463. The images must not overlap: each pixel is stored, not
 // added to.
+// The two forms add a pixel's terms in different orders, and a plan's pairs
+// are a capacity, which must not show in deterministic results: there the
+// pairs are taken to be ORDERED_PAIRS a record, about what scenes here have
+// (1.3 to 3). With far more the form without lists is still the faster one
+// there: 16000 Gaussians in one view of 64 tiles at 63 pairs a record 242 us
+// with lists and 218 without, of 1024 tiles at 17 219 and 196.
+constexpr int64_t ORDERED_PAIRS = 2;
+
 bool without_lists_i(const Problem& P, const sdgr_plan* plan)
 {
     const int launches = 3 + 3 * radix_passes_for(bits_pairs_i(P));
-    const double us = 0.65e-6 * (double)P.reads_i + 73e-6 * (double)plan->pairs_i +
+    const int64_t pairs =
+        P.det ? std::min(P.reads_i, ORDERED_PAIRS * P.records) : plan->pairs_i;
+    const double us = 0.65e-6 * (double)P.reads_i + 73e-6 * (double)pairs +
                       0.55e-3 * (double)P.max_n + 1.9e-3 * (double)P.tiles_i;
     return P.images_apart && us < 5.5 * launches;
 }

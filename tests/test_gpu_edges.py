@@ -378,3 +378,26 @@ def test_pairs_past_32_bits_overflow(cuda, n, plane):
     assert err.value.code == C.SDGR_EOVERFLOW
     if plane == "imaging":
         assert int((r.intensity_shares(res) > 0).sum()) == n   # all had pairs
+
+
+@pytest.mark.parametrize("n", [1000, 4000, 20000])
+def test_ordered_results_at_any_capacity(cuda, n):
+    """Deterministic images and gradients do not depend on the pairs a plan
+    has room for (the form of pass B is not chosen by them): an exact plan,
+    one with headroom and one for far more pairs agree bit for bit."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(n + 5, n, (2.0, 6.0, 6.0), 0.1, 0.5)
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    views = [grid_view(9, 7), grid_view(6, 6, azimuth=33.0)]
+    r = api.Renderer([g], views, api.RenderOptions(deterministic=True))
+    exact = r.plan()
+    cot = torch.as_tensor(np.random.default_rng(n).standard_normal(exact.image_floats)
+                          .astype(np.float32), device=cuda)
+    want = None
+    for plan in (exact, r.planned(0.1), r.plan_for(exact.pairs_c, 3_000_000)):
+        res = r.forward(plan)
+        got = {"images": res.images, **r.backward(res, cot)[0]}
+        r.status(res)
+        want = want or got
+        for k, t in got.items():
+            assert torch.equal(t, want[k]), k
