@@ -98,7 +98,8 @@ struct RasterParams {
     // each chain back to front instead of re-deriving the hits from the
     // footprint masks. A record is two header units (the previous record or
     // HIT_NONE, the hit count, whether it is the first of its batch of chunks
-    // and the record before the previous one; the list positions / 64 of the
+    // with its number in the tile above that bit, and the record before the
+    // previous one; the list positions / 64 of the
     // batch's four chunks) and then one 2-byte word per hit in processing
     // order (ray-major, each ray front to back): the entry in bits 0..5, its
     // chunk in the batch in bits 6..7, the ray (cell of the tile) in bits
@@ -127,11 +128,10 @@ constexpr uint32_t HIT_HEADER_UNITS = 2;
 // returning atomics, about 5 ns each (pass A's forward 286 us of which 160 on
 // 9k tiles of 500k Gaussians, 260 us of which 110 on 6k tiles of a 36-view
 // building). 64 parts of at least HIT_SUB_MIN units, each counter in a line
-// of its own; a tile that finds its part full tries the HIT_TRIES - 1 after it.
+// of its own; a tile that finds its part full goes on in another with room.
 constexpr int HIT_SUBS = 64;
 constexpr int HIT_TOP_STRIDE = 16;
 constexpr int64_t HIT_SUB_MIN = 16384;   // 256 KB
-constexpr int HIT_TRIES = 3;
 constexpr int PART_G = 6;      // floats per pair of the deterministic backward's sums
 constexpr int GC_STRIDE = 8;   // floats per record in grad_c and grad_i
 constexpr int HIT_PART_STRIDE = 8;   // floats per pair partial: six sums, the record, spare

@@ -459,6 +459,61 @@ k_pair_masks(const DevView* __restrict__ views, int nv, int64_t cap, RasterParam
     }
 }
 
+// A block of `take` units of the hit stream for a tile's records (the whole
+// wave calls): from part `sub` if it has room, else from another part whose
+// counter shows room, wherever it lies; sub is where the tile goes on. Only a
+// tile that finds its part full looks at others, HIT_LOOK - 1 spread over the
+// stream. Where these are mostly full too it asks once more and, in vain,
+// raises its part's counter past HIT_FULL, so that the tiles after it in that
+// part stop at their first request. Pass A of 500k Gaussians in one view, whose
+// stream fills everywhere, takes 134 us; with all 64 counters read and as many
+// requests as they promise 177, with the mark and three requests 144.
+constexpr int HIT_TRIES = 3;
+constexpr uint32_t HIT_LOOK = 8, HIT_STEP = 71;   // (a prime past HIT_SUBS: all parts in turn)
+constexpr unsigned long long HIT_FULL = 1ull << 40;
+
+__device__ __forceinline__ bool take_hit_block(const RasterParams& rp, uint32_t take,
+                                               uint32_t& sub, uint32_t& top)
+{
+    const uint32_t lane = (uint32_t)lane_id();
+    const unsigned long long cap = rp.hit_sub_cap;
+    auto ask = [&](uint32_t s) {
+        unsigned long long at = 0ull;
+        if (lane == 0u)
+            at = atomicAdd(&rp.hit_tops[s * HIT_TOP_STRIDE], (unsigned long long)take);
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
+                    (int)(uint32_t)(at >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    };
+    unsigned long long at = ask(sub);
+    if (at + take > cap) {
+        if (at >= HIT_FULL) return false;
+        const uint32_t first = sub, parts = min(rp.hit_subs, HIT_LOOK);
+        auto part = [&](uint32_t k) { return (first + HIT_STEP * k) % rp.hit_subs; };
+        unsigned long long used = cap;
+        if (lane > 0u && lane < parts)
+            used = __hip_atomic_load(&rp.hit_tops[part(lane) * HIT_TOP_STRIDE], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+        // parts at least half free: where they are a quarter, the stream fills
+        // unevenly; else it fills everywhere
+        uint64_t room = __ballot(2u * used <= cap && used + take <= cap);
+        const bool ample = 4u * (uint32_t)__popcll(room) >= parts;
+        if (!ample) room = __ballot(used + take <= cap);
+        for (int k = 0;; ++k, room &= room - 1ull) {
+            if (room == 0ull || k == (ample ? HIT_TRIES : 1)) {
+                if (lane == 0u && !ample)
+                    atomicAdd(&rp.hit_tops[first * HIT_TOP_STRIDE], HIT_FULL);
+                return false;
+            }
+            sub = part((uint32_t)__builtin_ctzll(room));
+            at = ask(sub);
+            if (at + take <= cap) break;
+        }
+    }
+    top = sub * rp.hit_sub_cap + (uint32_t)at;
+    return true;
+}
+
 // Pass A forward, one wave per non-empty 8x8 tile; the wave's rays are the
 // tile's 64 cells. The list is walked in 64-entry chunks aligned to the
 // global pair array; a chunk whose footprint summary misses every ray still
@@ -548,6 +603,7 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
     bool h_on = HITS;
     uint32_t h_top = 0u, h_end = 0u, h_blk = 128u, h_prev = HIT_NONE, h_rec = 0u, h_kept = 0u;
     uint32_t h_prev2 = HIT_NONE;   // the record before h_prev
+    uint32_t h_seq = 0u;           // records stored
     uint32_t h_sub = HITS ? blockIdx.x % rp.hit_subs : 0u;   // part of the stream
     // (a nonzero sum means a live ray hit the entry, so its record was
     // gathered and r_prev holds it: all eight sums are read at once, without
@@ -700,29 +756,13 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                     // room for the group's record (header and at most every
                     // hit); a new block when the tile's is short (sizes
                     // doubling up to 16 KB, so short tiles waste little and
-                    // long ones seldom ask), from the tile's part of the
-                    // stream or one of the next ones (never an earlier one:
-                    // a tile's records lie in increasing order)
+                    // long ones seldom ask)
                     const uint32_t units = HIT_HEADER_UNITS + (H + 7u) / 8u;
                     if (h_end - h_top < units) {
                         const uint32_t take = max(units, h_blk);
                         h_blk = min(2u * h_blk, 1024u);
-                        h_on = false;
-                        for (int k = 0; k < HIT_TRIES && h_sub < rp.hit_subs; ++k, ++h_sub) {
-                            unsigned long long base = 0ull;
-                            if (lane == 0)
-                                base = atomicAdd(&rp.hit_tops[h_sub * HIT_TOP_STRIDE],
-                                                 (unsigned long long)take);
-                            base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
-                                        (int)(uint32_t)(base >> 32)) << 32) |
-                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
-                            if (base + take <= rp.hit_sub_cap) {
-                                h_on = true;
-                                h_top = h_sub * rp.hit_sub_cap + (uint32_t)base;
-                                h_end = h_top + take;
-                                break;
-                            }
-                        }
+                        h_on = take_hit_block(rp, take, h_sub, h_top);
+                        h_end = h_top + take;
                         if (!h_on) h_prev = HIT_OVERFLOW;
                     }
                 }
@@ -835,9 +875,11 @@ k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
                 wave_lds_sync();
                 if (h_on && h_kept > 0u) {   // the group's record
                     if (lane == 0)
-                        rp.hits[h_rec] = make_uint4(h_prev, h_kept, fresh ? 1u : 0u, h_prev2);
+                        rp.hits[h_rec] =
+                            make_uint4(h_prev, h_kept, (h_seq << 1) | (fresh ? 1u : 0u), h_prev2);
                     if (lane == 1)
                         rp.hits[h_rec + 1] = make_uint4(s_chk[0], s_chk[1], s_chk[2], s_chk[3]);
+                    ++h_seq;
                     h_prev2 = h_prev;
                     h_prev = h_rec;
                     h_top = h_rec + HIT_HEADER_UNITS + (h_kept + 7u) / 8u;
@@ -1222,6 +1264,7 @@ k_raster_a_fwd_hits(const DevView* __restrict__ views, int nv, RasterParams rp,
         // tile writes into [h_top, h_end) and the block size it takes next
         bool h_on = true;
         uint32_t h_top = 0u, h_end = 0u, h_blk = 128u, h_prev = HIT_NONE, h_prev2 = HIT_NONE;
+        uint32_t h_seq = 0u;                         // records stored
         uint32_t h_sub = blockIdx.x % rp.hit_subs;   // part of the stream
         HitGroup G{0u, 0u, 0u, 1u, 0, 0};
         uint32_t kept = 0u;   // hits of it processed
@@ -1232,38 +1275,24 @@ k_raster_a_fwd_hits(const DevView* __restrict__ views, int nv, RasterParams rp,
             if (h_on && kept > 0u) {
                 // room for the group's record; a new block when the tile's is
                 // short (sizes doubling up to 16 KB, so short tiles waste
-                // little and long ones seldom ask), from the tile's part of
-                // the stream or one of the next ones (never an earlier one: a
-                // tile's records lie in increasing order)
+                // little and long ones seldom ask)
                 const uint32_t words = (kept + 7u) / 8u, units = HIT_HEADER_UNITS + words;
                 if (h_end - h_top < units) {
                     const uint32_t take = max(units, h_blk);
                     h_blk = min(2u * h_blk, 1024u);
-                    h_on = false;
-                    for (int k = 0; k < HIT_TRIES && h_sub < rp.hit_subs; ++k, ++h_sub) {
-                        unsigned long long at = 0ull;
-                        if (lane == 0)
-                            at = atomicAdd(&rp.hit_tops[h_sub * HIT_TOP_STRIDE],
-                                           (unsigned long long)take);
-                        at = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
-                                  (int)(uint32_t)(at >> 32)) << 32) |
-                             (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
-                        if (at + take <= rp.hit_sub_cap) {
-                            h_on = true;
-                            h_top = h_sub * rp.hit_sub_cap + (uint32_t)at;
-                            h_end = h_top + take;
-                            break;
-                        }
-                    }
+                    h_on = take_hit_block(rp, take, h_sub, h_top);
+                    h_end = h_top + take;
                     if (!h_on) h_prev = HIT_OVERFLOW;
                 }
                 if (h_on) {
                     uint4* to = rp.hits + h_top;
                     for (uint32_t i = lane; i < words; i += WAVE) to[HIT_HEADER_UNITS + i] = s_out[i];
-                    if (lane == 0) to[0] = make_uint4(h_prev, kept, fresh ? 1u : 0u, h_prev2);
+                    if (lane == 0)
+                        to[0] = make_uint4(h_prev, kept, (h_seq << 1) | (fresh ? 1u : 0u), h_prev2);
                     if (lane == 1)
                         to[1] = make_uint4(G.base + (G.off & 0xFFu), G.base + ((G.off >> 8) & 0xFFu),
                                            G.base + ((G.off >> 16) & 0xFFu), G.base + (G.off >> 24));
+                    ++h_seq;
                     h_prev2 = h_prev;
                     h_prev = h_top;
                     h_top += units;
@@ -2198,10 +2227,10 @@ k_raster_a_bwd(const DevView* __restrict__ views, int nv,
 // and scanned its rounds alone, with a second one storing, took 2.8 us per
 // round on the longest tiles (a full memory latency in each, however far
 // ahead the loads were issued).
-// Records that do not fit the stream, links that do not go back in it, record
-// ids past the record count and list positions past the pair count end the
-// walk or are skipped, so a stream that holds anything else cannot send the
-// kernel out of bounds.
+// Records that do not fit the stream, record numbers that do not fall along
+// the walk, record ids past the record count and list positions past the pair
+// count end the walk or are skipped, so a stream that holds anything else
+// cannot send the kernel out of bounds or keep it going.
 constexpr int HB_HELPERS = 4;
 constexpr int HB_THREADS = (2 + HB_HELPERS) * WAVE;
 
@@ -2370,13 +2399,13 @@ k_raster_a_bwd_hits(const DevView* __restrict__ views, int nv, RasterParams rp,
     const uint64_t cap = rp.hit_cap;
     uint32_t n_hits = 0, n_batch = 0;   // work counters
 
-    // the cursor: the record steps are taken from, its hits not yet taken,
-    // whether it is the first of its batch, its header (lanes 0..7; chunk k's
+    // the cursor: the record steps are taken from, its number in the tile, its
+    // hits not yet taken, whether it is the first of its batch, its header (lanes 0..7; chunk k's
     // list position in lane 4 + k), the record before it and the headers of
     // the two before it (a header names both, so two loads are in flight and
     // a step does not wait for one)
     uint32_t cur = HIT_NONE, left = 0u, prev = HIT_NONE, first = 0u, chunks = 0u;
-    uint32_t pend = 0u, pend2 = 0u;
+    uint32_t pend = 0u, pend2 = 0u, seq = 1u << 31;   // (past every record's number)
     int buf = 0;
     auto load_header = [&](uint32_t r) {
         return lane < 4 * (int)HIT_HEADER_UNITS && (uint64_t)r + HIT_HEADER_UNITS <= cap
@@ -2385,16 +2414,19 @@ k_raster_a_bwd_hits(const DevView* __restrict__ views, int nv, RasterParams rp,
     auto enter = [&](uint32_t r, uint32_t header) {
         const uint32_t pv = (uint32_t)__builtin_amdgcn_readlane((int)header, 0);
         const uint32_t kept = (uint32_t)__builtin_amdgcn_readlane((int)header, 1);
-        first = (uint32_t)__builtin_amdgcn_readlane((int)header, 2);
+        const uint32_t mark = (uint32_t)__builtin_amdgcn_readlane((int)header, 2);
         const uint32_t pv2 = (uint32_t)__builtin_amdgcn_readlane((int)header, 3);
-        if (kept == 0u || (uint64_t)r + HIT_HEADER_UNITS + (kept + 7u) / 8u > cap) {
+        if (kept == 0u || (uint64_t)r + HIT_HEADER_UNITS + (kept + 7u) / 8u > cap ||
+            mark >> 1 >= seq) {
             cur = HIT_NONE;
             return;
         }
+        first = mark & 1u;
+        seq = mark >> 1;
         chunks = header;
         cur = r;
         left = kept;
-        prev = pv < r ? pv : HIT_NONE;
+        prev = seq > 0u ? pv : HIT_NONE;
         pend = pend2;
         pend2 = load_header(pv2);   // (zeros for none: no hits, the walk ends)
     };

@@ -401,3 +401,63 @@ def test_ordered_results_at_any_capacity(cuda, n):
         want = want or got
         for k, t in got.items():
             assert torch.equal(t, want[k]), k
+
+
+@pytest.mark.parametrize("opaque_views", [0, 7])
+def test_hit_stream_reach(cuda, opaque_views):
+    """A tile of many thin Gaussians stores its hits wherever the stream has
+    room: the only tile of a call, and the one that starts in the last of
+    eight parts, past seven longer lists that hardly use theirs. Its gradients
+    are the oracle's."""
+    from paper_2506_21633_amd import api
+    thin = spread_scene(1, 20000, (0.5, 0.7, 0.5), 0.15, 0.4)
+    thin.ext[:] *= np.float32(1e-4)
+    dense = spread_scene(2, 40000, (0.5, 0.7, 0.5), 0.15, 0.4)
+    dense.ext[:] *= np.float32(20.0)
+    views = [scenes.View.from_degrees(40.0 * k, 40.0, 8, 0.2) for k in range(opaque_views + 1)]
+    views[-1].scene = 1
+    r = api.Renderer([api.GaussianTensors.from_numpy(s, cuda) for s in (dense, thin)], views)
+    plan = r.plan()
+    if opaque_views:
+        plan.hit_bytes = 8 * 16384 * 16
+    rng = np.random.default_rng(0)
+    G = [rng.standard_normal((8, 8)) for _ in views]
+    flat = torch.as_tensor(np.concatenate([x.ravel() for x in G]).astype(np.float32), device=cuda)
+    api.count_work(True)
+    try:
+        res = r.forward(plan)
+        d = r.backward(res, flat)[1]
+        r.status(res)
+        work = r.work_counters(res)
+    finally:
+        api.count_work(False)
+    assert work["hits_a_fwd"] * 2 > 3 * 16384 * 16   # more than three parts hold
+    assert work["tiles_a_bwd_rederived"] == 0
+    assert work["tiles_a_bwd_stored"] == len(views)
+    ref, _ = oracle.backward(thin, views[-1:], G[-1:])
+    for k, t in d.items():
+        a, b = t.cpu().numpy().ravel().astype(np.float64), ref[k].ravel()
+        assert float(a @ b / (np.linalg.norm(a) * np.linalg.norm(b))) >= GRAD_COS, k
+        assert np.linalg.norm(a - b) / np.linalg.norm(b) <= GRAD_L2, k
+
+
+@pytest.mark.parametrize("units", [200, 16384, 3 * 16384])
+def test_hit_stream_parts_of_many_tiles(cuda, units):
+    """The same where a wave takes a tile (over 1536 tiles): streams that run
+    out in some parts before others, with the bar of test_hit_stream_parts."""
+    from paper_2506_21633_amd import api
+    wide = (0.5, 0.8 * 40, 0.8 * 40 / math.cos(math.radians(45.0)))
+    scene = spread_scene(13, 12000, wide, 0.15, 0.6)
+    scene.means[9000:] *= np.float32(0.05)
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    r = api.Renderer([g], [grid_view(40, 40)])
+    cot = torch.as_tensor(np.random.default_rng(1).standard_normal(320 * 320)
+                          .astype(np.float32), device=cuda)
+    want = r.backward(r.forward(), cot)[0]
+    plan = r.plan()
+    plan.hit_bytes = min(plan.hit_bytes, 16 * units)
+    res = r.forward(plan)
+    got = r.backward(res, cot)[0]
+    r.status(res)
+    for k, t in want.items():   # FP32 rounding of re-derived against stored sums
+        assert elem_err(got[k].cpu().numpy(), t.cpu().numpy()) <= 1e-5, k
