@@ -1769,7 +1769,9 @@ k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scen
             sxy += dy * r1;
             syy += dy * dy * r0;
         }
-        dI = (s0 - rp.eps * sG) * rp.inv1meps;
+        // (an infinite cotangent, of whichever sign, outweighs the rest: the
+        // difference would make it NaN)
+        dI = (isinf(s0) ? s0 : s0 - rp.eps * sG) * rp.inv1meps;
         const float k = -0.5f * I * rp.inv1meps;   // dL/dq = k w
         dcx = -2.0f * k * (a * sx + b * sy);
         dcy = -2.0f * k * (b * sx + c * sy);

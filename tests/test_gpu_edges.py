@@ -461,3 +461,25 @@ def test_hit_stream_parts_of_many_tiles(cuda, units):
     r.status(res)
     for k, t in want.items():   # FP32 rounding of re-derived against stored sums
         assert elem_err(got[k].cpu().numpy(), t.cpu().numpy()) <= 1e-5, k
+
+
+def test_infinite_cotangent(cuda):
+    """An infinite cotangent of one pixel gives the amplitudes of the Gaussians
+    that reach it an infinite gradient of its sign, as the sum that defines
+    it, and leaves the others' as they are."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(4, 300, (1.0, 3.0, 3.0), 0.15, 0.5)
+    view = grid_view(6, 5)
+    rng = np.random.default_rng(4)
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    r = api.Renderer([g], [view])
+    for sign in (1.0, -1.0):
+        G = rng.standard_normal((view.img_h, view.img_w))
+        G[19, 23] = sign * np.inf
+        got = r.backward(r.forward(), torch.as_tensor(G.astype(np.float32), device=cuda))[0]
+        a = got["amp"].cpu().numpy().astype(np.float64)
+        want = oracle.backward(scene, [view], [G])[0]["amp"]
+        far = np.isfinite(want)
+        assert 0 < far.sum() < far.size
+        assert np.array_equal(a[~far], want[~far])
+        assert elem_err(a[far], want[far]) <= ELEM
