@@ -648,20 +648,23 @@ k_gather_rects(const uint32_t* __restrict__ order, const uint2* __restrict__ rec
 // through LDS, each thread scanning 8 consecutive counts, the next 8192
 // loading meanwhile); the total
 // optionally becomes a pair count in status (0 and the overflow flag when
-// above the capacity). All sums have 64 bits: 8192 counts of 256 records each
-// pass 2^32 where 262144 Gaussians have grown over 16384 tiles, and the total
-// has to show it. The offsets written have 32, unused after an overflow.
+// above the capacity). The total has 64 bits: 8192 counts of 256 records each
+// pass 2^32 where 262144 Gaussians have grown over 16384 tiles. The offsets
+// have 32, unused after an overflow; the threads keep the total beside them
+// (scanned in 64 bits too, the two scans of 72 views of 200k took 6 us more).
 __global__ void __launch_bounds__(1024)
 k_scan_blocks(uint32_t* __restrict__ a, int64_t n, int64_t cap, uint32_t* __restrict__ status,
               int slot)
 {
     constexpr int ITEMS = 8, NT = 1024, NWV = NT / WAVE, CH = NT * ITEMS;
     __shared__ uint32_t s_v[CH + CH / 32];   // padded: index k -> k + k / 32
-    __shared__ unsigned long long s_w[NWV];
-    __shared__ unsigned long long s_carry;
+    __shared__ uint32_t s_w[NWV];
+    __shared__ uint32_t s_carry;
+    __shared__ unsigned long long s_all[NWV];
     auto pad = [](int k) { return k + (k >> 5); };
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-    if (tid == 0) s_carry = 0ull;
+    if (tid == 0) s_carry = 0u;
+    unsigned long long all = 0ull;   // the thread's counts
     // the next chunk's counts load while this one is scanned and written
     uint32_t nx[ITEMS];
     auto load = [&](int64_t base) {
@@ -674,31 +677,33 @@ k_scan_blocks(uint32_t* __restrict__ a, int64_t n, int64_t cap, uint32_t* __rest
     load(0);
     for (int64_t base = 0; base < n; base += CH) {
 #pragma unroll
-        for (int k = 0; k < ITEMS; ++k) s_v[pad(k * NT + tid)] = nx[k];
+        for (int k = 0; k < ITEMS; ++k) {
+            s_v[pad(k * NT + tid)] = nx[k];
+            all += nx[k];
+        }
         __syncthreads();
         if (base + CH < n) load(base + CH);
-        uint32_t v[ITEMS];
-        unsigned long long sum = 0ull;
+        uint32_t v[ITEMS], sum = 0u;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             v[k] = s_v[pad(tid * ITEMS + k)];
             sum += v[k];
         }
-        unsigned long long inc = sum;
+        uint32_t inc = sum;
 #pragma unroll
         for (int d = 1; d < WAVE; d <<= 1) {
-            const unsigned long long t = __shfl_up(inc, d, WAVE);
+            const uint32_t t = __shfl_up(inc, d, WAVE);
             if (lane >= d) inc += t;
         }
         if (lane == WAVE - 1) s_w[w] = inc;
         __syncthreads();
-        unsigned long long off = 0ull, total = 0ull;
+        uint32_t off = 0u, total = 0u;
 #pragma unroll
         for (int k = 0; k < NWV; ++k) {
             if (k < w) off += s_w[k];
             total += s_w[k];
         }
-        uint32_t run = (uint32_t)(s_carry + off + inc - sum);
+        uint32_t run = s_carry + off + inc - sum;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             s_v[pad(tid * ITEMS + k)] = run;
@@ -713,8 +718,15 @@ k_scan_blocks(uint32_t* __restrict__ a, int64_t n, int64_t cap, uint32_t* __rest
         if (tid == 0) s_carry += total;
         __syncthreads();
     }
-    if (tid == 0 && slot >= 0) {
-        const unsigned long long tot = s_carry;
+    if (slot < 0) return;
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1)
+        all += (unsigned long long)__shfl_xor((long long)all, d, WAVE);
+    if (lane == 0) s_all[w] = all;
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long tot = 0ull;
+        for (int k = 0; k < NWV; ++k) tot += s_all[k];
         const bool over = tot > (unsigned long long)cap;
         status[ST_OVERFLOW] |= over ? 1u : 0u;
         status[slot] = over ? 0u : (uint32_t)tot;
