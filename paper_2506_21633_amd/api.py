@@ -198,6 +198,7 @@ class Renderer:
         self.options = options or RenderOptions()
         self.lib = C.lib()
         self.views_c, self.shapes, self.image_floats = _view_structs(views, scene_ids)
+        self._packed = bytes(self.views_c)   # as made here: images without gaps
         self.nv = len(views)
         self.opts_c = self.options.to_c()
         self._rebind()
@@ -252,9 +253,11 @@ class Renderer:
         state = _buf(plan.state_bytes, self.device)
         scratch = _buf(plan.fwd_scratch_bytes, self.device)
         # the forward writes every pixel of every view, and the views' images
-        # fill the buffer
-        images = torch.empty(max(int(plan.image_floats), 1), dtype=torch.float32,
-                             device=self.device)
+        # fill the buffer unless the caller has changed them
+        filled = (plan.image_floats == self.image_floats and
+                  bytes(self.views_c) == self._packed)
+        fresh = torch.empty if filled else torch.zeros
+        images = fresh(max(int(plan.image_floats), 1), dtype=torch.float32, device=self.device)
         C.check(self.lib.sdgr_forward(self.scenes_c, len(self.scenes), self.views_c, self.nv,
                                       ctypes.byref(self.opts_c), ctypes.byref(plan),
                                       state.data_ptr(), scratch.data_ptr(),

@@ -483,3 +483,26 @@ def test_infinite_cotangent(cuda):
         assert 0 < far.sum() < far.size
         assert np.array_equal(a[~far], want[~far])
         assert elem_err(a[far], want[far]) <= ELEM
+
+
+@pytest.mark.parametrize("n", [300, 70000])
+def test_images_with_a_gap_between_them(cuda, n):
+    """Views moved apart in the image buffer, in a call without imaging-plane
+    lists and one with them: the same images at their offsets, and zeros in
+    the floats no view covers, whatever the buffer's memory held before."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(n, n, (1.0, 4.0, 4.0), 0.05, 0.2)
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    r = api.Renderer([g], [grid_view(5, 6), grid_view(4, 4, azimuth=30.0)])
+    want = r.forward()
+    gap, start = 101, 40 * 48
+    r.views_c[1].img_offset = start + gap
+    plan = r.plan()
+    size = int(plan.image_floats)
+    assert size == want.images.numel() + gap
+    torch.full((size,), float("nan"), device=cuda)   # freed at once: the next one's memory
+    images = r.forward(plan).images.cpu().numpy()
+    assert np.all(images[start:start + gap] == 0.0)
+    for v, off in ((0, 0), (1, start + gap)):
+        img = want.image(v).cpu().numpy().ravel()
+        assert elem_err(images[off:off + img.size], img) <= ELEM, v
