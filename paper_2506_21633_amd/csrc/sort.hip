@@ -1170,13 +1170,16 @@ k_emit_i(const DevView* __restrict__ views, int nv, int64_t records,
 // a lane, and compacts the few with pairs (a fifth of the vehicle's) into one
 // table, from which it writes 64 pairs at a time. Per 64 records there were
 // two dozen pairs to write, so most of the time went into what is done once
-// per wave: with the scan, 72 views of 200k Gaussians (14.4M records) 110 us ->
-// 78, 16 views of a 2M-Gaussian block (32M) 347 -> 333. With fewer records
-// there are too few waves where records have many pairs: 3 views of the block
-// (6M) 61 against 74 with this, 5 (10M) 109 against 116, 8 (16M) 174 against
-// 177, one view of 500k 17 against 34 (26 views of the 200k, 5.2M, would take
-// 34 instead of 42).
-constexpr int64_t EMIT_I_MANY = 10000000;
+// per wave. A wave's pairs are a chain, though, so with many pairs a record it
+// takes more records until there are enough waves: the number grows as the
+// square of the pairs. Scan and emission, a wave per 64 records and per 256:
+// 200k vehicle (2.0 pairs a record in the plan) 8 views 19.5 and 20.1 us, 13
+// views 27.7 and 26.3, 26 views 44 and 36, 72 views 114 and 82; 200k building
+// (1.6) 36 views of 50k 26 and 28, 30 views 56 and 51; 2M block (6.1) 5 views
+// 113 and 118, 8 views 181 and 182, 16 views 355 and 341; 1M block in 14 views
+// (2.8) 136 and 122; 100k cube (17) 20 views 32 and 37.
+constexpr int64_t EMIT_I_MANY = 2000000;
+constexpr double EMIT_I_WIDE = 700000.0;   // records, times the square of the pairs a record
 
 struct EmitTable {
     uint32_t ex[4][256];       // first pair, relative to the wave's
@@ -1840,7 +1843,9 @@ hipError_t launch_emit_pairs_i(const DevView* views, int nv, int64_t records,
                                hipStream_t s)
 {
     if (records <= 0) return hipSuccess;
-    const bool many = records >= EMIT_I_MANY;
+    const double pairs = (double)cap_i / (double)records;
+    const bool many =
+        records >= EMIT_I_MANY && (double)records >= EMIT_I_WIDE * pairs * pairs;
     const int64_t per = many ? 4 : 1;
     hipLaunchKernelGGL(many ? k_emit_i_many : k_emit_i, dim3(grid256((records + per - 1) / per)),
                        dim3(256), 0, s, views, nv, records, rect_i, cnt_i, bscan_i, cap_c, cap_i,

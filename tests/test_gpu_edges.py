@@ -506,3 +506,28 @@ def test_images_with_a_gap_between_them(cuda, n):
     for v, off in ((0, 0), (1, start + gap)):
         img = want.image(v).cpu().numpy().ravel()
         assert elem_err(images[off:off + img.size], img) <= ELEM, v
+
+
+@pytest.mark.parametrize("nv,n", [(49, 40003), (50, 40003), (260, 8009), (2, 1048583)])
+def test_imaging_emission_rule(cuda, nv, n):
+    """Records of few pairs below and past where the imaging plane's emission
+    takes 256 to a wave, with view-major keys and (over 256 views) global
+    ones: in deterministic mode the images are those of two calls with half
+    the views each, within the rounding of FP32 sums."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(nv, n, (1.0, 3.0, 3.0), 0.005, 0.02)
+    views = [grid_view(3 + k % 2, 4, azimuth=1.4 * k) for k in range(nv)]
+    g = api.GaussianTensors.from_numpy(scene, cuda)
+    options = api.RenderOptions(deterministic=True)
+
+    def run(vs):
+        r = api.Renderer([g], vs, options)
+        plan = r.plan()
+        assert plan.pairs_i < 1.69 * plan.records   # 2M records decide
+        res = r.forward(plan)
+        r.status(res)
+        return res.images
+    got, half = run(views), (nv + 1) // 2
+    want = torch.cat([run(views[:half]), run(views[half:])])
+    assert want.abs().max() > 0
+    assert elem_err(got.cpu().numpy(), want.cpu().numpy()) <= 1e-6
