@@ -531,3 +531,99 @@ def test_imaging_emission_rule(cuda, nv, n):
     want = torch.cat([run(views[:half]), run(views[half:])])
     assert want.abs().max() > 0
     assert elem_err(got.cpu().numpy(), want.cpu().numpy()) <= 1e-6
+
+
+# The small views' lists hold up to 16384 records a view and 256 tiles a side,
+# and images form without lists up to 60000 records a view: these calls are
+# past both, where the scans, the sorts and the emissions work.
+MANY = 70000
+
+
+@pytest.mark.parametrize("mode", ["stored", "ordered"])
+@pytest.mark.parametrize("plane", ["computation", "imaging"])
+def test_overflow_of_sorted_lists(cuda, plane, mode):
+    """Too few pairs in the plan on one plane: reported by the scans, with a
+    backward after it, and the exact plan renders as the oracle does."""
+    from paper_2506_21633_amd import _capi as C
+    from paper_2506_21633_amd import api
+    scene = spread_scene(31, MANY, (1.0, 3.0, 3.0), 0.02, 0.1)
+    views = [grid_view(6, 5), grid_view(4, 4, azimuth=100.0)]
+    r = api.Renderer([api.GaussianTensors.from_numpy(scene, cuda)], views,
+                     api.RenderOptions(**MODES[mode]))
+    exact = r.plan()
+    pairs = (exact.pairs_c // 2, exact.pairs_i) if plane == "computation" else (exact.pairs_c, 1000)
+    res = r.forward(r.plan_for(*pairs))
+    r.backward(res, torch.ones_like(res.images))
+    with pytest.raises(C.SDGRError) as err:
+        r.status(res)
+    assert err.value.code == C.SDGR_EOVERFLOW
+    ok = r.forward(exact)
+    r.status(ok)
+    _, _, want = oracle.forward(scene, views)
+    for v in range(len(views)):
+        assert elem_err(ok.image(v).cpu().numpy(), want[v]) <= ELEM, v
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_more_views_than_segments(cuda, mode):
+    """Over 256 views with more tiles in all than the small views' lists take:
+    one depth sort and one pair sort over all views, and imaging-plane keys
+    that are global tile ids."""
+    from paper_2506_21633_amd import api
+    scene = spread_scene(18, 60, (0.6, 5.0, 4.0), 0.15, 0.4)
+    views = [grid_view(12 + k % 2, 11, azimuth=1.4 * k) for k in range(260)]
+    check(scene, views, cuda, api.RenderOptions(**MODES[mode]))
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_empty_views_between_sorted_ones(cuda, mode):
+    """Views of an empty scene first, last and between views of others: empty
+    segments of the sorts, blocks of records that end inside a view."""
+    from paper_2506_21633_amd import api
+    none = scenes.Scene(*(np.zeros((0,) + s, np.float32) for s in ((3,), (3,), (4,), (), ())))
+    sc = [spread_scene(20, MANY, (1.0, 3.0, 3.0), 0.02, 0.1), none,
+          spread_scene(21, 150, (1.0, 2.0, 2.0), 0.1, 0.3)]
+    which = [1, 0, 1, 1, 2, 1, 0, 2, 1]
+    views = [grid_view(4 + k % 2, 5, azimuth=25.0 * k) for k in range(len(which))]
+    for v, s in zip(views, which):
+        v.scene = s
+    rng = np.random.default_rng(22)
+    G = [rng.standard_normal((v.img_h, v.img_w)) for v in views]
+    _, images, grads = run_views(sc, views, cuda, api.RenderOptions(**MODES[mode]), G)
+    for s in (0, 2):
+        mine = [k for k, x in enumerate(which) if x == s]
+        vs = [scenes.View(**{**vars(views[k]), "scene": 0}) for k in mine]
+        _, _, want = oracle.forward(sc[s], vs)
+        for k, img in zip(mine, want):
+            assert elem_err(images[k], img) <= ELEM, k
+        ref, _ = oracle.backward(sc[s], vs, [G[k] for k in mine])
+        for name, t in grads[s].items():
+            a, b = t.ravel().astype(np.float64), ref[name].ravel()
+            assert float(a @ b / (np.linalg.norm(a) * np.linalg.norm(b))) >= GRAD_COS, (s, name)
+            assert np.linalg.norm(a - b) / np.linalg.norm(b) <= GRAD_L2, (s, name)
+    for k, x in enumerate(which):
+        if x == 1:
+            assert not images[k].any(), k
+
+
+def test_ordered_ragged_images_from_lists(cuda):
+    """Ragged images of the deterministic mode through the workgroups that
+    take a tile's list: edge tiles have lanes outside the image, which must
+    still take part in the transpose of the masks. A view that only grazes
+    Gaussian tails is held to the call's scale."""
+    from paper_2506_21633_amd import api
+    scene = scenes.vehicle(85, MANY)
+    views = []
+    for k, (w, h) in enumerate([(70, 52), (33, 17), (9, 61), (1, 5)]):
+        v = scenes.View.from_degrees(40.0 + 70.0 * k, 35.0, w, 0.07)
+        v.img_h = h
+        views.append(v)
+    r = api.Renderer([api.GaussianTensors.from_numpy(scene, cuda)], views,
+                     api.RenderOptions(deterministic=True))
+    res = r.forward()
+    r.status(res)
+    _, _, want = oracle.forward(scene, views)
+    top = max(np.abs(S).max() for S in want)
+    for v, S in enumerate(want):
+        scale = max(np.abs(S).max(), 1e-3 * top)
+        assert np.abs(res.image(v).cpu().numpy() - S).max() <= ELEM * scale, v
