@@ -193,23 +193,6 @@ __device__ __forceinline__ uint32_t float_order_bits(float f)
 
 // ---- wave64 helpers ------------------------------------------------------
 
-// Sum of v over the 64 lanes of the wave (all lanes must be active);
-// result is wave-uniform.
-__device__ __forceinline__ float wave_sum(float v)
-{
-    // quad sums
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
-    // 8-lane sums (row_half_mirror), then 16-lane row sums (row_mirror)
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));
-    float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return (r0 + r1) + (r2 + r3);
-}
-
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 __device__ __forceinline__ void wave_lds_sync()

@@ -259,8 +259,10 @@ k_densify_apply(DensifyArgs a, const uint8_t* __restrict__ act,
 
 // Exhaustive nearest neighbours, a query per lane; the reference points are
 // the same for the whole wave, so they come as scalar loads and cost the VALU
-// nothing. Bound by the VALU: 7 operations a pair, 5.7 * 10^12 pairs/s, of
-// the 5.6 * 10^12 that one instruction per cycle and CU makes at 2.4 GHz.
+// nothing. Bound by the VALU: 6.6 instructions a pair (three differences, a
+// product, two multiply-adds, half a three-operand minimum), 5.7 * 10^12
+// pairs/s of the 5.9 * 10^12 that a wave's instruction per cycle and CU makes
+// at 2.4 GHz.
 // With few queries the references are split over grid y, the parts' minima
 // meeting in d2 (distances are never negative, so their bits order as
 // unsigned; d2 starts at infinity then). 31k by 20k points take 108 us; a
@@ -686,11 +688,9 @@ int sdgr_image_metrics(const float* x, const float* ref, int32_t nimg, int32_t h
                        float data_range, float* ssim, float* mse, float* ref_max, void* stream)
 {
     clear_error();
-    if (nimg < 0) return einval("negative image count");
-    if (h < SSIM_WIN || w < SSIM_WIN) return einval("images smaller than the 11 x 11 window");
+    if (const int rc = check_metrics(x, ref, nimg, h, w, ssim, mse, ref_max)) return rc;
     if (!(data_range > 0.0f) || !std::isfinite(data_range)) return einval("data_range must be > 0");
     if (nimg == 0) return SDGR_OK;
-    if (const int rc = check_metrics(x, ref, nimg, h, w, ssim, mse, ref_max)) return rc;
     int ntx, nty;
     metrics_tiles(h, w, &ntx, &nty);
     hipLaunchKernelGGL(k_image_metrics, dim3((unsigned)nimg), dim3(256), 0, (hipStream_t)stream,
