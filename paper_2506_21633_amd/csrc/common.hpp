@@ -270,7 +270,7 @@ __device__ __forceinline__ uint32_t ikey_encode(bool vm, int v, uint32_t tile_i,
 // Segmented sorts (at most SEG_MAX segments, one per view): segment s holds
 // items [seg[s], seg[s+1]), its keys minus kb[s] are sorted, and it owns the
 // sort blocks tp[s] .. tp[s+1] - 1 (tp[S] = all blocks), each a run of tpb
-// 4096-item tiles of the segment (the last one shorter).
+// of the sort's tiles of the segment (the last one shorter).
 constexpr int SEG_MAX = 256;
 struct SegTable {
     uint32_t seg[SEG_MAX + 1];
@@ -402,7 +402,7 @@ hipError_t launch_params_backward(const DevView* views, const DevScene* scenes, 
 size_t params_part_floats(int nv, int64_t items, int sh_coeffs);
 
 // Sort grids have at most max_blocks blocks (each takes a contiguous run of
-// 4096-item tiles), between 256 and MAX_SORT_BLOCKS. Fewer, longer blocks
+// tiles of 1024, 2048 or 4096 items), between 256 and MAX_SORT_BLOCKS. Fewer, longer blocks
 // write longer runs per digit; more blocks hide more latency. Measured on
 // the 72-view vehicle: the depth sorts (four 8-bit passes) are fastest at
 // 2048, the pair sorts (one pass with wider digits) at 1024.
@@ -549,8 +549,9 @@ hipError_t launch_raster_b_direct(const DevView* views, int nv, int64_t tiles_c,
 hipError_t launch_ranges_i(const DevView* views, const uint32_t* keys, const uint32_t* status,
                            int64_t cap_i, int64_t tiles_c, int64_t tiles_i, bool vm,
                            uint2* ranges, hipStream_t s);
-// Deterministic pass B: one wave per imaging tile over its whole list (in
-// list order per pixel), from the imaging-plane tile ranges it builds.
+// Deterministic pass B: a workgroup per imaging tile, its waves over equal
+// runs of the list (in list order per pixel, then in wave order), from the
+// imaging-plane tile ranges it builds.
 hipError_t launch_raster_b_tiles(const DevView* views, int nv, int64_t pixels, int64_t cap_c,
                                  int64_t cap_i, int64_t tiles_c, int64_t tiles_i,
                                  const RasterParams& rp, const uint32_t* status,

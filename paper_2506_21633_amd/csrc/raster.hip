@@ -543,14 +543,18 @@ static_assert(HB_CHUNKS == 1 << HB_CHUNK_BITS, "chunk index bits of a stored hit
 // waves to a tile, which halves the chain of a long list: 8 views of 20k
 // Gaussians in 88 tiles 100 -> 63 us, 20 views of 80k in 718 tiles 142 -> 91.
 // More tiles fill the device with a wave each: 72 views of 200k in 2601 tiles
-// 375 against 453, 36 views of 50k in 6360 shorter ones 145 against 341.
+// 375 against 453, 36 views of 50k in 6360 shorter ones 145 against 341. Near
+// the line, a wave and nine to a tile: a vehicle of 80k in 1193 tiles 153 and
+// 136, 1526 161 and 178, 1789 163 and 205; of 200k in 1216 264 and 213, 1558 270
+// and 273, 1829 286 and 313; a building of 50k in 1218 83 and 70, 1566 90 and
+// 87, 1916 89 and 106; a block of 200k in 1553 74 and 67.
 constexpr uint32_t HF_TILES = 1536;
 
 // DET: deterministic mode (per-pair partials at their pre-sort positions).
-// HITS: the hits are stored for the backward. Only then may a group be cut by
-// ray: without stored hits the backward takes a ray's hits to be those in
-// front of its last used entry, with the optical depth this kernel's sums
-// give, so there the groups stay whole chunks of up to 4096 hits.
+// HITS: the hits are stored for the backward. Only then is a group cut by ray;
+// without stored hits the groups are whole chunks of up to 4096 hits. (The
+// backward that re-derives hits takes either: tiles that find the stream full
+// come to it from groups cut by ray, within 1e-5 of the stored hits' sums.)
 template <bool DET, bool HITS>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(1, HITS ? 8 : 2)))
 k_raster_a_fwd(const DevView* __restrict__ views, int nv, RasterParams rp,
@@ -1690,8 +1694,9 @@ struct __attribute__((packed, aligned(4))) Float4Unaligned { float v[4]; };
 // centre in registers -- no atomics, no tile list; dL/dI and the centre and
 // conic gradients are linear in those. Bound by the address units, a lane's
 // pixels lying in lines of their own: 16 views of a 2M-Gaussian block take
-// 3.1 ms, with a load per pixel 4.3; then by the records' bytes (72 views of
-// 200k 179 -> 168 us). It also clears the record's computation-plane gradient
+// 3.2 ms, with a load per pixel 4.3; then by the records' bytes (72 views of
+// 200k 179 -> 168 us with the signs of an L1 loss, with normal cotangents 262 ->
+// 260). It also clears the record's computation-plane gradient
 // sums for pass A.
 __global__ void __launch_bounds__(256)
 k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scenes, int nv,

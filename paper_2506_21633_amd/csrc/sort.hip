@@ -1440,7 +1440,7 @@ k_view_counts(const DevView* __restrict__ views, const uint2* __restrict__ rect_
 
 // The list of one tile (a workgroup): which of the view's records, in depth
 // order, cover it (a wave takes a quarter of them, 64 at a time), then the
-// list's entries at the places k_view_lists counted. Sets the pair count (0
+// list's entries at the places k_view_counts found. Sets the pair count (0
 // and the overflow flag above the capacity, with empty ranges).
 constexpr int TL_WAVES = 4;
 constexpr int TL_CHUNKS = VL_MAX / WAVE / TL_WAVES;   // of 64 records, per wave
