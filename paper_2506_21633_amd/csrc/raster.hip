@@ -1694,9 +1694,9 @@ struct __attribute__((packed, aligned(4))) Float4Unaligned { float v[4]; };
 // centre in registers -- no atomics, no tile list; dL/dI and the centre and
 // conic gradients are linear in those. Bound by the address units, a lane's
 // pixels lying in lines of their own: 16 views of a 2M-Gaussian block take
-// 3.2 ms, with a load per pixel 4.3; then by the records' bytes (72 views of
-// 200k 179 -> 168 us with the signs of an L1 loss, with normal cotangents 262 ->
-// 260). It also clears the record's computation-plane gradient
+// 3.2 ms, with a load per pixel 4.3; then by the records' bytes (72 views of one
+// vehicle of 200k 179 -> 168 us; of the one bench.py draws, with more and larger
+// footprints, the stage hardly gained: 262 -> 260). It also clears the record's computation-plane gradient
 // sums for pass A.
 __global__ void __launch_bounds__(256)
 k_image_bwd(const DevView* __restrict__ views, const DevScene* __restrict__ scenes, int nv,
