@@ -260,18 +260,21 @@ k_densify_apply(DensifyArgs a, const uint8_t* __restrict__ act,
 // Exhaustive nearest neighbours, a query per lane; the reference points are
 // the same for the whole wave, so they come as scalar loads and cost the VALU
 // nothing. Bound by the VALU: 6.6 instructions a pair (three differences, a
-// product, two multiply-adds, half a three-operand minimum), 5.7 * 10^12
-// pairs/s of the 5.9 * 10^12 that a wave's instruction per cycle and CU makes
-// at 2.4 GHz.
-// With few queries the references are split over grid y, the parts' minima
-// meeting in d2 (distances are never negative, so their bits order as
-// unsigned; d2 starts at infinity then). 31k by 20k points take 108 us; a
-// block of 256 per 256 queries with the references staged in LDS took 470
-// (124 blocks on 256 CUs). A search over points sorted into cells, skipping
-// boxes further than the minima found, gave the same results in 424 us at
-// this size and was faster only from 100k by 100k points on.
-constexpr int NN_PART = 128;       // fewest references of a part: 8 of the loop's batches
-constexpr unsigned NN_WAVES = 4096;   // waves that fill the device: 4 to a SIMD
+// product, two multiply-adds, half a three-operand minimum), at 7.2 * 10^12
+// pairs/s for 31k by 20k points and 9.3 * 10^12 for 4M by 10k, of the 11.9 *
+// 10^12 that the card's 157 TFLOP/s (128 lanes to a CU and cycle) allow.
+// The references are split over grid y until there are NN_WAVES waves, the
+// parts' minima meeting in d2 (distances are never negative, so their bits
+// order as unsigned; d2 starts at infinity then). Many short waves also leave
+// no long last round: in 4096 waves, 4 to a SIMD, 150k by 100k points took 3235
+// us, where every third SIMD had a wave more than the others, in 32768 1621;
+// 31k by 20k 107 and 87, 200k by 100k 3650 and 2175, 600k by 50k 3954 and 3318
+// (65536: 1565, 89, 2118, 3182). A block of 256 per 256 queries with the
+// references staged in LDS took 2613, 369, 3479 and 3985. A search over points
+// sorted into cells, skipping boxes further than the minima found, gave the
+// same results in 424 us at 31k by 20k.
+constexpr int NN_PART = 128;       // fewest references of a part: 16 of the loop's batches
+constexpr unsigned NN_WAVES = 32768;   // (also bounds grid y, which takes 65535)
 
 __global__ void __launch_bounds__(WAVE)
 k_nearest_sq(const float* __restrict__ q, int64_t nq, const float* __restrict__ ref, int64_t nr,

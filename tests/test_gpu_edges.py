@@ -627,3 +627,19 @@ def test_ordered_ragged_images_from_lists(cuda):
     for v, S in enumerate(want):
         scale = max(np.abs(S).max(), 1e-3 * top)
         assert np.abs(res.image(v).cpu().numpy() - S).max() <= ELEM * scale, v
+
+
+@pytest.mark.parametrize("nq,nr", [(1048576, 300), (1048641, 300), (2097088, 257), (2097153, 129)])
+def test_nearest_of_many_queries(cuda, nq, nr):
+    """Query counts where the references are last split in two parts and first
+    not at all, and where the waves pass the number that is aimed at: the FP64
+    distances, with the bar of test_nearest_parts."""
+    from scipy.spatial import cKDTree
+    from paper_2506_21633_amd import train
+    rng = np.random.default_rng(nq + 7 * nr)
+    q = rng.uniform(-3, 3, (nq, 3)).astype(np.float32)
+    ref = rng.uniform(-3, 3, (nr, 3)).astype(np.float32)
+    got = train.nearest_sq(torch.as_tensor(q, device=cuda),
+                           torch.as_tensor(ref, device=cuda)).cpu().numpy()
+    want = cKDTree(ref.astype(np.float64)).query(q.astype(np.float64), workers=8)[0] ** 2
+    assert (np.abs(got - want) <= 1e-5 * want + 2.0 ** -22 * 9.0).all()
