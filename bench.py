@@ -36,10 +36,11 @@ if ROOT not in sys.path:
 
 # MI355X published peaks
 HBM_PEAK_GBS = 8000.0
-# FP32 VALU issue rate without packed instructions: 256 CUs x 4 SIMDs x 16
-# lanes x 2.4 GHz = 39.3e12 lane-operations/s (an FMA counts once); the
-# transcendental unit runs at a quarter of that rate.
-VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+# FP32 VALU rate: 256 CUs x 128 lanes x 2.4 GHz = 78.6e12 lane-operations/s
+# (an FMA counts once: 157 TFLOP/s; the nearest-neighbour search, which has no
+# packed instructions, reaches 62e12); the transcendental unit runs at a
+# quarter of that rate.
+VALU_PEAK_TOPS = 256 * 128 * 2.4e9 / 1e12
 
 WORKLOADS = ("vehicle_200k", "building_50k", "fwd_1k", "large_2m")
 

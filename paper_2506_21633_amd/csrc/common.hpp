@@ -316,8 +316,7 @@ __device__ __forceinline__ uint32_t sat_u32(float x)
 // quadratic, widened by a slack that covers the rounding of the hardware
 // reciprocal and square root, so the mask holds every cell whose FP32 q is
 // below q_max (callers test q itself). Bit 8 * row + col. The eight rows are
-// all instruction issue (the masks of 25M pairs ran at two thirds of the
-// VALU's rate), so a row's cells lo..e-1 are two saturating conversions and
+// all instruction issue, so a row's cells lo..e-1 are two saturating conversions and
 // two bit-field masks, and a row out of reach is a negative square root's
 // NaN, which converts to none. TIGHT: the cells in which a row out of reach
 // by rounding counts as touching in its middle, and the slack is cut at whole

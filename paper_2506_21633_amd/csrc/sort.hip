@@ -1283,8 +1283,8 @@ constexpr int VL_WAVES = VL_THREADS / WAVE;
 
 // Depth rank of each record in its view: a workgroup takes 64 records (lane
 // = record), its waves share out the keys they are compared with, which are
-// scalar loads. Bound by the VALU, two operations a pair: 7300 records in
-// each of three views take 22 us, 1000 in one view 8, where the radix sort's
+// scalar loads. Two VALU operations a pair, a fifth of their rate where there
+// are this few waves: 7300 records in each of three views take 22 us, 1000 in one view 8, where the radix sort's
 // 12 launches took 66 and 48 (and a radix sort in one workgroup's LDS 35 and
 // 10).
 __global__ void __launch_bounds__(VL_THREADS)
